@@ -212,9 +212,10 @@ def work(case):
 def tolerance(case):
     """Labels, permutations and masks are decided in float64: exact.  Attention rounds probabilities and outputs
     to the inputs' type; each figure is about four times the distance from the path in 64 bits.  A prefix length
-    hangs on where a float32 sum meets tau: 0.2-0.3 % of the rows are off by one key from the 64-bit result."""
+    hangs on where a float32 sum meets tau: 0.2-0.3 % of the rows are off by one key from the 64-bit result
+    (the mean density moves by at most 1e-4: one row in a hundred, by one key of a hundred)."""
     if case["path"] == "density":
-        return {"rel": 2e-6, "differ": 1e-2}
+        return {"rel": 1e-4, "differ": 1e-2}
     if case["path"] == "cocluster":
         return {"rel": 1e-6, "max": 1e-5}
     return {"rel": 1e-2, "max": 0.1} if case["dtype"] == "bf16" else {"rel": 1e-5, "max": 1e-4}
