@@ -3,38 +3,49 @@
 //
 // For a query row i with logits s_t = <q_i, k_t> and p_t = softmax_t(scale * s_t) over all n keys,
 // the row's prefix length is the size of the shortest descending-sorted prefix of p whose sum
-// reaches tau.  Nothing is sorted: the prefix is { t : s_t >= theta_i } plus, when several keys
-// tie at theta_i, as many of them as are needed, and theta_i is found by bisection on the logit
-// value.  Every bisection step is one pass over all keys that accumulates, per row, the count and
-// the mass of { s_t >= mid }:
+// reaches tau.  Nothing is sorted: the row keeps a bracket [lo, hi) of logit values that holds the
+// prefix's last key, and every pass over the keys narrows it DEN_BINS-fold:
 //
-//   pass 0      row maximum m and minimum of the logits
-//   pass 1      Z = sum_t 2^((s_t - m) c2)  (c2 = scale * log2 e) and the key count
-//   pass 2...   mass / count above mid;  invariant  M(lo) >= tau Z > M(hi)
+//   pass 0      row maximum m and minimum of the logits, mean and variance of a sample of them
+//   pass 1      histogram over all keys of the masses 2^((s_t - m) c2)  (c2 = scale * log2 e): 64 equal
+//               bins around the value a normal distribution of the logits would give, the outer two
+//               open-ended.  The sum of the bins is Z; the bin in which the running mass from above
+//               meets tau Z is the bracket.
+//   pass 2...   rows whose bracket may hold more than DEN_CAP keys: the same histogram inside the
+//               bracket only.  Rows with fewer: the keys in it are collected into a list, and those
+//               above it counted; the row is done.
 //
-// until lo and hi enclose a single key, or are adjacent floats (ties).  The logits are recomputed
-// in every pass by the same instruction sequence, so they are bit-identical from pass to pass and
-// the bisection is consistent.  Masses are added in float32 inside a tile and in float64 across
-// tiles.
+// and the lists are ordered at the end.  75,600 keys take four or five passes where halving the
+// bracket took 29.  A bracket that shrinks to one float value holds ties, taken one at a time by a
+// division.  A bracket that equal bins cannot split (its width is not a usable float32) is split by
+// the order of the float bit patterns instead.
 //
-// bf16 inputs: S^T = K Q^T on v_mfma_f32_32x32x16_bf16, one query per lane column, 128 query rows
-// per workgroup, K in 64-key LDS tiles filled by direct global->LDS loads (same swizzle as the
-// attention kernel).  A row sample that yields fewer workgroups than the chip has compute units
-// (the offline profiling samples rows) would leave one wave per SIMD with nothing to hide its
-// latencies behind: such launches split the keys KS ways inside the workgroup (4 KS waves, wave
-// (rg, ks) takes the tiles ks, ks + KS, ... for row group rg) and combine the KS partial results
-// of a pass through LDS in the fixed order ks = 0, 1, ...  float32 inputs: a plain kernel, one
-// workgroup per row.
+// The logits are recomputed in every pass by the same instruction sequence, so they are
+// bit-identical from pass to pass, and a bin's edges are the exact floats at which the bin function
+// steps, so the histogram, the bracket and the list agree on every key.  Masses are added as 64-bit
+// fixed-point integers (LDS atomics): exact, hence independent of the order of the additions.
+//
+// S^T = K Q^T on the matrix cores (bf16: 32x32x16, float32: 32x32x2), one query per lane column.  A
+// workgroup owns 32 RG query rows and splits the keys KS ways (wave (rg, ks) takes the tiles ks,
+// ks + KS, ... for row group rg); K tiles come by direct global->LDS loads, swizzled as in the
+// attention kernel.  All waves add into one histogram per row.
+//
+// Bound (12 x 2,048 rows x 75,600 keys, d = 128, bf16): vector issue.  A logit of a histogram pass
+// costs ~60 vector cycles (exponential 16, bin index 12, fixed-point mass 20) against 16 of its
+// share of the matrix instruction.  Measured there: 24.7 ms for 29 passes of halving, 4.0-4.5 ms for
+// the four passes here (pass 0 0.6, pass 1 1.05, pass 2 1.4, the collecting pass 0.85).
+#include <math.h>
+
 #include <type_traits>
 
 #include "common.h"
 
 #define LOG2E_F 1.4426950408889634f
-#define DEN_KT 64
-#define DEN_MAX_PASSES 48   // 2 + at most ~34 halvings of a float interval; a hard stop
+#define DEN_MAX_PASSES 48   // pass 0, pass 1, and far more splits than a float interval allows; a hard stop
 
 typedef __attribute__((ext_vector_type(8))) __bf16 den_bf16x8;
 typedef __attribute__((ext_vector_type(16))) float den_f32x16;
+typedef unsigned long long den_u64;
 
 struct DensityArgs {
     const void* q;
@@ -42,8 +53,10 @@ struct DensityArgs {
     const int32_t* rows;     // nullable: query row indices shared by all slices
     int32_t* prefix_len;     // [bh, n_rows]
     int32_t* passes;         // nullable [bh]: most passes over the keys any workgroup of the slice made
-    int n, n_rows;
+    int n, n_rows, bh;
     float scale, tau;
+    float z_tau;             // normal quantile of 1 - tau: where pass 1 centres its bins
+    double fix;              // 2^S: masses are integers in units of 2^-S, n 2^S < 2^62
 };
 
 // next representable float above x (x finite or +inf)
@@ -54,321 +67,450 @@ __device__ __forceinline__ float next_up(float x) {
     return __uint_as_float((u >> 31) ? u - 1 : u + 1);
 }
 
-// Per-row bisection state, identical in the two lanes (or all threads) that share a row.
-struct RowState {
-    float m, mn, nmb, thr, lo, hi;
-    double target, m_hi;
-    int c_lo, c_hi;
-    bool done;
+// float order as unsigned integer order (adding +0 turns -0 into +0), and back
+__device__ __forceinline__ uint32_t float_key(float x) {
+    const uint32_t u = __float_as_uint(x + 0.f);
+    return u ^ ((u >> 31) ? 0xffffffffu : 0x80000000u);
+}
+__device__ __forceinline__ float key_float(uint32_t k) {
+    return __uint_as_float(k ^ ((k >> 31) ? 0x80000000u : 0xffffffffu));
+}
+
+// p in units of 2^-S, rounded to nearest: p 2^S < 2^52, so adding 2^52 leaves the integer in the mantissa
+__device__ __forceinline__ den_u64 to_fixed(float p, double fix) {
+    const long long u = __double_as_longlong(fma((double)p, fix, 4503599627370496.0));
+    return (den_u64)u & 0xfffffffffffffULL;
+}
+
+// What a lane needs of its row during a pass.
+struct Bracket {
+    float lo, hi;            // lo <= s < hi is inside
+    float inv, off;          // equal bins: floor(s inv + off), clamped
+    uint32_t mode;           // DEN_EQUAL, DEN_ORDER (bits 8.. = shift), DEN_COLLECT, DEN_DONE
 };
+enum { DEN_EQUAL = 0, DEN_ORDER = 1, DEN_COLLECT = 2, DEN_DONE = 3 };
 
-__device__ __forceinline__ void row_state_init(RowState& r) {
-    r.m = -INFINITY; r.mn = INFINITY; r.nmb = 0.f; r.thr = -3.4028234e38f; r.lo = 0.f; r.hi = 0.f;
-    r.target = 0.0; r.m_hi = 0.0; r.c_lo = 0; r.c_hi = 0; r.done = false;
+template <int BINS>
+__device__ __forceinline__ int equal_bin(float s, float inv, float off) {
+    return (int)__builtin_amdgcn_fmed3f(fmaf(s, inv, off), 0.f, (float)(BINS - 1));
 }
 
-// End of a pass: fold the pass result (row max/min, or mass and count above thr) into the state.
-__device__ __forceinline__ void row_state_step(RowState& r, int pass, float mx, float mn, double mass, int cnt,
-                                               float c2, float tau) {
-    if (pass == 0) {
-        r.m = mx;
-        r.mn = mn;
-        r.nmb = -mx * c2;
-        return;
+template <int BINS>
+__device__ __forceinline__ int bracket_bin(float s, const Bracket& r) {     // s >= r.lo
+    if ((r.mode & 255u) == DEN_ORDER) {
+        const uint32_t b = (float_key(s) - float_key(r.lo)) >> (r.mode >> 8);
+        return (int)(b < BINS - 1 ? b : BINS - 1);
     }
-    if (pass == 1) {
-        r.target = (double)tau * mass;
-        r.c_lo = cnt;
-        r.c_hi = 0;
-        r.m_hi = 0.0;
-        r.lo = r.mn;
-        r.hi = next_up(r.m);
-    } else if (!r.done) {
-        if (mass >= r.target) {
-            r.lo = r.thr;
-            r.c_lo = cnt;
-        } else {
-            r.hi = r.thr;
-            r.c_hi = cnt;
-            r.m_hi = mass;
-        }
+    return equal_bin<BINS>(s, r.inv, r.off);
+}
+
+// Smallest float of [lo, hi] whose bin is at least `bin` (hi if there is none): the exact lower edge.
+template <int BINS>
+__device__ __forceinline__ float bin_edge(int bin, float lo, float hi, const Bracket& r) {
+    uint32_t a = float_key(lo), b = float_key(hi);
+    while (a < b) {
+        const uint32_t mid = a + (b - a) / 2;
+        if (bracket_bin<BINS>(key_float(mid), r) >= bin) b = mid; else a = mid + 1;
     }
-    if (!r.done) {
-        if (r.c_lo - r.c_hi <= 1) {
-            r.done = true;
-        } else {
-            const float mid = r.lo + 0.5f * (r.hi - r.lo);
-            if (mid > r.lo && mid < r.hi)
-                r.thr = mid;
-            else
-                r.done = true;        // adjacent floats (or not finite): every key left ties at lo
-        }
+    return key_float(a) + 0.f;
+}
+
+// no float but lo itself in [lo, hi)
+__device__ __forceinline__ bool one_value(float lo, float hi) { return next_up(lo) >= hi; }
+
+// Bins for the bracket [lo, hi): equal ones unless the last split did not narrow it or they are no use.
+template <int BINS>
+__device__ __forceinline__ void set_bins(Bracket& r, bool by_order) {
+    r.inv = (float)BINS / (r.hi - r.lo);
+    r.off = -r.lo * r.inv;
+    r.mode = DEN_EQUAL;
+    if (by_order || !(r.inv > 0.f && r.inv < 1e37f) || !(fabsf(r.off) < 1e7f)) {
+        const uint32_t span = float_key(r.hi) - float_key(r.lo);
+        uint32_t shift = 0;
+        while (((span - 1) >> shift) >= (uint32_t)BINS) ++shift;
+        r.mode = DEN_ORDER | (shift << 8);
     }
 }
 
-__device__ __forceinline__ int row_state_result(const RowState& r, float c2, int n) {
-    const int ties = r.c_lo - r.c_hi;
-    int take = ties;
-    if (ties > 1) {
-        const float p = __builtin_amdgcn_exp2f(fmaf(r.lo, c2, r.nmb));
-        const double need = r.target - r.m_hi;
-        double t = p > 0.f ? ceil(need / (double)p) : (double)ties;
-        t = t < 1.0 ? 1.0 : (t > (double)ties ? (double)ties : t);
-        take = (int)t;
-    }
-    int len = r.c_hi + (take < 1 ? 1 : take);
-    return len < 1 ? 1 : (len > n ? n : len);
-}
-
-// per-row partial result of one pass, one per key split
+// Partial result of one pass for one row, one per key split
 struct PassPartial {
-    float mx, mn;
-    int cnt, pad;
-    double mass;
+    float mx, mn, sum, sq;   // pass 0
+    int cnt, samples;        // keys at or above hi; logits in sum / sq
 };
 
-template <int D, int KS, int NBUF>
-static constexpr size_t density_lds_bytes() {
-    return (size_t)NBUF * KS * DEN_KT * D * 2 + (KS > 1 ? (size_t)KS * 128 * sizeof(PassPartial) : 0);
-}
+template <typename T, int D>
+struct DenTile {
+    static constexpr int ROWB = D * (int)sizeof(T);
+    static constexpr int KEYS = 8192 / ROWB < 32 ? 32 : 8192 / ROWB;   // 8 KB a tile (16 KB for float32, d = 128)
+    static constexpr int BYTES = KEYS * ROWB;
+};
 
-template <int D, int KS, int NBUF>
-__global__ void __launch_bounds__(256 * KS)
-density_bf16_kernel(DensityArgs a) {
-    constexpr int DC = D / 16, CPR = D / 8, ROWB = D * 2, TILE = DEN_KT * ROWB, STAGE = KS * TILE;
-    constexpr int RPL = 64 / CPR;             // tile rows covered by one wave-load (1 KB)
-    constexpr int LPW = (DEN_KT / 4) / RPL;   // wave-loads per wave and step (a quarter of one tile)
-    static_assert(NBUF == 2 || NBUF == 3, "two or three stages");
-    extern __shared__ __attribute__((aligned(1024))) unsigned char k_lds[];
-    const int b = blockIdx.y, tid = threadIdx.x, lane = tid % 64, j = lane % 32, h = lane / 32;
-    const int wave = __builtin_amdgcn_readfirstlane(tid / 64), rg = wave % 4, ks = wave / 4;
+template <typename T, int D, int RG, int KS, int BINS>
+struct DenLds {
+    static constexpr int ROWS = 32 * RG;
+    static constexpr int STAGE = KS * DenTile<T, D>::BYTES;
+    static constexpr int HIST = 2 * STAGE;                             // [BINS][ROWS] u64, or a list of 2 BINS floats per row
+    static constexpr int PART = HIST + BINS * ROWS * 8;                // [KS][ROWS] PassPartial
+    static constexpr int STATE = PART + KS * ROWS * (int)sizeof(PassPartial);   // per row: bracket, nmb, list length
+    static constexpr int BYTES = STATE + 7 * ROWS * 4;
+    static_assert(2 * STAGE >= 2 * BINS * ROWS * 4, "the ordered lists reuse the K tiles");
+    static_assert(BYTES <= 160 * 1024, "LDS");
+};
+
+template <typename T, int D, int RG, int KS, int BINS>
+__global__ void __launch_bounds__(64 * RG * KS)
+density_kernel(DensityArgs a) {
+    using L = DenLds<T, D, RG, KS, BINS>;
+    constexpr bool BF16 = std::is_same<T, uint16_t>::value;
+    constexpr int ROWB = DenTile<T, D>::ROWB, KEYS = DenTile<T, D>::KEYS, TILE = DenTile<T, D>::BYTES;
+    constexpr int CPR = ROWB / 16, DC = ROWB / 32, NKB = KEYS / 32, ROWS = L::ROWS, STAGE = L::STAGE;
+    constexpr int NW = RG * KS, NT = 64 * NW, CAP = 2 * BINS;
+    constexpr int RPL = 1024 / ROWB;                       // tile rows covered by one wave-load (1 KB)
+    constexpr int LOADS = STAGE / 1024, LPW = (LOADS + NW - 1) / NW;
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+    den_u64* hist = (den_u64*)(lds + L::HIST);
+    float* list = (float*)(lds + L::HIST);                 // entry e of row r: word 2 ((e / 2) ROWS + r) + e % 2
+    PassPartial* part = (PassPartial*)(lds + L::PART);
+    float* st_lo = (float*)(lds + L::STATE);
+    float* st_hi = st_lo + ROWS;
+    float* st_inv = st_hi + ROWS;
+    float* st_off = st_inv + ROWS;
+    uint32_t* st_mode = (uint32_t*)(st_off + ROWS);
+    float* st_nmb = (float*)(st_mode + ROWS);
+    int* st_len = (int*)(st_nmb + ROWS);                   // keys collected
+
+    // consecutive workgroups of one slice on one XCD: they read the same keys at the same time
+    const int wps = (a.n_rows + ROWS - 1) / ROWS, total = wps * a.bh;
+    const int per_xcd = (total + 7) / 8;
+    const int wg = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
+    if ((int)(blockIdx.x / 8) >= per_xcd || wg >= total) return;
+    const int b = wg / wps, row_base = (wg % wps) * ROWS;
+    const int tid = threadIdx.x, lane = tid % 64, j = lane % 32, h = lane / 32;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64), rg = wave % RG, ks = wave / RG;
     const int n = a.n;
-    const int rloc = 32 * rg + j;
-    const int ridx = blockIdx.x * 128 + rloc;
-    const bool rvalid = ridx < a.n_rows;
-    int qrow = rvalid ? (a.rows ? a.rows[ridx] : ridx) : 0;
+    const int row = 32 * rg + j;                           // of the workgroup
+    const bool rvalid = row_base + row < a.n_rows;
+    int qrow = rvalid ? (a.rows ? a.rows[row_base + row] : row_base + row) : 0;
     qrow = qrow < 0 ? 0 : (qrow >= n ? n - 1 : qrow);
     const unsigned char* kg = (const unsigned char*)a.k + (size_t)b * n * ROWB;
-    const int n_tiles = (n + DEN_KT - 1) / DEN_KT;
-    const int n_steps = (n_tiles + KS - 1) / KS;     // a step = KS tiles, one per key split
+    const int n_tiles = (n + KEYS - 1) / KEYS;
+    const int n_steps = (n_tiles + KS - 1) / KS;           // a step = KS tiles, one per key split
 
-    // wave (rg, ks) fetches quarter rg of the tile its key split consumes in step `step`
     auto issue = [&](int step, int buf) {
 #pragma unroll
         for (int i = 0; i < LPW; ++i) {
-            const int rl = (rg * LPW + i) * RPL + lane / CPR;       // tile row
-            int row = (step * KS + ks) * DEN_KT + rl;
-            row = row < n ? row : n - 1;                            // rows past the end are masked or unused
+            int l = wave + i * NW;
+            l = l < LOADS ? l : LOADS - 1;                 // the last load may be issued twice, with the same bytes
+            const int tile = l / (TILE / 1024), rl = (l % (TILE / 1024)) * RPL + lane / CPR;
+            int key = (step * KS + tile) * KEYS + rl;
+            key = key < n ? key : n - 1;                   // rows past the end are masked or unused
             const int chunk = (lane % CPR) ^ (rl % CPR);
-            load_global_to_lds_16(kg + (size_t)row * ROWB + chunk * 16,
-                                  lds_address(k_lds) + buf * STAGE + ks * TILE + (rg * LPW + i) * RPL * ROWB);
+            load_global_to_lds_16(kg + (size_t)key * ROWB + chunk * 16, lds_address(lds) + buf * STAGE + l * 1024);
         }
     };
-#pragma unroll
-    for (int p = 0; p < NBUF - 1; ++p) issue(p % n_steps, p);
+    issue(0, 0);
 
-    den_bf16x8 qf[DC];
+    uint4 qf[DC];                                          // contraction elements of chunk 2 c + h
     {
-        const uint4* src = (const uint4*)((const uint16_t*)a.q + ((size_t)b * n + qrow) * D);
+        const uint4* src = (const uint4*)((const unsigned char*)a.q + ((size_t)b * n + qrow) * ROWB);
 #pragma unroll
-        for (int c = 0; c < DC; ++c) qf[c] = __builtin_bit_cast(den_bf16x8, rvalid ? src[2 * c + h] : make_uint4(0, 0, 0, 0));
+        for (int c = 0; c < DC; ++c) qf[c] = src[2 * c + h];
     }
     int koff[DC];
 #pragma unroll
     for (int c = 0; c < DC; ++c) koff[c] = j * ROWB + (((2 * c + h) ^ (j % CPR)) * 16);
     // the compiler's wait for the Q loads must not end up inside the tile loop
 #pragma unroll
-    for (int c = 0; c < DC; ++c) asm volatile("" ::"v"(qf[c]));
+    for (int c = 0; c < DC; ++c) asm volatile("" ::"v"(qf[c].x), "v"(qf[c].y), "v"(qf[c].z), "v"(qf[c].w));
 
     const float c2 = a.scale * LOG2E_F;
-    RowState st;
-    row_state_init(st);
-    float mx = -INFINITY, mn = INFINITY;
-    double mass = 0.0;
-    int cnt = 0;
-    int pass = 0, step = 0;
-    // steps are consumed in one running sequence g = pass * n_steps + step; step g sits in stage
-    // g % NBUF and the next NBUF - 1 steps are in flight or landed
-    for (int g = 0;; ++g) {
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPW * (NBUF - 2)) : "memory");   // all but the newest steps' loads
-        __syncthreads();
-        {
-            int ns = step + NBUF - 1;
-            ns = ns >= n_steps ? ns % n_steps : ns;      // wraps into the next pass (n_steps may be 1 or 2)
-            issue(ns, (g + NBUF - 1) % NBUF);
-        }
-        const int kt = step * KS + ks;
-        if (kt < n_tiles) {
-            const unsigned char* base = k_lds + (g % NBUF) * STAGE + ks * TILE;
-            den_f32x16 s[2];
+    const bool owner = ks == 0 && h == 0;                  // this thread keeps the row's state
+    // owner's state: bracket, mass above it, target mass, keys above it, length if already known
+    Bracket br = {0.f, 0.f, 0.f, 0.f, rvalid ? (uint32_t)DEN_EQUAL : (uint32_t)DEN_DONE};
+    float row_max = 0.f, row_min = 0.f;
+    den_u64 m_hi = 0, target = 0;
+    int c_hi = 0, known_len = -1;
+    int g = 0;                                             // running step number: stage g % 2
+
+    // One pass; body(s, valid) sees every logit of this lane's row and key split.
+    auto over_keys = [&](auto body) {
+        for (int step = 0; step < n_steps; ++step, ++g) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            issue(step + 1 < n_steps ? step + 1 : 0, (g + 1) & 1);     // wraps into the next pass
+            const int kt = step * KS + ks;
+            if (kt < n_tiles) {
+                const unsigned char* base = lds + (g & 1) * STAGE + ks * TILE;
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+                for (int kb = 0; kb < NKB; ++kb) {
+                    den_f32x16 s;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) s[kb][v] = 0.f;
+                    for (int v = 0; v < 16; ++v) s[v] = 0.f;
 #pragma unroll
-            for (int c = 0; c < DC; ++c) {
-                const den_bf16x8 a0 = __builtin_bit_cast(den_bf16x8, *(const uint4*)(base + koff[c]));
-                const den_bf16x8 a1 = __builtin_bit_cast(den_bf16x8, *(const uint4*)(base + 32 * ROWB + koff[c]));
-                s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, qf[c], s[0], 0, 0, 0);
-                s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, qf[c], s[1], 0, 0, 0);
-            }
-            const bool ragged = kt == n_tiles - 1 && (n % DEN_KT) != 0;
-            if (pass == 0) {
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const bool valid = !ragged || kt * DEN_KT + 32 * kb + 8 * (v / 4) + 4 * h + (v % 4) < n;
-                        mx = fmaxf(mx, valid ? s[kb][v] : -INFINITY);
-                        mn = fminf(mn, valid ? s[kb][v] : INFINITY);
+                    for (int c = 0; c < DC; ++c) {
+                        const uint4 kf = *(const uint4*)(base + kb * 32 * ROWB + koff[c]);
+                        if constexpr (BF16) {
+                            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(den_bf16x8, kf),
+                                                                        __builtin_bit_cast(den_bf16x8, qf[c]), s, 0, 0, 0);
+                        } else {
+                            s = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(kf.x), __uint_as_float(qf[c].x), s, 0, 0, 0);
+                            s = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(kf.y), __uint_as_float(qf[c].y), s, 0, 0, 0);
+                            s = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(kf.z), __uint_as_float(qf[c].z), s, 0, 0, 0);
+                            s = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(kf.w), __uint_as_float(qf[c].w), s, 0, 0, 0);
+                        }
                     }
-            } else {
-                float ts = 0.f;
+                    const int first = kt * KEYS + 32 * kb;
+                    if (first + 32 > n) {                  // ragged end: keys past it sort below everything
 #pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const bool valid = !ragged || kt * DEN_KT + 32 * kb + 8 * (v / 4) + 4 * h + (v % 4) < n;
-                        const float sv = s[kb][v];
-                        const float p = __builtin_amdgcn_exp2f(fmaf(sv, c2, st.nmb));
-                        const bool ge = valid && sv >= st.thr;
-                        ts += ge ? p : 0.f;
-                        cnt += ge ? 1 : 0;
+                        for (int v = 0; v < 16; ++v)
+                            if (first + 8 * (v / 4) + 4 * h + (v % 4) >= n) s[v] = -INFINITY;
+                        body(s, true, step);
+                    } else {
+                        body(s, false, step);
                     }
-                mass += (double)ts;
-            }
-        }
-        if (++step == n_steps) {
-            // both half-waves hold half of each row's keys: exchange and combine
-            {
-                auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(mx), __float_as_int(mx), false, false);
-                mx = fmaxf(__int_as_float(r[0]), __int_as_float(r[1]));
-                r = __builtin_amdgcn_permlane32_swap(__float_as_int(mn), __float_as_int(mn), false, false);
-                mn = fminf(__int_as_float(r[0]), __int_as_float(r[1]));
-                r = __builtin_amdgcn_permlane32_swap(cnt, cnt, false, false);
-                cnt = (int)r[0] + (int)r[1];
-                const long long mb = __double_as_longlong(mass);
-                const int lo32 = (int)(mb & 0xffffffffLL), hi32 = (int)(mb >> 32);
-                auto rl = __builtin_amdgcn_permlane32_swap(lo32, lo32, false, false);
-                auto rh = __builtin_amdgcn_permlane32_swap(hi32, hi32, false, false);
-                const double m0 = __longlong_as_double(((long long)(int)rh[0] << 32) | (unsigned int)rl[0]);
-                const double m1 = __longlong_as_double(((long long)(int)rh[1] << 32) | (unsigned int)rl[1]);
-                mass = m0 + m1;      // (own, other) in one half, (other, own) in the other: same sum
-            }
-            if constexpr (KS > 1) {
-                // the key splits of a row group exchange their partial results; every wave then adds
-                // them in the order ks = 0, 1, ..., so all of them step the same row state
-                PassPartial* part = (PassPartial*)(k_lds + (size_t)NBUF * STAGE);
-                if (h == 0) part[ks * 128 + rloc] = PassPartial{mx, mn, cnt, 0, mass};
-                __syncthreads();
-                PassPartial t = part[rloc];
-#pragma unroll
-                for (int o = 1; o < KS; ++o) {
-                    const PassPartial u = part[o * 128 + rloc];
-                    t.mx = fmaxf(t.mx, u.mx);
-                    t.mn = fminf(t.mn, u.mn);
-                    t.cnt += u.cnt;
-                    t.mass += u.mass;
                 }
-                mx = t.mx; mn = t.mn; cnt = t.cnt; mass = t.mass;
             }
-            row_state_step(st, pass, mx, mn, mass, cnt, c2, a.tau);
-            mass = 0.0;
-            cnt = 0;
-            step = 0;
-            ++pass;
-            // also orders this pass's reads of the partial results before the next pass's writes
-            const int all_done = __syncthreads_and((st.done || !rvalid) ? 1 : 0);
-            if (all_done || pass >= DEN_MAX_PASSES) break;
+        }
+    };
+    // Publish the row's bracket for the next pass and clear what that pass adds into.
+    auto publish = [&]() {
+        const bool off = br.mode == DEN_DONE;
+        st_lo[row] = off ? INFINITY : br.lo;
+        st_hi[row] = off ? INFINITY : br.hi;
+        st_inv[row] = br.inv;
+        st_off[row] = br.off;
+        st_mode[row] = br.mode;
+        if (!off) {
+            st_len[row] = 0;
+            if (br.mode != DEN_COLLECT)
+                for (int i = 0; i < BINS; ++i) hist[i * ROWS + row] = 0;
+        }
+    };
+    // Walk the bins from the top: the one in which the mass reaches the target becomes the bracket.
+    auto narrow = [&](float lowest, float highest) {
+        const Bracket was = br;
+        den_u64 mass = 0;
+        int bin = BINS - 1;
+        for (; bin >= 0; --bin) {
+            mass = hist[bin * ROWS + row];
+            if (m_hi + mass >= target || bin == 0) break;
+            m_hi += mass;
+        }
+        br.lo = bin == 0 ? lowest : bin_edge<BINS>(bin, lowest, highest, was);
+        br.hi = bin == BINS - 1 ? highest : bin_edge<BINS>(bin + 1, lowest, highest, was);
+        const den_u64 p_lo = to_fixed(__builtin_amdgcn_exp2f(fmaf(br.lo, c2, st_nmb[row])), a.fix);
+        // at most mass / p_lo keys; collect when they surely fit, when there is nothing left to split, and
+        // when the masses are too small to tell (the list's length then does)
+        if (mass <= p_lo * (den_u64)(CAP - 8) || one_value(br.lo, br.hi))
+            br.mode = DEN_COLLECT;
+        else
+            set_bins<BINS>(br, br.lo == was.lo && br.hi == was.hi);
+    };
+
+    // ---- pass 0
+    {
+        float mx = -INFINITY, mn = INFINITY, sum = 0.f, sq = 0.f;
+        int samples = 0;
+        over_keys([&](const den_f32x16& s, bool ragged, int step) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                mx = fmaxf(mx, s[v]);
+                mn = fminf(mn, ragged && s[v] == -INFINITY ? INFINITY : s[v]);
+            }
+            if ((step & 3) == 0 && !ragged) {              // a quarter of the keys is plenty for the first guess
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    sum += s[v];
+                    sq = fmaf(s[v], s[v], sq);
+                }
+                samples += 16;
+            }
+        });
+        auto other = [&](float x) {      // the half-wave's other half of the row's keys
+            auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
+            return __int_as_float(h == 0 ? (int)r[1] : (int)r[0]);
+        };
+        const float omx = other(mx), omn = other(mn), osum = other(sum), osq = other(sq);
+        if (h == 0) part[ks * ROWS + row] = PassPartial{fmaxf(mx, omx), fminf(mn, omn), sum + osum, sq + osq, 0, 2 * samples};
+        __syncthreads();
+        if (owner) {
+            mx = -INFINITY; mn = INFINITY; sum = 0.f; sq = 0.f; samples = 0;
+            for (int o = 0; o < KS; ++o) {
+                const PassPartial u = part[o * ROWS + row];
+                mx = fmaxf(mx, u.mx);
+                mn = fminf(mn, u.mn);
+                sum += u.sum;
+                sq += u.sq;
+                samples += u.samples;
+            }
+            row_max = mx;
+            row_min = mn + 0.f;
+            st_nmb[row] = -mx * c2;
+            // normal logits of mean mu and deviation sd: their masses are normal about mu + scale sd^2 (natural
+            // units), so the prefix ends z_tau sd from there; +-1.25 sd around it, inside [min, max]
+            const float mu = samples ? sum / samples : 0.5f * (mx + mn);
+            const float var = samples ? sq / samples - mu * mu : 0.f;
+            const float sd = sqrtf(fmaxf(var, 0.f));
+            float guess = mu + a.scale * sd * sd + a.z_tau * sd;
+            guess = fminf(fmaxf(guess, mn + 1.25f * sd), mx - 1.25f * sd);
+            const bool usable = sd > 0.f && guess - 1.25f * sd > mn && guess + 1.25f * sd < mx;
+            br.lo = usable ? guess - 1.25f * sd : row_min;
+            br.hi = usable ? guess + 1.25f * sd : next_up(mx);
+            if (br.mode != DEN_DONE) {
+                set_bins<BINS>(br, false);
+                if (br.mode != DEN_EQUAL) {                // pass 1 has equal bins only: everything in the lowest
+                    br.inv = 0.f;
+                    br.off = 0.f;
+                    br.mode = DEN_EQUAL;
+                }
+            }
+            publish();
+        }
+        __syncthreads();
+    }
+
+    // ---- pass 1
+    {
+        const float inv = st_inv[row], off = st_off[row], nmb = st_nmb[row];
+        over_keys([&](const den_f32x16& s, bool, int) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float p = __builtin_amdgcn_exp2f(fmaf(s[v], c2, nmb));
+                atomicAdd(&hist[equal_bin<BINS>(s[v], inv, off) * ROWS + row], to_fixed(p, a.fix));
+                if (v % 4 == 3) __builtin_amdgcn_sched_barrier(0);      // 16 at once would not fit the registers
+            }
+        });
+        __syncthreads();
+        if (owner) {
+            if (br.mode != DEN_DONE) {
+                den_u64 z = 0;
+                for (int i = 0; i < BINS; ++i) z += hist[i * ROWS + row];
+                const double t = ceil((double)a.tau * (double)z);
+                target = (den_u64)t;
+                if (!(row_max < INFINITY) || !(row_min > -INFINITY) || target == 0) {
+                    br.mode = DEN_DONE;                    // not finite: any length will do
+                    known_len = 1;
+                } else {
+                    narrow(row_min, next_up(row_max));
+                }
+            }
+            publish();
         }
     }
+    int pass = 2;
+    while (!__syncthreads_and(!owner || br.mode == DEN_DONE) && pass < DEN_MAX_PASSES) {
+        // ---- later passes: only keys inside the bracket cost more than three comparisons
+        int cnt = 0;
+        {
+            const Bracket r = {st_lo[row], st_hi[row], st_inv[row], st_off[row], st_mode[row]};
+            const float nmb = st_nmb[row];
+            over_keys([&](const den_f32x16& s, bool, int) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const bool above = s[v] >= r.hi;
+                    cnt += above ? 1 : 0;
+                    if (!above && s[v] >= r.lo) {
+                        if (r.mode == DEN_COLLECT) {
+                            const int e = atomicAdd(&st_len[row], 1);
+                            if (e < CAP) list[2 * ((e / 2) * ROWS + row) + e % 2] = s[v];
+                        } else {
+                            const float p = __builtin_amdgcn_exp2f(fmaf(s[v], c2, nmb));
+                            atomicAdd(&hist[bracket_bin<BINS>(s[v], r) * ROWS + row], to_fixed(p, a.fix));
+                        }
+                    }
+                }
+            });
+        }
+        {
+            auto r = __builtin_amdgcn_permlane32_swap(cnt, cnt, false, false);
+            if (h == 0) part[ks * ROWS + row].cnt = (int)r[0] + (int)r[1];
+        }
+        __syncthreads();
+        if (owner) {
+            if (br.mode == DEN_COLLECT) {
+                c_hi = 0;
+                for (int o = 0; o < KS; ++o) c_hi += part[o * ROWS + row].cnt;
+                const int len = st_len[row];
+                if (len <= CAP) {
+                    br.mode = DEN_DONE;
+                } else if (one_value(br.lo, br.hi)) {     // ties: as many as the target needs
+                    const den_u64 p = to_fixed(__builtin_amdgcn_exp2f(fmaf(br.lo, c2, st_nmb[row])), a.fix);
+                    den_u64 take = p ? (target - m_hi + p - 1) / p : (den_u64)len;
+                    take = take < 1 ? 1 : (take > (den_u64)len ? (den_u64)len : take);
+                    known_len = c_hi + (int)take;
+                    br.mode = DEN_DONE;
+                } else {                                   // more keys than their masses suggested
+                    set_bins<BINS>(br, true);
+                }
+            } else if (br.mode != DEN_DONE) {
+                narrow(br.lo, br.hi);
+            }
+            publish();
+        }
+        ++pass;
+    }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // loads issued for the pass that never ran
+    __syncthreads();
+    // ---- order the lists: every entry counts the entries before it and puts its mass at that position
+    float* ordered = (float*)lds;                          // [CAP][ROWS], over the K tiles
+    for (int i = tid; i < CAP * ROWS; i += NT) {
+        const int r = i % ROWS, e = i / ROWS;
+        if (st_mode[r] != DEN_DONE) continue;              // stopped by the pass limit: no list
+        const int len = st_len[r];
+        if (len > CAP || e >= len) continue;
+        const float v = list[2 * ((e / 2) * ROWS + r) + e % 2];
+        int rank = 0;
+        for (int o = 0; o < len; ++o) {
+            const float u = list[2 * ((o / 2) * ROWS + r) + o % 2];
+            rank += (u > v || (u == v && o < e)) ? 1 : 0;
+        }
+        if (rank < CAP) ordered[rank * ROWS + r] = __builtin_amdgcn_exp2f(fmaf(v, c2, st_nmb[r]));
+    }
+    __syncthreads();
     if (a.passes && tid == 0) atomicMax(&a.passes[b], pass);
-    if (rvalid && h == 0 && ks == 0) a.prefix_len[(size_t)b * a.n_rows + ridx] = row_state_result(st, c2, n);
+    if (owner && rvalid) {
+        int len = known_len;
+        if (len < 0) {
+            len = c_hi;
+            if (br.mode == DEN_DONE) {
+                den_u64 m = m_hi;
+                for (int i = 0; i < st_len[row]; ++i) {
+                    m += to_fixed(ordered[i * ROWS + row], a.fix);
+                    ++len;
+                    if (m >= target) break;
+                }
+            }
+        }
+        a.prefix_len[(size_t)b * a.n_rows + row_base + row] = len < 1 ? 1 : (len > n ? n : len);
+    }
 }
 
-template <int D, int KS, int NBUF>
-static int launch_density_bf16(const DensityArgs& a, int bh, hipStream_t stream) {
+template <typename T, int D, int RG, int KS, int BINS>
+static int launch_density(const DensityArgs& a, hipStream_t stream) {
     static unsigned char opted_in[SVOO_MAX_DEVICES];
-    constexpr int lds = (int)density_lds_bytes<D, KS, NBUF>();
-    auto kern = density_bf16_kernel<D, KS, NBUF>;
-    if (!opt_in_dynamic_lds((const void*)kern, lds, opted_in)) return SVOO_ERR_HIP;
-    hipLaunchKernelGGL(kern, dim3((a.n_rows + 127) / 128, bh), dim3(256 * KS), lds, stream, a);
+    constexpr int bytes = DenLds<T, D, RG, KS, BINS>::BYTES;
+    auto kern = density_kernel<T, D, RG, KS, BINS>;
+    if (!opt_in_dynamic_lds((const void*)kern, bytes, opted_in)) return SVOO_ERR_HIP;
+    const long long total = (long long)((a.n_rows + 32 * RG - 1) / (32 * RG)) * a.bh;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((total + 7) / 8 * 8)), dim3(64 * RG * KS), bytes, stream, a);
     return SVOO_OK;
 }
 
-// Fewer workgroups than the chip can hold at one per compute unit (or two): split the keys inside
-// the workgroup so that every SIMD still has several waves.
-template <int D>
-static int dispatch_density_bf16(const DensityArgs& a, int bh, hipStream_t stream) {
-    const long long wgs = (long long)((a.n_rows + 127) / 128) * bh;
-    if (wgs <= 256) return launch_density_bf16<D, 4, 2>(a, bh, stream);
-    if (wgs <= 512) return launch_density_bf16<D, 2, 2>(a, bh, stream);
-    return launch_density_bf16<D, 1, 3>(a, bh, stream);
-}
-
-// ---------------------------------------------------------------------------------------------
-// float32 inputs (and a plain reference shape of the same algorithm): one workgroup per query
-// row, every thread owns the keys tid, tid + 256, ...; logits by a fixed-order FMA chain.
-// ---------------------------------------------------------------------------------------------
+// One workgroup fits a compute unit (its histograms and K stages fill the LDS) and runs for the whole launch,
+// so the rows per workgroup are the fewest with which one round of the 256 units covers all rows: 12 x 2,048
+// rows are 192 workgroups of 128 rows, a quarter of the chip idle, or 256 of 96.
 template <typename T, int D>
-__global__ void __launch_bounds__(256)
-density_rowwise_kernel(DensityArgs a) {
-    __shared__ float qs[D];
-    __shared__ float red_f[2][256];
-    __shared__ double red_d[256];
-    __shared__ int red_i[256];
-    const int b = blockIdx.y, ridx = blockIdx.x, tid = threadIdx.x, n = a.n;
-    int qrow = a.rows ? a.rows[ridx] : ridx;
-    qrow = qrow < 0 ? 0 : (qrow >= n ? n - 1 : qrow);
-    const T* qg = (const T*)a.q + ((size_t)b * n + qrow) * D;
-    const T* kg = (const T*)a.k + (size_t)b * n * D;
-    auto as_f32 = [](const T* p) -> float {
-        if constexpr (std::is_same<T, float>::value) return *p;
-        else return bf16_to_f32(*(const uint16_t*)p);
-    };
-    if (tid < D) qs[tid] = as_f32(qg + tid);
-    __syncthreads();
-    const float c2 = a.scale * LOG2E_F;
-    RowState st;
-    row_state_init(st);
-    int pass = 0;
-    for (; pass < DEN_MAX_PASSES; ++pass) {
-        float mx = -INFINITY, mn = INFINITY;
-        double mass = 0.0;
-        int cnt = 0;
-        for (int t = tid; t < n; t += 256) {
-            const T* kr = kg + (size_t)t * D;
-            float sv = 0.f;
-            for (int c = 0; c < D; ++c) sv = fmaf(qs[c], as_f32(kr + c), sv);
-            if (pass == 0) {
-                mx = fmaxf(mx, sv);
-                mn = fminf(mn, sv);
-            } else if (sv >= st.thr) {
-                mass += (double)__builtin_amdgcn_exp2f(fmaf(sv, c2, st.nmb));
-                ++cnt;
-            }
-        }
-        red_f[0][tid] = mx;
-        red_f[1][tid] = mn;
-        red_d[tid] = mass;
-        red_i[tid] = cnt;
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if (tid < w) {
-                red_f[0][tid] = fmaxf(red_f[0][tid], red_f[0][tid + w]);
-                red_f[1][tid] = fminf(red_f[1][tid], red_f[1][tid + w]);
-                red_d[tid] += red_d[tid + w];
-                red_i[tid] += red_i[tid + w];
-            }
-            __syncthreads();
-        }
-        row_state_step(st, pass, red_f[0][0], red_f[1][0], red_d[0], red_i[0], c2, a.tau);
-        __syncthreads();
-        if (st.done) break;          // uniform: every thread holds the same state
+static int dispatch_density(const DensityArgs& a, hipStream_t stream) {
+    auto wgs = [&](int rg) { return (long long)((a.n_rows + 32 * rg - 1) / (32 * rg)) * a.bh; };
+    if constexpr (std::is_same<T, float>::value) {
+        if (wgs(1) <= 256) return launch_density<T, D, 1, 4, 32>(a, stream);
+        return launch_density<T, D, 2, 4, 32>(a, stream);
+    } else {
+        if (wgs(1) <= 256) return launch_density<T, D, 1, 8, 64>(a, stream);
+        if (wgs(2) <= 256) return launch_density<T, D, 2, 6, 64>(a, stream);
+        if (wgs(3) <= 256) return launch_density<T, D, 3, 4, 64>(a, stream);
+        return launch_density<T, D, 4, 4, 64>(a, stream);
     }
-    if (a.passes && tid == 0) atomicMax(&a.passes[b], pass + 1 < DEN_MAX_PASSES ? pass + 1 : DEN_MAX_PASSES);
-    if (tid == 0) a.prefix_len[(size_t)b * a.n_rows + ridx] = row_state_result(st, c2, n);
 }
 
 // density[b] = mean_i prefix_len[b, i] / n: integer sum in a fixed order, one division
@@ -392,6 +534,16 @@ __global__ void density_clear_kernel(int32_t* p, int count) {
     if (i < count) p[i] = 0;
 }
 
+// x with P(N(0, 1) <= x) = p, by bisection on erfc; only a first guess hangs on it
+static double normal_quantile(double p) {
+    double lo = -6.0, hi = 6.0;
+    for (int i = 0; i < 40; ++i) {
+        const double mid = 0.5 * (lo + hi);
+        if (0.5 * erfc(-mid * 0.7071067811865476) < p) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
 extern "C" int svoo_attention_density(const svoo_shape* shape, const void* q, const void* k, const int32_t* rows,
                                       int32_t n_rows, float tau, float scale, int32_t* prefix_len, double* density,
                                       int32_t* passes, void* hip_stream) {
@@ -402,20 +554,19 @@ extern "C" int svoo_attention_density(const svoo_shape* shape, const void* q, co
     if (n_rows < 1 || n_rows > shape->n || (!rows && n_rows != shape->n)) return SVOO_ERR_INVALID_ARG;
     if (!(tau > 0.0f) || !(tau <= 1.0f) || !(scale > 0.0f) || !(scale < 1e30f)) return SVOO_ERR_INVALID_ARG;
     hipStream_t stream = (hipStream_t)hip_stream;
-    DensityArgs a = {q, k, rows, prefix_len, passes, shape->n, n_rows, scale, tau};
+    // fixed-point unit: n masses of at most 1 (and a rounding) stay below 2^62, one mass below 2^51
+    int bits = 0;
+    while ((1LL << bits) < shape->n) ++bits;
+    const int s_bits = 61 - bits < 50 ? 61 - bits : 50;
+    DensityArgs a = {q, k, rows, prefix_len, passes, shape->n, n_rows, shape->bh, scale, tau,
+                     (float)normal_quantile(1.0 - (double)tau), (double)(1LL << s_bits)};
     if (passes)
         hipLaunchKernelGGL(density_clear_kernel, dim3((shape->bh + 255) / 256), dim3(256), 0, stream, passes, shape->bh);
-    if (shape->dtype == SVOO_BF16) {
-        st = shape->d == 128 ? dispatch_density_bf16<128>(a, shape->bh, stream)
-                             : dispatch_density_bf16<64>(a, shape->bh, stream);
-        if (st != SVOO_OK) return st;
-    } else {
-        dim3 grid(n_rows, shape->bh);
-        if (shape->d == 128)
-            hipLaunchKernelGGL((density_rowwise_kernel<float, 128>), grid, dim3(256), 0, stream, a);
-        else
-            hipLaunchKernelGGL((density_rowwise_kernel<float, 64>), grid, dim3(256), 0, stream, a);
-    }
+    if (shape->dtype == SVOO_BF16)
+        st = shape->d == 128 ? dispatch_density<uint16_t, 128>(a, stream) : dispatch_density<uint16_t, 64>(a, stream);
+    else
+        st = shape->d == 128 ? dispatch_density<float, 128>(a, stream) : dispatch_density<float, 64>(a, stream);
+    if (st != SVOO_OK) return st;
     hipLaunchKernelGGL(density_mean_kernel, dim3(shape->bh), dim3(1024), 0, stream, prefix_len, density, n_rows,
                        shape->n);
     return launch_status();

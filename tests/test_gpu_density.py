@@ -125,6 +125,41 @@ def test_density_ties_uniform_and_geometric(dtype):
         assert abs(H.to_np(dens)[0] - want / n) < 1e-15
 
 
+@pytest.mark.parametrize("dtype,d,n,n_rows,kind", [
+    ("bf16", 128, 97, 33, "spread"), ("bf16", 64, 1000, 65, "ties"), ("bf16", 128, 4099, 97, "outlier"),
+    ("bf16", 64, 8193, 129, "flat"), ("bf16", 128, 700, 700, "ties"), ("f32", 128, 1025, 31, "outlier"),
+    ("f32", 64, 999, 70, "flat"), ("f32", 128, 3000, 65, "ties")])
+def test_density_bracket_splits(dtype, d, n, n_rows, kind):
+    """Row counts on both sides of 32, 64, 96 and 128 rows per workgroup (by repeating the head so that one
+    round of the chip no longer holds them), and logits that the equal bins of the first histogram split
+    badly: masses over hundreds of octaves, a few values with more ties than a list holds, one key far
+    above the rest, keys within a few float steps of each other.  Checked against the oracle; a cumulative
+    mass within SLACK of tau may decide either way (float32 logits: the derivation above)."""
+    rng = np.random.default_rng(n)
+    q = rng.standard_normal((1, n, d)).astype(np.float32)
+    k = rng.standard_normal((1, n, d)).astype(np.float32)
+    if kind == "spread":
+        k *= 40.0
+    elif kind == "ties":
+        k = k[:, rng.integers(0, 7, n)]
+    elif kind == "outlier":
+        k[0, n // 2] = 50.0 * q[0, 0]
+    else:
+        k = 1.0 + np.round(2.0 * k) / 128.0
+    if dtype == "bf16":
+        q, k = synth.round_to_bf16(q), synth.round_to_bf16(k)
+    rows = rng.integers(0, n, n_rows).astype(np.int32)
+    rows[0] = 0
+    tau32 = float(np.float32(0.95))
+    ref = so.attention_density(q[0], k[0], H.scale_of(d), tau32, rows=rows)
+    for copies in (1, 9, 120):
+        plen, _ = svoo.attention_density(H.to_dev(np.tile(q, (copies, 1, 1)), dtype), H.to_dev(np.tile(k, (copies, 1, 1)), dtype),
+                                         tau32, H.scale_of(d), rows=H.to_dev(rows))
+        plen = H.to_np(plen)
+        compare_prefix(plen[0], ref, max_near=max(2, n_rows // 20))
+        assert (plen == plen[0]).all()
+
+
 def test_density_full_size_head_of_config2():
     """One head at the real shape (75,600 keys), 1,024 sampled query rows, tau = 0.95."""
     cfg = synth.CONFIGS[2]
