@@ -16,7 +16,7 @@
 // (256 rows), which halves the K/V traffic out of L2 per flop (each K/V tile is fetched once per
 // workgroup).
 //
-// f32 kernel: 4 lanes per query row, plain float32 FMAs, same schedule and key stream.
+// f32 kernel: the same transposes on v_mfma_f32_32x32x2_f32, same schedule and key stream.
 #include <type_traits>
 
 #include "common.h"
@@ -26,8 +26,6 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 #define ATT_THREADS 256
 #define KT 64                 // keys per tile
-#define K_PITCH 272           // bytes per K row in LDS (256 + 16 pad)
-#define VT_PITCH 144          // bytes per V^T row in LDS (KT*2 + 16 pad)
 #define LOG2E 1.4426950408889634f
 
 // ---------------------------------------------------------------------------------------------
@@ -188,16 +186,6 @@ __device__ __forceinline__ bool setup_tile(const AttnArgs& a, int bm, int32_t* s
     if (tid == 0) seg_cum[cnt] = ti.total;
     __syncthreads();
     return true;
-}
-
-// Sorted key row of logical stream position p (p < total): last segment s with seg_cum[s] <= p.
-__device__ __forceinline__ int stream_row(const int32_t* seg_start, const int32_t* seg_cum, int n_seg, int p) {
-    int lo = 0, hi = n_seg;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (seg_cum[mid] <= p) lo = mid; else hi = mid;
-    }
-    return seg_start[lo] + (p - seg_cum[lo]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -671,108 +659,228 @@ sparse_attn_bf16_kernel(AttnArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// float32 kernel: 64 query rows per workgroup, 4 lanes per row, each lane owns D/4 columns
-// (interleaved in groups of 4: lane part p owns columns 16 c + 4 p .. +3), keys staged 32 at a time
+// float32 kernel, head dimension D (64 or 128): both contractions on v_mfma_f32_32x32x2_f32, float32 operands
+// and accumulation throughout.  Four waves = RG groups of 32 query rows x KS key splits; a stage of the key
+// stream is 32 KS keys, wave (rg, ks) takes its ks-th 32-key block, the KS partial results are merged at the
+// end.  As in the bf16 kernel the transposes are computed (one query per lane):
+//   S^T = K_tile Q^T    the contraction index of a 16-byte chunk pair (2 c, 2 c + 1) is split over the two half
+//                       waves: one ds_read_b128 per lane feeds four instructions
+//   O^T += V^T P^T      instruction v contracts the two keys whose probabilities lane halves hold in accumulator
+//                       v, so P is the B operand as it stands; row i of the e-th 32-row block of O^T is column
+//                       (D / 32) i + e, so one read of D / 32 adjacent floats feeds all blocks and every
+//                       lane ends with runs of adjacent output columns
+// K and V have one buffer each: K of the next stage is fetched while the second product runs, V of this stage
+// while the first one does, behind two barriers per stage; at 8,192 matrix cycles per 32 x 32 block (d = 128)
+// against 64 KB per stage the loads have 4,096 cycles to land, and two workgroups (64 KB + tables each) fit a CU.
+// Bound: the float32 matrix rate (157 TFLOP/s).  12 x 8,190 x 128 at keep 0.2: 2.98 ms with plain FMAs (four
+// lanes per query row), 1.11 ms here; dense 8.29 -> 3.13 ms = 131 TFLOP/s.
 // ---------------------------------------------------------------------------------------------
-#define BM_F32 64
-#define KT_F32 32
+template <int D, int RG, int KS>
+struct F32Lds {
+    static constexpr int ROWB = D * 4, KEYS = 32 * KS, TILE = KEYS * ROWB;
+    static constexpr int BYTES = 2 * TILE + (2 * SVOO_MAX_K + 8) * 4;      // K, V, segment tables
+};
 
-template <int D>
-__global__ void __launch_bounds__(ATT_THREADS)
+template <int D, int RG, int KS>
+__global__ void __launch_bounds__(ATT_THREADS, KS == 2 ? 2 : 1)
 sparse_attn_f32_kernel(AttnArgs a) {
-    constexpr int NC = D / 16;  // float4 chunks per lane
-    __shared__ int32_t seg_start[SVOO_MAX_K];
-    __shared__ int32_t seg_cum[SVOO_MAX_K + 1];
-    __shared__ int32_t scan[ATT_THREADS];
-    __shared__ int32_t rowidx[KT_F32];
-    __shared__ float4 k_lds[KT_F32 * D / 4];
-    __shared__ float4 v_lds[KT_F32 * D / 4];
+    using L = F32Lds<D, RG, KS>;
+    static_assert(RG * KS == 4, "four waves");
+    constexpr int ROWB = L::ROWB, KEYS = L::KEYS, TILE = L::TILE;
+    constexpr int CPR = ROWB / 16, DC = D / 8, DB = D / 32;
+    constexpr int RPL = 64 / CPR, RW = KEYS / 4, LPW = RW / RPL;       // as in the bf16 kernel
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    unsigned char* k_lds = smem;
+    unsigned char* v_lds = smem + TILE;
+    int32_t* seg_start = (int32_t*)(smem + 2 * TILE);
+    int32_t* seg_cum = seg_start + SVOO_MAX_K;
 
     TileInfo ti;
-    if (!setup_tile<ATT_THREADS>(a, BM_F32, seg_start, seg_cum, scan, ti)) return;
+    if (!setup_tile<ATT_THREADS>(a, 32 * RG, seg_start, seg_cum, (int32_t*)smem, ti)) return;
     const int b = blockIdx.y, tid = threadIdx.x;
-    const int qrow = tid / 4, part = tid % 4;
-    const bool qvalid = qrow < ti.qn;
-    const float4* qg = (const float4*)a.q + (size_t)b * a.n * (D / 4);
-    const float4* kg = (const float4*)a.k + (size_t)b * a.n * (D / 4);
-    const float4* vg = (const float4*)a.v + (size_t)b * a.n * (D / 4);
-    float4 qv[NC], ov[NC];
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64), rg = wave % RG, ks = wave / RG;
+    const int lane = tid % 64, j = lane % 32, h = lane / 32;
+    const unsigned char* kg = (const unsigned char*)a.k + (size_t)b * a.n * ROWB;
+    const unsigned char* vg = (const unsigned char*)a.v + (size_t)b * a.n * ROWB;
+    const int total = ti.total;
+    const int n_tiles = (total + KEYS - 1) / KEYS;
+
+    // key-stream walk, one stage ahead: this lane tracks stage row RW wave + lane % RW
+    int seg = 0, seg_end = 0, seg_delta = 0;
+    if (total > 0) {
+        seg_end = seg_cum[1];
+        seg_delta = seg_start[0] - seg_cum[0];
+    }
+    int rows[LPW];
+    auto prepare = [&](int t) {              // call with t = 0, 1, 2, ... in order
+        int p = t * KEYS + RW * wave + (lane % RW);
+        p = p < total ? p : total - 1;       // rows past the end re-read the last key (masked later)
+        while (p >= seg_end) {               // terminates: p < total = seg_cum[n_seg]
+            ++seg;
+            seg_end = seg_cum[seg + 1];
+            seg_delta = seg_start[seg] - seg_cum[seg];
+        }
+        const int myrow = p + seg_delta;
+#pragma unroll
+        for (int i = 0; i < LPW; ++i) rows[i] = __shfl(myrow, i * RPL + lane / CPR);
+    };
+    auto issue = [&](const unsigned char* src, unsigned char* dst, bool swizzle) {
+#pragma unroll
+        for (int i = 0; i < LPW; ++i) {
+            const int rl = RW * wave + i * RPL + lane / CPR;
+            const int chunk = swizzle ? (lane % CPR) ^ (rl % CPR) : lane % CPR;
+            load_global_to_lds_16(src + (size_t)rows[i] * ROWB + chunk * 16,
+                                  lds_address(dst) + (RW * wave + i * RPL) * ROWB);
+        }
+    };
+
+    const int qrow = 32 * rg + j;
+    const bool qvalid = qrow < ti.qn, wave_active = 32 * rg < ti.qn;
     int qtok = ti.q0 + (qvalid ? qrow : 0);     // token whose row this is: gathered / scattered through q_perm
     if (a.q_perm) qtok = clamp_row(a.q_perm[(size_t)b * a.n + qtok], a.n);
+    float4 qf[DC];                              // contraction elements of chunk 2 c + h
+    {
+        const float4* src = (const float4*)((const unsigned char*)a.q + ((size_t)b * a.n + qtok) * ROWB);
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        qv[c] = qvalid ? qg[(size_t)qtok * (D / 4) + 4 * c + part] : make_float4(0, 0, 0, 0);
-        ov[c] = make_float4(0, 0, 0, 0);
+        for (int c = 0; c < DC; ++c) qf[c] = src[2 * c + h];
     }
-    float m = -INFINITY, lsum = 0.f;
-    const int n_tiles = (ti.total + KT_F32 - 1) / KT_F32;
+    // the compiler's wait for these loads must not end up inside the stage loop
+#pragma unroll
+    for (int c = 0; c < DC; ++c) asm volatile("" ::"v"(qf[c].x), "v"(qf[c].y), "v"(qf[c].z), "v"(qf[c].w));
+    const unsigned char* k_base = k_lds + (32 * ks + j) * ROWB;
+    const unsigned char* v_base = v_lds + (32 * ks + 4 * h) * ROWB + j * (DB * 4);
+
+    f32x16 o[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
+    const float c2 = a.scale * LOG2E;
+    const float th_raw = RESCALE_LOG2 / c2;
+    float m_used = -INFINITY;                   // reference max (raw logits) the probabilities are scaled by
+    float lsum = 0.f;                           // this lane's share of the row sum
+
+    if (n_tiles > 0) {
+        prepare(0);
+        issue(kg, k_lds, true);
+    }
     for (int kt = 0; kt < n_tiles; ++kt) {
-        __syncthreads();
-        if (tid < KT_F32) {
-            const int p = kt * KT_F32 + tid;
-            rowidx[tid] = p < ti.total ? stream_row(seg_start, seg_cum, ti.n_seg, p) : -1;
-        }
-        __syncthreads();
-        for (int e = tid; e < KT_F32 * D / 4; e += ATT_THREADS) {
-            const int row = e / (D / 4), col = e % (D / 4);
-            const int g = rowidx[row];
-            k_lds[e] = g >= 0 ? kg[(size_t)g * (D / 4) + col] : make_float4(0, 0, 0, 0);
-            v_lds[e] = g >= 0 ? vg[(size_t)g * (D / 4) + col] : make_float4(0, 0, 0, 0);
-        }
-        __syncthreads();
-        const int valid = ti.total - kt * KT_F32 < KT_F32 ? ti.total - kt * KT_F32 : KT_F32;
-        float sc[KT_F32];
-        float mx = -INFINITY;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();                        // K of this stage is there, V of the last one is used up
+        issue(vg, v_lds, false);
+        f32x16 s;
 #pragma unroll
-        for (int key = 0; key < KT_F32; ++key) {
-            float s = 0.f;
+        for (int v = 0; v < 16; ++v) s[v] = 0.f;
+        if (wave_active) {
 #pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                const float4 kv = k_lds[key * (D / 4) + 4 * c + part];
-                s = fmaf(qv[c].x, kv.x, s);
-                s = fmaf(qv[c].y, kv.y, s);
-                s = fmaf(qv[c].z, kv.z, s);
-                s = fmaf(qv[c].w, kv.w, s);
-            }
-            s += __shfl_xor(s, 1);
-            s += __shfl_xor(s, 2);
-            s = key < valid ? s * a.scale : -INFINITY;
-            sc[key] = s;
-            mx = fmaxf(mx, s);
-        }
-        const float m_new = fmaxf(m, mx);
-        const float alpha = expf(m - m_new);
-        m = m_new;
-        lsum *= alpha;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            ov[c].x *= alpha;
-            ov[c].y *= alpha;
-            ov[c].z *= alpha;
-            ov[c].w *= alpha;
-        }
-#pragma unroll
-        for (int key = 0; key < KT_F32; ++key) {
-            const float p = expf(sc[key] - m_new);
-            lsum += p;
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                const float4 vv = v_lds[key * (D / 4) + 4 * c + part];
-                ov[c].x = fmaf(p, vv.x, ov[c].x);
-                ov[c].y = fmaf(p, vv.y, ov[c].y);
-                ov[c].z = fmaf(p, vv.z, ov[c].z);
-                ov[c].w = fmaf(p, vv.w, ov[c].w);
+            for (int c = 0; c < DC; ++c) {
+                const float4 kf = *(const float4*)(k_base + (((2 * c + h) ^ (j % CPR)) * 16));
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.x, qf[c].x, s, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.y, qf[c].y, s, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.z, qf[c].z, s, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.w, qf[c].w, s, 0, 0, 0);
             }
         }
-    }
-    if (qvalid) {
-        const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
-        float4* og = (float4*)a.out + ((size_t)b * a.n + qtok) * (D / 4);
+        if (kt + 1 < n_tiles) prepare(kt + 1);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();                        // V of this stage is there, K is used up
+        if (kt + 1 < n_tiles) issue(kg, k_lds, true);
+        if (!wave_active) continue;
+        const int first = kt * KEYS + 32 * ks;
+        if (first + 32 > total) {               // keys past the end of the stream get -inf
 #pragma unroll
-        for (int c = 0; c < NC; ++c)
-            og[4 * c + part] = make_float4(ov[c].x * inv, ov[c].y * inv, ov[c].z * inv, ov[c].w * inv);
-        if (a.lse && part == 0) a.lse[(size_t)b * a.n + qtok] = lsum > 0.f ? m + logf(lsum) : -INFINITY;
+            for (int v = 0; v < 16; ++v)
+                if (first + 8 * (v / 4) + 4 * h + (v % 4) >= total) s[v] = -INFINITY;
+        }
+        float mx = s[0];
+#pragma unroll
+        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
+        {
+            const int mi = __float_as_int(mx);
+            auto r = __builtin_amdgcn_permlane32_swap(mi, mi, false, false);
+            mx = fmaxf(__int_as_float(r[0]), __int_as_float(r[1]));
+        }
+        if (__any(mx > m_used + th_raw)) {
+            const float m_new = fmaxf(m_used, mx);
+            // rows that have seen no key yet keep zeros: (-inf) - (-inf) must not reach the exponential
+            const float alpha = m_used == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_used - m_new) * c2);
+            m_used = m_new;
+            lsum *= alpha;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
+        }
+        const float mb = m_used == -INFINITY ? 0.f : m_used * c2;      // a split may have met masked keys only
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            s[v] = __builtin_amdgcn_exp2f(fmaf(s[v], c2, -mb));
+            lsum += s[v];
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const float* vp = (const float*)(v_base + (8 * (v / 4) + (v % 4)) * ROWB);
+            float vf[DB];
+            if constexpr (DB == 4) {
+                const float4 t = *(const float4*)vp;
+                vf[0] = t.x; vf[1] = t.y; vf[2] = t.z; vf[3] = t.w;
+            } else {
+                const float2 t = *(const float2*)vp;
+                vf[0] = t.x; vf[1] = t.y;
+            }
+#pragma unroll
+            for (int db = 0; db < DB; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[db], s[v], o[db], 0, 0, 0);
+        }
     }
+
+    // ---- merge the key splits, normalise, store.  Lane (j, h) holds O[q = j][DB (8 (v/4) + 4 h + v%4) + db].
+    float ltot;
+    {
+        const int li = __float_as_int(lsum);
+        auto r = __builtin_amdgcn_permlane32_swap(li, li, false, false);
+        ltot = __int_as_float(r[0]) + __int_as_float(r[1]);
+    }
+    __syncthreads();                            // all waves are done with the K / V tiles
+    constexpr int PARK = (16 * DB + 2) * 64;
+    static_assert((KS - 1) * RG * PARK * 4 <= 2 * TILE, "parked partials exceed the tiles");
+    if (ks > 0 && wave_active) {
+        float* park = (float*)smem + ((ks - 1) * RG + rg) * PARK;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) park[(16 * db + v) * 64 + lane] = o[db][v];
+        park[(16 * DB) * 64 + lane] = m_used;
+        park[(16 * DB + 1) * 64 + lane] = ltot;
+    }
+    __syncthreads();
+    if (ks > 0 || !wave_active) return;
+#pragma unroll
+    for (int g = 1; g < KS; ++g) {
+        const float* park = (const float*)smem + ((g - 1) * RG + rg) * PARK;
+        const float m_b = park[(16 * DB) * 64 + lane], l_b = park[(16 * DB + 1) * 64 + lane];
+        const float m_new = fmaxf(m_used, m_b);
+        const float sa = m_used == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_used - m_new) * c2);
+        const float sb = m_b == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_b - m_new) * c2);
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) o[db][v] = o[db][v] * sa + park[(16 * db + v) * 64 + lane] * sb;
+        ltot = ltot * sa + l_b * sb;
+        m_used = m_new;
+    }
+    if (!qvalid) return;
+    const float inv = ltot > 0.f ? 1.f / ltot : 0.f;
+    float* og = (float*)a.out + ((size_t)b * a.n + qtok) * D;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        float* dst = og + DB * (8 * (v / 4) + 4 * h + (v % 4));
+        if constexpr (DB == 4)
+            *(float4*)dst = make_float4(o[0][v] * inv, o[1][v] * inv, o[2][v] * inv, o[3][v] * inv);
+        else
+            *(float2*)dst = make_float2(o[0][v] * inv, o[1][v] * inv);
+    }
+    if (a.lse && h == 0)
+        a.lse[(size_t)b * a.n + qtok] = ltot > 0.f ? (m_used * c2 + log2f(ltot)) * 0.6931471805599453f : -INFINITY;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -794,9 +902,25 @@ static int launch_bf16(dim3 grid, const AttnArgs& a, hipStream_t stream) {
     return SVOO_OK;
 }
 
+template <int D, int RG, int KS>
+static int launch_f32(dim3 grid, const AttnArgs& a, hipStream_t stream) {
+    auto kern = sparse_attn_f32_kernel<D, RG, KS>;
+    constexpr int lds_bytes = F32Lds<D, RG, KS>::BYTES;
+    static unsigned char opted_in[SVOO_MAX_DEVICES];
+    if (!opt_in_dynamic_lds((const void*)kern, lds_bytes, opted_in)) return SVOO_ERR_HIP;
+    hipLaunchKernelGGL(kern, grid, dim3(ATT_THREADS), lds_bytes, stream, a);
+    return SVOO_OK;
+}
+
 // dense = one-block layout: every workgroup reads the same key stream
 static int launch_sparse(const svoo_shape* s, AttnArgs& a, int32_t* tile_prefix, bool dense, hipStream_t stream) {
-    const int bm = s->dtype == SVOO_BF16 ? 32 * (dense ? DENSE_NW : SVOO_SPARSE_NW) : BM_F32;
+    // float32: 64-row tiles with two key splits; 32-row tiles with four when that many 64-row tiles (half of
+    // the query blocks end in a partial one) would leave compute units idle.  One head of 1,024 x 64 in 16
+    // blocks 26 -> 21 us, four 30 -> 22, but eight (192 tiles) 31 -> 34; dense, where all tiles are equally
+    // long, 128 tiles 559 -> 349 us and 256 1,052 -> 686.
+    const long long tiles64 = (long long)s->bh * ((s->n + 63) / 64 + (dense ? 0 : a.kq / 2));
+    const bool few = tiles64 <= (dense ? 256 : 128);
+    const int bm = s->dtype == SVOO_BF16 ? 32 * (dense ? DENSE_NW : SVOO_SPARSE_NW) : (few ? 32 : 64);
     hipLaunchKernelGGL(attn_schedule_kernel, dim3(s->bh), dim3(1024), 0, stream, a.q_offsets, tile_prefix, a.kq, bm,
                        s->n);
     a.tile_prefix = tile_prefix;
@@ -814,9 +938,10 @@ static int launch_sparse(const svoo_shape* s, AttnArgs& a, int32_t* tile_prefix,
         if (st != SVOO_OK) return st;
     } else {
         if (s->d == 128)
-            hipLaunchKernelGGL(sparse_attn_f32_kernel<128>, grid, dim3(ATT_THREADS), 0, stream, a);
+            st = few ? launch_f32<128, 1, 4>(grid, a, stream) : launch_f32<128, 2, 2>(grid, a, stream);
         else
-            hipLaunchKernelGGL(sparse_attn_f32_kernel<64>, grid, dim3(ATT_THREADS), 0, stream, a);
+            st = few ? launch_f32<64, 1, 4>(grid, a, stream) : launch_f32<64, 2, 2>(grid, a, stream);
+        if (st != SVOO_OK) return st;
     }
     return launch_status();
 }

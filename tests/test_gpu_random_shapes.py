@@ -100,3 +100,38 @@ def test_layer_random_small_shapes(seed):
         H.compare_mask(gpu_mask, mask, margins, what)
         ref = so.sparse_attention(q[b], k[b], v[b], lq, lk, gpu_mask, scale)
         H.assert_attn_close(out[b], ref, dtype, what)
+
+
+@pytest.mark.parametrize("d,n,kq,copies", [(128, 257, 5, 40), (64, 400, 9, 24), (128, 63, 2, 90), (64, 129, 1, 70)])
+def test_float32_attention_with_enough_tiles_for_64_row_workgroups(d, n, kq, copies):
+    """The cases above have so few tiles that float32 runs in 32-row workgroups; here the slice is repeated
+    until the 64-row ones are chosen (ragged query tiles and key stages, a query block without keys, row
+    moves through q_perm, log-sum-exp).  Bound: the acceptance bar of float32 inputs (1e-5)."""
+    rng = np.random.default_rng(n)
+    q, k, v = ((1.5 * rng.standard_normal((1, n, d))).astype(np.float32) for _ in range(3))
+    kk = 6
+    lq = rng.integers(0, kq, (1, n)).astype(np.int32)
+    lk = rng.integers(0, kk, (1, n)).astype(np.int32)
+    mask = rng.random((kq, kk)) < 0.6
+    mask[kq - 1] = kq == 1
+    scale = H.scale_of(d)
+    tile = lambda x: H.to_dev(np.tile(x, (copies,) + (1,) * (x.ndim - 1)))
+    cnt = mask.sum(1).astype(np.int32)[None]
+    lst = np.full((1, kq, kk), -1, dtype=np.int32)
+    for r in range(kq):
+        lst[0, r, :cnt[0, r]] = np.nonzero(mask[r])[0]
+    qd, kd, vd = tile(q), tile(k), tile(v)
+    perm_q, q_off, (qs,) = svoo.permute(tile(lq), kq, [qd])
+    _, k_off, (ks, vs) = svoo.permute(tile(lk), kk, [kd, vd])
+    o_sorted, lse = svoo.block_sparse_attn(qs, ks, vs, q_off, k_off, tile(cnt), tile(lst), scale, want_lse=True)
+    out = H.to_np(svoo.unpermute(o_sorted, perm_q))
+    fused = H.to_np(svoo.block_sparse_attn_tokens(qd, perm_q, ks, vs, q_off, k_off, tile(cnt), tile(lst), scale))
+    dense, lse_d = svoo.attn(qd, kd, vd, scale, want_lse=True)
+    H.assert_attn_close(out[0], so.sparse_attention(q[0], k[0], v[0], lq[0], lk[0], mask, scale), "f32", "sparse")
+    H.assert_attn_close(H.to_np(dense)[0], so.dense_attention(q[0], k[0], v[0], scale), "f32", "dense")
+    assert np.array_equal(out, fused)
+    for x in (out, H.to_np(dense), H.to_np(lse), H.to_np(lse_d)):
+        assert (x == x[:1]).all()
+    logits = scale * (q[0].astype(np.float64) @ k[0].T.astype(np.float64))
+    ref = np.log(np.exp(logits).sum(1))
+    assert np.abs(H.to_np(lse_d)[0] - ref).max() <= 1e-5
