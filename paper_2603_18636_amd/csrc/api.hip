@@ -22,14 +22,14 @@ extern "C" int32_t svoo_version(void) { return 200; }
 
 extern "C" size_t svoo_permute_workspace_bytes(const svoo_shape* shape, int32_t n_clusters) {
     if (check_shape(shape, false) != SVOO_OK || n_clusters < 1 || n_clusters > SVOO_MAX_K) return 0;
-    return align_up(sort_scratch_ints(shape->bh, shape->n, n_clusters) * sizeof(int32_t), 256);
+    return align_up(sort_scratch_ints(shape->bh, shape->n, n_clusters, false) * sizeof(int32_t), 256);
 }
 
 extern "C" size_t svoo_workspace_bytes(const svoo_shape* shape) {
     if (check_shape(shape, true) != SVOO_OK) return 0;
     size_t need = cluster_ws_bytes(shape);
     const int kmax = shape->kq > shape->kk ? shape->kq : shape->kk;
-    const size_t sort_need = align_up(sort_scratch_ints(shape->bh, shape->n, kmax) * sizeof(int32_t), 256);
+    const size_t sort_need = align_up(sort_scratch_ints(shape->bh, shape->n, kmax, false) * sizeof(int32_t), 256);
     if (sort_need > need) need = sort_need;
     const size_t attn_need = attn_ws_bytes(shape);
     if (attn_need > need) need = attn_need;

@@ -21,11 +21,6 @@
 // ---------------------------------------------------------------------------------------------
 // small helpers
 // ---------------------------------------------------------------------------------------------
-__global__ void fill_i32_kernel(int32_t* p, int32_t v, size_t count) {
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) p[i] = v;
-}
-
 template <typename T>
 __device__ __forceinline__ double load_as_f64(const T* p);
 template <>
@@ -49,40 +44,37 @@ __device__ __forceinline__ void load_pair<float>(const float* p, double& a, doub
     b = (double)u.y;
 }
 
-// The per-slice words the next assignment accumulates into (degenerate flag, largest row norm, queue
-// length) are cleared by the kernel that precedes it in the stream, not by a launch of their own.
+// The per-slice words the next assignment accumulates into (degenerate flag, largest row norm) are
+// cleared by the kernel that precedes it in the stream, not by a launch of their own.
 __device__ __forceinline__ void clear_words(int32_t* clear, int clear_n) {
     if (clear && blockIdx.x == 0 && blockIdx.y == 0)
         for (int i = threadIdx.x; i < clear_n; i += blockDim.x) clear[i] = 0;
 }
 
-// c64[b, c, :] = x[b, idx[b, c], :]   or   c64 = (double) init_c
+// Start of a run, one launch for up to two sides (blockIdx.z): c64[b, c, :] = x[b, idx[b, c], :], or
+// (double) init_c.  x may be null when init_c is given.
+struct InitSide {
+    const void* x;
+    const int32_t* idx;
+    const float* init_c;
+    double* c64;
+    int k;
+};
 template <typename T>
-__global__ void init_centroids_kernel(const T* __restrict__ x, const int32_t* __restrict__ idx,
-                                      const float* __restrict__ init_c, double* __restrict__ c64, int n, int k,
-                                      int d, int32_t* __restrict__ clear, int clear_n) {
+__global__ void init_centroids_kernel(InitSide s0, InitSide s1, int n, int d, int32_t* __restrict__ clear, int clear_n) {
     const int b = blockIdx.y, c = blockIdx.x, t = threadIdx.x;
-    clear_words(clear, clear_n);
-    if (t >= d) return;
+    if (blockIdx.z == 0) clear_words(clear, clear_n);
+    const InitSide s = blockIdx.z ? s1 : s0;
+    if (t >= d || c >= s.k) return;
     double v;
-    if (init_c) {
-        v = (double)init_c[((size_t)b * k + c) * d + t];
+    if (s.init_c) {
+        v = (double)s.init_c[((size_t)b * s.k + c) * d + t];
     } else {
-        int i = idx[(size_t)b * k + c];
+        int i = s.idx[(size_t)b * s.k + c];
         i = i < 0 ? 0 : (i >= n ? n - 1 : i);
-        v = load_as_f64<T>(x + ((size_t)b * n + i) * d + t);
+        v = load_as_f64<T>((const T*)s.x + ((size_t)b * n + i) * d + t);
     }
-    c64[((size_t)b * k + c) * d + t] = v;
-}
-
-__global__ void f64_to_f32_kernel(const double* __restrict__ src, float* __restrict__ dst, size_t count) {
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) dst[i] = (float)src[i];
-}
-
-__global__ void f32_to_f64_kernel(const float* __restrict__ src, double* __restrict__ dst, size_t count) {
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) dst[i] = (double)src[i];
+    s.c64[((size_t)b * s.k + c) * d + t] = v;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -94,8 +86,8 @@ __global__ void f32_to_f64_kernel(const float* __restrict__ src, double* __restr
 // the instruction's four contraction slots is valid as long as A and B agree); accumulator v of
 // the lane holds C(m0 + kq + 4 v, n0 + i).  AK2 / BK2: the lane's two A / B values are adjacent
 // in memory and 16-byte aligned, so one load fetches both.
-// Used for G = C_opp^T C_opp (needed by slices with a degenerate anchor only; the other two small
-// products of a half-step are inside anchor_w_kernel).
+// Used for G = C_opp^T C_opp (the other two small
+// products of a half-step are inside anchor_w_kernel; only the objective needs this one).
 // ---------------------------------------------------------------------------------------------
 struct GemmArgs {
     const double* a;
@@ -104,7 +96,6 @@ struct GemmArgs {
     int m, n, k;
     long long a_batch, b_batch, c_batch;
     int a_sm, a_sk, b_sk, b_sn;
-    const int32_t* only_if;   // nullable: per-batch flag; the batch is skipped when it is 0
 };
 
 typedef __attribute__((ext_vector_type(4))) double f64x4;
@@ -124,7 +115,6 @@ __device__ __forceinline__ void load_k_pair(const double* __restrict__ row, int 
 
 template <bool AK2, bool BK2>
 __global__ void __launch_bounds__(64) gemm_f64_kernel(GemmArgs g) {
-    if (g.only_if && g.only_if[blockIdx.z] == 0) return;
     const double* a = g.a + (size_t)blockIdx.z * g.a_batch;
     const double* b = g.b + (size_t)blockIdx.z * g.b_batch;
     double* c = g.c + (size_t)blockIdx.z * g.c_batch;
@@ -177,71 +167,33 @@ static void launch_gemm(const GemmArgs& g, int batch, hipStream_t stream) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Tiled float64 contraction of a 64-token tile against the rows of a matrix B [rows_b, D]:
-//   MODE_ARGMAX    B = W; per token the row j maximising the score, lowest j on ties
-//   MODE_QUADFORM  B = G (D x D, symmetric); per token x^T G x
-// 256 threads = 16 x 16; thread (ty, tx) owns tokens 4ty..4ty+3 and B rows 4tx..4tx+3 of the
-// current 64-row block.  The token tile stays in LDS as float64 for the whole kernel.
+// Quadratic form nx^2 = x^T G x of every token (float64), G symmetric D x D: only the objective, a
+// diagnostic, asks for it.  One 64-token tile per workgroup: 256 threads = 16 x 16; thread (ty, tx) owns
+// tokens 4ty..4ty+3 and rows 4tx..4tx+3 of the current 64-row block of G.  The token tile stays in LDS as
+// float64.
 // ---------------------------------------------------------------------------------------------
-enum { MODE_ARGMAX = 0, MODE_QUADFORM = 1 };
-
-template <typename T, int D, int MODE>
+template <typename T, int D>
 __global__ void __launch_bounds__(256)
-token_tile_kernel(const T* __restrict__ x, const double* __restrict__ bmat, int rows_b,
-                  const double* __restrict__ bterm, const int32_t* __restrict__ flags,
-                  const double* __restrict__ nx2, const int32_t* __restrict__ list,
-                  const int32_t* __restrict__ list_count, int32_t force_general, int32_t* __restrict__ labels,
-                  double* __restrict__ quad_out, int n) {
+quadform_kernel(const T* __restrict__ x, const double* __restrict__ gram, double* __restrict__ quad_out, int n) {
     extern __shared__ double smem[];
     double* xs = smem;                 // [D][65]
     double* ws = smem + D * 65;        // [16][65]
     double* red_s = ws + 16 * 65;      // [64][16]
-    int32_t* red_j = (int32_t*)(red_s + 64 * 16);  // [64][16]
-    int32_t* tok = red_j + 64 * 16;    // [64]
-
-    const int b = blockIdx.y;
-    const int count = list ? list_count[b] : n;
-    // nx^2 is only consumed by slices with a degenerate anchor unless the caller forces it
-    if (MODE == MODE_QUADFORM && !force_general && flags[b] == 0) return;
+    const int b = blockIdx.y, t0 = blockIdx.x * 64;
     const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
-    // one tile per workgroup when the grid covers every tile; a smaller grid walks the tiles
-    for (int t0 = blockIdx.x * 64; t0 < count; t0 += gridDim.x * 64) {
-    __syncthreads();   // the previous tile's last LDS reads are done
-    if (tid < 64) {
-        const int p = t0 + tid;
-        tok[tid] = p < count ? (list ? list[(size_t)b * n + p] : p) : -1;
-    }
-    __syncthreads();
-    // stage the token tile: thread -> token tid/4, elements part*4 .. +3 of every 16-chunk
     {
-        const int token = tid / 4, part = tid % 4;
-        const int ti = tok[token];
-        const T* src = x + ((size_t)b * n + (ti < 0 ? 0 : ti)) * D;
+        const int token = tid / 4, part = tid % 4, ti = t0 + token;
+        const T* src = x + ((size_t)b * n + (ti < n ? ti : 0)) * D;
         for (int kc = 0; kc < D; kc += 16)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int col = kc + part * 4 + e;
-                xs[col * 65 + token] = ti < 0 ? 0.0 : load_as_f64<T>(src + col);
+                xs[col * 65 + token] = ti < n ? load_as_f64<T>(src + col) : 0.0;
             }
     }
-    const bool general = MODE == MODE_ARGMAX && (force_general || flags[b] != 0);
-    double nx_tok[4] = {0, 0, 0, 0};
-    if (general) {
-        for (int a = 0; a < 4; ++a) {
-            const int ti = tok[ty * 4 + a];
-            const double v = (ti < 0 || !nx2) ? 1.0 : nx2[(size_t)b * n + ti];   // no nx2: plain k-means scores
-            const double r = sqrt(v > 0.0 ? v : 0.0);
-            nx_tok[a] = r > NORM_FLOOR ? r : NORM_FLOOR;
-        }
-    }
-    double best[4];
-    int bestj[4] = {0, 0, 0, 0};
     double quad[4] = {0, 0, 0, 0};
-    for (int a = 0; a < 4; ++a) best[a] = -INFINITY;
-    const double* bm = bmat + (size_t)b * rows_b * D;
-    const double* bt = bterm ? bterm + (size_t)b * rows_b : nullptr;
-
-    for (int r0 = 0; r0 < rows_b; r0 += 64) {
+    const double* bm = gram + (size_t)b * D * D;
+    for (int r0 = 0; r0 < D; r0 += 64) {
         double acc[4][4];
 #pragma unroll
         for (int a = 0; a < 4; ++a)
@@ -251,10 +203,9 @@ token_tile_kernel(const T* __restrict__ x, const double* __restrict__ bmat, int 
             __syncthreads();
             {
                 const int row = tid / 4, part = tid % 4;
-                const int j = r0 + row;
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    ws[(part * 4 + e) * 65 + row] = j < rows_b ? bm[(size_t)j * D + kc + part * 4 + e] : 0.0;
+                    ws[(part * 4 + e) * 65 + row] = bm[(size_t)(r0 + row) * D + kc + part * 4 + e];
             }
             __syncthreads();
 #pragma unroll
@@ -271,234 +222,99 @@ token_tile_kernel(const T* __restrict__ x, const double* __restrict__ bmat, int 
             }
         }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int j = r0 + tx * 4 + e;
-            if (j < rows_b) {
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-                for (int a = 0; a < 4; ++a) {
-                    if (MODE == MODE_ARGMAX) {
-                        const double val = general ? 2.0 * acc[a][e] - nx_tok[a] * bt[j] : acc[a][e];
-                        if (val > best[a]) {
-                            best[a] = val;
-                            bestj[a] = j;
-                        }
-                    } else {
-                        quad[a] = fma(acc[a][e], xs[j * 65 + ty * 4 + a], quad[a]);
-                    }
-                }
-            }
-        }
+            for (int a = 0; a < 4; ++a) quad[a] = fma(acc[a][e], xs[(r0 + tx * 4 + e) * 65 + ty * 4 + a], quad[a]);
     }
     __syncthreads();
-    for (int a = 0; a < 4; ++a) {
-        red_s[(ty * 4 + a) * 16 + tx] = MODE == MODE_ARGMAX ? best[a] : quad[a];
-        red_j[(ty * 4 + a) * 16 + tx] = bestj[a];
-    }
+    for (int a = 0; a < 4; ++a) red_s[(ty * 4 + a) * 16 + tx] = quad[a];
     __syncthreads();
-    if (tid < 64 && tok[tid] >= 0) {
-        if (MODE == MODE_ARGMAX) {
-            double bv = red_s[tid * 16];
-            int bj = red_j[tid * 16];
-            for (int u = 1; u < 16; ++u) {
-                const double v = red_s[tid * 16 + u];
-                const int j = red_j[tid * 16 + u];
-                if (v > bv || (v == bv && j < bj)) {
-                    bv = v;
-                    bj = j;
-                }
-            }
-            labels[(size_t)b * n + tok[tid]] = bj;
-        } else {
-            double s = 0.0;
-            for (int u = 0; u < 16; ++u) s += red_s[tid * 16 + u];
-            quad_out[(size_t)b * n + tok[tid]] = s;
-        }
+    if (tid < 64 && t0 + tid < n) {
+        double s = 0.0;
+        for (int u = 0; u < 16; ++u) s += red_s[tid * 16 + u];
+        quad_out[(size_t)b * n + t0 + tid] = s;
     }
-    }   // tile loop
 }
 
-// ---------------------------------------------------------------------------------------------
-// Float64 decision for the queued tokens of the matrix-core pre-filter: one workgroup per token
-// (strided over the queue), one thread per centroid (j = tid, tid + 256, ...).  The token sits in
-// LDS; thread j walks column j of the TRANSPOSED score matrix W^T [d, k_own], so that the 256
-// threads read consecutive doubles, and adds the d products in index order -- the same fixed
-// order, hence the same bits, as token_tile_kernel<MODE_ARGMAX>.  No cross-lane sums; one
-// (value, index) reduction per token at the end.
-// ---------------------------------------------------------------------------------------------
-#define LIST_BATCH 32   // loads of W^T in flight per thread
 template <typename T, int D>
-__global__ void __launch_bounds__(256)
-assign_list_kernel(const T* __restrict__ x, const double* __restrict__ wt, int k_own,
-                   const double* __restrict__ bterm, const int32_t* __restrict__ flags,
-                   const double* __restrict__ nx2, const int32_t* __restrict__ list,
-                   const int32_t* __restrict__ list_count, int32_t force_general, int32_t* __restrict__ labels,
-                   int n) {
-    __shared__ double xs[D];
-    __shared__ double best_v[4];
-    __shared__ int32_t best_j[4];
-    const int b = blockIdx.y, tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
-    int count = list_count[b];
-    count = count > n ? n : count;
-    const bool general = force_general || flags[b] != 0;
-    const double* wb = wt + (size_t)b * D * k_own;
-    for (int p = blockIdx.x; p < count; p += gridDim.x) {
-        int ti = list[(size_t)b * n + p];
-        ti = ti < 0 ? 0 : (ti >= n ? n - 1 : ti);
-        if (tid < D) xs[tid] = load_as_f64<T>(x + ((size_t)b * n + ti) * D + tid);
-        double nx = 0.0;
-        if (general) {
-            const double v = nx2 ? nx2[(size_t)b * n + ti] : 1.0;   // no nx2: plain k-means scores
-            const double r = sqrt(v > 0.0 ? v : 0.0);
-            nx = r > NORM_FLOOR ? r : NORM_FLOOR;
-        }
-        __syncthreads();
-        double best = -INFINITY;
-        int bj = 0x7fffffff;
-        for (int j = tid; j < k_own; j += 256) {         // ascending j per thread: ">" keeps the lowest index
-            const double* wc = wb + j;
-            double sum = 0.0;
-            // LIST_BATCH loads in flight, then their products: the fence keeps the compiler from turning the
-            // batch into one load and one wait at a time (the loads are long round trips)
-#pragma unroll 1
-            for (int c0 = 0; c0 < D; c0 += LIST_BATCH) {
-                double wv[LIST_BATCH];
-#pragma unroll
-                for (int u = 0; u < LIST_BATCH; ++u) wv[u] = wc[(size_t)(c0 + u) * k_own];
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int u = 0; u < LIST_BATCH; ++u) sum = fma(xs[c0 + u], wv[u], sum);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            const double val = general ? 2.0 * sum - nx * bterm[(size_t)b * k_own + j] : sum;
-            if (val > best || bj == 0x7fffffff) {
-                best = val;
-                bj = j;
-            }
-        }
-        // (value, index) maximum, lowest index among equal values: within the wave, then across the four
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const double ov = __shfl_xor(best, off);
-            const int oj = __shfl_xor(bj, off);
-            if (oj != 0x7fffffff && (bj == 0x7fffffff || ov > best || (ov == best && oj < bj))) {
-                best = ov;
-                bj = oj;
-            }
-        }
-        if (lane == 0) {
-            best_v[wave] = best;
-            best_j[wave] = bj;
-        }
-        __syncthreads();
-        if (tid == 0) {
-            double bv = best_v[0];
-            int jj = best_j[0];
-            for (int u = 1; u < 4; ++u)
-                if (best_j[u] != 0x7fffffff && (jj == 0x7fffffff || best_v[u] > bv || (best_v[u] == bv && best_j[u] < jj))) {
-                    bv = best_v[u];
-                    jj = best_j[u];
-                }
-            labels[(size_t)b * n + ti] = jj == 0x7fffffff ? 0 : jj;
-        }
-        __syncthreads();
-    }
-}
-
-template <int D>
-static constexpr size_t token_tile_lds() {
-    return (size_t)(D * 65 + 16 * 65 + 64 * 16) * sizeof(double) + (64 * 16 + 64) * sizeof(int32_t);
-}
-
-template <typename T, int D, int MODE>
-static void launch_token_tile(const T* x, const double* bmat, int rows_b, const double* bterm, const int32_t* flags,
-                              const double* nx2, const int32_t* list, const int32_t* list_count, int force_general,
-                              int32_t* labels, double* quad_out, int bh, int n, hipStream_t stream) {
-    auto kern = token_tile_kernel<T, D, MODE>;
+static void launch_quadform(const void* x, const double* gram, double* quad_out, int bh, int n, hipStream_t stream) {
+    auto kern = quadform_kernel<T, D>;
+    constexpr size_t lds = (size_t)(D * 65 + 16 * 65 + 64 * 16) * sizeof(double);
     static unsigned char opted_in[SVOO_MAX_DEVICES];
-    if (!opt_in_dynamic_lds((const void*)kern, (int)token_tile_lds<D>(), opted_in))
+    if (!opt_in_dynamic_lds((const void*)kern, (int)lds, opted_in))
         return;   // the failure stays recorded as HIP's last error: the caller's launch_status() reports it
-    // The quadratic form is skipped by every slice without a degenerate anchor unless it is forced:
-    // a small grid that walks the tiles keeps that common case at a few microseconds.
-    const int tiles = (n + 63) / 64;
-    const bool mostly_skipped = MODE == MODE_QUADFORM && !force_general;
-    dim3 grid(mostly_skipped && tiles > 64 ? 64 : tiles, bh);
-    hipLaunchKernelGGL(kern, grid, dim3(256), token_tile_lds<D>(), stream, x, bmat, rows_b, bterm, flags, nx2, list,
-                       list_count, force_general, labels, quad_out, n);
-}
-
-template <int MODE>
-static void dispatch_token_tile(const svoo_shape* s, const void* x, const double* bmat, int rows_b,
-                                const double* bterm, const int32_t* flags, const double* nx2, const int32_t* list,
-                                const int32_t* list_count, int force_general, int32_t* labels, double* quad_out,
-                                hipStream_t stream) {
-    if (s->dtype == SVOO_BF16) {
-        if (s->d == 128)
-            launch_token_tile<uint16_t, 128, MODE>((const uint16_t*)x, bmat, rows_b, bterm, flags, nx2, list,
-                                                   list_count, force_general, labels, quad_out, s->bh, s->n, stream);
-        else
-            launch_token_tile<uint16_t, 64, MODE>((const uint16_t*)x, bmat, rows_b, bterm, flags, nx2, list,
-                                                  list_count, force_general, labels, quad_out, s->bh, s->n, stream);
-    } else {
-        if (s->d == 128)
-            launch_token_tile<float, 128, MODE>((const float*)x, bmat, rows_b, bterm, flags, nx2, list, list_count,
-                                                force_general, labels, quad_out, s->bh, s->n, stream);
-        else
-            launch_token_tile<float, 64, MODE>((const float*)x, bmat, rows_b, bterm, flags, nx2, list, list_count,
-                                               force_general, labels, quad_out, s->bh, s->n, stream);
-    }
+    hipLaunchKernelGGL(kern, dim3((n + 63) / 64, bh), dim3(256), lds, stream, (const T*)x, gram, quad_out, n);
 }
 
 // ---------------------------------------------------------------------------------------------
-// bf16 matrix-core pre-filter for the assignment (bf16 tokens only).
+// Matrix-core pre-filter of the assignment, and the float64 decision of what it leaves open.
 //
-// W is split into two bf16 terms, W = W_hi + W_lo + r with |r| <= 2^-17 |W| element-wise; tokens
-// are exact in bf16, so  f_j = <x, W_hi_j> + <x, W_lo_j>  (fp32 accumulation on the matrix cores)
+// bf16 tokens: W is split into two bf16 terms, W = W_hi + W_lo + r with |r| <= 2^-17 |W| element-wise;
+// tokens are exact in bf16, so  f_j = <x, W_hi_j> + <x, W_lo_j>  (fp32 accumulation on the matrix cores)
 // satisfies |f_j - <x, W_j>| <= eps ||x|| ||W_j|| with eps covering the split remainder and the
-// fp32 accumulation of 2 d products.  If best - second > 2 eps ||x|| max_j ||W_j|| the fast
-// argmax is the exact argmax; otherwise (and for every token of a slice with a degenerate
-// anchor) the token is queued and the float64 kernel decides.  Equal scores have gap 0 and are
-// therefore always decided by the float64 kernel, which breaks ties towards the lowest index.
-//
-// Tokens are the B operand (one token per lane column, loaded straight from global memory into
-// registers, 64 tokens per wave), W blocks of 32 centroids are the A operand, streamed through
-// LDS with direct global->LDS loads and an XOR swizzle, double buffered.  S^T layout: lane
-// (j, h) holds for token j the centroids 32 cb + 8 (v/4) + 4 h + v%4.
+// fp32 accumulation of 2 d products.  float32 tokens: W rounded to float32, f_j on the float32 matrix
+// instruction; rounding (2^-24) and the accumulation of d products stay within the same eps.  If
+// best - second > 2 eps ||x|| max_j ||W_j|| the fast argmax is the exact argmax; otherwise (and for every
+// token of a slice with a degenerate anchor) the workgroup decides the token in float64.  Equal
+// scores have gap 0 and are therefore always decided in float64, lowest index first.
 // ---------------------------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
-#define ASSIGN_LIST_WGS 256   // workgroups per slice that share the queue of undecided tokens
 #define FAST_EPS 3.1e-5f   // 2^-16 + 256 * 2^-24, twice the analytic bound for d <= 128
 
-// The split of a float64 score matrix for the pre-filter as a launch of its own (k-means, where W is the
-// centroid array itself): 16 rows per workgroup (one wave takes four of them), one atomic per workgroup;
-// also writes W^T in float64
-template <int D>
+// Score matrix in the form the pre-filter reads: two bf16 arrays, or one float32 array over the same bytes.
+template <typename T>
+__device__ __forceinline__ void store_split(double v, size_t o, uint16_t* w_hi, uint16_t* w_lo);
+template <>
+__device__ __forceinline__ void store_split<uint16_t>(double v, size_t o, uint16_t* w_hi, uint16_t* w_lo) {
+    const uint16_t hb = f32_to_bf16((float)v);
+    w_hi[o] = hb;
+    w_lo[o] = f32_to_bf16((float)(v - (double)bf16_to_f32(hb)));
+}
+template <>
+__device__ __forceinline__ void store_split<float>(double v, size_t o, uint16_t* w_hi, uint16_t*) {
+    ((float*)w_hi)[o] = (float)v;
+}
+
+__device__ __forceinline__ float norm_rounded_up(double sq) {
+    float nrm = (float)sqrt(sq);
+    nrm = nrm * 1.0000002f + 1e-37f;
+    return nrm < 3.0e38f ? nrm : 3.0e38f;      // NaN as well
+}
+
+// k-means, where W is the centroid array itself: split of W, W^T in float64, ||c_j||^2 (and its half as
+// float32, zero in the padding up to a multiple of 32 rows), largest row norm.  16 rows per workgroup (one
+// wave takes four of them), one atomic per workgroup.
+template <typename T, int D>
 __global__ void __launch_bounds__(256)
-split_w_kernel(const double* __restrict__ w64, uint16_t* __restrict__ whi, uint16_t* __restrict__ wlo,
-               double* __restrict__ wt, int32_t* __restrict__ wmax_bits, int k_own) {
+kmeans_w_kernel(const double* __restrict__ c64, uint16_t* __restrict__ w_hi, uint16_t* __restrict__ w_lo,
+                double* __restrict__ wt, double* __restrict__ bterm, float* __restrict__ half_sq,
+                int32_t* __restrict__ wmax_bits, int k, int kpad) {
     __shared__ float wave_max[4];
     const int b = blockIdx.y, wave = threadIdx.x / 64, lane = threadIdx.x % 64;
     float mx = 0.f;
     for (int r = 0; r < 4; ++r) {
-        const int j = blockIdx.x * 16 + wave * 4 + r;
-        if (j >= k_own) break;                         // uniform per wave
+        const int j = blockIdx.x * 16 + wave * 4 + r;      // uniform per wave
+        if (j >= k) {
+            if (lane == 0 && j < kpad) half_sq[(size_t)b * kpad + j] = 0.f;
+            continue;
+        }
         double sq = 0.0;
         for (int t = lane; t < D; t += 64) {
-            const size_t o = ((size_t)b * k_own + j) * D + t;
-            const double v = w64[o];
-            const uint16_t hb = f32_to_bf16((float)v);
-            whi[o] = hb;
-            wlo[o] = f32_to_bf16((float)(v - (double)bf16_to_f32(hb)));
-            wt[((size_t)b * D + t) * k_own + j] = v;       // W^T [d, k_own] for the float64 queue kernel
+            const size_t o = ((size_t)b * k + j) * D + t;
+            const double v = c64[o];
+            store_split<T>(v, o, w_hi, w_lo);
+            wt[((size_t)b * D + t) * k + j] = v;
             sq = fma(v, v, sq);
         }
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
-        float nrm = (float)sqrt(sq);
-        nrm = nrm * 1.0000002f + 1e-37f;   // round up
-        if (!(nrm < 3.0e38f)) nrm = 3.0e38f;
-        mx = fmaxf(mx, nrm);
+        if (lane == 0) {
+            bterm[(size_t)b * k + j] = sq;
+            half_sq[(size_t)b * kpad + j] = (float)(0.5 * sq);
+        }
+        mx = fmaxf(mx, norm_rounded_up(sq));
     }
     if (lane == 0) wave_max[wave] = mx;
     __syncthreads();
@@ -512,17 +328,17 @@ split_w_kernel(const double* __restrict__ w64, uint16_t* __restrict__ whi, uint1
 //   P    = C_own[16 rows] C_opp^T          (float64 matrix instruction, tiles kept in LDS)
 //   P^   = rows of P divided by max(||row||, floor);  b_j, degenerate flag
 //   W    = P^ C_opp                        (16 x D)
-//   and, for bf16 tokens, W's two-term bf16 split, W^T and the slice's largest row norm.
+//   and W in the pre-filter's form, W^T, the slice's largest row norm (W itself for the objective only).
 // One launch instead of GEMM, normalisation, GEMM and split; the K_own x K_opp matrix never leaves
 // the chip.  Eight waves: wave w owns the column tiles w, w + 8, .. of each product and two rows of
 // the row-wise steps.  Lane (i, kq) = (lane % 16, lane / 16) feeds row / column i and the contraction
 // indices k0 + 2 kq, k0 + 2 kq + 1 of a block of 8; accumulator v holds row kq + 4 v, column i.
 #define ANCHOR_WAVES 8
-template <int D>
+template <typename T, int D>
 __global__ void __launch_bounds__(64 * ANCHOR_WAVES)
 anchor_w_kernel(const double* __restrict__ c_own, const double* __restrict__ c_opp, int k_own, int k_opp,
                 double* __restrict__ w64, double* __restrict__ bterm, int32_t* __restrict__ flags,
-                uint16_t* __restrict__ whi, uint16_t* __restrict__ wlo, double* __restrict__ wt,
+                uint16_t* __restrict__ w_hi, uint16_t* __restrict__ w_lo, double* __restrict__ wt,
                 int32_t* __restrict__ wmax_bits) {
     extern __shared__ __attribute__((aligned(16))) double anchor_lds[];
     constexpr int NW = ANCHOR_WAVES, RPW = 16 / NW;      // rows per wave in the row-wise steps
@@ -629,7 +445,7 @@ anchor_w_kernel(const double* __restrict__ c_own, const double* __restrict__ c_o
         }
     }
     __syncthreads();
-    // ---- outputs: W, and for the matrix-core pre-filter its bf16 split, W^T and the largest row norm
+    // ---- outputs
     float mx = 0.f;
     for (int r = 0; r < RPW; ++r) {
         const int j = row0 + RPW * wave + r;
@@ -638,39 +454,30 @@ anchor_w_kernel(const double* __restrict__ c_own, const double* __restrict__ c_o
         for (int t = lane; t < D; t += 64) {
             const size_t o = ((size_t)b * k_own + j) * D + t;
             const double v = wtile[(RPW * wave + r) * (D + 2) + t];
-            w64[o] = v;
-            if (whi) {
-                const uint16_t hb = f32_to_bf16((float)v);
-                whi[o] = hb;
-                wlo[o] = f32_to_bf16((float)(v - (double)bf16_to_f32(hb)));
-                wt[((size_t)b * D + t) * k_own + j] = v;
-            }
+            if (w64) w64[o] = v;
+            store_split<T>(v, o, w_hi, w_lo);
+            wt[((size_t)b * D + t) * k_own + j] = v;
             sq = fma(v, v, sq);
         }
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
-        float nrm = (float)sqrt(sq);
-        nrm = nrm * 1.0000002f + 1e-37f;   // round up
-        if (!(nrm < 3.0e38f)) nrm = 3.0e38f;
-        mx = fmaxf(mx, nrm);
+        mx = fmaxf(mx, norm_rounded_up(sq));
     }
-    if (whi) {
-        if (lane == 0) wave_max[wave] = mx;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            float m = wave_max[0];
+    if (lane == 0) wave_max[wave] = mx;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float m = wave_max[0];
 #pragma unroll
-            for (int w = 1; w < NW; ++w) m = fmaxf(m, wave_max[w]);
-            atomicMax(&wmax_bits[b], __float_as_int(m));   // non-negative floats order like their bit patterns
-        }
+        for (int w = 1; w < NW; ++w) m = fmaxf(m, wave_max[w]);
+        atomicMax(&wmax_bits[b], __float_as_int(m));   // non-negative floats order like their bit patterns
     }
 }
 
-template <int D>
+template <typename T, int D>
 static void launch_anchor_w(const double* c_own, const double* c_opp, int k_own, int k_opp, int bh, double* w64,
-                            double* bterm, int32_t* flags, uint16_t* whi, uint16_t* wlo, double* wt,
+                            double* bterm, int32_t* flags, uint16_t* w_hi, uint16_t* w_lo, double* wt,
                             int32_t* wmax_bits, hipStream_t stream) {
-    auto kern = anchor_w_kernel<D>;
+    auto kern = anchor_w_kernel<T, D>;
     const int pitch = ((k_opp + 31) / 32) * 32 + 2;
     const int lds = (16 * pitch + 16 * (D + 2)) * (int)sizeof(double);
     // the LDS need grows with k_opp: opt in once for the largest (k_opp = 1024) so that the flag holds for every call
@@ -679,30 +486,61 @@ static void launch_anchor_w(const double* c_own, const double* c_opp, int k_own,
     if (!opt_in_dynamic_lds((const void*)kern, lds_max, opted_in))
         return;   // stays recorded as HIP's last error: the caller's launch_status() reports it
     hipLaunchKernelGGL(kern, dim3((k_own + 15) / 16, bh), dim3(64 * ANCHOR_WAVES), lds, stream, c_own, c_opp, k_own,
-                       k_opp, w64, bterm, flags, whi, wlo, wt, wmax_bits);
+                       k_opp, w64, bterm, flags, w_hi, w_lo, wt, wmax_bits);
 }
 
+struct AssignArgs {
+    const void* x;
+    const uint16_t* w_hi;          // bf16: high term; float32: W
+    const uint16_t* w_lo;          // bf16: low term
+    const double* wt;              // W^T [d, k_own]
+    const double* bterm;           // anchor terms b_j (k-means: ||c_j||^2)
+    const double* c_opp;           // [k_opp, d]: token norms of slices with a degenerate anchor
+    const float* half_sq;          // k-means: ||c_j||^2 / 2, padded to a multiple of 32 per slice
+    const int32_t* wmax_bits;
+    const int32_t* flags;
+    int32_t* labels;
+    int32_t* chunk_hist;           // nullable: label counts of this workgroup's ASSIGN_CHUNK tokens
+    int n, k_own, k_opp;
+};
+
+// Tokens are the B operand (one token per lane column, loaded straight from global memory into
+// registers, 64 tokens per wave), W blocks of 32 centroids are the A operand, streamed through
+// LDS with direct global->LDS loads and an XOR swizzle, double buffered.  S^T layout: lane
+// (j, h) holds for token j the centroids 32 cb + 8 (v/4) + 4 h + v%4.
+//
+// The tokens the pre-filter leaves open (0.3 per workgroup at 12 x 75,600 in the first iteration, fewer
+// later) are decided at the end by all 256 threads, a centroid each, with the other workgroup of the compute unit
+// running beside: as a launch of its own over a global queue that was 20-24 us per half-step, a fifth of it.
+// The workgroup also knows the label counts of its ASSIGN_CHUNK tokens, which saves the sort its pass over the
+// labels.
+//
 // BIAS: score_j = <x, W_j> - half_sq[j] (k-means on raw rows: W = C, half_sq = ||c_j||^2 / 2, one
 // float per centroid, slices padded to a multiple of 32 entries); the margin then also covers the
 // float32 rounding of the bias and of the subtraction.
-template <int D, bool BIAS>
+#define LIST_BATCH 32   // loads of W^T in flight per thread
+template <typename T, int D, bool BIAS>
 __global__ void __launch_bounds__(256, 2)
-assign_mfma_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ whi, const uint16_t* __restrict__ wlo,
-                   const int32_t* __restrict__ wmax_bits, const int32_t* __restrict__ flags,
-                   const float* __restrict__ half_sq, int32_t* __restrict__ labels, int32_t* __restrict__ list,
-                   int32_t* __restrict__ list_count, int n, int k_own) {
-    constexpr int DC = D / 16, CPR = D / 8, ROWB = D * 2;
-    constexpr int HALF = 32 * ROWB;          // one 32-centroid block of W_hi (or W_lo)
+assign_kernel(AssignArgs a) {
+    constexpr bool BF16 = std::is_same<T, uint16_t>::value;
+    constexpr int ROWB = D * (int)sizeof(T), CPR = ROWB / 16, DC = ROWB / 32;
+    constexpr int BLOCK = 32 * ROWB;         // 32 centroids of one term
+    constexpr int TERMS = BF16 ? 2 : 1;
     constexpr int RPL = 64 / CPR;            // rows per wave-load
-    constexpr int LPW = (32 / RPL) / 4;      // wave-loads per wave for one half block
-    __shared__ __attribute__((aligned(1024))) unsigned char wl[2 * 2 * HALF];   // [buf][hi|lo][32][ROWB]
+    constexpr int LPW = (32 / RPL) / 4;      // wave-loads per wave for one block of one term
+    static_assert(LPW >= 1 && ASSIGN_CHUNK == 256, "geometry");
+    __shared__ __attribute__((aligned(1024))) unsigned char wl[2 * TERMS * BLOCK];   // [buf][term][32][ROWB]
+    __shared__ int32_t lab[256], open[256], n_open;
+    const int n = a.n, k_own = a.k_own;
     const int b = blockIdx.y, tid = threadIdx.x, lane = tid % 64, j = lane % 32, h = lane / 32;
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64);     // uniform: what derives from it stays scalar
-    const int t0 = blockIdx.x * 256 + 64 * wave;
-    const unsigned char* whb = (const unsigned char*)whi + (size_t)b * k_own * ROWB;
-    const unsigned char* wlb = (const unsigned char*)wlo + (size_t)b * k_own * ROWB;
+    const int g0 = blockIdx.x * 256, t0 = g0 + 64 * wave;
+    const T* x = (const T*)a.x + (size_t)b * n * D;
+    const unsigned char* whb = (const unsigned char*)a.w_hi + (size_t)b * k_own * ROWB;
+    const unsigned char* wlb = (const unsigned char*)a.w_lo + (size_t)b * k_own * ROWB;
     const int n_blocks = (k_own + 31) / 32;
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(wl));
+    if (tid == 0) n_open = 0;
 
     auto issue_block = [&](int cb, int buf) {
 #pragma unroll
@@ -712,9 +550,9 @@ assign_mfma_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ 
             row = row < k_own ? row : k_own - 1;
             const int chunk = (lane % CPR) ^ (rl % CPR);
             const uint32_t goff = (uint32_t)row * ROWB + chunk * 16;
-            const uint32_t loff = lds0 + buf * 2 * HALF + (wave * LPW + i) * RPL * ROWB;
+            const uint32_t loff = lds0 + buf * TERMS * BLOCK + (wave * LPW + i) * RPL * ROWB;
             load_rows_to_lds_16(goff, whb, loff);
-            load_rows_to_lds_16(goff, wlb, loff + HALF);
+            if (BF16) load_rows_to_lds_16(goff, wlb, loff + BLOCK);
         }
     };
     issue_block(0, 0);
@@ -722,22 +560,26 @@ assign_mfma_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ 
     // token fragments and squared norms (the norm only scales the margin below, whose constant has a factor
     // of two in hand: the packed dot product's own rounding does not matter).  Rows past the end are read
     // from the last token instead of being predicated; their results are never stored.
-    bf16x8_t xf[2][DC];
+    uint4 xf[2][DC];
     float xn2[2];
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb) {
         const int tok = t0 + 32 * tb + j;
-        const uint4* src = (const uint4*)(x + ((size_t)b * n + (tok < n ? tok : n - 1)) * D);
+        const uint4* src = (const uint4*)(x + (size_t)(tok < n ? tok : n - 1) * D);
         float acc = 0.f;
 #pragma unroll
         for (int c = 0; c < DC; ++c) {
             const uint4 u = src[2 * c + h];
-            xf[tb][c] = __builtin_bit_cast(bf16x8_t, u);
+            xf[tb][c] = u;
             const uint32_t wds[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const bf16x2_t pr = __builtin_bit_cast(bf16x2_t, wds[e]);
-                acc = __builtin_amdgcn_fdot2_f32_bf16(pr, pr, acc, false);
+                if constexpr (BF16) {
+                    const bf16x2_t pr = __builtin_bit_cast(bf16x2_t, wds[e]);
+                    acc = __builtin_amdgcn_fdot2_f32_bf16(pr, pr, acc, false);
+                } else {
+                    acc = fmaf(__uint_as_float(wds[e]), __uint_as_float(wds[e]), acc);
+                }
             }
         }
         const int ai = __float_as_int(acc);
@@ -751,7 +593,7 @@ assign_mfma_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ 
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
-        for (int c = 0; c < DC; ++c) asm volatile("" ::"v"(xf[tb][c]));
+        for (int c = 0; c < DC; ++c) asm volatile("" ::"v"(xf[tb][c].x), "v"(xf[tb][c].y), "v"(xf[tb][c].z), "v"(xf[tb][c].w));
 
     float best[2] = {-INFINITY, -INFINITY}, second[2] = {-INFINITY, -INFINITY};
     int bidx[2] = {0, 0}, lidx[2] = {0, 0};
@@ -760,7 +602,7 @@ assign_mfma_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ 
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (cb + 1 < n_blocks) issue_block(cb + 1, buf ^ 1);
-        const unsigned char* base = wl + buf * 2 * HALF;
+        const unsigned char* base = wl + buf * TERMS * BLOCK;
         f32x16_t acc[2];
 #pragma unroll
         for (int tb = 0; tb < 2; ++tb)
@@ -768,17 +610,30 @@ assign_mfma_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ 
             for (int v = 0; v < 16; ++v) acc[tb][v] = 0.f;
 #pragma unroll
         for (int c = 0; c < DC; ++c) {
-            const bf16x8_t ah = __builtin_bit_cast(bf16x8_t, *(const uint4*)(base + koff[c]));
-            const bf16x8_t al = __builtin_bit_cast(bf16x8_t, *(const uint4*)(base + HALF + koff[c]));
+            const uint4 wh = *(const uint4*)(base + koff[c]);
+            if constexpr (BF16) {
+                const bf16x8_t ah = __builtin_bit_cast(bf16x8_t, wh);
+                const bf16x8_t al = __builtin_bit_cast(bf16x8_t, *(const uint4*)(base + BLOCK + koff[c]));
 #pragma unroll
-            for (int tb = 0; tb < 2; ++tb) {
-                acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, xf[tb][c], acc[tb], 0, 0, 0);
-                acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, xf[tb][c], acc[tb], 0, 0, 0);
+                for (int tb = 0; tb < 2; ++tb) {
+                    const bf16x8_t xv = __builtin_bit_cast(bf16x8_t, xf[tb][c]);
+                    acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, xv, acc[tb], 0, 0, 0);
+                    acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, xv, acc[tb], 0, 0, 0);
+                }
+            } else {
+                const float wv[4] = {__uint_as_float(wh.x), __uint_as_float(wh.y), __uint_as_float(wh.z), __uint_as_float(wh.w)};
+#pragma unroll
+                for (int tb = 0; tb < 2; ++tb) {
+                    const uint4 u = xf[tb][c];
+                    const float xv[4] = {__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w)};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[tb] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[e], xv[e], acc[tb], 0, 0, 0);
+                }
             }
         }
         const int cbase = 32 * cb;      // uniform; the lane's own offset 4 h is added to the winner once, after the loop
         if (BIAS) {
-            const float4* hb = (const float4*)(half_sq + (size_t)b * (32 * n_blocks) + cbase + 4 * h);
+            const float4* hb = (const float4*)(a.half_sq + (size_t)b * (32 * n_blocks) + cbase + 4 * h);
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const float4 t = hb[2 * g];
@@ -819,8 +674,8 @@ assign_mfma_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ 
     }
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb) bidx[tb] += 4 * h;
-    const float wmax = __int_as_float(wmax_bits[b]);
-    const bool degenerate = flags[b] != 0;
+    const float wmax = __int_as_float(a.wmax_bits[b]);
+    const bool degenerate = !BIAS && a.flags[b] != 0;
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb) {
         auto rb = __builtin_amdgcn_permlane32_swap(__float_as_int(best[tb]), __float_as_int(best[tb]), false, false);
@@ -831,19 +686,147 @@ assign_mfma_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ 
         const float s0 = __int_as_float(rs[0]), s1 = __int_as_float(rs[1]);
         const float fb = fmaxf(b0, b1);
         const float fs = fmaxf(fminf(b0, b1), fmaxf(s0, s1));
-        const int fi = b0 >= b1 ? (int)ri[0] : (int)ri[1];
+        int fi = b0 >= b1 ? (int)ri[0] : (int)ri[1];
+        fi = fi < k_own ? fi : k_own - 1;                  // scores that are not numbers may leave any index
         const int tok = t0 + 32 * tb + j;
-        if (h == 0 && tok < n) {
+        if (h == 0) {
             const float xw = sqrtf(xn2[tb]) * wmax;
             const float margin = BIAS ? 2.0f * (FAST_EPS * xw + 2.4e-7f * (0.5f * wmax * wmax + xw))   // 2^-22
                                       : 2.0f * FAST_EPS * xw;
             const bool sure = (fb - fs) > margin;          // false for NaN as well
-            labels[(size_t)b * n + tok] = fi;
-            if (degenerate || !sure) {
-                const int pos = atomicAdd(&list_count[b], 1);
-                if (pos >= 0 && pos < n) list[(size_t)b * n + pos] = tok;   // always true when the counter started at zero
+            lab[tok - g0] = fi;
+            if ((degenerate || !sure) && tok < n) open[atomicAdd(&n_open, 1)] = tok - g0;
+        }
+    }
+    __syncthreads();        // labels and the list of open tokens are there; nobody reads wl any more
+
+    // ---- float64 decisions, TB tokens at a time.  The tokens sit in LDS; thread j walks column j of W^T, so
+    // that the threads read consecutive doubles, and adds the d products in index order: fixed, no
+    // cross-lane sums.  One (value, index) reduction per token at the end.
+    const int count = n_open;
+    double* xs = (double*)wl;                              // [TB][D]
+    double* red_v = xs + 4 * D;                            // [4 waves][TB]
+    int32_t* red_j = (int32_t*)(red_v + 16);               // [4 waves][TB]
+    auto decide = [&](auto tb_c, int p) {
+        constexpr int TB = decltype(tb_c)::value;
+        for (int e = tid; e < TB * D; e += 256) xs[e] = load_as_f64<T>(x + (size_t)(g0 + open[p + e / D]) * D + e % D);
+        __syncthreads();
+        double nx[TB];
+#pragma unroll
+        for (int t = 0; t < TB; ++t) nx[t] = 1.0;          // k-means scores
+        if (degenerate) {                                  // nx = ||x C_opp^T||: a row of C_opp per thread
+            double s2[TB];
+#pragma unroll
+            for (int t = 0; t < TB; ++t) s2[t] = 0.0;
+            for (int c = tid; c < a.k_opp; c += 256) {
+                const double* row = a.c_opp + ((size_t)b * a.k_opp + c) * D;
+                double dot[TB];
+#pragma unroll
+                for (int t = 0; t < TB; ++t) dot[t] = 0.0;
+                for (int e = 0; e < D; ++e)
+#pragma unroll
+                    for (int t = 0; t < TB; ++t) dot[t] = fma(xs[t * D + e], row[e], dot[t]);
+#pragma unroll
+                for (int t = 0; t < TB; ++t) s2[t] = fma(dot[t], dot[t], s2[t]);
+            }
+#pragma unroll
+            for (int t = 0; t < TB; ++t) {
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1) s2[t] += __shfl_xor(s2[t], off);
+                if (lane == 0) red_v[wave * TB + t] = s2[t];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int t = 0; t < TB; ++t) {
+                const double r = sqrt(red_v[t] + red_v[TB + t] + red_v[2 * TB + t] + red_v[3 * TB + t]);
+                nx[t] = r > NORM_FLOOR ? r : NORM_FLOOR;
+            }
+            __syncthreads();
+        }
+        double best_v[TB];
+        int best_j[TB];
+#pragma unroll
+        for (int t = 0; t < TB; ++t) {
+            best_v[t] = -INFINITY;
+            best_j[t] = 0x7fffffff;
+        }
+        for (int c = tid; c < k_own; c += 256) {           // ascending per thread: ">" keeps the lowest index
+            const double* wc = a.wt + (size_t)b * D * k_own + c;
+            double sum[TB];
+#pragma unroll
+            for (int t = 0; t < TB; ++t) sum[t] = 0.0;
+            // LIST_BATCH loads in flight, then their products: the fence keeps the compiler from turning the
+            // batch into one load and one wait at a time (the loads are long round trips)
+#pragma unroll 1
+            for (int c0 = 0; c0 < D; c0 += LIST_BATCH) {
+                double wv[LIST_BATCH];
+#pragma unroll
+                for (int u = 0; u < LIST_BATCH; ++u) wv[u] = wc[(size_t)(c0 + u) * k_own];
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < LIST_BATCH; ++u)
+#pragma unroll
+                    for (int t = 0; t < TB; ++t) sum[t] = fma(xs[t * D + c0 + u], wv[u], sum[t]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            const bool general = BIAS || degenerate;
+            const double bj = general ? a.bterm[(size_t)b * k_own + c] : 0.0;
+#pragma unroll
+            for (int t = 0; t < TB; ++t) {
+                const double val = general ? 2.0 * sum[t] - nx[t] * bj : sum[t];
+                if (val > best_v[t] || best_j[t] == 0x7fffffff) {
+                    best_v[t] = val;
+                    best_j[t] = c;
+                }
             }
         }
+        // (value, index) maximum, lowest index among equal values: within the wave, then across the four
+        auto wins = [](double ov, int oj, double v, int jj) {
+            return oj != 0x7fffffff && (jj == 0x7fffffff || ov > v || (ov == v && oj < jj));
+        };
+#pragma unroll
+        for (int t = 0; t < TB; ++t) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                const double ov = __shfl_xor(best_v[t], off);
+                const int oj = __shfl_xor(best_j[t], off);
+                if (wins(ov, oj, best_v[t], best_j[t])) {
+                    best_v[t] = ov;
+                    best_j[t] = oj;
+                }
+            }
+            if (lane == 0) {
+                red_v[wave * TB + t] = best_v[t];
+                red_j[wave * TB + t] = best_j[t];
+            }
+        }
+        __syncthreads();
+        if (tid < TB) {
+            double bv = red_v[tid];
+            int jj = red_j[tid];
+            for (int u = 1; u < 4; ++u)
+                if (wins(red_v[u * TB + tid], red_j[u * TB + tid], bv, jj)) {
+                    bv = red_v[u * TB + tid];
+                    jj = red_j[u * TB + tid];
+                }
+            lab[open[p + tid]] = jj == 0x7fffffff ? 0 : jj;
+        }
+        __syncthreads();
+    };
+    int p = 0;
+    for (; p + 4 <= count; p += 4) decide(std::integral_constant<int, 4>{}, p);
+    for (; p < count; ++p) decide(std::integral_constant<int, 1>{}, p);
+
+    // ---- labels and their counts
+    if (g0 + tid < n) a.labels[(size_t)b * n + g0 + tid] = lab[tid];
+    if (a.chunk_hist) {
+        int32_t* hist = (int32_t*)(wl + 6144);             // behind the decision's scratch
+        for (int c = tid; c < k_own; c += 256) hist[c] = 0;
+        __syncthreads();
+        if (g0 + tid < n) atomicAdd(&hist[lab[tid]], 1);
+        __syncthreads();
+        int32_t* out = a.chunk_hist + ((size_t)b * gridDim.x + blockIdx.x) * k_own;
+        for (int c = tid; c < k_own; c += 256) out[c] = hist[c];
     }
 }
 
@@ -998,25 +981,6 @@ objective_sum_kernel(const double* __restrict__ terms, double* __restrict__ out,
 // Independent k-means on raw rows: argmin_j ||x - c_j||^2 = argmax_j 2 <x, c_j> - ||c_j||^2, i.e.
 // the same scoring kernels with W = C, anchor term ||c_j||^2 and token norm 1.
 // ---------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(128)
-kmeans_prep_kernel(const double* __restrict__ c64, double* __restrict__ bterm, float* __restrict__ half_sq, int k,
-                   int kpad, int d) {
-    __shared__ double red[128];
-    const int b = blockIdx.y, j = blockIdx.x, t = threadIdx.x;
-    double v = 0.0;
-    if (j < k && t < d) v = c64[((size_t)b * k + j) * d + t];
-    red[t] = v * v;
-    __syncthreads();
-    for (int s = 64; s > 0; s >>= 1) {
-        if (t < s) red[t] += red[t + s];
-        __syncthreads();
-    }
-    if (t == 0) {
-        if (j < k) bterm[(size_t)b * k + j] = red[0];
-        half_sq[(size_t)b * kpad + j] = j < k ? (float)(0.5 * red[0]) : 0.f;
-    }
-}
-
 // terms[i] = ||x_i - c_{L_i}||^2, summed term by term
 template <typename T>
 __global__ void __launch_bounds__(256)
@@ -1041,9 +1005,9 @@ kmeans_inertia_terms_kernel(const T* __restrict__ x, const double* __restrict__ 
 // ---------------------------------------------------------------------------------------------
 struct ClusterWs {
     double *c64q, *c64k, *w64, *wt64, *gram, *bterm, *nx2, *terms;
-    uint16_t *whi, *wlo;
+    uint16_t *w_hi, *w_lo;
     float* half_sq;
-    int32_t *flags, *wmax_bits, *list_count, *list, *perm, *offsets, *chunk_hist;
+    int32_t *flags, *wmax_bits, *perm, *offsets, *chunk_hist;
     size_t bytes;
 };
 
@@ -1059,74 +1023,55 @@ static ClusterWs carve_cluster_ws(const svoo_shape* s, void* ws) {
     w.bterm = c.take<double>(bh * kmax);
     w.nx2 = c.take<double>(bh * (size_t)s->n);
     w.terms = c.take<double>(bh * (size_t)s->n);
-    w.whi = c.take<uint16_t>(bh * kmax * s->d);
-    w.wlo = c.take<uint16_t>(bh * kmax * s->d);
+    w.w_hi = c.take<uint16_t>(2 * bh * kmax * s->d);      // two bf16 terms, or one float32 array
+    w.w_lo = w.w_hi + bh * kmax * s->d;
     w.half_sq = c.take<float>(bh * ((kmax + 31) / 32 * 32));
-    w.flags = c.take<int32_t>(3 * bh);      // flags | wmax_bits | list_count, cleared by one fill
+    w.flags = c.take<int32_t>(2 * bh);      // flags | wmax_bits, cleared together
     w.wmax_bits = w.flags + bh;
-    w.list_count = w.flags + 2 * bh;
-    w.list = c.take<int32_t>(bh * (size_t)s->n);
     w.perm = c.take<int32_t>(bh * (size_t)s->n);
     w.offsets = c.take<int32_t>(bh * (kmax + 1));
-    w.chunk_hist = c.take<int32_t>(sort_scratch_ints(s->bh, s->n, (int)kmax));
+    w.chunk_hist = c.take<int32_t>(sort_scratch_ints(s->bh, s->n, (int)kmax, true));
     w.bytes = c.used;
     return w;
 }
 
 size_t cluster_ws_bytes(const svoo_shape* s) { return carve_cluster_ws(s, nullptr).bytes; }
 
-// One half-step's assignment: labels of x against own-side centroids through opp-side anchors.
-// want_nx2: also fill w.nx2 (needed for the objective) even if no anchor is degenerate.
-// words_cleared: the preceding kernel of the stream has zeroed w.flags / wmax_bits / list_count.
+template <typename T, int D, bool BIAS>
+static void launch_assign(const svoo_shape* s, const ClusterWs& w, const void* x, const double* c_opp, int k_own,
+                          int k_opp, int32_t* labels, int32_t* chunk_hist, hipStream_t stream) {
+    AssignArgs a = {x, w.w_hi, w.w_lo, w.wt64, w.bterm, c_opp, w.half_sq, w.wmax_bits, w.flags, labels, chunk_hist,
+                    s->n, k_own, k_opp};
+    hipLaunchKernelGGL((assign_kernel<T, D, BIAS>), dim3(sort_chunks(s->n, true), s->bh), dim3(256), 0, stream, a);
+}
+
+// One half-step's assignment: labels of x against own-side centroids through opp-side anchors; chunk_hist
+// (nullable) receives the label counts the sort starts from.  want_objective: also fill w.w64 and w.nx2.
+// The preceding kernel of the stream has zeroed w.flags and w.wmax_bits.
+template <typename T, int D>
+static void assign_side_t(const svoo_shape* s, const ClusterWs& w, const void* x, const double* c_own, int k_own,
+                          const double* c_opp, int k_opp, int32_t* labels, int32_t* chunk_hist, bool want_objective,
+                          hipStream_t stream) {
+    const int bh = s->bh;
+    launch_anchor_w<T, D>(c_own, c_opp, k_own, k_opp, bh, want_objective ? w.w64 : nullptr, w.bterm, w.flags, w.w_hi,
+                          w.w_lo, w.wt64, w.wmax_bits, stream);
+    if (want_objective) {      // G[a, b] = sum_c c_opp[c, a] * c_opp[c, b], nx^2 = x^T G x
+        GemmArgs g3 = {c_opp, c_opp, w.gram, D, D, k_opp, (long long)k_opp * D, (long long)k_opp * D, (long long)D * D,
+                       1, D, D, 1};
+        launch_gemm(g3, bh, stream);
+        launch_quadform<T, D>(x, w.gram, w.nx2, bh, s->n, stream);
+    }
+    launch_assign<T, D, false>(s, w, x, c_opp, k_own, k_opp, labels, chunk_hist, stream);
+}
+
 static int assign_side(const svoo_shape* s, const ClusterWs& w, const void* x, const double* c_own, int k_own,
-                       const double* c_opp, int k_opp, int32_t* labels, bool want_nx2, bool words_cleared,
+                       const double* c_opp, int k_opp, int32_t* labels, int32_t* chunk_hist, bool want_objective,
                        hipStream_t stream) {
-    const int d = s->d, bh = s->bh;
-    if (!words_cleared)
-        hipLaunchKernelGGL(fill_i32_kernel, dim3((3 * bh + 255) / 256), dim3(256), 0, stream, w.flags, 0,
-                           (size_t)3 * bh);
-    // W = Norm(C_own C_opp^T) C_opp with b_j and the degenerate flags; for bf16 tokens also the split of W,
-    // its transpose and the largest row norm for the matrix-core pre-filter
-    {
-        const bool bf16 = s->dtype == SVOO_BF16;
-        uint16_t* whi = bf16 ? w.whi : nullptr;
-        if (d == 128)
-            launch_anchor_w<128>(c_own, c_opp, k_own, k_opp, bh, w.w64, w.bterm, w.flags, whi, w.wlo, w.wt64,
-                                 w.wmax_bits, stream);
-        else
-            launch_anchor_w<64>(c_own, c_opp, k_own, k_opp, bh, w.w64, w.bterm, w.flags, whi, w.wlo, w.wt64,
-                                w.wmax_bits, stream);
-    }
-    // G[a, b] = sum_c c_opp[c, a] * c_opp[c, b]
-    // (only slices with a degenerate anchor need it, unless the objective is wanted)
-    GemmArgs g3 = {c_opp, c_opp, w.gram, d, d, k_opp, (long long)k_opp * d, (long long)k_opp * d, (long long)d * d,
-                   1, d, d, 1, want_nx2 ? nullptr : w.flags};
-    launch_gemm(g3, bh, stream);
-    // nx^2 = x^T G x: every workgroup of a slice without degenerate anchors exits at once unless the
-    // objective wants it, so the launch sequence never depends on device-side flags.
-    dispatch_token_tile<MODE_QUADFORM>(s, x, w.gram, d, nullptr, w.flags, nullptr, nullptr, nullptr, want_nx2 ? 1 : 0,
-                                       nullptr, w.nx2, stream);
-    if (s->dtype == SVOO_BF16) {
-        // matrix-core pre-filter decides the clear cases; float64 decides the queued rest
-        dim3 agrid((s->n + 255) / 256, bh);
-        if (d == 128) {
-            hipLaunchKernelGGL((assign_mfma_kernel<128, false>), agrid, dim3(256), 0, stream, (const uint16_t*)x, w.whi,
-                               w.wlo, w.wmax_bits, w.flags, nullptr, labels, w.list, w.list_count, s->n, k_own);
-        } else {
-            hipLaunchKernelGGL((assign_mfma_kernel<64, false>), agrid, dim3(256), 0, stream, (const uint16_t*)x, w.whi,
-                               w.wlo, w.wmax_bits, w.flags, nullptr, labels, w.list, w.list_count, s->n, k_own);
-        }
-        dim3 lgrid(s->n < ASSIGN_LIST_WGS ? s->n : ASSIGN_LIST_WGS, bh);
-        if (d == 128)
-            hipLaunchKernelGGL((assign_list_kernel<uint16_t, 128>), lgrid, dim3(256), 0, stream, (const uint16_t*)x,
-                               w.wt64, k_own, w.bterm, w.flags, w.nx2, w.list, w.list_count, 0, labels, s->n);
-        else
-            hipLaunchKernelGGL((assign_list_kernel<uint16_t, 64>), lgrid, dim3(256), 0, stream, (const uint16_t*)x,
-                               w.wt64, k_own, w.bterm, w.flags, w.nx2, w.list, w.list_count, 0, labels, s->n);
-    } else {
-        dispatch_token_tile<MODE_ARGMAX>(s, x, w.w64, k_own, w.bterm, w.flags, w.nx2, nullptr, nullptr, 0, labels,
-                                         nullptr, stream);
-    }
+    auto go = [&](auto fn) { fn(s, w, x, c_own, k_own, c_opp, k_opp, labels, chunk_hist, want_objective, stream); };
+    if (s->dtype == SVOO_BF16)
+        s->d == 128 ? go(assign_side_t<uint16_t, 128>) : go(assign_side_t<uint16_t, 64>);
+    else
+        s->d == 128 ? go(assign_side_t<float, 128>) : go(assign_side_t<float, 64>);
     return launch_status();
 }
 
@@ -1142,15 +1087,14 @@ static void launch_objective(const svoo_shape* s, const ClusterWs& w, const void
     hipLaunchKernelGGL(objective_sum_kernel, dim3(s->bh), dim3(1024), 0, stream, w.terms, out, s->n, out_stride);
 }
 
-static void launch_init_centroids(const svoo_shape* s, const void* x, const int32_t* idx, const float* init_c,
-                                  double* c64, int k, int32_t* clear, int clear_n, hipStream_t stream) {
-    dim3 grid(k, s->bh);
+// s1.k = 0: one side only
+static void launch_init_centroids(const svoo_shape* s, const InitSide& s0, const InitSide& s1, int32_t* clear,
+                                  int clear_n, hipStream_t stream) {
+    dim3 grid(s0.k > s1.k ? s0.k : s1.k, s->bh, s1.k > 0 ? 2 : 1);
     if (s->dtype == SVOO_BF16)
-        hipLaunchKernelGGL(init_centroids_kernel<uint16_t>, grid, dim3(128), 0, stream, (const uint16_t*)x, idx, init_c,
-                           c64, s->n, k, s->d, clear, clear_n);
+        hipLaunchKernelGGL(init_centroids_kernel<uint16_t>, grid, dim3(128), 0, stream, s0, s1, s->n, s->d, clear, clear_n);
     else
-        hipLaunchKernelGGL(init_centroids_kernel<float>, grid, dim3(128), 0, stream, (const float*)x, idx, init_c, c64,
-                           s->n, k, s->d, clear, clear_n);
+        hipLaunchKernelGGL(init_centroids_kernel<float>, grid, dim3(128), 0, stream, s0, s1, s->n, s->d, clear, clear_n);
 }
 
 // perm_* / *_offsets (all four or none): the cluster-order layout of the returned labels, which the
@@ -1172,34 +1116,34 @@ static int cocluster_impl(const svoo_shape* shape, const void* q, const void* k,
     if (ws_bytes < w.bytes) return SVOO_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t stream = (hipStream_t)hip_stream;
 
-    launch_init_centroids(shape, q, init_q_idx, init_cq, w.c64q, shape->kq, nullptr, 0, stream);
-    launch_init_centroids(shape, k, init_k_idx, init_ck, w.c64k, shape->kk, w.flags, 3 * shape->bh, stream);
+    launch_init_centroids(shape, InitSide{q, init_q_idx, init_cq, w.c64q, shape->kq},
+                          InitSide{k, init_k_idx, init_ck, w.c64k, shape->kk}, w.flags, 2 * shape->bh, stream);
     for (int it = 0; it < iters; ++it) {
         const bool last = it == iters - 1;
         // Step A: keys against query anchors (old C_q), own centroids old C_k.
-        st = assign_side(shape, w, k, w.c64k, shape->kk, w.c64q, shape->kq, labels_k, objective != nullptr, true,
-                         stream);
+        st = assign_side(shape, w, k, w.c64k, shape->kk, w.c64q, shape->kq, labels_k, w.chunk_hist,
+                         objective != nullptr, stream);
         if (st != SVOO_OK) return st;
         if (objective)
             launch_objective(shape, w, k, shape->kk, labels_k, objective + (size_t)it * 2, iters * 2, stream);
         int32_t* pk = last && perm_k ? perm_k : w.perm;
         int32_t* ok = last && perm_k ? k_offsets : w.offsets;
-        st = sort_labels(shape->bh, shape->n, shape->kk, labels_k, pk, ok, nullptr, w.chunk_hist, stream);
+        st = sort_labels(shape->bh, shape->n, shape->kk, labels_k, pk, ok, w.chunk_hist, true, stream);
         if (st != SVOO_OK) return st;
         launch_centroid_update(shape, k, pk, ok, w.c64k, last ? ck : nullptr, last ? counts_k : nullptr, shape->kk,
-                               w.flags, 3 * shape->bh, stream);
+                               w.flags, 2 * shape->bh, stream);
         // Step B: queries against the NEW key anchors, own centroids the OLD C_q.
-        st = assign_side(shape, w, q, w.c64q, shape->kq, w.c64k, shape->kk, labels_q, objective != nullptr, true,
-                         stream);
+        st = assign_side(shape, w, q, w.c64q, shape->kq, w.c64k, shape->kk, labels_q, w.chunk_hist,
+                         objective != nullptr, stream);
         if (st != SVOO_OK) return st;
         if (objective)
             launch_objective(shape, w, q, shape->kq, labels_q, objective + (size_t)it * 2 + 1, iters * 2, stream);
         int32_t* pq = last && perm_q ? perm_q : w.perm;
         int32_t* oq = last && perm_q ? q_offsets : w.offsets;
-        st = sort_labels(shape->bh, shape->n, shape->kq, labels_q, pq, oq, nullptr, w.chunk_hist, stream);
+        st = sort_labels(shape->bh, shape->n, shape->kq, labels_q, pq, oq, w.chunk_hist, true, stream);
         if (st != SVOO_OK) return st;
         launch_centroid_update(shape, q, pq, oq, w.c64q, last ? cq : nullptr, last ? counts_q : nullptr, shape->kq,
-                               w.flags, 3 * shape->bh, stream);
+                               w.flags, 2 * shape->bh, stream);
     }
     return launch_status();
 }
@@ -1238,38 +1182,29 @@ extern "C" int svoo_assign(const svoo_shape* shape, const void* x, const float* 
     const ClusterWs w = carve_cluster_ws(&s, ws);
     if (ws_bytes < w.bytes) return SVOO_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t stream = (hipStream_t)hip_stream;
-    const size_t n_own = (size_t)s.bh * k_own * s.d, n_opp = (size_t)s.bh * k_opp * s.d;
-    hipLaunchKernelGGL(f32_to_f64_kernel, dim3((n_own + 255) / 256), dim3(256), 0, stream, c_own, w.c64q, n_own);
-    hipLaunchKernelGGL(f32_to_f64_kernel, dim3((n_opp + 255) / 256), dim3(256), 0, stream, c_opp, w.c64k, n_opp);
-    return assign_side(&s, w, x, w.c64q, k_own, w.c64k, k_opp, labels, false, false, stream);
+    launch_init_centroids(&s, InitSide{nullptr, nullptr, c_own, w.c64q, k_own},
+                          InitSide{nullptr, nullptr, c_opp, w.c64k, k_opp}, w.flags, 2 * s.bh, stream);
+    return assign_side(&s, w, x, w.c64q, k_own, w.c64k, k_opp, labels, nullptr, false, stream);
 }
 
-// One Lloyd assignment: labels of x against centroids c64 [bh, k, d].
+// One Lloyd assignment: labels of x against centroids c64 [bh, k, d].  The preceding kernel of the stream has
+// zeroed w.wmax_bits.
+template <typename T, int D>
+static void kmeans_assign_t(const svoo_shape* s, const ClusterWs& w, const void* x, const double* c64, int k,
+                            int32_t* labels, hipStream_t stream) {
+    const int kpad = (k + 31) / 32 * 32;
+    hipLaunchKernelGGL((kmeans_w_kernel<T, D>), dim3(kpad / 16, s->bh), dim3(256), 0, stream, c64, w.w_hi, w.w_lo,
+                       w.wt64, w.bterm, w.half_sq, w.wmax_bits, k, kpad);
+    launch_assign<T, D, true>(s, w, x, nullptr, k, 0, labels, w.chunk_hist, stream);
+}
+
 static int kmeans_assign(const svoo_shape* s, const ClusterWs& w, const void* x, const double* c64, int k,
                          int32_t* labels, hipStream_t stream) {
-    const int d = s->d, bh = s->bh, kpad = (k + 31) / 32 * 32;
-    hipLaunchKernelGGL(fill_i32_kernel, dim3((3 * bh + 255) / 256), dim3(256), 0, stream, w.flags, 0,
-                       (size_t)3 * bh);
-    hipLaunchKernelGGL(kmeans_prep_kernel, dim3(kpad, bh), dim3(128), 0, stream, c64, w.bterm, w.half_sq, k, kpad, d);
-    if (s->dtype == SVOO_BF16) {
-        dim3 sgrid((k + 15) / 16, bh), agrid((s->n + 255) / 256, bh), lgrid(s->n < ASSIGN_LIST_WGS ? s->n : ASSIGN_LIST_WGS, bh);
-        if (d == 128) {
-            hipLaunchKernelGGL(split_w_kernel<128>, sgrid, dim3(256), 0, stream, c64, w.whi, w.wlo, w.wt64, w.wmax_bits, k);
-            hipLaunchKernelGGL((assign_mfma_kernel<128, true>), agrid, dim3(256), 0, stream, (const uint16_t*)x, w.whi,
-                               w.wlo, w.wmax_bits, w.flags, w.half_sq, labels, w.list, w.list_count, s->n, k);
-            hipLaunchKernelGGL((assign_list_kernel<uint16_t, 128>), lgrid, dim3(256), 0, stream, (const uint16_t*)x,
-                               w.wt64, k, w.bterm, w.flags, nullptr, w.list, w.list_count, 1, labels, s->n);
-        } else {
-            hipLaunchKernelGGL(split_w_kernel<64>, sgrid, dim3(256), 0, stream, c64, w.whi, w.wlo, w.wt64, w.wmax_bits, k);
-            hipLaunchKernelGGL((assign_mfma_kernel<64, true>), agrid, dim3(256), 0, stream, (const uint16_t*)x, w.whi,
-                               w.wlo, w.wmax_bits, w.flags, w.half_sq, labels, w.list, w.list_count, s->n, k);
-            hipLaunchKernelGGL((assign_list_kernel<uint16_t, 64>), lgrid, dim3(256), 0, stream, (const uint16_t*)x,
-                               w.wt64, k, w.bterm, w.flags, nullptr, w.list, w.list_count, 1, labels, s->n);
-        }
-    } else {
-        dispatch_token_tile<MODE_ARGMAX>(s, x, c64, k, w.bterm, w.flags, nullptr, nullptr, nullptr, 1, labels, nullptr,
-                                         stream);
-    }
+    auto go = [&](auto fn) { fn(s, w, x, c64, k, labels, stream); };
+    if (s->dtype == SVOO_BF16)
+        s->d == 128 ? go(kmeans_assign_t<uint16_t, 128>) : go(kmeans_assign_t<uint16_t, 64>);
+    else
+        s->d == 128 ? go(kmeans_assign_t<float, 128>) : go(kmeans_assign_t<float, 64>);
     return launch_status();
 }
 
@@ -1298,7 +1233,8 @@ extern "C" int svoo_kmeans(const svoo_shape* shape, const void* x, int32_t k, co
     const ClusterWs w = carve_cluster_ws(&s, ws);
     if (ws_bytes < w.bytes) return SVOO_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t stream = (hipStream_t)hip_stream;
-    launch_init_centroids(&s, x, init_idx, init_c, w.c64q, k, nullptr, 0, stream);
+    launch_init_centroids(&s, InitSide{x, init_idx, init_c, w.c64q, k}, InitSide{nullptr, nullptr, nullptr, nullptr, 0},
+                          w.flags, 2 * s.bh, stream);
     for (int it = 0; it < iters; ++it) {
         const bool last = it == iters - 1;
         st = kmeans_assign(&s, w, x, w.c64q, k, labels, stream);
@@ -1314,10 +1250,10 @@ extern "C" int svoo_kmeans(const svoo_shape* shape, const void* x, int32_t k, co
             hipLaunchKernelGGL(objective_sum_kernel, dim3(s.bh), dim3(1024), 0, stream, w.terms, inertia + it, s.n,
                                iters);
         }
-        st = sort_labels(s.bh, s.n, k, labels, w.perm, w.offsets, nullptr, w.chunk_hist, stream);
+        st = sort_labels(s.bh, s.n, k, labels, w.perm, w.offsets, w.chunk_hist, true, stream);
         if (st != SVOO_OK) return st;
         launch_centroid_update(&s, x, w.perm, w.offsets, w.c64q, last ? c : nullptr, last ? counts : nullptr, k,
-                               nullptr, 0, stream);
+                               w.flags, 2 * s.bh, stream);
     }
     return launch_status();
 }

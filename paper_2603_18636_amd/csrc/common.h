@@ -111,8 +111,15 @@ static inline bool opt_in_dynamic_lds(const void* kernel, int bytes, unsigned ch
 // ---------------------------------------------------------------------------------------------
 // internal entry points shared between translation units
 // ---------------------------------------------------------------------------------------------
-// Stable counting sort of labels [bh, n] into perm / offsets (and counts, nullable).
-// chunk_hist: scratch int32 [bh * sort_chunks(n) * n_clusters].
-size_t sort_scratch_ints(int bh, int n, int n_clusters);
+// Stable counting sort of labels [bh, n] into perm / offsets.
+// chunk_hist: scratch of sort_scratch_ints(); have_hist: it already holds the label counts of every
+// ASSIGN_CHUNK tokens.
+#define ASSIGN_CHUNK 256
+#define LABEL_CHUNK 512
+static inline int sort_chunks(int n, bool have_hist) {
+    const int chunk = have_hist ? ASSIGN_CHUNK : LABEL_CHUNK;
+    return (n + chunk - 1) / chunk;
+}
+size_t sort_scratch_ints(int bh, int n, int n_clusters, bool have_hist);
 int sort_labels(int bh, int n, int n_clusters, const int32_t* labels, int32_t* perm, int32_t* offsets,
-                int32_t* counts, int32_t* chunk_hist, hipStream_t stream);
+                int32_t* chunk_hist, bool have_hist, hipStream_t stream);

@@ -1,23 +1,26 @@
 // Cluster-contiguous layout: stable counting sort of labels, row gather (permute) and row
 // scatter (un-permute).  Pure integer work and data movement; HBM-bandwidth bound.
 //
-// Sort of one slice (n tokens, K bins), three launches:
-//   hist     one wave per 512-token chunk counts its labels in LDS (integer atomics) and writes a
-//            K-entry histogram for the chunk
-//   scan     one workgroup per slice: per bin, exclusive prefix over chunks (bin-major, chunk-minor
-//            order = stable order), bin totals = cluster sizes, exclusive scan of totals = offsets
+// Sort of one slice (n tokens, K bins) in chunks:
+//   hist     K-entry histogram per chunk: written by the assignment kernel, whose workgroups own a chunk of
+//            256 tokens each, or by one wave per 512 tokens where only labels are at hand
+//   scan     (more than SORT_DIRECT_CHUNKS chunks) per bin, inclusive prefix over the chunks, in place: the
+//            row before a chunk is where its tokens start, the last row the bin totals.  A workgroup takes
+//            64 bins, its 16 waves a sixteenth of the chunks each
 //   scatter  one wave per chunk walks its tokens 64 at a time in index order; lanes with equal
 //            labels find each other with one ballot per label bit and are ranked by lane, so equal
-//            labels keep ascending token order
+//            labels keep ascending token order.  Every workgroup scans the K bin totals for the cluster
+//            offsets itself, and with few chunks it sums the histograms before its own instead of the scan
 #include "common.h"
 
-#define SORT_CHUNK 512
 #define SORT_WAVES 4
+// Up to this many chunks every scatter wave sums the histograms itself: 32 loads in flight per bin cost less
+// than the scan's launch (1 x 1,024 tokens, 16 bins: 24.7 us per half-step against 26.1 with the scan; 12 x 8,190,
+// 64 bins: 61.0 against 63.3; but 12 x 32,760 = 128 chunks: 97 against 91).
+#define SORT_DIRECT_CHUNKS 32
 
-static inline int sort_chunks(int n) { return (n + SORT_CHUNK - 1) / SORT_CHUNK; }
-
-size_t sort_scratch_ints(int bh, int n, int n_clusters) {
-    return (size_t)bh * sort_chunks(n) * n_clusters;
+size_t sort_scratch_ints(int bh, int n, int n_clusters, bool have_hist) {
+    return (size_t)bh * sort_chunks(n, have_hist) * n_clusters;
 }
 
 __device__ __forceinline__ int clamp_label(int l, int k) { return l < 0 ? 0 : (l >= k ? k - 1 : l); }
@@ -33,8 +36,8 @@ sort_hist_kernel(const int32_t* __restrict__ labels, int32_t* __restrict__ chunk
     __syncthreads();
     if (chunk < nchunks) {
         const int32_t* lab = labels + (size_t)b * n;
-        const int start = chunk * SORT_CHUNK;
-        for (int g = 0; g < SORT_CHUNK / SVOO_WAVE; ++g) {
+        const int start = chunk * LABEL_CHUNK;
+        for (int g = 0; g < LABEL_CHUNK / SVOO_WAVE; ++g) {
             int i = start + g * SVOO_WAVE + lane;
             if (i < n) atomicAdd(&hist[clamp_label(lab[i], k)], 1);
         }
@@ -46,92 +49,103 @@ sort_hist_kernel(const int32_t* __restrict__ labels, int32_t* __restrict__ chunk
     }
 }
 
-// One workgroup of 1024 threads per slice.  The threads form G = 1024 / K' groups (K' = bins rounded
-// up to a multiple of 64); group g owns a contiguous range of chunks, thread (g, j) bin j of them.
-// Pass 1 totals each (group, bin); the group totals are prefixed per bin; pass 2 rewrites the chunk
-// histograms as exclusive prefixes.  Then the bin totals are scanned over bins for the offsets.
 __global__ void __launch_bounds__(1024)
-sort_scan_kernel(int32_t* __restrict__ chunk_hist, int32_t* __restrict__ offsets, int32_t* __restrict__ counts,
-                 int k, int nchunks) {
-    __shared__ int32_t tot[1024];
-    __shared__ int32_t scan[1024];
-    const int b = blockIdx.x, tid = threadIdx.x;
-    const int kp = (k + 63) / 64 * 64;
-    const int groups = 1024 / kp;            // >= 1 because k <= 1024
-    const int g = tid / kp, j = tid % kp;
-    const bool live = g < groups && j < k;
-    const int cpg = (nchunks + groups - 1) / groups;
-    const int c0 = g * cpg, c1 = (c0 + cpg < nchunks) ? c0 + cpg : nchunks;
+sort_scan_kernel(int32_t* __restrict__ chunk_hist, int k, int nchunks) {
+    __shared__ int32_t tot[16][64];
+    const int b = blockIdx.y, g = threadIdx.x / 64, lane = threadIdx.x % 64, j = blockIdx.x * 64 + lane;
+    const int cpg = (nchunks + 15) / 16;
+    const int c0 = g * cpg < nchunks ? g * cpg : nchunks, c1 = c0 + cpg < nchunks ? c0 + cpg : nchunks;
     int32_t* h = chunk_hist + (size_t)b * nchunks * k;
     int sum = 0;
-    if (live) {
+    if (j < k) {
 #pragma unroll 8
         for (int c = c0; c < c1; ++c) sum += h[(size_t)c * k + j];
     }
-    tot[tid] = live ? sum : 0;
+    tot[g][lane] = sum;
     __syncthreads();
-    int base = 0, total = 0;
-    if (live) {
-        for (int gg = 0; gg < groups; ++gg) {
-            const int v = tot[gg * kp + j];
-            base += gg < g ? v : 0;
-            total += v;
-        }
-        int running = base;
+    if (j >= k) return;
+    int running = 0;
+#pragma unroll
+    for (int gg = 0; gg < 16; ++gg) running += gg < g ? tot[gg][lane] : 0;
 #pragma unroll 8
-        for (int c = c0; c < c1; ++c) {
-            const int v = h[(size_t)c * k + j];
-            h[(size_t)c * k + j] = running;
-            running += v;
-        }
-    }
-    const int mine = (live && g == 0) ? total : 0;   // bin totals, one thread per bin
-    const bool owner = live && g == 0;
-    // scan over bins: owners sit at tid = j < kp <= 1024
-    scan[tid] = (tid < kp) ? mine : 0;
-    __syncthreads();
-    for (int s = 1; s < 1024; s <<= 1) {
-        int v = (tid >= s) ? scan[tid - s] : 0;
-        __syncthreads();
-        scan[tid] += v;
-        __syncthreads();
-    }
-    if (owner) {
-        offsets[(size_t)b * (k + 1) + j] = scan[j] - total;
-        if (counts) counts[(size_t)b * k + j] = total;
-        if (j == k - 1) offsets[(size_t)b * (k + 1) + k] = scan[j];
+    for (int c = c0; c < c1; ++c) {
+        running += h[(size_t)c * k + j];
+        h[(size_t)c * k + j] = running;
     }
 }
 
+template <bool DIRECT, int CHUNK>
 __global__ void __launch_bounds__(SORT_WAVES* SVOO_WAVE)
 sort_scatter_kernel(const int32_t* __restrict__ labels, const int32_t* __restrict__ chunk_hist,
-                    const int32_t* __restrict__ offsets, int32_t* __restrict__ perm, int n, int k, int nchunks) {
+                    int32_t* __restrict__ offsets, int32_t* __restrict__ perm, int n, int k, int nchunks) {
+    constexpr int NT = SORT_WAVES * SVOO_WAVE, GROUPS = CHUNK / SVOO_WAVE;
     extern __shared__ int32_t lds[];
-    const int wave = threadIdx.x / SVOO_WAVE, lane = threadIdx.x % SVOO_WAVE;
+    __shared__ int32_t wave_sum[SORT_WAVES];
+    const int tid = threadIdx.x, wave = tid / SVOO_WAVE, lane = tid % SVOO_WAVE;
     const int b = blockIdx.y;
     const int chunk = blockIdx.x * SORT_WAVES + wave;
     const bool active = chunk < nchunks;
-    int32_t* cnt = lds + wave * k;
-    if (active) {
-        const int32_t* base = chunk_hist + ((size_t)b * nchunks + chunk) * k;
-        const int32_t* off = offsets + (size_t)b * (k + 1);
-        for (int j = lane; j < k; j += SVOO_WAVE) cnt[j] = off[j] + base[j];
-    }
-    __syncthreads();
+    int32_t* off = lds;                        // [k] bin totals, then first positions of the clusters
+    int32_t* cnt = lds + k + wave * k;         // [k] next position of each label in this chunk
+    const int32_t* h = chunk_hist + (size_t)b * nchunks * k;
     const int32_t* lab = labels + (size_t)b * n;
-    int32_t* out = perm + (size_t)b * n;
-    const int start = chunk * SORT_CHUNK;
-    const unsigned long long lt_mask = (1ull << lane) - 1ull;
-    int label_bits = 0;
-    while ((1 << label_bits) < k) ++label_bits;
-    int mine[SORT_CHUNK / SVOO_WAVE];     // all of the lane's labels requested at once
+    const int start = chunk * CHUNK;
+    int mine[GROUPS];                          // all of the lane's labels requested at once
 #pragma unroll
-    for (int g = 0; g < SORT_CHUNK / SVOO_WAVE; ++g) {
+    for (int g = 0; g < GROUPS; ++g) {
         const int i = start + g * SVOO_WAVE + lane;
         mine[g] = (active && i < n) ? clamp_label(lab[i], k) : -1;
     }
+    if (DIRECT) {
+        for (int j = lane; j < k; j += SVOO_WAVE) {
+            int base = 0, total = 0;
+#pragma unroll 8
+            for (int c = 0; c < nchunks; ++c) {
+                const int v = h[(size_t)c * k + j];
+                total += v;
+                base += c < chunk ? v : 0;
+            }
+            cnt[j] = base;
+            if (wave == 0) off[j] = total;
+        }
+    } else {
+        for (int j = tid; j < k; j += NT) off[j] = h[(size_t)(nchunks - 1) * k + j];
+        if (active)
+            for (int j = lane; j < k; j += SVOO_WAVE) cnt[j] = chunk > 0 ? h[(size_t)(chunk - 1) * k + j] : 0;
+    }
+    __syncthreads();
+    // exclusive scan of the totals: thread t owns `per` adjacent bins
+    const int per = (k + NT - 1) / NT, j0 = tid * per;
+    int sum = 0;
+    for (int u = 0; u < per; ++u) sum += j0 + u < k ? off[j0 + u] : 0;
+    int incl = sum;
 #pragma unroll
-    for (int g = 0; g < SORT_CHUNK / SVOO_WAVE; ++g) {
+    for (int s = 1; s < SVOO_WAVE; s <<= 1) {
+        const int v = __shfl_up(incl, s);
+        incl += lane >= s ? v : 0;
+    }
+    if (lane == SVOO_WAVE - 1) wave_sum[wave] = incl;
+    __syncthreads();
+    int run = incl - sum;
+    for (int w = 0; w < wave; ++w) run += wave_sum[w];
+    for (int u = 0; u < per; ++u)
+        if (j0 + u < k) {
+            const int v = off[j0 + u];
+            off[j0 + u] = run;
+            if (blockIdx.x == 0) offsets[(size_t)b * (k + 1) + j0 + u] = run;
+            run += v;
+            if (blockIdx.x == 0 && j0 + u == k - 1) offsets[(size_t)b * (k + 1) + k] = run;
+        }
+    __syncthreads();
+    if (!active) return;
+    for (int j = lane; j < k; j += SVOO_WAVE) cnt[j] += off[j];
+    __builtin_amdgcn_wave_barrier();
+    int32_t* out = perm + (size_t)b * n;
+    const unsigned long long lt_mask = (1ull << lane) - 1ull;
+    int label_bits = 0;
+    while ((1 << label_bits) < k) ++label_bits;
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g) {
         const int i = start + g * SVOO_WAVE + lane;
         const int label = mine[g];
         const bool valid = label >= 0;
@@ -154,16 +168,31 @@ sort_scatter_kernel(const int32_t* __restrict__ labels, const int32_t* __restric
     }
 }
 
-int sort_labels(int bh, int n, int k, const int32_t* labels, int32_t* perm, int32_t* offsets, int32_t* counts,
-                int32_t* chunk_hist, hipStream_t stream) {
-    const int nchunks = sort_chunks(n);
+template <int CHUNK>
+static void launch_scatter(dim3 grid, const int32_t* labels, int32_t* chunk_hist, int32_t* offsets, int32_t* perm, int n,
+                           int k, int nchunks, hipStream_t stream) {
+    const size_t lds = (size_t)(SORT_WAVES + 1) * k * sizeof(int32_t);
+    if (nchunks <= SORT_DIRECT_CHUNKS) {
+        hipLaunchKernelGGL((sort_scatter_kernel<true, CHUNK>), grid, dim3(SORT_WAVES * SVOO_WAVE), lds, stream, labels,
+                           chunk_hist, offsets, perm, n, k, nchunks);
+    } else {
+        hipLaunchKernelGGL(sort_scan_kernel, dim3((k + 63) / 64, grid.y), dim3(1024), 0, stream, chunk_hist, k, nchunks);
+        hipLaunchKernelGGL((sort_scatter_kernel<false, CHUNK>), grid, dim3(SORT_WAVES * SVOO_WAVE), lds, stream, labels,
+                           chunk_hist, offsets, perm, n, k, nchunks);
+    }
+}
+
+int sort_labels(int bh, int n, int k, const int32_t* labels, int32_t* perm, int32_t* offsets, int32_t* chunk_hist,
+                bool have_hist, hipStream_t stream) {
+    const int nchunks = sort_chunks(n, have_hist);
     dim3 grid((nchunks + SORT_WAVES - 1) / SORT_WAVES, bh);
-    const size_t lds = (size_t)SORT_WAVES * k * sizeof(int32_t);
-    hipLaunchKernelGGL(sort_hist_kernel, grid, dim3(SORT_WAVES * SVOO_WAVE), lds, stream, labels, chunk_hist, n, k,
-                       nchunks);
-    hipLaunchKernelGGL(sort_scan_kernel, dim3(bh), dim3(1024), 0, stream, chunk_hist, offsets, counts, k, nchunks);
-    hipLaunchKernelGGL(sort_scatter_kernel, grid, dim3(SORT_WAVES * SVOO_WAVE), lds, stream, labels, chunk_hist,
-                       offsets, perm, n, k, nchunks);
+    if (have_hist) {
+        launch_scatter<ASSIGN_CHUNK>(grid, labels, chunk_hist, offsets, perm, n, k, nchunks, stream);
+    } else {
+        hipLaunchKernelGGL(sort_hist_kernel, grid, dim3(SORT_WAVES * SVOO_WAVE), SORT_WAVES * k * sizeof(int32_t), stream,
+                           labels, chunk_hist, n, k, nchunks);
+        launch_scatter<LABEL_CHUNK>(grid, labels, chunk_hist, offsets, perm, n, k, nchunks, stream);
+    }
     return launch_status();
 }
 
@@ -224,10 +253,10 @@ extern "C" int svoo_permute(const svoo_shape* shape, const int32_t* labels, int3
         ptrs.dst[t] = (uint4*)dst[t];
     }
     if ((((uintptr_t)ws) & 255u) != 0) return SVOO_ERR_INVALID_ARG;
-    const size_t need = align_up(sort_scratch_ints(shape->bh, shape->n, n_clusters) * sizeof(int32_t), 256);
+    const size_t need = align_up(sort_scratch_ints(shape->bh, shape->n, n_clusters, false) * sizeof(int32_t), 256);
     if (ws_bytes < need) return SVOO_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t stream = (hipStream_t)hip_stream;
-    st = sort_labels(shape->bh, shape->n, n_clusters, labels, perm, offsets, nullptr, (int32_t*)ws, stream);
+    st = sort_labels(shape->bh, shape->n, n_clusters, labels, perm, offsets, (int32_t*)ws, false, stream);
     if (st != SVOO_OK) return st;
     return move_rows<true>(shape, n_tensors, ptrs, perm, stream);
 }

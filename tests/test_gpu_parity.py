@@ -133,6 +133,31 @@ def test_assign_degenerate_anchor_in_one_of_two_slices_many_tiles(dtype):
     assert (got[0][4100:4130] == 5).all() and got[0][77] == 5
 
 
+@pytest.mark.parametrize("dtype,d,n,k_own,k_opp", [("bf16", 128, 257, 33, 20), ("bf16", 64, 600, 300, 7), ("bf16", 64, 2, 2, 1),
+                                                   ("f32", 128, 255, 31, 40), ("f32", 64, 1025, 1024, 16),
+                                                   ("f32", 128, 512, 32, 300), ("f32", 64, 66, 1, 3)])
+@pytest.mark.parametrize("degenerate", [False, True])
+def test_assign_when_the_pre_filter_decides_nothing(dtype, d, n, k_own, k_opp, degenerate):
+    """Every own-side centroid twice: best and second-best scores are equal for every token, so all of them are
+    decided in float64 (tokens in groups of four and one at a time, workgroups with 1 to 256 open tokens,
+    more and fewer centroids than threads) and the lower of the two indices must win; with an all-zero
+    centroid the general form of the distance decides."""
+    rng = np.random.default_rng(n + k_own)
+    x, own, opp = (rng.standard_normal(s).astype(np.float32) for s in ((2, n, d), (2, k_own, d), (2, k_opp, d)))
+    half = (k_own + 1) // 2
+    if degenerate:
+        own[0, 0] = 0.0
+    own[:, half:] = own[:, : k_own - half]
+    if dtype == "bf16":
+        x = synth.round_to_bf16(x)
+    got = H.to_np(svoo.assign(H.to_dev(x, dtype), H.to_dev(own), H.to_dev(opp)))
+    for b in range(2):
+        ref, best, second = H.oracle_assign(x[b], own[b], opp[b])
+        assert (got[b] < half).all()
+        if k_opp > 1:                                 # one opposite centroid: every affinity row is +1 or -1
+            np.testing.assert_array_equal(got[b], ref)
+
+
 @pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 128)])
 def test_key_partition_follows_the_query_anchors(dtype, d):
     """The paper's intuition example (Sec. 4.2; fixture tests/golden/query_dependent_key_partition.txt) through
