@@ -314,6 +314,36 @@ def test_dense_attn_matches_oracle(dtype, d, n):
         np.testing.assert_allclose(lse[b], lse_ref, atol=2e-2 if dtype == "bf16" else 1e-4)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d,n,step", [(128, 300, 0.02), (64, 300, 0.5), (128, 97, 8.0), (64, 1000, -0.5), (128, 64, 40.0)])
+def test_attention_when_the_logits_keep_rising(dtype, d, n, step):
+    """The reference maximum follows the stream only when it is exceeded by far: key t has logit ~ step * t in
+    even rows (from a fraction of an octave per 32 keys to thousands of octaves), the other way round in every
+    fourth row and ordinary logits in the rest, so that the rows of one wave raise their reference at
+    different keys, by finite and by overflowing factors.  Dense and with the keys split between waves."""
+    rng = np.random.default_rng(n)
+    q, k, v = (rng.standard_normal((1, n, d)).astype(np.float32) for _ in range(3))
+    scale = 1.0 / 8.0
+    k[0, :, 0] = np.arange(n) * step
+    q[0, :, 0] = 0.0
+    q[0, ::2, 0] = 8.0
+    q[0, ::4, 0] = -8.0
+    if dtype == "bf16":
+        q, k, v = (synth.round_to_bf16(x) for x in (q, k, v))
+    out, lse = svoo.attn(H.to_dev(q, dtype), H.to_dev(k, dtype), H.to_dev(v, dtype), scale, want_lse=True)
+    logits = scale * (q[0].astype(np.float64) @ k[0].T.astype(np.float64))
+    m = logits.max(1)
+    ref = m + np.log(np.exp(logits - m[:, None]).sum(1))
+    # a float32 logit: d roundings of a running sum that one product dominates, then scale, base and reference;
+    # bf16 probabilities: 2^-9 of the sum at worst
+    logit_err = (d + 4) * 2.0 ** -24 * np.abs(logits).max()
+    assert np.abs(H.to_np(lse)[0] - ref).max() <= (2.0 ** -9 if dtype == "bf16" else 1e-6) + logit_err
+    w = np.exp(logits - ref[:, None])
+    err = np.abs(H.to_np(out)[0] - w @ v[0].astype(np.float64)).max()
+    # probabilities off by a factor 1 +- 2 logit_err (their own and the sum's), times the largest value
+    assert err <= (2e-2 if dtype == "bf16" else 1e-5) + 2 * logit_err * np.abs(v).max()
+
+
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64), ("bf16", 64), ("f32", 128)])
 def test_sparse_attn_matches_oracle_random_mask(dtype, d):
     """Random labels (ragged cluster sizes, some empty) and a random mask: pins the key-stream walk,
