@@ -1,0 +1,73 @@
+// Shared by the co-clustering kernels: element loads, the split of the score matrix, margins.
+#pragma once
+
+#include "common.h"
+
+#define NORM_FLOOR 1e-12
+
+typedef __attribute__((ext_vector_type(4))) double f64x4;
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
+typedef __attribute__((ext_vector_type(16))) float f32x16_t;
+#define FAST_EPS 3.1e-5f   // 2^-16 + 256 * 2^-24, twice the analytic bound for d <= 128
+
+// Score matrix in the form the pre-filter reads: two bf16 arrays, or one float32 array over the same bytes.
+template <typename T>
+__device__ __forceinline__ void store_split(double v, size_t o, uint16_t* w_hi, uint16_t* w_lo);
+template <>
+__device__ __forceinline__ void store_split<uint16_t>(double v, size_t o, uint16_t* w_hi, uint16_t* w_lo) {
+    const uint16_t hb = f32_to_bf16((float)v);
+    w_hi[o] = hb;
+    w_lo[o] = f32_to_bf16((float)(v - (double)bf16_to_f32(hb)));
+}
+template <>
+__device__ __forceinline__ void store_split<float>(double v, size_t o, uint16_t* w_hi, uint16_t*) {
+    ((float*)w_hi)[o] = (float)v;
+}
+
+__device__ __forceinline__ float norm_rounded_up(double sq) {
+    float nrm = (float)sqrt(sq);
+    nrm = nrm * 1.0000002f + 1e-37f;
+    return nrm < 3.0e38f ? nrm : 3.0e38f;      // NaN as well
+}
+
+template <typename T>
+__device__ __forceinline__ double load_as_f64(const T* p);
+template <>
+__device__ __forceinline__ double load_as_f64<uint16_t>(const uint16_t* p) { return (double)bf16_to_f32(*p); }
+template <>
+__device__ __forceinline__ double load_as_f64<float>(const float* p) { return (double)*p; }
+
+template <typename T>
+__device__ __forceinline__ void load8_as_f64(const T* p, double (&v)[8]);
+template <>
+__device__ __forceinline__ void load8_as_f64<uint16_t>(const uint16_t* p, double (&v)[8]) {
+    const uint4 u = *(const uint4*)p;
+    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        v[2 * e] = (double)__uint_as_float(w[e] << 16);
+        v[2 * e + 1] = (double)__uint_as_float(w[e] & 0xffff0000u);
+    }
+}
+template <>
+__device__ __forceinline__ void load8_as_f64<float>(const float* p, double (&v)[8]) {
+    const float4 a = *(const float4*)p, b = *(const float4*)(p + 4);
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+}
+
+// A half-step of few clusters and tokens in two launches (cluster_small.hip): labels, c_own and, where asked for,
+// the float32 centroids, counts and cluster-order layout.
+struct SmallStep {
+    const void* x;
+    double* c_own;
+    const double* c_opp;
+    int k_own, k_opp;
+    int32_t* labels;
+    float* c32;                  // nullable, as the rest
+    int32_t* counts;
+    int32_t* perm;
+    int32_t* offsets;
+};
+bool small_fits(const svoo_shape* s);
+int small_half_step(const svoo_shape* s, const SmallStep& st, hipStream_t stream);

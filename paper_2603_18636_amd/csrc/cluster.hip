@@ -14,36 +14,11 @@
 // float64 in a fixed order.
 #include <type_traits>
 
-#include "common.h"
-
-#define NORM_FLOOR 1e-12
+#include "cluster.h"
 
 // ---------------------------------------------------------------------------------------------
 // small helpers
 // ---------------------------------------------------------------------------------------------
-template <typename T>
-__device__ __forceinline__ double load_as_f64(const T* p);
-template <>
-__device__ __forceinline__ double load_as_f64<uint16_t>(const uint16_t* p) { return (double)bf16_to_f32(*p); }
-template <>
-__device__ __forceinline__ double load_as_f64<float>(const float* p) { return (double)*p; }
-
-// two consecutive elements as float64 (4-byte / 8-byte aligned address)
-template <typename T>
-__device__ __forceinline__ void load_pair(const T* p, double& a, double& b);
-template <>
-__device__ __forceinline__ void load_pair<uint16_t>(const uint16_t* p, double& a, double& b) {
-    const uint32_t u = *(const uint32_t*)p;
-    a = (double)__uint_as_float(u << 16);
-    b = (double)__uint_as_float(u & 0xffff0000u);
-}
-template <>
-__device__ __forceinline__ void load_pair<float>(const float* p, double& a, double& b) {
-    const float2 u = *(const float2*)p;
-    a = (double)u.x;
-    b = (double)u.y;
-}
-
 // The per-slice words the next assignment accumulates into (degenerate flag, largest row norm) are
 // cleared by the kernel that precedes it in the stream, not by a launch of their own.
 __device__ __forceinline__ void clear_words(int32_t* clear, int clear_n) {
@@ -97,8 +72,6 @@ struct GemmArgs {
     long long a_batch, b_batch, c_batch;
     int a_sm, a_sk, b_sk, b_sn;
 };
-
-typedef __attribute__((ext_vector_type(4))) double f64x4;
 
 template <bool K2>
 __device__ __forceinline__ void load_k_pair(const double* __restrict__ row, int k, int k_end, int sk, double& v0,
@@ -258,31 +231,6 @@ static void launch_quadform(const void* x, const double* gram, double* quad_out,
 // token of a slice with a degenerate anchor) the workgroup decides the token in float64.  Equal
 // scores have gap 0 and are therefore always decided in float64, lowest index first.
 // ---------------------------------------------------------------------------------------------
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
-typedef __attribute__((ext_vector_type(16))) float f32x16_t;
-#define FAST_EPS 3.1e-5f   // 2^-16 + 256 * 2^-24, twice the analytic bound for d <= 128
-
-// Score matrix in the form the pre-filter reads: two bf16 arrays, or one float32 array over the same bytes.
-template <typename T>
-__device__ __forceinline__ void store_split(double v, size_t o, uint16_t* w_hi, uint16_t* w_lo);
-template <>
-__device__ __forceinline__ void store_split<uint16_t>(double v, size_t o, uint16_t* w_hi, uint16_t* w_lo) {
-    const uint16_t hb = f32_to_bf16((float)v);
-    w_hi[o] = hb;
-    w_lo[o] = f32_to_bf16((float)(v - (double)bf16_to_f32(hb)));
-}
-template <>
-__device__ __forceinline__ void store_split<float>(double v, size_t o, uint16_t* w_hi, uint16_t*) {
-    ((float*)w_hi)[o] = (float)v;
-}
-
-__device__ __forceinline__ float norm_rounded_up(double sq) {
-    float nrm = (float)sqrt(sq);
-    nrm = nrm * 1.0000002f + 1e-37f;
-    return nrm < 3.0e38f ? nrm : 3.0e38f;      // NaN as well
-}
-
 // k-means, where W is the centroid array itself: split of W, W^T in float64, ||c_j||^2 (and its half as
 // float32, zero in the padding up to a multiple of 32 rows), largest row norm.  16 rows per workgroup (one
 // wave takes four of them), one atomic per workgroup.
@@ -837,24 +785,6 @@ assign_kernel(AssignArgs a) {
 // 16-byte load for bf16) of the rows g, g+G, g+2G, ... of its group, then the G partial sums are
 // added in group order.
 // ---------------------------------------------------------------------------------------------
-template <typename T>
-__device__ __forceinline__ void load8_as_f64(const T* p, double (&v)[8]);
-template <>
-__device__ __forceinline__ void load8_as_f64<uint16_t>(const uint16_t* p, double (&v)[8]) {
-    const uint4 u = *(const uint4*)p;
-    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        v[2 * e] = (double)__uint_as_float(w[e] << 16);
-        v[2 * e + 1] = (double)__uint_as_float(w[e] & 0xffff0000u);
-    }
-}
-template <>
-__device__ __forceinline__ void load8_as_f64<float>(const float* p, double (&v)[8]) {
-    const float4 a = *(const float4*)p, b = *(const float4*)(p + 4);
-    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-}
-
 #define CU_ROWS 8   // rows in flight per lane (4: 41 us, 8: 38 us, 12: 43 us per launch at 12 x 75,600 x 128 bf16; was 47 with 2)
 template <typename T, int D>
 __global__ void __launch_bounds__(256)
@@ -1120,6 +1050,17 @@ static int cocluster_impl(const svoo_shape* shape, const void* q, const void* k,
                           InitSide{k, init_k_idx, init_ck, w.c64k, shape->kk}, w.flags, 2 * shape->bh, stream);
     for (int it = 0; it < iters; ++it) {
         const bool last = it == iters - 1;
+        if (!objective && small_fits(shape)) {
+            st = small_half_step(shape, SmallStep{k, w.c64k, w.c64q, shape->kk, shape->kq, labels_k, last ? ck : nullptr,
+                                                  last ? counts_k : nullptr, last ? perm_k : nullptr,
+                                                  last ? k_offsets : nullptr}, stream);
+            if (st != SVOO_OK) return st;
+            st = small_half_step(shape, SmallStep{q, w.c64q, w.c64k, shape->kq, shape->kk, labels_q, last ? cq : nullptr,
+                                                  last ? counts_q : nullptr, last ? perm_q : nullptr,
+                                                  last ? q_offsets : nullptr}, stream);
+            if (st != SVOO_OK) return st;
+            continue;
+        }
         // Step A: keys against query anchors (old C_q), own centroids old C_k.
         st = assign_side(shape, w, k, w.c64k, shape->kk, w.c64q, shape->kq, labels_k, w.chunk_hist,
                          objective != nullptr, stream);

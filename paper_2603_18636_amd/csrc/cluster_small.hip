@@ -1,0 +1,423 @@
+// Algorithm 1 with few clusters and tokens: a half-step in two launches.
+//
+// The general path (cluster.hip) runs four or five dependent kernels per half-step.  With up to SMALL_MAX_K
+// clusters a side and SMALL_MAX_N tokens each of them takes 4-9 us whatever it has to do, so here
+//   assign   every workgroup builds the score matrix W of the slice itself, in LDS, while its tokens are on their way
+//            (P = C_own C_opp^T, row norms, W = P^ C_opp: 2-7 us, as long as the launch it replaces), then decides
+//            its 256 tokens: pre-filter, float64 decision of what that leaves open
+//   update   the workgroup of a cluster finds its members in the labels itself (n labels, one pass; the labels
+//            below its own are its offset), so there is no sort; it leaves the cluster-order layout on the way
+// Same arithmetic and the same bits as the general path: the same float64 products in the same order in W and in the
+// decisions, and in the means the same row groups.
+// Measured per half-step: 1 x 1,024 x 64 float32, 16 blocks 24.3 -> 14.8 us; 3 x 2,945 x 64 bf16, 24 / 40 blocks
+// 28.8 -> 20.8; 3 x 4,096 x 128, 32 blocks 33.5 -> 25.8.  One workgroup per slice for all iterations (no launches
+// in between) was slower: 22 and 38 us for the first two, the pre-filter alone keeps a compute unit busy for 11-14.
+#include <type_traits>
+
+#include "cluster.h"
+
+#define SMALL_MAX_N 8192
+#define SMALL_MAX_K 64
+#define SMALL_WAVES 8      // 32 tokens each
+
+struct SmallAssign {
+    const void* x;
+    const double* c_own;
+    const double* c_opp;
+    int32_t* labels;
+    int n, k_own, k_opp;
+};
+
+// LDS layout in bytes, the same on both sides
+template <typename T, int D>
+struct SmallLds {
+    static constexpr int CP = D + 2, WP = D + 1;       // row pitches in doubles: C_opp (pairs), W (columns)
+    static constexpr int ROWB = D * (int)sizeof(T);    // one term of one row of the split
+    static constexpr int TERMS = sizeof(T) == 2 ? 2 : 1;
+    static constexpr int BLOCK = 32 * ROWB;
+    int pitch, split, c_opp, ph, bterm, bytes;         // W in float64 takes C_opp's place once it is used up
+    __host__ __device__ SmallLds(int k_own, int k_opp) {
+        const int own16 = (k_own + 15) / 16 * 16, own32 = (k_own + 31) / 32 * 32;
+        pitch = (k_opp + 15) / 16 * 16 + 2;
+        const int c = k_opp * CP * 8, w = own16 * WP * 8;
+        split = 0;                                     // first: its swizzle wants whole rows aligned
+        c_opp = split + own32 / 32 * TERMS * BLOCK;
+        ph = c_opp + (c > w ? c : w);
+        bterm = ph + own16 * pitch * 8;
+        bytes = bterm + own16 * 8;
+    }
+};
+
+template <typename T, int D>
+__global__ void __launch_bounds__(64 * SMALL_WAVES)
+assign_small_kernel(SmallAssign a) {
+    using L = SmallLds<T, D>;
+    constexpr bool BF16 = std::is_same<T, uint16_t>::value;
+    constexpr int CP = L::CP, WP = L::WP, ROWB = L::ROWB, CPR = ROWB / 16, DC = ROWB / 32, BLOCK = L::BLOCK;
+    constexpr int NW = SMALL_WAVES, NT = 64 * NW;
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+    __shared__ int32_t wmax_bits, degenerate_s, n_open;
+    __shared__ int32_t open[32 * NW];
+    const int n = a.n, k_own = a.k_own, k_opp = a.k_opp;
+    const L l(k_own, k_opp);
+    unsigned char* split = lds + l.split;
+    double* opp_s = (double*)(lds + l.c_opp);
+    double* w64 = (double*)(lds + l.c_opp);
+    double* ph = (double*)(lds + l.ph);
+    double* bterm = (double*)(lds + l.bterm);
+    const int b = blockIdx.y, tid = threadIdx.x, lane = tid % 64;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int i16 = lane % 16, kq4 = lane / 16, j = lane % 32, h = lane / 32;
+    const T* x = (const T*)a.x + (size_t)b * n * D;
+    const double* c_own = a.c_own + (size_t)b * k_own * D;
+    const double* c_opp = a.c_opp + (size_t)b * k_opp * D;
+    const int pitch = l.pitch, rt = (k_own + 15) / 16, ct = (k_opp + 15) / 16;
+
+    // ---- this wave's tokens, for later; C_opp into LDS
+    const int tok = blockIdx.x * (32 * NW) + 32 * wave + j;
+    uint4 xf[DC];
+    {
+        const uint4* src = (const uint4*)(x + (size_t)(tok < n ? tok : n - 1) * D);
+#pragma unroll
+        for (int c = 0; c < DC; ++c) xf[c] = src[2 * c + h];
+    }
+    for (int e = tid; e < k_opp * D / 2; e += NT) {
+        const int r = e / (D / 2), t = e % (D / 2);
+        *(double2*)(opp_s + r * CP + 2 * t) = ((const double2*)c_opp)[e];
+    }
+    if (tid == 0) {
+        wmax_bits = 0;
+        degenerate_s = 0;
+        n_open = 0;
+    }
+    __syncthreads();
+
+    // ---- P = C_own C_opp^T, one 16 x 16 tile per wave and trip; lane (i, kq) feeds row / column i and the
+    // contraction indices 2 kq, 2 kq + 1 of a block of 8; accumulator v holds row kq + 4 v, column i
+    for (int job = wave; job < rt * ct; job += NW) {
+        const int r0 = job / ct * 16, col = job % ct * 16 + i16;
+        const double* ar = c_own + (size_t)(r0 + i16 < k_own ? r0 + i16 : k_own - 1) * D + 2 * kq4;
+        const double* br = opp_s + (col < k_opp ? col : k_opp - 1) * CP + 2 * kq4;
+        double2 av[D / 8];
+#pragma unroll
+        for (int kb = 0; kb < D / 8; ++kb) av[kb] = *(const double2*)(ar + 8 * kb);
+        f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int kb = 0; kb < D / 8; ++kb) {
+            const double2 bv = *(const double2*)(br + 8 * kb);
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[kb].x, bv.x, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[kb].y, bv.y, acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) ph[(r0 + kq4 + 4 * v) * pitch + col] = col < k_opp ? acc[v] : 0.0;
+    }
+    __syncthreads();
+    // ---- row-wise L2 normalisation, b_j, degenerate flag (k_opp <= 64: a column per lane)
+    for (int r = wave; r < k_own; r += NW) {
+        const double p = lane < k_opp ? ph[r * pitch + lane] : 0.0;
+        double sq = p * p;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
+        const double nrm = sqrt(sq);
+        if (lane < k_opp) ph[r * pitch + lane] = p / (nrm > NORM_FLOOR ? nrm : NORM_FLOOR);
+        if (lane == 0) {
+            const bool degenerate = !(nrm >= NORM_FLOOR);
+            const double q = nrm / NORM_FLOOR;
+            bterm[r] = degenerate ? q * q : 1.0;
+            if (degenerate) degenerate_s = 1;
+        }
+    }
+    __syncthreads();
+    // ---- W = P^ C_opp, at most four 16 x 16 tiles per wave, kept in registers until C_opp's LDS is free
+    {
+        constexpr int JOBS = SMALL_MAX_K / 16 * (D / 16) / NW;
+        f64x4 acc[JOBS];
+#pragma unroll
+        for (int u = 0; u < JOBS; ++u) {
+            acc[u] = f64x4{0.0, 0.0, 0.0, 0.0};
+            const int job = wave + u * NW;
+            if (job < rt * (D / 16)) {
+                const double* ar = ph + (job / (D / 16) * 16 + i16) * pitch + 2 * kq4;
+                const double* bc = opp_s + job % (D / 16) * 16 + i16;
+                for (int k0 = 0; k0 < ct * 16; k0 += 16) {
+#pragma unroll
+                    for (int v = 0; v < 2; ++v) {
+                        const double2 av = *(const double2*)(ar + k0 + 8 * v);
+                        const int k = k0 + 8 * v + 2 * kq4;
+                        const double b0 = k < k_opp ? bc[k * CP] : 0.0;
+                        const double b1 = k + 1 < k_opp ? bc[(k + 1) * CP] : 0.0;
+                        acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.x, b0, acc[u], 0, 0, 0);
+                        acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.y, b1, acc[u], 0, 0, 0);
+                    }
+                }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < JOBS; ++u) {
+            const int job = wave + u * NW;
+            if (job < rt * (D / 16))
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    w64[(job / (D / 16) * 16 + kq4 + 4 * v) * WP + job % (D / 16) * 16 + i16] = acc[u][v];
+        }
+    }
+    __syncthreads();
+    // ---- W in the pre-filter's form, swizzled as its tiles are read, and the largest row norm
+    for (int r = wave; r < k_own; r += NW) {
+        unsigned char* blk = split + r / 32 * (L::TERMS * BLOCK);
+        const int rl = r % 32;
+        double sq = 0.0;
+#pragma unroll
+        for (int t = lane; t < D; t += 64) {
+            const double v = w64[r * WP + t];
+            const int byte = t * (int)sizeof(T);
+            const int at = rl * ROWB + (((byte / 16) ^ (rl % CPR)) * 16) + byte % 16;
+            store_split<T>(v, 0, (uint16_t*)(blk + at), (uint16_t*)(blk + BLOCK + at));
+            sq = fma(v, v, sq);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
+        if (lane == 0) atomicMax(&wmax_bits, __float_as_int(norm_rounded_up(sq)));
+    }
+    __syncthreads();
+
+    // ---- pre-filter (assign_kernel's arithmetic and margin)
+    const float wmax = __int_as_float(wmax_bits);
+    const bool degenerate = degenerate_s != 0;
+    {
+        float xn2 = 0.f;
+#pragma unroll
+        for (int c = 0; c < DC; ++c) {
+            const uint32_t wds[4] = {xf[c].x, xf[c].y, xf[c].z, xf[c].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if constexpr (BF16) {
+                    const bf16x2_t pr = __builtin_bit_cast(bf16x2_t, wds[e]);
+                    xn2 = __builtin_amdgcn_fdot2_f32_bf16(pr, pr, xn2, false);
+                } else {
+                    xn2 = fmaf(__uint_as_float(wds[e]), __uint_as_float(wds[e]), xn2);
+                }
+            }
+        }
+        auto swap = [](float v) {
+            return __builtin_amdgcn_permlane32_swap(__float_as_int(v), __float_as_int(v), false, false);
+        };
+        {
+            auto r = swap(xn2);
+            xn2 = __int_as_float(r[0]) + __int_as_float(r[1]);
+        }
+        float best = -INFINITY, second = -INFINITY;
+        int bidx = 0;
+        for (int cb = 0; cb * 32 < k_own; ++cb) {
+            const unsigned char* base = split + cb * (L::TERMS * BLOCK) + j * ROWB;
+            f32x16_t acc;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+            for (int c = 0; c < DC; ++c) {
+                const int at = ((2 * c + h) ^ (j % CPR)) * 16;
+                const uint4 wh = *(const uint4*)(base + at);
+                if constexpr (BF16) {
+                    const bf16x8_t xv = __builtin_bit_cast(bf16x8_t, xf[c]);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, wh), xv, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        __builtin_bit_cast(bf16x8_t, *(const uint4*)(base + BLOCK + at)), xv, acc, 0, 0, 0);
+                } else {
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(wh.x), __uint_as_float(xf[c].x), acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(wh.y), __uint_as_float(xf[c].y), acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(wh.z), __uint_as_float(xf[c].z), acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(wh.w), __uint_as_float(xf[c].w), acc, 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int idx = 32 * cb + 8 * (v / 4) + 4 * h + (v % 4);
+                const float val = idx < k_own ? acc[v] : -INFINITY;     // rows past the end were never written
+                second = __builtin_amdgcn_fmed3f(best, second, val);
+                bidx = val > best ? idx : bidx;
+                best = val > best ? val : best;
+            }
+        }
+        auto rb = swap(best), rs = swap(second);
+        auto ri = __builtin_amdgcn_permlane32_swap(bidx, bidx, false, false);
+        const float b0 = __int_as_float(rb[0]), b1 = __int_as_float(rb[1]);
+        const float fb = fmaxf(b0, b1), fs = fmaxf(fminf(b0, b1), fmaxf(__int_as_float(rs[0]), __int_as_float(rs[1])));
+        if (h == 0 && tok < n) {
+            const int fi = b0 >= b1 ? (int)ri[0] : (int)ri[1];
+            const bool sure = (fb - fs) > 2.0f * FAST_EPS * sqrtf(xn2) * wmax;      // false for NaN as well
+            if (degenerate || !sure)
+                open[atomicAdd(&n_open, 1)] = tok;
+            else
+                a.labels[(size_t)b * n + tok] = fi < k_own ? fi : k_own - 1;
+        }
+    }
+    __syncthreads();
+    // ---- float64 decision of the open tokens, one per wave: lane = centroid, products added in index order
+    const int count = n_open;
+    for (int p = wave; p < count; p += NW) {
+        const int t = __builtin_amdgcn_readfirstlane(open[p]);
+        const T* xr = x + (size_t)t * D;
+        const float x0 = (float)load_as_f64<T>(xr + lane), x1 = D > 64 ? (float)load_as_f64<T>(xr + (D > 64 ? 64 : 0) + lane) : 0.f;
+        auto at = [&](int c) {
+            return (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int(c < 64 ? x0 : x1), c % 64));
+        };
+        double sum = 0.0;
+        const double* wr = w64 + (lane < k_own ? lane : k_own - 1) * WP;
+#pragma unroll 32
+        for (int c = 0; c < D; ++c) sum = fma(at(c), wr[c], sum);
+        double val = sum;
+        if (degenerate) {                              // nx = ||x C_opp^T||
+            const double* row = c_opp + (size_t)(lane < k_opp ? lane : 0) * D;
+            double s = 0.0;
+#pragma unroll 16
+            for (int c = 0; c < D; ++c) s = fma(at(c), row[c], s);
+            double sq = lane < k_opp ? s * s : 0.0;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
+            const double r = sqrt(sq);
+            val = 2.0 * sum - (r > NORM_FLOOR ? r : NORM_FLOOR) * bterm[lane < k_own ? lane : k_own - 1];
+        }
+        int idx = lane < k_own ? lane : 0x7fffffff;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const double ov = __shfl_xor(val, o);
+            const int oi = __shfl_xor(idx, o);
+            if (oi != 0x7fffffff && (idx == 0x7fffffff || ov > val || (ov == val && oi < idx))) {
+                val = ov;
+                idx = oi;
+            }
+        }
+        if (lane == 0) a.labels[(size_t)b * n + t] = idx;
+    }
+}
+
+// One workgroup per (cluster, slice).  Wave w looks through the w-th quarter of the labels, 64 at a time (all in
+// flight at once), counts its members and the labels below; the members then go into LDS in token order.
+template <typename T, int D, int UNITS>
+__global__ void __launch_bounds__(256)
+update_small_kernel(const T* __restrict__ x, const int32_t* __restrict__ labels, double* __restrict__ c64,
+                    float* __restrict__ c32, int32_t* __restrict__ counts, int32_t* __restrict__ perm,
+                    int32_t* __restrict__ offsets, int n, int k) {
+    constexpr int LANES = D / 8, GROUPS = 256 / LANES;
+    __shared__ double part[GROUPS][D];
+    __shared__ uint16_t member[UNITS * 256];
+    __shared__ int32_t wave_cnt[4], wave_below[4];
+    const int b = blockIdx.y, j = blockIdx.x, tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
+    const int32_t* lab = labels + (size_t)b * n;
+    const int units = (n + 255) / 256, t0 = wave * units * 64 + lane;      // tokens t0, t0 + 64, ...
+    int mine[UNITS];
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) mine[u] = u < units && t0 + 64 * u < n ? lab[t0 + 64 * u] : 0x7fffffff;
+    int cnt = 0, below = 0;
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+        cnt += __popcll(__ballot(mine[u] == j));
+        below += __popcll(__ballot(mine[u] < j));
+    }
+    if (lane == 0) {
+        wave_cnt[wave] = cnt;
+        wave_below[wave] = below;
+    }
+    __syncthreads();
+    int run = 0, total = 0, beg = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        run += w < wave ? wave_cnt[w] : 0;
+        total += wave_cnt[w];
+        beg += wave_below[w];
+    }
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+        const unsigned long long bal = __ballot(mine[u] == j);
+        if (mine[u] == j) member[run + __popcll(bal & ((1ull << lane) - 1ull))] = (uint16_t)(t0 + 64 * u);
+        run += __popcll(bal);
+    }
+    __syncthreads();
+    // the general path's sums: row group g takes the members g, g + GROUPS, ..., the groups are added in order
+    const int le = tid % LANES, grp = tid / LANES;
+    const T* xb = x + (size_t)b * n * D + 8 * le;
+    double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    constexpr int ROWS = 8;
+    for (int p = grp; p < total; p += ROWS * GROUPS) {
+        double v[ROWS][8];
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            const int q = p + r * GROUPS < total ? p + r * GROUPS : total - 1;
+            load8_as_f64<T>(xb + (size_t)member[q] * D, v[r]);
+        }
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r)
+            if (p + r * GROUPS < total)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) s[e] += v[r][e];
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) part[grp][8 * le + e] = s[e];
+    __syncthreads();
+    if (tid < D) {
+        const size_t o = ((size_t)b * k + j) * D + tid;
+        if (total > 0) {                               // an empty cluster keeps its centroid
+            double t = part[0][tid];
+            for (int g = 1; g < GROUPS; ++g) t += part[g][tid];
+            c64[o] = t / (double)total;
+        }
+        if (c32) c32[o] = (float)c64[o];
+    }
+    if (tid == 0) {
+        if (counts) counts[(size_t)b * k + j] = total;
+        if (offsets) {
+            offsets[(size_t)b * (k + 1) + j] = beg;
+            if (j == k - 1) offsets[(size_t)b * (k + 1) + k] = beg + total;
+        }
+    }
+    if (perm)
+        for (int p = tid; p < total; p += 256) perm[(size_t)b * n + beg + p] = member[p];
+}
+
+template <typename T, int D>
+static bool small_assign(const svoo_shape* s, const SmallAssign& a, hipStream_t stream) {
+    auto kern = assign_small_kernel<T, D>;
+    constexpr int most = 140 * 1024;                   // 64 + 64 clusters, d = 128: 133 KB
+    static unsigned char opted_in[SVOO_MAX_DEVICES];
+    if (!opt_in_dynamic_lds((const void*)kern, most, opted_in)) return false;
+    const int bytes = SmallLds<T, D>(a.k_own, a.k_opp).bytes;
+    hipLaunchKernelGGL(kern, dim3((a.n + 32 * SMALL_WAVES - 1) / (32 * SMALL_WAVES), s->bh), dim3(64 * SMALL_WAVES), bytes,
+                       stream, a);
+    return true;
+}
+
+template <typename T, int D>
+static bool small_half_step(const svoo_shape* s, const SmallStep& st, hipStream_t stream) {
+    const SmallAssign a = {st.x, st.c_own, st.c_opp, st.labels, s->n, st.k_own, st.k_opp};
+    if (!small_assign<T, D>(s, a, stream)) return false;
+    auto update = [&](auto units) {
+        auto kern = update_small_kernel<T, D, decltype(units)::value>;
+        hipLaunchKernelGGL(kern, dim3(st.k_own, s->bh), dim3(256), 0, stream, (const T*)st.x, st.labels, st.c_own, st.c32,
+                           st.counts, st.perm, st.offsets, s->n, st.k_own);
+    };
+    if (s->n <= 2048)
+        update(std::integral_constant<int, 8>{});
+    else
+        update(std::integral_constant<int, SMALL_MAX_N / 256>{});
+    return true;
+}
+
+// What the launch saved is worth is the time W takes in every workgroup: up to 4,096 elements a side (3 x 4,096
+// tokens, 64 blocks: 29.6 against 30.3 us per half-step at d = 64, but 40.9 against 36.5 at d = 128), and not more
+// workgroups than the chip runs at once, fewer the larger W is (40 x 4,096 x 64, 24 blocks = 0.98 M: 33.1 against
+// 37.5; 12 x 8,192 x 128, 32 blocks = 1.57 M: 42.6 against 46.0; 40 of those 92 against 64).
+bool small_fits(const svoo_shape* s) {
+    if (s->n > SMALL_MAX_N || s->kq > SMALL_MAX_K || s->kk > SMALL_MAX_K) return false;
+    const long long w = (long long)(s->kq > s->kk ? s->kq : s->kk) * s->d;
+    return w <= 4096 && w * s->bh * ((s->n + 255) / 256) <= 1600000;
+}
+
+int small_half_step(const svoo_shape* s, const SmallStep& st, hipStream_t stream) {
+    bool ok;
+    if (s->dtype == SVOO_BF16)
+        ok = s->d == 128 ? small_half_step<uint16_t, 128>(s, st, stream) : small_half_step<uint16_t, 64>(s, st, stream);
+    else
+        ok = s->d == 128 ? small_half_step<float, 128>(s, st, stream) : small_half_step<float, 64>(s, st, stream);
+    return ok ? launch_status() : SVOO_ERR_HIP;
+}

@@ -191,6 +191,39 @@ def run_cocluster_case(h, iters, dtype, want_objective=False):
     return out, ref
 
 
+@pytest.mark.parametrize("dtype,d,n,kq,kk,bh", [
+    ("bf16", 64, 1, 1, 1, 2), ("bf16", 128, 32, 32, 17, 2), ("f32", 64, 257, 64, 33, 1), ("bf16", 64, 2048, 64, 64, 1),
+    ("bf16", 64, 2049, 5, 64, 2), ("f32", 128, 8192, 16, 31, 1), ("bf16", 64, 8193, 16, 16, 1), ("f32", 128, 700, 32, 33, 1),
+    ("bf16", 64, 300, 65, 20, 1), ("bf16", 128, 8192, 32, 32, 13)])
+def test_cocluster_at_the_edges_of_the_two_launch_path(dtype, d, n, kq, kk, bh):
+    """Slices with few clusters and tokens take two launches per half-step, larger ones the general path: sizes on
+    both sides of every line of that rule, one token, full and empty clusters, zero rows (an exact tie, decided
+    in float64), layout outputs.  Labels must be the oracle's except at proven near-ties; means to float32."""
+    rng = np.random.default_rng(n + kq)
+    q, k = (rng.standard_normal((1, n, d)).astype(np.float32) for _ in range(2))
+    if n > 100:
+        q[0, 50:60] = 0.0
+        k[0, n - 7:] = k[0, :7]
+    if dtype == "bf16":
+        q, k = synth.round_to_bf16(q), synth.round_to_bf16(k)
+    iq = rng.choice(n, kq, replace=False).astype(np.int32)[None]
+    ik = rng.choice(n, kk, replace=False).astype(np.int32)[None]
+    rep = lambda x, dt=None: H.to_dev(np.tile(x, (bh,) + (1,) * (x.ndim - 1)), dt)
+    layer = svoo.Layer(bh, n, d, H.torch_dtype(dtype), kq, kk, H.DEV)
+    layer.step_cocluster_sorted(rep(q, dtype), rep(k, dtype), rep(iq), rep(ik), 2)
+    steps, _ = H.gpu_cocluster_steps(rep(q, dtype), rep(k, dtype), rep(iq), rep(ik), 2)
+    ref = H.resync_cocluster(q[0], k[0], iq[0], ik[0], 2, H.slice_steps(steps, bh - 1))
+    for side, nc in (("q", kq), ("k", kk)):
+        labels = H.to_np(getattr(layer, f"labels_{side}"))
+        assert (labels == ref[f"labels_{side}"]).all()
+        assert (H.to_np(getattr(layer, f"counts_{side}")) == ref[f"counts_{side}"]).all()
+        c = H.to_np(getattr(layer, f"c{side}"))
+        assert (c == c[:1]).all() and np.abs(c[0] - ref[f"c{side}"]).max() <= 2.0 ** -22 * np.abs(ref[f"c{side}"]).max()
+        perm, off = so.stable_permutation(labels[0], nc)
+        assert (H.to_np(getattr(layer, f"perm_{side}")) == perm).all()
+        assert (H.to_np(getattr(layer, f"{side}_offsets")) == off).all()
+
+
 @pytest.mark.parametrize("dtype,d,iters", [("bf16", 128, 3), ("f32", 64, 5), ("bf16", 64, 2)])
 def test_cocluster_matches_oracle(dtype, d, iters):
     h = small_cfg1_head(d=d, dtype=dtype)
