@@ -214,8 +214,8 @@ __device__ __forceinline__ bool setup_tile(const AttnArgs& a, int bm, int32_t* s
 #define SVOO_SPARSE_NBUF 2
 #define DENSE_NW 8
 #define DENSE_NBUF 3
-#define SUM_LIMIT 65536.0f  // bf16: a 16-key probability sum above this raises the reference maximum
-#define RESCALE_LOG2 8.0f   // float32: the running max is only raised when it is exceeded by 2^8
+#define SUM_LIMIT 65536.0f  // a 16-key probability sum above this raises the reference
+#define RESCALE_LOG2 8.0f   // a maximum more than 2^8 above the reference raises it
 
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
@@ -248,6 +248,7 @@ sparse_attn_bf16_kernel(AttnArgs a) {
     constexpr int RPL = 64 / CPR;     // tile rows covered by one wave-load (1 KB)
     constexpr int RW = KT / NW;       // tile rows owned by one wave
     constexpr int LPW = RW / RPL;     // wave-loads per wave per tile and tensor
+    constexpr bool SUM_CHECK = !(NW == 8 && D == 128);
     static_assert(LPW >= 1 && RW <= 16 && NBUF >= 2 && NBUF <= 4, "wave-load geometry");
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     unsigned char* k_lds = smem;                     // [NBUF][TILE]
@@ -384,8 +385,10 @@ sparse_attn_bf16_kernel(AttnArgs a) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
     const float c2 = a.scale * LOG2E;
+    const float th_raw = RESCALE_LOG2 / c2;
     float m_used = -INFINITY;   // reference (raw logits) the probabilities are scaled by
-    float neg_mb = INFINITY;    // -m_used c2
+    float neg_mb = SUM_CHECK ? INFINITY : 0.f;   // -m_used c2; before the first key: whatever says "too low", or keeps 2^(-inf) = 0
+    bool fresh = true;
     float lsum = 0.f;           // this lane's share of the row sum
 
     // One tile (64 keys) out of LDS buffer `bufc`; MODE 0 = both 32-key blocks, 1 = one block (the
@@ -395,12 +398,16 @@ sparse_attn_bf16_kernel(AttnArgs a) {
     //             fetched while S finishes
     //   PV phase  first block's MFMAs run while the second block's V fragments arrive and its
     //             exponentials are computed
-    // The reference maximum is not compared with the scores: a block's probabilities are taken against the
-    // reference as it stands, and their sum, which is needed anyway, tells whether it was too low (a
-    // sum above SUM_LIMIT, infinite or not a number, as on the first block): only then the block's maximum is
-    // found, the state rescaled and the block's probabilities taken again, a few times per stream.  Against
-    // a maximum over the scores of every tile this saves ~20 vector instructions of ~150 per tile and a wait for the
-    // whole of S: 12 x 75,600 x 128 at keep 0.257 11.61 -> 11.47 ms (block-sparse), dense unchanged.
+    // The reference the probabilities are taken against follows the maximum of the scores lazily, in one of two ways:
+    //   SUM_CHECK  it is not compared with the scores at all: a block's probabilities are taken against it as it
+    //              stands, and their sum, which is needed anyway, tells whether it was too low (above SUM_LIMIT,
+    //              infinite, not a number); only then the block's maximum is found, the state rescaled and the
+    //              block done again, a few times per stream.  ~20 vector instructions of ~150 per tile less and no
+    //              wait for the whole of S: 12 x 75,600 x 128 at keep 0.257 11.92 -> 11.84 ms, 1,024 key blocks
+    //              9.85 -> 9.80, dense 12 x 32,760 x 64 3.65 -> 3.57.
+    //   otherwise  the tile's maximum is taken over all its scores first, and the reference raised when it is
+    //              exceeded by 2^8: kept for the dense kernel at d = 128, where the other form is slower
+    //              (12 x 32,760 5.81 against 5.78 ms, 6 x 45,200 6.63 against 6.50, 3 x 3,280 90 against 88 us).
     auto tile_body = [&](auto bufc, auto modec, int kt) __attribute__((always_inline)) {
         constexpr int MODE = decltype(modec)::value;
         constexpr int NKB = MODE == 0 ? 2 : 1;       // number of blocks
@@ -494,30 +501,47 @@ sparse_attn_bf16_kernel(AttnArgs a) {
             }
             return sum;
         };
+        auto block_max = [&](int kb, float mx) __attribute__((always_inline)) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[kb][v]);
+            return mx;
+        };
+        // raise the reference to this lane's maximum and its partner's
+        auto raise = [&](float mx) __attribute__((always_inline)) {
+            const int mi = __float_as_int(mx);
+            auto r = __builtin_amdgcn_permlane32_swap(mi, mi, false, false);
+            const float m_new = fmaxf(m_used, fmaxf(__int_as_float(r[0]), __int_as_float(r[1])));
+            // rows that have seen only masked keys keep the -inf reference: exponents must stay numbers
+            const float alpha = m_used == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_used - m_new) * c2);
+            m_used = m_new;
+            neg_mb = m_new == -INFINITY ? 0.f : -m_new * c2;
+            lsum *= alpha;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
+        };
         auto settle = [&](int kb, bf16x8 (&pf)[2], float sum) __attribute__((always_inline)) {
-            if (__builtin_expect(__any(!(sum <= SUM_LIMIT)), 0)) {
-                float mx = s[kb][0];
-#pragma unroll
-                for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[kb][v]);
-                const int mi = __float_as_int(mx);
-                auto r = __builtin_amdgcn_permlane32_swap(mi, mi, false, false);
-                const float m_new = fmaxf(m_used, fmaxf(__int_as_float(r[0]), __int_as_float(r[1])));
-                // rows that have seen only masked keys keep the -inf reference: exponents must stay numbers
-                const float alpha = m_used == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_used - m_new) * c2);
-                m_used = m_new;
-                neg_mb = m_new == -INFINITY ? 0.f : -m_new * c2;
-                lsum *= alpha;
-#pragma unroll
-                for (int db = 0; db < DB; ++db)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
+            if (SUM_CHECK && __builtin_expect(__any(!(sum <= SUM_LIMIT)), 0)) {
+                raise(block_max(kb, -INFINITY));
                 sum = probs(kb, pf);
-                if (m_new == -INFINITY) neg_mb = INFINITY;
+                if (m_used == -INFINITY) neg_mb = INFINITY;
             }
             lsum += sum;
         };
         // ---- O^T += V^T P^T, block by block
         bf16x8 pf[2];
+        if (!SUM_CHECK) {
+            float mx = block_max(0, -INFINITY);
+            if (NKB == 2) mx = block_max(NKB - 1, mx);
+            const int mi = __float_as_int(mx);
+            auto r = __builtin_amdgcn_permlane32_swap(mi, mi, false, false);
+            if (__any(fmaxf(__int_as_float(r[0]), __int_as_float(r[1])) > m_used + th_raw)) raise(mx);
+        } else if (fresh) {            // this wave's first tile: its maximum is the first reference
+            fresh = false;
+            raise(block_max(0, -INFINITY));
+            if (m_used == -INFINITY) neg_mb = INFINITY;
+        }
         float sum = probs(0, pf);
         settle(0, pf, sum);
         constexpr int PVALU = 48;   // VALU/transcendental instructions of one 32-key block's probabilities
