@@ -11,6 +11,11 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 #define FAST_EPS 3.1e-5f   // 2^-16 + 256 * 2^-24, twice the analytic bound for d <= 128
 
+// Below these a token's squared norm or its largest score have lost bits to float32's underflow, and the margins
+// that are built on them say nothing: such tokens are decided in float64.
+#define FAST_MIN 1e-30f
+__device__ __forceinline__ bool norms_in_range(float xn2, float xw) { return xn2 >= FAST_MIN && xw >= FAST_MIN; }
+
 // Score matrix in the form the pre-filter reads: two bf16 arrays, or one float32 array over the same bytes.
 template <typename T>
 __device__ __forceinline__ void store_split(double v, size_t o, uint16_t* w_hi, uint16_t* w_lo);

@@ -641,7 +641,7 @@ assign_kernel(AssignArgs a) {
             const float xw = sqrtf(xn2[tb]) * wmax;
             const float margin = BIAS ? 2.0f * (FAST_EPS * xw + 2.4e-7f * (0.5f * wmax * wmax + xw))   // 2^-22
                                       : 2.0f * FAST_EPS * xw;
-            const bool sure = (fb - fs) > margin;          // false for NaN as well
+            const bool sure = (fb - fs) > margin && norms_in_range(xn2[tb], xw);      // false for NaN as well
             lab[tok - g0] = fi;
             if ((degenerate || !sure) && tok < n) open[atomicAdd(&n_open, 1)] = tok - g0;
         }

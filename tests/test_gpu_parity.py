@@ -637,3 +637,30 @@ def test_cocluster_sorted_layout_equals_permute():
         assert torch.equal(getattr(a, name), getattr(b, name)), name
     for name in ("q_sorted", "k_sorted", "v_sorted"):
         assert torch.equal(getattr(a, name).view(torch.int16), getattr(b, name).view(torch.int16)), name
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n,scale", [(4096, 1.0), (4096, 1e-25), (9000, 1.0), (9000, 1e-25)])
+def test_labels_of_tokens_whose_squared_norm_leaves_float32(dtype, n, scale):
+    """Tokens moved to a near tie of their two best scores, with squared norms of 1e-48: the fast scores' error
+    bound underflows there, so only the float64 decision may speak.  n = 4,096 takes the two-launch half-step."""
+    d, kq, kk = 64, 16, 24
+    rng = np.random.default_rng(7)
+    cq, ck = (rng.standard_normal((c, d)).astype(np.float32) for c in (kq, kk))
+    p = ck.astype(np.float64) @ cq.astype(np.float64).T
+    w = p / np.linalg.norm(p, axis=1, keepdims=True) @ cq.astype(np.float64)
+    x = rng.standard_normal((n, d))
+    order = np.argsort(x @ w.T, axis=1)
+    diff = w[order[:, -1]] - w[order[:, -2]]
+    x -= diff * ((x * diff).sum(1) / (diff * diff).sum(1))[:, None]
+    x = (x * scale).astype(np.float32)
+    x = synth.round_to_bf16(x) if dtype == "bf16" else x
+    score = x.astype(np.float64) @ w.T
+    top = np.sort(score, axis=1)
+    clear = top[:, -1] - top[:, -2] > 1e-13 * np.abs(top).max(axis=1)       # float64's own rounding
+    assert clear.mean() > 0.99
+    q = synth.round_to_bf16(rng.standard_normal((n, d)).astype(np.float32))
+    res = svoo.cocluster(H.to_dev(q[None], dtype), H.to_dev(x[None], dtype), iters=1, init_cq=H.to_dev(cq[None]),
+                         init_ck=H.to_dev(ck[None]))
+    got = H.to_np(res["labels_k"])[0]
+    assert (got == score.argmax(axis=1))[clear].all()
