@@ -224,6 +224,30 @@ def test_cocluster_at_the_edges_of_the_two_launch_path(dtype, d, n, kq, kk, bh):
         assert (H.to_np(getattr(layer, f"{side}_offsets")) == off).all()
 
 
+@pytest.mark.parametrize("dtype,d,n,kq,kk", [("bf16", 64, 300, 16, 24), ("f32", 128, 281, 9, 1), ("f32", 64, 1100, 1, 63),
+                                             ("bf16", 128, 25, 3, 11), ("bf16", 64, 9000, 40, 17)])
+def test_cocluster_with_padding_tokens_as_anchors(dtype, d, n, kq, kk):
+    """Zero rows at the end of both sides, one of them the first anchor of each side: its affinity row is below the
+    Norm floor, so the general form of the distance decides every token of the slice in float64 (workgroups
+    with a few open tokens and with 256, odd numbers of centroids; the last size takes the general path)."""
+    rng = np.random.default_rng(n)
+    q, k = (rng.standard_normal((1, n, d)).astype(np.float32) for _ in range(2))
+    pad = max(3, n // 10)
+    q[0, n - pad:] = 0.0
+    k[0, n - pad:] = 0.0
+    if dtype == "bf16":
+        q, k = synth.round_to_bf16(q), synth.round_to_bf16(k)
+    anchors = [rng.choice(n - pad, c, replace=False).astype(np.int32)[None] for c in (kq, kk)]
+    for a in anchors:
+        a[0, 0] = n - 1 if a.shape[1] > 1 else a[0, 0]
+    dev = [H.to_dev(q, dtype), H.to_dev(k, dtype), *map(H.to_dev, anchors)]
+    steps, _ = H.gpu_cocluster_steps(*dev, 2)
+    ref = H.resync_cocluster(q[0], k[0], anchors[0][0], anchors[1][0], 2, H.slice_steps(steps, 0))
+    res = svoo.cocluster(*dev, iters=2)
+    for side in "qk":
+        assert (H.to_np(res[f"labels_{side}"])[0] == ref[f"labels_{side}"]).all()
+
+
 @pytest.mark.parametrize("dtype,d,iters", [("bf16", 128, 3), ("f32", 64, 5), ("bf16", 64, 2)])
 def test_cocluster_matches_oracle(dtype, d, iters):
     h = small_cfg1_head(d=d, dtype=dtype)
