@@ -330,6 +330,35 @@ def test_block_mask_bit_exact(mode, kq, kk, d):
             assert (lst[b, r, cnt[b, r]:] == -1).all()
 
 
+# distinct key centroids (1: one full bin, all blocks tied), their spread (40: most weights below 2^-32)
+@pytest.mark.parametrize("distinct,spread", [(1, 1), (3, 1), (50, 2), (400, 2), (400, 40)])
+@pytest.mark.parametrize("kk", [1, 15, 64, 255, 256, 257, 511, 513, 1024])
+def test_block_mask_ties_and_full_bins(distinct, spread, kk):
+    """Centroids of small integers: every logit is exact in any order of the additions, so that equal blocks tie on
+    both sides and the order among them is the lower index first."""
+    rng = np.random.default_rng(kk * 31 + distinct + spread)
+    bh, kq, d = 2, 7, 64
+    cq = rng.integers(-2, 3, size=(bh, kq, d)).astype(np.float32)
+    pool = spread * rng.integers(-1, 2, size=(distinct, d))
+    ck = pool[rng.integers(0, distinct, size=(bh, kk))].astype(np.float32)
+    nq = np.full((bh, kq), 3, dtype=np.int32)
+    nk = rng.choice([0, 4, 4, 12], size=(bh, kk)).astype(np.int32)
+    nk[:, 0] = 4
+    for keep, tau in ((0.3, 1.0), (0.9, 0.83), (1.0, 0.61), (0.05, 0.83)):
+        ratios = np.full(bh, keep, dtype=np.float32)
+        tau32, scale = float(np.float32(tau)), H.scale_of(d)
+        cnt, lst, bitmap = svoo.block_mask(H.to_dev(cq), H.to_dev(ck), H.to_dev(nq), H.to_dev(nk), H.to_dev(ratios),
+                                           tau32, 0.1, scale)
+        cnt, lst, bitmap = H.to_np(cnt), H.to_np(lst), H.to_np(bitmap)
+        for b in range(bh):
+            ref = so.block_mask(cq[b], ck[b], nq[b], nk[b], ratios[b], tau32, 0.1, scale)
+            assert (bitmap[b].astype(bool) == ref).all()
+            for r in range(kq):
+                assert cnt[b, r] == ref[r].sum()
+                assert (lst[b, r, :cnt[b, r]] == np.nonzero(ref[r])[0]).all()
+                assert (lst[b, r, cnt[b, r]:] == -1).all()
+
+
 @pytest.mark.parametrize("keep,kk,want", [(0.3, 20, 6), (0.2, 1000, 200), (0.1, 1000, 100), (0.7, 10, 7), (0.26, 4, 2)])
 def test_block_mask_decimal_keep_is_the_real_number(keep, kk, want):
     """keep crosses the boundary as a float32 (0.3f * 20 = 6.0000002): the budget is still ceil of the
