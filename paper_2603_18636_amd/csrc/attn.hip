@@ -214,8 +214,7 @@ __device__ __forceinline__ bool setup_tile(const AttnArgs& a, int bm, int32_t* s
 #define SVOO_SPARSE_NBUF 2
 #define DENSE_NW 8
 #define DENSE_NBUF 3
-#define SUM_LIMIT 65536.0f  // a 16-key probability sum above this raises the reference
-#define RESCALE_LOG2 8.0f   // a maximum more than 2^8 above the reference raises it
+#define RESCALE_LOG2 8.0f   // the running max is only raised when it is exceeded by 2^8
 
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
@@ -248,7 +247,6 @@ sparse_attn_bf16_kernel(AttnArgs a) {
     constexpr int RPL = 64 / CPR;     // tile rows covered by one wave-load (1 KB)
     constexpr int RW = KT / NW;       // tile rows owned by one wave
     constexpr int LPW = RW / RPL;     // wave-loads per wave per tile and tensor
-    constexpr bool SUM_CHECK = !(NW == 8 && D == 128);
     static_assert(LPW >= 1 && RW <= 16 && NBUF >= 2 && NBUF <= 4, "wave-load geometry");
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     unsigned char* k_lds = smem;                     // [NBUF][TILE]
@@ -386,39 +384,28 @@ sparse_attn_bf16_kernel(AttnArgs a) {
         for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
     const float c2 = a.scale * LOG2E;
     const float th_raw = RESCALE_LOG2 / c2;
-    float m_used = -INFINITY;   // reference (raw logits) the probabilities are scaled by
-    float neg_mb = SUM_CHECK ? INFINITY : 0.f;   // -m_used c2; before the first key: whatever says "too low", or keeps 2^(-inf) = 0
-    bool fresh = true;
+    float m_used = -INFINITY;   // reference max (raw logits) the probabilities are scaled by
     float lsum = 0.f;           // this lane's share of the row sum
 
-    // One tile (64 keys) out of LDS buffer `bufc`; MODE 0 = both 32-key blocks, 1 = one block (the
-    // key-split wave's own block, whose offset is already folded into the read addresses).  LDS reads are issued in
-    // batches ahead of the matrix instructions that consume them (the LDS latency is ~100 cycles, one MFMA is 32):
-    //   S phase   K fragments in batches of DC/2, two batches in flight; V fragments of the first block are
-    //             fetched while S finishes
+    // One tile (64 keys) out of LDS buffer BUF; MODE 0 = both 32-key blocks, 1 = one block (the
+    // key-split wave's own block, whose offset is already folded into the read addresses).  LDS reads are issued in batches ahead of the matrix
+    // instructions that consume them (the LDS latency is ~100 cycles, one MFMA is 32):
+    //   S phase   K fragments in batches of DC/2, two batches in flight
+    //   softmax   V fragments of the first block are fetched while S finishes
     //   PV phase  first block's MFMAs run while the second block's V fragments arrive and its
     //             exponentials are computed
-    // The reference the probabilities are taken against follows the maximum of the scores lazily, in one of two ways:
-    //   SUM_CHECK  it is not compared with the scores at all: a block's probabilities are taken against it as it
-    //              stands, and their sum, which is needed anyway, tells whether it was too low (above SUM_LIMIT,
-    //              infinite, not a number); only then the block's maximum is found, the state rescaled and the
-    //              block done again, a few times per stream.  ~20 vector instructions of ~150 per tile less and no
-    //              wait for the whole of S: 12 x 75,600 x 128 at keep 0.257 11.92 -> 11.84 ms, 1,024 key blocks
-    //              9.85 -> 9.80, dense 12 x 32,760 x 64 3.65 -> 3.57.
-    //   otherwise  the tile's maximum is taken over all its scores first, and the reference raised when it is
-    //              exceeded by 2^8: kept for the dense kernel at d = 128, where the other form is slower
-    //              (12 x 32,760 5.81 against 5.78 ms, 6 x 45,200 6.63 against 6.50, 3 x 3,280 90 against 88 us).
-    auto tile_body = [&](auto bufc, auto modec, int kt) __attribute__((always_inline)) {
+    auto tile_body = [&](auto bufc, auto modec, int kt) {
+        constexpr int BUF = decltype(bufc)::value;
         constexpr int MODE = decltype(modec)::value;
+        constexpr int KB0 = 0;
         constexpr int NKB = MODE == 0 ? 2 : 1;       // number of blocks
         constexpr int HB = DC / 2;
-        constexpr int boff = decltype(bufc)::value * TILE;
         auto kfrag = [&](int kb, int c) {
-            const uint32_t addr = (uint32_t)(koff[c] + boff + kb * 32 * ROWB);
+            const uint32_t addr = (uint32_t)(koff[c] + BUF * TILE + kb * 32 * ROWB);
             return __builtin_bit_cast(bf16x8, *(const __attribute__((address_space(3))) uint4*)(uintptr_t)addr);
         };
         auto vfrag = [&](int kb, int t, int db) {
-            const int cst = boff + (32 * kb + 16 * t) * ROWB;
+            const int cst = BUF * TILE + (32 * kb + 16 * t) * ROWB;
             const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
                 (__attribute__((address_space(3))) bf16x4*)(uintptr_t)(uint32_t)(voff[0][db] + cst));
             const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
@@ -433,9 +420,9 @@ sparse_attn_bf16_kernel(AttnArgs a) {
         bf16x8 fa[HB], fb[HB];
         bf16x8 vf[2][DB];
 #pragma unroll
-        for (int c = 0; c < HB; ++c) fa[c] = kfrag(0, c);
+        for (int c = 0; c < HB; ++c) fa[c] = kfrag(KB0, c);
 #pragma unroll
-        for (int c = 0; c < HB; ++c) fb[c] = kfrag(0, HB + c);
+        for (int c = 0; c < HB; ++c) fb[c] = kfrag(KB0, HB + c);
         if (NKB == 2) {
 #pragma unroll
             for (int c = 0; c < HB; ++c) {
@@ -452,7 +439,7 @@ sparse_attn_bf16_kernel(AttnArgs a) {
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int db = 0; db < DB; ++db) vf[t][db] = vfrag(0, t, db);
+            for (int db = 0; db < DB; ++db) vf[t][db] = vfrag(KB0, t, db);
 #pragma unroll
         for (int c = 0; c < HB; ++c)
             s[NKB - 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[c], qf[c], s[NKB - 1], 0, 0, 0);
@@ -474,7 +461,8 @@ sparse_attn_bf16_kernel(AttnArgs a) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x100, (2 * 2 * DB) / (2 * HB), 0);
         }
-        if (kt == n_tiles - 1 && (total % KT) != 0) {     // ragged last tile: keys past the end of the stream get -inf
+        // ragged last tile: keys past the end of the stream get -inf
+        if (kt == n_tiles - 1 && (total % KT) != 0) {
             const int base = kt * KT + 4 * h;
 #pragma unroll
             for (int kb = 0; kb < NKB; ++kb)
@@ -482,71 +470,47 @@ sparse_attn_bf16_kernel(AttnArgs a) {
                 for (int v = 0; v < 16; ++v)
                     if (base + kb_off + 32 * kb + 8 * (v / 4) + (v % 4) >= total) s[kb][v] = -INFINITY;
         }
-        const bf16x2 ones2 = __builtin_bit_cast(bf16x2, 0x3f803f80u);
-        auto probs = [&](int kb, bf16x8 (&pf)[2]) __attribute__((always_inline)) {
-            float sum = 0.f;
+        float mx = s[0][0];
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                uint32_t w[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float p0 = __builtin_amdgcn_exp2f(fmaf(s[kb][8 * t + 2 * e], c2, neg_mb));
-                    const float p1 = __builtin_amdgcn_exp2f(fmaf(s[kb][8 * t + 2 * e + 1], c2, neg_mb));
-                    w[e] = pack2_bf16(p0, p1);
-                    // the row sum takes the two ROUNDED probabilities, the same values the second
-                    // contraction multiplies: one dot-product instruction with (1, 1) instead of two adds
-                    sum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w[e]), ones2, sum, false);
-                }
-                pf[t] = __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3]));
-            }
-            return sum;
-        };
-        auto block_max = [&](int kb, float mx) __attribute__((always_inline)) {
+        for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
             for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[kb][v]);
-            return mx;
-        };
-        // raise the reference to this lane's maximum and its partner's
-        auto raise = [&](float mx) __attribute__((always_inline)) {
+        {
             const int mi = __float_as_int(mx);
             auto r = __builtin_amdgcn_permlane32_swap(mi, mi, false, false);
-            const float m_new = fmaxf(m_used, fmaxf(__int_as_float(r[0]), __int_as_float(r[1])));
-            // rows that have seen only masked keys keep the -inf reference: exponents must stay numbers
-            const float alpha = m_used == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_used - m_new) * c2);
+            mx = fmaxf(__int_as_float(r[0]), __int_as_float(r[1]));
+        }
+        if (__any(mx > m_used + th_raw)) {
+            const float m_new = fmaxf(m_used, mx);
+            const float alpha = __builtin_amdgcn_exp2f((m_used - m_new) * c2);   // 0 on the first tile
             m_used = m_new;
-            neg_mb = m_new == -INFINITY ? 0.f : -m_new * c2;
             lsum *= alpha;
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
-        };
-        auto settle = [&](int kb, bf16x8 (&pf)[2], float sum) __attribute__((always_inline)) {
-            if (SUM_CHECK && __builtin_expect(__any(!(sum <= SUM_LIMIT)), 0)) {
-                raise(block_max(kb, -INFINITY));
-                sum = probs(kb, pf);
-                if (m_used == -INFINITY) neg_mb = INFINITY;
+        }
+        // a key-split wave may have seen only masked keys so far (-inf reference): keep exp2 finite
+        const float mb = (MODE != 0 && m_used == -INFINITY) ? 0.f : m_used * c2;
+        const bf16x2 ones2 = __builtin_bit_cast(bf16x2, 0x3f803f80u);
+        auto probs = [&](int kb, int t) {
+            uint32_t w[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float p0 = __builtin_amdgcn_exp2f(fmaf(s[kb][8 * t + 2 * e], c2, -mb));
+                const float p1 = __builtin_amdgcn_exp2f(fmaf(s[kb][8 * t + 2 * e + 1], c2, -mb));
+                w[e] = pack2_bf16(p0, p1);
+                // the row sum takes the two ROUNDED probabilities, the same values the second
+                // contraction multiplies: one dot-product instruction with (1, 1) instead of two adds
+                lsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w[e]), ones2, lsum, false);
             }
-            lsum += sum;
+            return __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3]));
         };
         // ---- O^T += V^T P^T, block by block
         bf16x8 pf[2];
-        if (!SUM_CHECK) {
-            float mx = block_max(0, -INFINITY);
-            if (NKB == 2) mx = block_max(NKB - 1, mx);
-            const int mi = __float_as_int(mx);
-            auto r = __builtin_amdgcn_permlane32_swap(mi, mi, false, false);
-            if (__any(fmaxf(__int_as_float(r[0]), __int_as_float(r[1])) > m_used + th_raw)) raise(mx);
-        } else if (fresh) {            // this wave's first tile: its maximum is the first reference
-            fresh = false;
-            raise(block_max(0, -INFINITY));
-            if (m_used == -INFINITY) neg_mb = INFINITY;
-        }
-        float sum = probs(0, pf);
-        settle(0, pf, sum);
-        constexpr int PVALU = 48;   // VALU/transcendental instructions of one 32-key block's probabilities
+        pf[0] = probs(0, 0);
+        pf[1] = probs(0, 1);
         if (NKB == 2) {
-            bf16x8 pn[2];
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -554,23 +518,27 @@ sparse_attn_bf16_kernel(AttnArgs a) {
                     o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[t][db], pf[t], o[db], 0, 0, 0);
                     vf[t][db] = vfrag(1, t, db);
                 }
-            sum = probs(1, pn);
-            // each MFMA of block 0 paired with two V reads of block 1 and a slice of block 1's exponentials
-#pragma unroll
-            for (int i = 0; i < 2 * DB; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-                __builtin_amdgcn_sched_group_barrier(0x402, PVALU / (2 * DB), 0);
-            }
-            settle(1, pn, sum);
-            pf[0] = pn[0];
-            pf[1] = pn[1];
+            pf[0] = probs(1, 0);
+            pf[1] = probs(1, 1);
         }
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int db = 0; db < DB; ++db)
                 o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[t][db], pf[t], o[db], 0, 0, 0);
+        constexpr int PVALU = 48;   // VALU/transcendental instructions of one 32-key block's probabilities
+        // pipeline: exponentials of the first block, then (two-block tiles) each MFMA of block 0
+        // paired with two V reads of block 1 and a slice of block 1's exponentials, then the rest
+        __builtin_amdgcn_sched_group_barrier(0x402, PVALU, 0);
+        if (NKB == 2) {
+#pragma unroll
+            for (int i = 0; i < 2 * DB; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                __builtin_amdgcn_sched_group_barrier(0x402, PVALU / (2 * DB), 0);
+            }
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 2 * DB, 0);
     };
 
     // Have the Q fragments arrive here: otherwise the compiler's wait for them sits inside the tile

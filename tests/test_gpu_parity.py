@@ -430,6 +430,54 @@ def test_attention_when_the_logits_keep_rising(dtype, d, n, step):
     assert err <= (2e-2 if dtype == "bf16" else 1e-5) + 2 * logit_err * np.abs(v).max()
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64)])
+@pytest.mark.parametrize("delta", [5.5, 11.0, 60.0])
+def test_sparse_attn_when_the_logits_jump(dtype, d, delta):
+    """Block-sparse attention whose reference maximum has to rise in mid-stream: from one key on the logits are
+    `delta` higher (2^7.9, 2^15.9 and 2^86 in the probabilities) in even rows, lower in every fourth and as
+    before in the rest.  The jump falls into the first and into the second 32-key block of a tile, streams are
+    ragged, and query blocks of 20, 60 and 200 rows take the four-way, the two-way and no key split.  Large
+    values (what is summed up must stay in float32's range while the reference is behind) and ordinary ones."""
+    n, scale = 280, 1.0 / 8.0
+    rng = np.random.default_rng(int(delta) + d)
+    q_off, k_off = np.array([0, 20, 80, 280]), np.array([0, 70, 140, 210, 280])
+    lists = [[0, 1, 2, 3], [0, 2, 3], [0, 1, 2, 3]]
+    cnt = np.array([[len(x) for x in lists]], dtype=np.int32)
+    lst = np.array([[x + [-1] * (4 - len(x)) for x in lists]], dtype=np.int32)
+    kept = np.zeros((n, n), dtype=bool)
+    for r, blocks in enumerate(lists):
+        for j in blocks:
+            kept[q_off[r]:q_off[r + 1], k_off[j]:k_off[j + 1]] = True
+    for jump, size in ((40, 1.0), (70, 1.0), (130, 1e34), (165, 1e34)):
+        q, k, v = (rng.standard_normal((1, n, d)).astype(np.float32) for _ in range(3))
+        v *= size
+        k[0, :, 0] = np.where(np.arange(n) >= jump, delta, 0.0)
+        q[0, :, 0] = 0.0
+        q[0, ::2, 0] = 8.0
+        q[0, ::4, 0] = -8.0
+        if dtype == "bf16":
+            q, k, v = (synth.round_to_bf16(x) for x in (q, k, v))
+        qd, kd, vd = (H.to_dev(x, dtype) for x in (q, k, v))
+        index = [H.to_dev(x[None].astype(np.int32)) for x in (q_off, k_off)] + [H.to_dev(cnt), H.to_dev(lst)]
+        out, lse = svoo.block_sparse_attn(qd, kd, vd, *index, scale, want_lse=True)
+        perm = rng.permutation(n).astype(np.int32)             # token order: sorted row p is token perm[p]
+        token_q = np.empty_like(q)
+        token_q[0, perm] = q[0]
+        fused, fused_lse = svoo.block_sparse_attn_tokens(H.to_dev(token_q, dtype), H.to_dev(perm[None]), kd, vd, *index,
+                                                         scale, want_lse=True)
+        assert np.array_equal(H.to_np(fused)[0][perm], H.to_np(out)[0])
+        assert np.array_equal(H.to_np(fused_lse)[0][perm], H.to_np(lse)[0])
+        logits = np.where(kept, scale * (q[0].astype(np.float64) @ k[0].T.astype(np.float64)), -np.inf)
+        m = logits.max(1)
+        ref = m + np.log(np.exp(logits - m[:, None]).sum(1))
+        # bounds as in the test above
+        logit_err = (d + 4) * 2.0 ** -24 * np.abs(logits[kept]).max()
+        assert np.abs(H.to_np(lse)[0] - ref).max() <= (2.0 ** -9 if dtype == "bf16" else 1e-6) + logit_err
+        w = np.exp(logits - ref[:, None])
+        err = np.abs(H.to_np(out)[0] / size - w @ (v[0].astype(np.float64) / size)).max()
+        assert err <= (2e-2 if dtype == "bf16" else 1e-5) + 2 * logit_err * np.abs(v).max() / size
+
+
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64), ("bf16", 64), ("f32", 128)])
 def test_sparse_attn_matches_oracle_random_mask(dtype, d):
     """Random labels (ragged cluster sizes, some empty) and a random mask: pins the key-stream walk,
