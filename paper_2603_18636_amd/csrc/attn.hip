@@ -383,8 +383,9 @@ sparse_attn_bf16_kernel(AttnArgs a) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
     const float c2 = a.scale * LOG2E;
-    const float th_raw = RESCALE_LOG2 / c2;
+    const float th_raw = fminf(RESCALE_LOG2 / c2, 3.4028234e38f);     // finite: -inf + th_raw has to stay -inf
     float m_used = -INFINITY;   // reference max (raw logits) the probabilities are scaled by
+    float neg_mb = 0.f;         // -m_used c2; before the first finite logit 0, so that 2^(-inf) stays a number
     float lsum = 0.f;           // this lane's share of the row sum
 
     // One tile (64 keys) out of LDS buffer BUF; MODE 0 = both 32-key blocks, 1 = one block (the
@@ -482,23 +483,23 @@ sparse_attn_bf16_kernel(AttnArgs a) {
         }
         if (__any(mx > m_used + th_raw)) {
             const float m_new = fmaxf(m_used, mx);
-            const float alpha = __builtin_amdgcn_exp2f((m_used - m_new) * c2);   // 0 on the first tile
+            // rows without a finite logit yet keep the -inf reference: (-inf) - (-inf) must not reach the exponential
+            const float alpha = m_used == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_used - m_new) * c2);
             m_used = m_new;
+            neg_mb = m_new == -INFINITY ? 0.f : -m_new * c2;
             lsum *= alpha;
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
         }
-        // a key-split wave may have seen only masked keys so far (-inf reference): keep exp2 finite
-        const float mb = (MODE != 0 && m_used == -INFINITY) ? 0.f : m_used * c2;
         const bf16x2 ones2 = __builtin_bit_cast(bf16x2, 0x3f803f80u);
         auto probs = [&](int kb, int t) {
             uint32_t w[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float p0 = __builtin_amdgcn_exp2f(fmaf(s[kb][8 * t + 2 * e], c2, -mb));
-                const float p1 = __builtin_amdgcn_exp2f(fmaf(s[kb][8 * t + 2 * e + 1], c2, -mb));
+                const float p0 = __builtin_amdgcn_exp2f(fmaf(s[kb][8 * t + 2 * e], c2, neg_mb));
+                const float p1 = __builtin_amdgcn_exp2f(fmaf(s[kb][8 * t + 2 * e + 1], c2, neg_mb));
                 w[e] = pack2_bf16(p0, p1);
                 // the row sum takes the two ROUNDED probabilities, the same values the second
                 // contraction multiplies: one dot-product instruction with (1, 1) instead of two adds

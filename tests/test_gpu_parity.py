@@ -478,6 +478,35 @@ def test_sparse_attn_when_the_logits_jump(dtype, d, delta):
         assert err <= (2e-2 if dtype == "bf16" else 1e-5) + 2 * logit_err * np.abs(v).max() / size
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64)])
+def test_attention_with_keys_out_of_reach_and_with_a_tiny_scale(dtype, d):
+    """Rows whose logits start with 64, 100 or no -inf (a product beyond float32's range): those keys weigh nothing and
+    the rows are ordinary otherwise.  And a scale below 2^-125, where 2^8 above the reference is no longer
+    a float32: logits of about 1 all the same."""
+    rng = np.random.default_rng(d)
+    n = 333
+    for far, scale in ((64, 0.1), (100, 0.1), (0, 1e-38)):
+        q, k, v = (rng.standard_normal((1, n, d)).astype(np.float32) for _ in range(3))
+        if far:
+            q[0, :, 0] = np.where(np.arange(n) % 3 == 0, 2.0 ** 100, 0.0)
+            k[0, :, 0] = np.where(np.arange(n) < far, -(2.0 ** 100), 0.0)
+        else:
+            q, k = q * np.float32(2e18), k * np.float32(2e18)
+        if dtype == "bf16":
+            q, k, v = (synth.round_to_bf16(x) for x in (q, k, v))
+        logits = scale * (q[0].astype(np.float64) @ k[0].T.astype(np.float64))
+        logits[logits < -1e30] = -np.inf
+        m = logits.max(1)
+        ref = m + np.log(np.exp(logits - m[:, None]).sum(1))
+        want = np.exp(logits - ref[:, None]) @ v[0].astype(np.float64)
+        qd, kd, vd = (H.to_dev(x, dtype) for x in (q, k, v))
+        sparse = [H.to_dev(np.array(x, dtype=np.int32)[None]) for x in ([0, 20, 70, n], [0, n], [1, 1, 1], [[0], [0], [0]])]
+        for out, lse in (svoo.attn(qd, kd, vd, scale, want_lse=True),
+                         svoo.block_sparse_attn(qd, kd, vd, *sparse, scale, want_lse=True)):
+            H.assert_attn_close(H.to_np(out)[0], want, dtype, f"far {far}")
+            assert np.abs(H.to_np(lse)[0] - ref).max() <= (1e-2 if dtype == "bf16" else 1e-4)
+
+
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64), ("bf16", 64), ("f32", 128)])
 def test_sparse_attn_matches_oracle_random_mask(dtype, d):
     """Random labels (ragged cluster sizes, some empty) and a random mask: pins the key-stream walk,
