@@ -757,8 +757,10 @@ sparse_attn_f32_kernel(AttnArgs a) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
     const float c2 = a.scale * LOG2E;
-    const float th_raw = RESCALE_LOG2 / c2;
-    float m_used = -INFINITY;                   // reference max (raw logits) the probabilities are scaled by
+    // Reference of the probabilities 2^(s c2 - ref), in octaves.  It lies RESCALE_LOG2 above the maximum it was set by
+    // and is raised when a score passes it, so no probability exceeds 1 and the sums stay as far from
+    // overflow as the values are.
+    float ref = -INFINITY;
     float lsum = 0.f;                           // this lane's share of the row sum
 
     if (n_tiles > 0) {
@@ -801,21 +803,22 @@ sparse_attn_f32_kernel(AttnArgs a) {
             auto r = __builtin_amdgcn_permlane32_swap(mi, mi, false, false);
             mx = fmaxf(__int_as_float(r[0]), __int_as_float(r[1]));
         }
-        if (__any(mx > m_used + th_raw)) {
-            const float m_new = fmaxf(m_used, mx);
+        const float top = mx * c2;
+        if (__any(top > ref)) {
+            const float ref_new = fmaxf(ref, top + RESCALE_LOG2);
             // rows that have seen no key yet keep zeros: (-inf) - (-inf) must not reach the exponential
-            const float alpha = m_used == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_used - m_new) * c2);
-            m_used = m_new;
+            const float alpha = ref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ref - ref_new);
+            ref = ref_new;
             lsum *= alpha;
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
         }
-        const float mb = m_used == -INFINITY ? 0.f : m_used * c2;      // a split may have met masked keys only
+        const float off = ref == -INFINITY ? 0.f : -ref;               // a split may have met masked keys only
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            s[v] = __builtin_amdgcn_exp2f(fmaf(s[v], c2, -mb));
+            s[v] = __builtin_amdgcn_exp2f(fmaf(s[v], c2, off));
             lsum += s[v];
         }
 #pragma unroll
@@ -850,7 +853,7 @@ sparse_attn_f32_kernel(AttnArgs a) {
         for (int db = 0; db < DB; ++db)
 #pragma unroll
             for (int v = 0; v < 16; ++v) park[(16 * db + v) * 64 + lane] = o[db][v];
-        park[(16 * DB) * 64 + lane] = m_used;
+        park[(16 * DB) * 64 + lane] = ref;
         park[(16 * DB + 1) * 64 + lane] = ltot;
     }
     __syncthreads();
@@ -858,16 +861,16 @@ sparse_attn_f32_kernel(AttnArgs a) {
 #pragma unroll
     for (int g = 1; g < KS; ++g) {
         const float* park = (const float*)smem + ((g - 1) * RG + rg) * PARK;
-        const float m_b = park[(16 * DB) * 64 + lane], l_b = park[(16 * DB + 1) * 64 + lane];
-        const float m_new = fmaxf(m_used, m_b);
-        const float sa = m_used == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_used - m_new) * c2);
-        const float sb = m_b == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_b - m_new) * c2);
+        const float ref_b = park[(16 * DB) * 64 + lane], l_b = park[(16 * DB + 1) * 64 + lane];
+        const float ref_new = fmaxf(ref, ref_b);
+        const float sa = ref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ref - ref_new);
+        const float sb = ref_b == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ref_b - ref_new);
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
             for (int v = 0; v < 16; ++v) o[db][v] = o[db][v] * sa + park[(16 * db + v) * 64 + lane] * sb;
         ltot = ltot * sa + l_b * sb;
-        m_used = m_new;
+        ref = ref_new;
     }
     if (!qvalid) return;
     const float inv = ltot > 0.f ? 1.f / ltot : 0.f;
@@ -881,7 +884,7 @@ sparse_attn_f32_kernel(AttnArgs a) {
             *(float2*)dst = make_float2(o[0][v] * inv, o[1][v] * inv);
     }
     if (a.lse && h == 0)
-        a.lse[(size_t)b * a.n + qtok] = ltot > 0.f ? (m_used * c2 + log2f(ltot)) * 0.6931471805599453f : -INFINITY;
+        a.lse[(size_t)b * a.n + qtok] = ltot > 0.f ? (ref + log2f(ltot)) * 0.6931471805599453f : -INFINITY;
 }
 
 // ---------------------------------------------------------------------------------------------

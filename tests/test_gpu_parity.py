@@ -430,7 +430,7 @@ def test_attention_when_the_logits_keep_rising(dtype, d, n, step):
     assert err <= (2e-2 if dtype == "bf16" else 1e-5) + 2 * logit_err * np.abs(v).max()
 
 
-@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64)])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
 @pytest.mark.parametrize("delta", [5.5, 11.0, 60.0])
 def test_sparse_attn_when_the_logits_jump(dtype, d, delta):
     """Block-sparse attention whose reference maximum has to rise in mid-stream: from one key on the logits are
@@ -448,7 +448,8 @@ def test_sparse_attn_when_the_logits_jump(dtype, d, delta):
     for r, blocks in enumerate(lists):
         for j in blocks:
             kept[q_off[r]:q_off[r + 1], k_off[j]:k_off[j + 1]] = True
-    for jump, size in ((40, 1.0), (70, 1.0), (130, 1e34), (165, 1e34)):
+    large = 1e34 if dtype == "bf16" else 1e36                  # float32 raises its reference at once
+    for jump, size in ((40, 1.0), (70, 1.0), (130, large), (165, large)):
         q, k, v = (rng.standard_normal((1, n, d)).astype(np.float32) for _ in range(3))
         v *= size
         k[0, :, 0] = np.where(np.arange(n) >= jump, delta, 0.0)
@@ -478,7 +479,7 @@ def test_sparse_attn_when_the_logits_jump(dtype, d, delta):
         assert err <= (2e-2 if dtype == "bf16" else 1e-5) + 2 * logit_err * np.abs(v).max() / size
 
 
-@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64)])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
 def test_attention_with_keys_out_of_reach_and_with_a_tiny_scale(dtype, d):
     """Rows whose logits start with 64, 100 or no -inf (a product beyond float32's range): those keys weigh nothing and
     the rows are ordinary otherwise.  And a scale below 2^-125, where 2^8 above the reference is no longer
