@@ -665,7 +665,10 @@ sparse_attn_bf16_kernel(AttnArgs a) {
 // stream is 32 KS keys, wave (rg, ks) takes its ks-th 32-key block, the KS partial results are merged at the
 // end.  As in the bf16 kernel the transposes are computed (one query per lane):
 //   S^T = K_tile Q^T    the contraction index of a 16-byte chunk pair (2 c, 2 c + 1) is split over the two half
-//                       waves: one ds_read_b128 per lane feeds four instructions
+//                       waves: one ds_read_b128 per lane feeds four instructions.
+//                       Four chains of D / 4 products, added up: one chain of D was 1.2-2.4 times as
+//                       far from the 64-bit result as four lanes of plain FMAs, four chains 0.3-0.95 times (2-3 %
+//                       of the time, 1.05 -> 1.08 ms at the size below)
 //   O^T += V^T P^T      instruction v contracts the two keys whose probabilities lane halves hold in accumulator
 //                       v, so P is the B operand as it stands; row i of the e-th 32-row block of O^T is column
 //                       (D / 32) i + e, so one read of D / 32 adjacent floats feeds all blocks and every
@@ -772,16 +775,22 @@ sparse_attn_f32_kernel(AttnArgs a) {
         __syncthreads();                        // K of this stage is there, V of the last one is used up
         issue(vg, v_lds, false);
         f32x16 s;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) s[v] = 0.f;
         if (wave_active) {
 #pragma unroll
-            for (int c = 0; c < DC; ++c) {
-                const float4 kf = *(const float4*)(k_base + (((2 * c + h) ^ (j % CPR)) * 16));
-                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.x, qf[c].x, s, 0, 0, 0);
-                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.y, qf[c].y, s, 0, 0, 0);
-                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.z, qf[c].z, s, 0, 0, 0);
-                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.w, qf[c].w, s, 0, 0, 0);
+            for (int part = 0; part < 4; ++part) {
+                f32x16 t;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) t[v] = 0.f;
+#pragma unroll
+                for (int c = part * DC / 4; c < (part + 1) * DC / 4; ++c) {
+                    const float4 kf = *(const float4*)(k_base + (((2 * c + h) ^ (j % CPR)) * 16));
+                    t = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.x, qf[c].x, t, 0, 0, 0);
+                    t = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.y, qf[c].y, t, 0, 0, 0);
+                    t = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.z, qf[c].z, t, 0, 0, 0);
+                    t = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.w, qf[c].w, t, 0, 0, 0);
+                }
+#pragma unroll
+                for (int v = 0; v < 16; ++v) s[v] = part ? s[v] + t[v] : t[v];
             }
         }
         if (kt + 1 < n_tiles) prepare(kt + 1);

@@ -508,6 +508,30 @@ def test_attention_with_keys_out_of_reach_and_with_a_tiny_scale(dtype, d):
             assert np.abs(H.to_np(lse)[0] - ref).max() <= (1e-2 if dtype == "bf16" else 1e-4)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_float32_logits_round_like_four_chains(d):
+    """Two keys that differ little: the output is the logistic function of the difference of two logits, whose error is
+    that of the float32 sums behind them.  Its root mean square over 4,096 rows must be that of sums in four chains
+    of d / 4 products (emulated here; the sampling error is 1.1 %, and exponent and output add 1e-7 each; one
+    chain of d is 1.6 times as far off)."""
+    rng = np.random.default_rng(d)
+    bh = 2048
+    q, k = (rng.standard_normal((bh, 2, d)).astype(np.float32) for _ in range(2))
+    k[:, 1] = k[:, 0] + np.float32(1e-3) * rng.standard_normal((bh, d)).astype(np.float32)
+    v = np.zeros((bh, 2, d), dtype=np.float32)
+    v[:, 0] = 1.0
+    out = H.to_np(svoo.attn(H.to_dev(q), H.to_dev(k), H.to_dev(v), 1.0))[:, :, 0].astype(np.float64)
+    part = np.zeros((bh, 2, 2, 4), dtype=np.float32)          # slice, query, key, chain
+    prod = q.astype(np.float64)[:, :, None, :] * k.astype(np.float64)[:, None, :, :]
+    for c in range(d // 4):
+        part = (part + prod.reshape(bh, 2, 2, 4, d // 4)[..., c]).astype(np.float32)
+    emulated = ((part[..., 0] + part[..., 1]) + part[..., 2] + part[..., 3]).astype(np.float64)
+    exact = prod.sum(-1)
+    gap = lambda s: 1.0 / (1.0 + np.exp(s[:, :, 1] - s[:, :, 0]))
+    rms = lambda x: float(np.sqrt(np.square(x).mean()))
+    assert rms(out - gap(exact)) <= math.hypot(1.05 * rms(gap(emulated) - gap(exact)), 1.2e-7)
+
+
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64), ("bf16", 64), ("f32", 128)])
 def test_sparse_attn_matches_oracle_random_mask(dtype, d):
     """Random labels (ragged cluster sizes, some empty) and a random mask: pins the key-stream walk,
