@@ -686,7 +686,7 @@ struct F32Lds {
 };
 
 template <int D, int RG, int KS>
-__global__ void __launch_bounds__(ATT_THREADS, KS == 2 ? 2 : 1)
+__global__ void __launch_bounds__(ATT_THREADS, KS == 2 || D == 64 ? 2 : 1)
 sparse_attn_f32_kernel(AttnArgs a) {
     using L = F32Lds<D, RG, KS>;
     static_assert(RG * KS == 4, "four waves");
@@ -796,7 +796,13 @@ sparse_attn_f32_kernel(AttnArgs a) {
         if (kt + 1 < n_tiles) prepare(kt + 1);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();                        // V of this stage is there, K is used up
-        if (kt + 1 < n_tiles) issue(kg, k_lds, true);
+        if (kt + 1 < n_tiles) {
+            issue(kg, k_lds, true);
+        } else if (total % KEYS != 0) {         // rows past the end weigh 0, which the last key's V need not survive
+            uint4* rest = (uint4*)(v_lds + (total % KEYS) * ROWB);
+            for (int e = tid; e < (KEYS - total % KEYS) * CPR; e += ATT_THREADS) rest[e] = make_uint4(0, 0, 0, 0);
+            __syncthreads();
+        }
         if (!wave_active) continue;
         const int first = kt * KEYS + 32 * ks;
         if (first + 32 > total) {               // keys past the end of the stream get -inf

@@ -508,6 +508,20 @@ def test_attention_with_keys_out_of_reach_and_with_a_tiny_scale(dtype, d):
             assert np.abs(H.to_np(lse)[0] - ref).max() <= (1e-2 if dtype == "bf16" else 1e-4)
 
 
+@pytest.mark.parametrize("copies", [1, 160])        # 32-row and 64-row workgroups
+@pytest.mark.parametrize("d,n", [(64, 97), (128, 97), (128, 1), (64, 130)])
+def test_float32_attention_with_an_infinite_value(d, n, copies):
+    """An infinite value of the last key of a ragged stage comes out as it went in: nothing multiplies it by the zero
+    weight of the places behind the end of the stream."""
+    rng = np.random.default_rng(n)
+    q, k, v = (rng.standard_normal((1, n, d)).astype(np.float32) for _ in range(3))
+    v[0, n - 1, 3], v[0, n - 1, d - 1] = np.inf, -np.inf
+    q, k, v = (H.to_dev(np.tile(x, (copies, 1, 1))) for x in (q, k, v))
+    out = H.to_np(svoo.attn(q, k, v, 0.1))
+    assert (out[:, :, 3] == np.inf).all() and (out[:, :, d - 1] == -np.inf).all()
+    assert np.isfinite(np.delete(out, [3, d - 1], axis=2)).all()
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_float32_logits_round_like_four_chains(d):
     """Two keys that differ little: the output is the logistic function of the difference of two logits, whose error is
