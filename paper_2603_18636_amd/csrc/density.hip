@@ -232,7 +232,9 @@ density_kernel(DensityArgs a) {
     int c_hi = 0, known_len = -1;
     int g = 0;                                             // running step number: stage g % 2
 
-    // One pass; body(s, valid) sees every logit of this lane's row and key split.
+    auto of_slice = [&](int first, int v) { return first + 8 * (v / 4) + 4 * h + (v % 4) < n; };
+    // One pass; body(s, ragged, first) sees every logit of this lane's row and key split, 32 keys from `first` on; of a
+    // ragged block the logits past the end are -inf.
     auto over_keys = [&](auto body) {
         for (int step = 0; step < n_steps; ++step, ++g) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -263,10 +265,10 @@ density_kernel(DensityArgs a) {
                     if (first + 32 > n) {                  // ragged end: keys past it sort below everything
 #pragma unroll
                         for (int v = 0; v < 16; ++v)
-                            if (first + 8 * (v / 4) + 4 * h + (v % 4) >= n) s[v] = -INFINITY;
-                        body(s, true, step);
+                            if (!of_slice(first, v)) s[v] = -INFINITY;
+                        body(s, true, first);
                     } else {
-                        body(s, false, step);
+                        body(s, false, first);
                     }
                 }
             }
@@ -307,17 +309,60 @@ density_kernel(DensityArgs a) {
             set_bins<BINS>(br, br.lo == was.lo && br.hi == was.hi);
     };
 
-    // ---- pass 0
-    {
-        float mx = -INFINITY, mn = INFINITY, sum = 0.f, sq = 0.f;
-        int samples = 0;
-        over_keys([&](const den_f32x16& s, bool ragged, int step) {
+    auto other = [&](float x) {          // the half-wave's other half of the row's keys
+        auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
+        return __int_as_float(h == 0 ? (int)r[1] : (int)r[0]);
+    };
+    // Some row of the workgroup has a logit that is no finite number, which is rare: extremes without the NaNs and
+    // the logits above -inf counted.  A row with an infinite logit gets that count as its length, a key whose
+    // logit is NaN weighs nothing.
+    auto look_again = [&]() {
+        float mx = -INFINITY, mn = INFINITY;
+        int cnt = 0;
+        over_keys([&](const den_f32x16& s, bool ragged, int first) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 mx = fmaxf(mx, s[v]);
-                mn = fminf(mn, ragged && s[v] == -INFINITY ? INFINITY : s[v]);
+                mn = fminf(mn, ragged && !of_slice(first, v) ? INFINITY : s[v]);
+                cnt += s[v] > -INFINITY ? 1 : 0;
             }
-            if ((step & 3) == 0 && !ragged) {              // a quarter of the keys is plenty for the first guess
+        });
+        mx = fmaxf(mx, other(mx));
+        mn = fminf(mn, other(mn));
+        cnt += __float_as_int(other(__int_as_float(cnt)));
+        __syncthreads();                                   // the owners have read what pass 0 left here
+        if (h == 0) part[ks * ROWS + row] = PassPartial{mx, mn, 0.f, 0.f, cnt, 0};
+        __syncthreads();
+        if (owner) {
+            row_max = -INFINITY;
+            row_min = INFINITY;
+            cnt = 0;
+            for (int o = 0; o < KS; ++o) {
+                const PassPartial u = part[o * ROWS + row];
+                row_max = fmaxf(row_max, u.mx);
+                row_min = fminf(row_min, u.mn);
+                cnt += u.cnt;
+            }
+            row_min += 0.f;
+            if (!(row_max < INFINITY && row_min > -INFINITY)) {
+                br.mode = DEN_DONE;
+                known_len = cnt;
+            }
+        }
+    };
+
+    // ---- pass 0
+    bool careful;
+    {
+        float mx = -INFINITY, mn = INFINITY, sum = 0.f, sq = 0.f;
+        int samples = 0;
+        over_keys([&](const den_f32x16& s, bool ragged, int first) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                mx = __builtin_elementwise_maximum(mx, s[v]);      // keeps a NaN, for the look below
+                mn = fminf(mn, ragged && !of_slice(first, v) ? INFINITY : s[v]);
+            }
+            if ((first / (KEYS * KS) & 3) == 0 && !ragged) {       // a quarter of the keys is plenty for the first guess
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     sum += s[v];
@@ -326,18 +371,15 @@ density_kernel(DensityArgs a) {
                 samples += 16;
             }
         });
-        auto other = [&](float x) {      // the half-wave's other half of the row's keys
-            auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
-            return __int_as_float(h == 0 ? (int)r[1] : (int)r[0]);
-        };
         const float omx = other(mx), omn = other(mn), osum = other(sum), osq = other(sq);
-        if (h == 0) part[ks * ROWS + row] = PassPartial{fmaxf(mx, omx), fminf(mn, omn), sum + osum, sq + osq, 0, 2 * samples};
+        if (h == 0)
+            part[ks * ROWS + row] = PassPartial{__builtin_elementwise_maximum(mx, omx), fminf(mn, omn), sum + osum, sq + osq, 0, 2 * samples};
         __syncthreads();
         if (owner) {
             mx = -INFINITY; mn = INFINITY; sum = 0.f; sq = 0.f; samples = 0;
             for (int o = 0; o < KS; ++o) {
                 const PassPartial u = part[o * ROWS + row];
-                mx = fmaxf(mx, u.mx);
+                mx = __builtin_elementwise_maximum(mx, u.mx);
                 mn = fminf(mn, u.mn);
                 sum += u.sum;
                 sq += u.sq;
@@ -345,6 +387,12 @@ density_kernel(DensityArgs a) {
             }
             row_max = mx;
             row_min = mn + 0.f;
+        }
+        careful = __syncthreads_or(owner && rvalid && !(row_max < INFINITY && row_min > -INFINITY));
+        if (careful) look_again();
+        if (owner) {
+            mx = row_max;
+            mn = row_min;
             st_nmb[row] = -mx * c2;
             // normal logits of mean mu and deviation sd: their masses are normal about mu + scale sd^2 (natural
             // units), so the prefix ends z_tau sd from there; +-1.25 sd around it, inside [min, max]
@@ -372,7 +420,10 @@ density_kernel(DensityArgs a) {
     // ---- pass 1
     {
         const float inv = st_inv[row], off = st_off[row], nmb = st_nmb[row];
-        over_keys([&](const den_f32x16& s, bool, int) {
+        over_keys([&](den_f32x16& s, bool, int) {
+            if (careful)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) s[v] = s[v] == s[v] ? s[v] : -INFINITY;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const float p = __builtin_amdgcn_exp2f(fmaf(s[v], c2, nmb));
@@ -387,12 +438,7 @@ density_kernel(DensityArgs a) {
                 for (int i = 0; i < BINS; ++i) z += hist[i * ROWS + row];
                 const double t = ceil((double)a.tau * (double)z);
                 target = (den_u64)t;
-                if (!(row_max < INFINITY) || !(row_min > -INFINITY) || target == 0) {
-                    br.mode = DEN_DONE;                    // not finite: any length will do
-                    known_len = 1;
-                } else {
-                    narrow(row_min, next_up(row_max));
-                }
+                narrow(row_min, next_up(row_max));
             }
             publish();
         }
@@ -467,7 +513,7 @@ density_kernel(DensityArgs a) {
         if (rank < CAP) ordered[rank * ROWS + r] = __builtin_amdgcn_exp2f(fmaf(v, c2, st_nmb[r]));
     }
     __syncthreads();
-    if (a.passes && tid == 0) atomicMax(&a.passes[b], pass);
+    if (a.passes && tid == 0) atomicMax(&a.passes[b], pass + (careful ? 1 : 0));
     if (owner && rvalid) {
         int len = known_len;
         if (len < 0) {

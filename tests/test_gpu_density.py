@@ -176,3 +176,38 @@ def test_density_full_size_head_of_config2():
     d_gpu, d_ref = H.to_np(dens)[0], ref["density"]
     print(f"config 2 density: gpu {d_gpu:.6f} oracle {d_ref:.6f}, {near} of 1024 prefix lengths differ within rounding")
     assert abs(d_gpu - d_ref) <= 1e-4 * d_ref
+
+
+@pytest.mark.parametrize("dtype,d,n", [("bf16", 128, 97), ("bf16", 64, 1000), ("f32", 128, 333), ("f32", 64, 64)])
+def test_density_with_logits_that_are_no_finite_numbers(dtype, d, n):
+    """Products beyond float32's range and keys or queries that hold a NaN.  A row with an infinite logit has the number
+    of its logits above -inf as its length, a key whose logit is NaN weighs nothing, a row of NaNs has length 1;
+    the other rows of the workgroup are the oracle's."""
+    rng = np.random.default_rng(n)
+    q, k = (rng.standard_normal((1, n, d)).astype(np.float32) for _ in range(2))
+    q[0, :, 0] = 0.0
+    q[0, 3::5, 0] = 2.0 ** 100
+    q[0, 4::5, 0] = -(2.0 ** 100)
+    k[0, :, 0] = 0.0
+    low = rng.choice(n, 7, replace=False)
+    k[0, low, 0] = -(2.0 ** 100)
+    q[0, 2] = np.nan
+    lost = int(rng.integers(n))
+    k[0, lost, d - 1] = np.nan
+    if dtype == "bf16":
+        q, k = synth.round_to_bf16(q), synth.round_to_bf16(k)
+    tau32 = float(np.float32(0.95))
+    got = {}
+    for bad in (False, True):               # without and with the key that is NaN
+        kk = k if bad else np.nan_to_num(k)
+        plen, _ = svoo.attention_density(H.to_dev(q, dtype), H.to_dev(kk, dtype), tau32, H.scale_of(d))
+        got[bad] = H.to_np(plen)[0]
+        keys = np.arange(n) != lost if bad else np.ones(n, dtype=bool)
+        left = int(keys.sum())
+        row = np.arange(n)
+        assert got[bad][2] == 1
+        assert (got[bad][(row % 5 == 3) & (row != 2)] == left - int(keys[low].sum())).all()      # -inf logits
+        assert (got[bad][row % 5 == 4] == left).all()                                            # +inf logits
+        rows = row[(row % 5 < 3) & (row != 2)]
+        ref = so.attention_density(q[0], kk[0][keys], H.scale_of(d), tau32, rows=rows)
+        compare_prefix(got[bad][rows], ref, max_near=max(2, n // 50))
