@@ -229,7 +229,7 @@ density_kernel(DensityArgs a) {
     Bracket br = {0.f, 0.f, 0.f, 0.f, rvalid ? (uint32_t)DEN_EQUAL : (uint32_t)DEN_DONE};
     float row_max = 0.f, row_min = 0.f;
     den_u64 m_hi = 0, target = 0;
-    int c_hi = 0, known_len = -1;
+    int c_hi = 0, known_len = -1, valid = n;               // valid: keys whose logit is a number
     int g = 0;                                             // running step number: stage g % 2
 
     auto of_slice = [&](int first, int v) { return first + 8 * (v / 4) + 4 * h + (v % 4) < n; };
@@ -288,6 +288,11 @@ density_kernel(DensityArgs a) {
                 for (int i = 0; i < BINS; ++i) hist[i * ROWS + row] = 0;
         }
     };
+    // of `count` keys of mass p below the mass m_hi: as many as reach the target
+    auto ties_taken = [&](den_u64 p, int count) {
+        const den_u64 take = p ? (target - m_hi + p - 1) / p : (den_u64)count;
+        return take < 1 ? 1 : (take > (den_u64)count ? count : (int)take);
+    };
     // Walk the bins from the top: the one in which the mass reaches the target becomes the bracket.
     auto narrow = [&](float lowest, float highest) {
         const Bracket was = br;
@@ -344,6 +349,7 @@ density_kernel(DensityArgs a) {
                 cnt += u.cnt;
             }
             row_min += 0.f;
+            valid = cnt;
             if (!(row_max < INFINITY && row_min > -INFINITY)) {
                 br.mode = DEN_DONE;
                 known_len = cnt;
@@ -404,6 +410,13 @@ density_kernel(DensityArgs a) {
             const bool usable = sd > 0.f && guess - 1.25f * sd > mn && guess + 1.25f * sd < mx;
             br.lo = usable ? guess - 1.25f * sd : row_min;
             br.hi = usable ? guess + 1.25f * sd : next_up(mx);
+            if (br.mode != DEN_DONE && row_min == row_max) {
+                // all logits equal (a zero query): as many as the target needs, no further pass
+                const den_u64 p = to_fixed(__builtin_amdgcn_exp2f(fmaf(row_max, c2, st_nmb[row])), a.fix);
+                target = (den_u64)ceil((double)a.tau * (double)(p * (den_u64)valid));
+                known_len = ties_taken(p, valid);
+                br.mode = DEN_DONE;
+            }
             if (br.mode != DEN_DONE) {
                 set_bins<BINS>(br, false);
                 if (br.mode != DEN_EQUAL) {                // pass 1 has equal bins only: everything in the lowest
@@ -414,11 +427,12 @@ density_kernel(DensityArgs a) {
             }
             publish();
         }
-        __syncthreads();
     }
 
     // ---- pass 1
-    {
+    int pass = 1;
+    if (!__syncthreads_and(!owner || br.mode == DEN_DONE)) {
+        ++pass;
         const float inv = st_inv[row], off = st_off[row], nmb = st_nmb[row];
         over_keys([&](den_f32x16& s, bool, int) {
             if (careful)
@@ -443,7 +457,6 @@ density_kernel(DensityArgs a) {
             publish();
         }
     }
-    int pass = 2;
     while (!__syncthreads_and(!owner || br.mode == DEN_DONE) && pass < DEN_MAX_PASSES) {
         // ---- later passes: only keys inside the bracket cost more than three comparisons
         int cnt = 0;
@@ -481,9 +494,7 @@ density_kernel(DensityArgs a) {
                     br.mode = DEN_DONE;
                 } else if (one_value(br.lo, br.hi)) {     // ties: as many as the target needs
                     const den_u64 p = to_fixed(__builtin_amdgcn_exp2f(fmaf(br.lo, c2, st_nmb[row])), a.fix);
-                    den_u64 take = p ? (target - m_hi + p - 1) / p : (den_u64)len;
-                    take = take < 1 ? 1 : (take > (den_u64)len ? (den_u64)len : take);
-                    known_len = c_hi + (int)take;
+                    known_len = c_hi + ties_taken(p, len);
                     br.mode = DEN_DONE;
                 } else {                                   // more keys than their masses suggested
                     set_bins<BINS>(br, true);

@@ -211,3 +211,24 @@ def test_density_with_logits_that_are_no_finite_numbers(dtype, d, n):
         rows = row[(row % 5 < 3) & (row != 2)]
         ref = so.attention_density(q[0], kk[0][keys], H.scale_of(d), tau32, rows=rows)
         compare_prefix(got[bad][rows], ref, max_near=max(2, n // 50))
+
+
+@pytest.mark.parametrize("dtype,d,n,rows", [("bf16", 128, 97, 97), ("bf16", 64, 1000, 300), ("f32", 128, 333, 65), ("f32", 64, 1, 1)])
+def test_density_of_rows_with_equal_logits_takes_one_pass(dtype, d, n, rows):
+    """Zero queries (padding): the length is known once the extremes are, also in a workgroup of other rows."""
+    rng = np.random.default_rng(n)
+    q, k = (synth.round_to_bf16(rng.standard_normal((1, n, d)).astype(np.float32)) for _ in range(2))
+    index = H.to_dev(rng.choice(n, rows, replace=False).astype(np.int32))
+    for tau in (0.3, 0.95, 1.0):
+        tau32 = float(np.float32(tau))
+        plen, _, passes = svoo.attention_density(H.to_dev(0.0 * q, dtype), H.to_dev(k, dtype), tau, H.scale_of(d), rows=index,
+                                                 want_passes=True)
+        assert (H.to_np(plen) == math.ceil(tau32 * n)).all() and (H.to_np(passes) == 1).all()
+        half = q.copy()
+        half[0, ::2] = 0.0
+        plen, _ = svoo.attention_density(H.to_dev(half, dtype), H.to_dev(k, dtype), tau, H.scale_of(d), rows=index)
+        even = H.to_np(index) % 2 == 0
+        assert (H.to_np(plen)[0][even] == math.ceil(tau32 * n)).all()
+        if tau < 1.0:
+            ref = so.attention_density(half[0], k[0], H.scale_of(d), tau32, rows=H.to_np(index))
+            compare_prefix(H.to_np(plen)[0], ref, max_near=max(2, rows // 50))
