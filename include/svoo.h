@@ -282,9 +282,12 @@ int svoo_row_recall(const svoo_shape* shape, const float* lse_kept_sorted, const
  * paper uses 0.95); prefix_len [bh, n_rows] int32; density [bh] float64; passes (nullable) [bh]
  * int32 = number of passes over the keys the slowest row group of the slice needed (what the
  * call cost: passes x n_rows x n x d multiply-adds).  shape->kq / kk are ignored.  No workspace.
- * Logits in float32 (matrix cores, float32 accumulation), masses float32, added exactly as 64-bit
- * fixed-point numbers: a result does not depend on the order of the additions and is the same on
- * every run.  No sort of the row: the cut is bracketed by histograms over the logit value and the last
+ * Logits in float32 (matrix cores, float32 accumulation), masses float32, rounded to 64-bit
+ * fixed-point numbers and added exactly: a result does not depend on the order of the additions and is
+ * the same on every run.  The roundings of a row add up to 2^-26 of its mass at most (up to 2^18 keys the
+ * unit is 2^(b-61) for 2^(b-1) < n <= 2^b, beyond that it follows the row's mass and costs a pass more).
+ * A key whose logit is NaN weighs nothing; a row with an infinite logit has the number of its logits
+ * above -inf as its length (1 if there is none).  No sort of the row: the cut is bracketed by histograms over the logit value and the last
  * few keys are ordered, four or five passes over the keys at 75,600 keys, so a call costs that many
  * score-matrix computations for the listed rows.
  */

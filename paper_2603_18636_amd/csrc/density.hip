@@ -41,6 +41,7 @@
 #include "common.h"
 
 #define LOG2E_F 1.4426950408889634f
+#define DEN_REFINE_N (1 << 18)   // more keys: masses in the unit of the row (svoo_attention_density says why)
 #define DEN_MAX_PASSES 48   // pass 0, pass 1, and far more splits than a float interval allows; a hard stop
 
 typedef __attribute__((ext_vector_type(8))) __bf16 den_bf16x8;
@@ -56,7 +57,8 @@ struct DensityArgs {
     int n, n_rows, bh;
     float scale, tau;
     float z_tau;             // normal quantile of 1 - tau: where pass 1 centres its bins
-    double fix;              // 2^S: masses are integers in units of 2^-S, n 2^S < 2^62
+    int fix_bits;            // S: masses are integers in units of 2^-S, n 2^S < 2^62
+    double fix;              // 2^S
 };
 
 // next representable float above x (x finite or +inf)
@@ -151,13 +153,14 @@ struct DenLds {
     static constexpr int STAGE = KS * DenTile<T, D>::BYTES;
     static constexpr int HIST = 2 * STAGE;                             // [BINS][ROWS] u64, or a list of 2 BINS floats per row
     static constexpr int PART = HIST + BINS * ROWS * 8;                // [KS][ROWS] PassPartial
-    static constexpr int STATE = PART + KS * ROWS * (int)sizeof(PassPartial);   // per row: bracket, nmb, list length
-    static constexpr int BYTES = STATE + 7 * ROWS * 4;
+    static constexpr int STATE = PART + KS * ROWS * (int)sizeof(PassPartial);   // per row: bracket, nmb, list length, unit
+    static constexpr int BYTES = STATE + 8 * ROWS * 4;
     static_assert(2 * STAGE >= 2 * BINS * ROWS * 4, "the ordered lists reuse the K tiles");
     static_assert(BYTES <= 160 * 1024, "LDS");
 };
 
-template <typename T, int D, int RG, int KS, int BINS>
+// REFINE: so many keys that pass 1 is done again in the unit that the row's own mass allows
+template <typename T, int D, int RG, int KS, int BINS, bool REFINE>
 __global__ void __launch_bounds__(64 * RG * KS)
 density_kernel(DensityArgs a) {
     using L = DenLds<T, D, RG, KS, BINS>;
@@ -178,6 +181,7 @@ density_kernel(DensityArgs a) {
     uint32_t* st_mode = (uint32_t*)(st_off + ROWS);
     float* st_nmb = (float*)(st_mode + ROWS);
     int* st_len = (int*)(st_nmb + ROWS);                   // keys collected
+    int* st_fix = st_len + ROWS;                           // S of the row's masses
 
     // consecutive workgroups of one slice on one XCD: they read the same keys at the same time
     const int wps = (a.n_rows + ROWS - 1) / ROWS, total = wps * a.bh;
@@ -229,6 +233,7 @@ density_kernel(DensityArgs a) {
     Bracket br = {0.f, 0.f, 0.f, 0.f, rvalid ? (uint32_t)DEN_EQUAL : (uint32_t)DEN_DONE};
     float row_max = 0.f, row_min = 0.f;
     den_u64 m_hi = 0, target = 0;
+    double fix = a.fix;
     int c_hi = 0, known_len = -1, valid = n;               // valid: keys whose logit is a number
     int g = 0;                                             // running step number: stage g % 2
 
@@ -305,7 +310,7 @@ density_kernel(DensityArgs a) {
         }
         br.lo = bin == 0 ? lowest : bin_edge<BINS>(bin, lowest, highest, was);
         br.hi = bin == BINS - 1 ? highest : bin_edge<BINS>(bin + 1, lowest, highest, was);
-        const den_u64 p_lo = to_fixed(__builtin_amdgcn_exp2f(fmaf(br.lo, c2, st_nmb[row])), a.fix);
+        const den_u64 p_lo = to_fixed(__builtin_amdgcn_exp2f(fmaf(br.lo, c2, st_nmb[row])), fix);
         // at most mass / p_lo keys; collect when they surely fit, when there is nothing left to split, and
         // when the masses are too small to tell (the list's length then does)
         if (mass <= p_lo * (den_u64)(CAP - 8) || one_value(br.lo, br.hi))
@@ -412,8 +417,9 @@ density_kernel(DensityArgs a) {
             br.hi = usable ? guess + 1.25f * sd : next_up(mx);
             if (br.mode != DEN_DONE && row_min == row_max) {
                 // all logits equal (a zero query): as many as the target needs, no further pass
-                const den_u64 p = to_fixed(__builtin_amdgcn_exp2f(fmaf(row_max, c2, st_nmb[row])), a.fix);
-                target = (den_u64)ceil((double)a.tau * (double)(p * (den_u64)valid));
+                const den_u64 p = to_fixed(__builtin_amdgcn_exp2f(fmaf(row_max, c2, st_nmb[row])), fix);
+                const den_u64 z = p * (den_u64)valid;
+                target = a.tau < 1.f ? (den_u64)ceil((double)a.tau * (double)z) : z;
                 known_len = ties_taken(p, valid);
                 br.mode = DEN_DONE;
             }
@@ -432,29 +438,42 @@ density_kernel(DensityArgs a) {
     // ---- pass 1
     int pass = 1;
     if (!__syncthreads_and(!owner || br.mode == DEN_DONE)) {
-        ++pass;
         const float inv = st_inv[row], off = st_off[row], nmb = st_nmb[row];
-        over_keys([&](den_f32x16& s, bool, int) {
-            if (careful)
+        for (int round = 0;; ++round) {
+            ++pass;
+            over_keys([&](den_f32x16& s, bool, int) {
+                if (careful)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) s[v] = s[v] == s[v] ? s[v] : -INFINITY;
+                    for (int v = 0; v < 16; ++v) s[v] = s[v] == s[v] ? s[v] : -INFINITY;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const float p = __builtin_amdgcn_exp2f(fmaf(s[v], c2, nmb));
-                atomicAdd(&hist[equal_bin<BINS>(s[v], inv, off) * ROWS + row], to_fixed(p, a.fix));
-                if (v % 4 == 3) __builtin_amdgcn_sched_barrier(0);      // 16 at once would not fit the registers
-            }
-        });
-        __syncthreads();
-        if (owner) {
-            if (br.mode != DEN_DONE) {
-                den_u64 z = 0;
+                for (int v = 0; v < 16; ++v) {
+                    const float p = __builtin_amdgcn_exp2f(fmaf(s[v], c2, nmb));
+                    atomicAdd(&hist[equal_bin<BINS>(s[v], inv, off) * ROWS + row], to_fixed(p, fix));
+                    if (v % 4 == 3) __builtin_amdgcn_sched_barrier(0);      // 16 at once would not fit the registers
+                }
+            });
+            __syncthreads();
+            den_u64 z = 0;
+            if (owner && br.mode != DEN_DONE)
                 for (int i = 0; i < BINS; ++i) z += hist[i * ROWS + row];
-                const double t = ceil((double)a.tau * (double)z);
-                target = (den_u64)t;
-                narrow(row_min, next_up(row_max));
+            if (round == (REFINE ? 1 : 0)) {
+                if (owner) {
+                    if (br.mode != DEN_DONE) {
+                        target = a.tau < 1.f ? (den_u64)ceil((double)a.tau * (double)z) : z;
+                        narrow(row_min, next_up(row_max));
+                    }
+                    publish();
+                }
+                break;
             }
-            publish();
+            if (owner) {                                   // n masses of half a unit more at most
+                const int octaves = 64 - __clzll((long long)(z + (den_u64)n / 2 + 1)) - a.fix_bits;
+                const int s_bits = 61 - octaves < 50 ? 61 - octaves : 50;
+                st_fix[row] = s_bits > a.fix_bits ? s_bits : a.fix_bits;
+                publish();
+            }
+            __syncthreads();
+            fix = ldexp(1.0, st_fix[row]);
         }
     }
     while (!__syncthreads_and(!owner || br.mode == DEN_DONE) && pass < DEN_MAX_PASSES) {
@@ -474,7 +493,7 @@ density_kernel(DensityArgs a) {
                             if (e < CAP) list[2 * ((e / 2) * ROWS + row) + e % 2] = s[v];
                         } else {
                             const float p = __builtin_amdgcn_exp2f(fmaf(s[v], c2, nmb));
-                            atomicAdd(&hist[bracket_bin<BINS>(s[v], r) * ROWS + row], to_fixed(p, a.fix));
+                            atomicAdd(&hist[bracket_bin<BINS>(s[v], r) * ROWS + row], to_fixed(p, fix));
                         }
                     }
                 }
@@ -493,7 +512,7 @@ density_kernel(DensityArgs a) {
                 if (len <= CAP) {
                     br.mode = DEN_DONE;
                 } else if (one_value(br.lo, br.hi)) {     // ties: as many as the target needs
-                    const den_u64 p = to_fixed(__builtin_amdgcn_exp2f(fmaf(br.lo, c2, st_nmb[row])), a.fix);
+                    const den_u64 p = to_fixed(__builtin_amdgcn_exp2f(fmaf(br.lo, c2, st_nmb[row])), fix);
                     known_len = c_hi + ties_taken(p, len);
                     br.mode = DEN_DONE;
                 } else {                                   // more keys than their masses suggested
@@ -532,7 +551,7 @@ density_kernel(DensityArgs a) {
             if (br.mode == DEN_DONE) {
                 den_u64 m = m_hi;
                 for (int i = 0; i < st_len[row]; ++i) {
-                    m += to_fixed(ordered[i * ROWS + row], a.fix);
+                    m += to_fixed(ordered[i * ROWS + row], fix);
                     ++len;
                     if (m >= target) break;
                 }
@@ -542,11 +561,11 @@ density_kernel(DensityArgs a) {
     }
 }
 
-template <typename T, int D, int RG, int KS, int BINS>
+template <typename T, int D, int RG, int KS, int BINS, bool REFINE = false>
 static int launch_density(const DensityArgs& a, hipStream_t stream) {
     static unsigned char opted_in[SVOO_MAX_DEVICES];
     constexpr int bytes = DenLds<T, D, RG, KS, BINS>::BYTES;
-    auto kern = density_kernel<T, D, RG, KS, BINS>;
+    auto kern = density_kernel<T, D, RG, KS, BINS, REFINE>;
     if (!opt_in_dynamic_lds((const void*)kern, bytes, opted_in)) return SVOO_ERR_HIP;
     const long long total = (long long)((a.n_rows + 32 * RG - 1) / (32 * RG)) * a.bh;
     hipLaunchKernelGGL(kern, dim3((unsigned)((total + 7) / 8 * 8)), dim3(64 * RG * KS), bytes, stream, a);
@@ -559,6 +578,11 @@ static int launch_density(const DensityArgs& a, hipStream_t stream) {
 template <typename T, int D>
 static int dispatch_density(const DensityArgs& a, hipStream_t stream) {
     auto wgs = [&](int rg) { return (long long)((a.n_rows + 32 * rg - 1) / (32 * rg)) * a.bh; };
+    if (a.n > DEN_REFINE_N) {
+        constexpr int FEW = std::is_same<T, float>::value ? 4 : 8, BINS = std::is_same<T, float>::value ? 32 : 64;
+        if (wgs(1) <= 256) return launch_density<T, D, 1, FEW, BINS, true>(a, stream);
+        return launch_density<T, D, FEW / 2, 4, BINS, true>(a, stream);
+    }
     if constexpr (std::is_same<T, float>::value) {
         if (wgs(1) <= 256) return launch_density<T, D, 1, 4, 32>(a, stream);
         return launch_density<T, D, 2, 4, 32>(a, stream);
@@ -611,12 +635,16 @@ extern "C" int svoo_attention_density(const svoo_shape* shape, const void* q, co
     if (n_rows < 1 || n_rows > shape->n || (!rows && n_rows != shape->n)) return SVOO_ERR_INVALID_ARG;
     if (!(tau > 0.0f) || !(tau <= 1.0f) || !(scale > 0.0f) || !(scale < 1e30f)) return SVOO_ERR_INVALID_ARG;
     hipStream_t stream = (hipStream_t)hip_stream;
-    // fixed-point unit: n masses of at most 1 (and a rounding) stay below 2^62, one mass below 2^51
+    // Fixed-point unit: n masses of at most 1 (and a rounding) stay below 2^62, one mass below 2^51.  The n roundings
+    // of half a unit are 2^-26 of a row's mass at most up to 2^18 keys, less than float32 sums of 64 keys would
+    // round; beyond that the unit that allows for rows of mass n is too coarse for rows of mass 1 (2^-14 at
+    // 2^24 keys), and pass 1 is done again in the row's own (2 x 524,293 x 64, 512 rows: 10.6 -> 12.8 ms).
     int bits = 0;
     while ((1LL << bits) < shape->n) ++bits;
     const int s_bits = 61 - bits < 50 ? 61 - bits : 50;
     DensityArgs a = {q, k, rows, prefix_len, passes, shape->n, n_rows, shape->bh, scale, tau,
-                     (float)normal_quantile(1.0 - (double)tau), (double)(1LL << s_bits)};
+                     (float)normal_quantile(1.0 - (double)tau), s_bits,
+                     (double)(1LL << s_bits)};
     if (passes)
         hipLaunchKernelGGL(density_clear_kernel, dim3((shape->bh + 255) / 256), dim3(256), 0, stream, passes, shape->bh);
     if (shape->dtype == SVOO_BF16)

@@ -232,3 +232,19 @@ def test_density_of_rows_with_equal_logits_takes_one_pass(dtype, d, n, rows):
         if tau < 1.0:
             ref = so.attention_density(half[0], k[0], H.scale_of(d), tau32, rows=H.to_np(index))
             compare_prefix(H.to_np(plen)[0], ref, max_near=max(2, rows // 50))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_density_sees_the_mass_of_a_million_tiny_keys(dtype):
+    """One key of mass 1 and 2^20 - 1 of mass 2^-43, together 2^-23 more: a share 1 - 2^-24 of it needs the large
+    one and half of the others.  Nothing in units of 2^-41, in which 2^20 keys of mass 1 are summed up.  Bound:
+    scale and logit are rounded to 2^-24 each, which moves the exponent 43 by 5e-6 at most."""
+    n, d = 1 << 20, 64
+    q = torch.zeros((1, n, d), dtype=H.torch_dtype(dtype), device=H.DEV)
+    k = torch.zeros_like(q)
+    q[0, :, 0] = 1.0
+    k[0, :, 0] = -1.0
+    k[0, 7, 0] = 0.0
+    rows = torch.arange(40, dtype=torch.int32, device=H.DEV)
+    plen, _ = svoo.attention_density(q, k, float(np.float32(1.0 - 2.0 ** -24)), 43.0 * math.log(2.0), rows=rows)
+    assert (np.abs(H.to_np(plen) - 2.0 ** 19) <= 16).all()
