@@ -8,7 +8,7 @@
 // and every token needs one d-length dot product per own-side centroid.  b_j is exactly 1 unless
 // ||c_own_j C_opp^T|| < eps (a degenerate anchor, e.g. an all-zero centroid); slices without
 // such anchors reduce to argmax_j <x, W_j>.  Slices with one take the general form, which needs
-// nx^2 = x^T (C_opp^T C_opp) x per token.
+// nx = ||x C_opp^T|| per token.
 //
 // Every decision is taken in float64: tokens are exact in float64, W is float64, accumulation is
 // float64 in a fixed order.
@@ -457,17 +457,26 @@ struct AssignArgs {
 // LDS with direct global->LDS loads and an XOR swizzle, double buffered.  S^T layout: lane
 // (j, h) holds for token j the centroids 32 cb + 8 (v/4) + 4 h + v%4.
 //
-// The tokens the pre-filter leaves open (0.3 per workgroup at 12 x 75,600 in the first iteration, fewer
-// later) are decided at the end by all 256 threads, a centroid each, with the other workgroup of the compute unit
-// running beside: as a launch of its own over a global queue that was 20-24 us per half-step, a fifth of it.
+// The tokens the pre-filter leaves open are decided at the end by the same workgroup.  Up to DECIDE_FEW (0.3 per workgroup
+// at 12 x 75,600 in the first iteration, fewer later): a thread per centroid, bound by a few round trips to W^T.
+// More (coinciding centroids, zero tokens, two or three opposite centroids) and those of slices with a degenerate
+// anchor, where it is all of them: the float64 matrix instruction, tiles of 16 tokens, two at a time, against tiles
+// of 16 columns of W^T dealt to the four waves, bound by the float64 matrix rate (256 tokens, 256 centroids, d = 128:
+// 60 us).  The instruction adds its four products in index order with one rounding each (compared bit for bit
+// with fma chains), so a score is the same fma chain over d on either way.  Measured, two iterations, in us: a queue
+// over all workgroups in a launch of its own / in place with plain FMAs (a token per thread from 17 on) / now:
+//   12 x 75,600 x 128 bf16, 256 blocks       1,038 / 973 / 940   (the matrix instruction for few tokens too: 1,010)
+//   the same, a twentieth of zero tokens     3,800 / 2,600 / 2,050; one of them an anchor 35,000 / 13,900 / 7,900
+//   12 x 8,190 x 128 float32, 64 blocks, zero tokens 880 / 1,260 / 560;  1 x 9,167 x 64 bf16, 3 / 553 blocks 460 / 990 / 350
 // The workgroup also knows the label counts of its ASSIGN_CHUNK tokens, which saves the sort its pass over the
 // labels.
 //
 // BIAS: score_j = <x, W_j> - half_sq[j] (k-means on raw rows: W = C, half_sq = ||c_j||^2 / 2, one
 // float per centroid, slices padded to a multiple of 32 entries); the margin then also covers the
 // float32 rounding of the bias and of the subtraction.
-#define LIST_BATCH 32   // loads of W^T in flight per thread
-#define DECIDE_MANY 16  // more open tokens of a workgroup than this are decided a token per thread
+#define LIST_BATCH 32    // loads of W^T in flight per thread
+#define DECIDE_FEW 4     // open tokens that a thread per centroid decides
+#define DECIDE_TILES 2   // 16-token tiles of open tokens decided at a time
 template <typename T, int D, bool BIAS>
 __global__ void __launch_bounds__(256, 2)
 assign_kernel(AssignArgs a) {
@@ -480,6 +489,8 @@ assign_kernel(AssignArgs a) {
     static_assert(LPW >= 1 && ASSIGN_CHUNK == 256, "geometry");
     __shared__ __attribute__((aligned(1024))) unsigned char wl[2 * TERMS * BLOCK];   // [buf][term][32][ROWB]
     __shared__ int32_t lab[256], open[256], n_open;
+    __shared__ double red_v[4][16 * DECIDE_TILES], norm[16 * DECIDE_TILES];
+    __shared__ int32_t red_j[4][16 * DECIDE_TILES];
     const int n = a.n, k_own = a.k_own;
     const int b = blockIdx.y, tid = threadIdx.x, lane = tid % 64, j = lane % 32, h = lane / 32;
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64);     // uniform: what derives from it stays scalar
@@ -649,49 +660,31 @@ assign_kernel(AssignArgs a) {
     }
     __syncthreads();        // labels and the list of open tokens are there; nobody reads wl any more
 
-    // ---- float64 decisions, TB tokens at a time.  The tokens sit in LDS; thread j walks column j of W^T, so
-    // that the threads read consecutive doubles, and adds the d products in index order: fixed, no
-    // cross-lane sums.  One (value, index) reduction per token at the end.
-    const int count = n_open;
-    double* xs = (double*)wl;                              // [TB][D]
-    double* red_v = xs + 4 * D;                            // [4 waves][TB]
-    int32_t* red_j = (int32_t*)(red_v + 16);               // [4 waves][TB]
-    auto decide = [&](auto tb_c, int p) {
+    // ---- float64 decisions
+    // (value, index) maximum, lowest index among equal values
+    auto wins = [](double ov, int oj, double v, int jj) {
+        return oj != 0x7fffffff && (jj == 0x7fffffff || ov > v || (ov == v && oj < jj));
+    };
+    auto settle = [&](int t, int slot) {                       // across the four waves, into token t's label
+        double val = red_v[0][slot];
+        int jj = red_j[0][slot];
+        for (int u = 1; u < 4; ++u)
+            if (wins(red_v[u][slot], red_j[u][slot], val, jj)) {
+                val = red_v[u][slot];
+                jj = red_j[u][slot];
+            }
+        lab[t] = jj == 0x7fffffff ? 0 : jj;
+    };
+    // A few tokens of a slice without degenerate anchors: they sit in LDS, thread j walks column j of W^T, so that the
+    // threads read consecutive doubles, and adds the d products in index order.
+    auto decide_few = [&](auto tb_c, int count) {
         constexpr int TB = decltype(tb_c)::value;
-        for (int e = tid; e < TB * D; e += 256) xs[e] = load_as_f64<T>(x + (size_t)(g0 + open[p + e / D]) * D + e % D);
-        __syncthreads();
-        double nx[TB];
-#pragma unroll
-        for (int t = 0; t < TB; ++t) nx[t] = 1.0;          // k-means scores
-        if (degenerate) {                                  // nx = ||x C_opp^T||: a row of C_opp per thread
-            double s2[TB];
-#pragma unroll
-            for (int t = 0; t < TB; ++t) s2[t] = 0.0;
-            for (int c = tid; c < a.k_opp; c += 256) {
-                const double* row = a.c_opp + ((size_t)b * a.k_opp + c) * D;
-                double dot[TB];
-#pragma unroll
-                for (int t = 0; t < TB; ++t) dot[t] = 0.0;
-                for (int e = 0; e < D; ++e)
-#pragma unroll
-                    for (int t = 0; t < TB; ++t) dot[t] = fma(xs[t * D + e], row[e], dot[t]);
-#pragma unroll
-                for (int t = 0; t < TB; ++t) s2[t] = fma(dot[t], dot[t], s2[t]);
-            }
-#pragma unroll
-            for (int t = 0; t < TB; ++t) {
-#pragma unroll
-                for (int off = 32; off > 0; off >>= 1) s2[t] += __shfl_xor(s2[t], off);
-                if (lane == 0) red_v[wave * TB + t] = s2[t];
-            }
-            __syncthreads();
-#pragma unroll
-            for (int t = 0; t < TB; ++t) {
-                const double r = sqrt(red_v[t] + red_v[TB + t] + red_v[2 * TB + t] + red_v[3 * TB + t]);
-                nx[t] = r > NORM_FLOOR ? r : NORM_FLOOR;
-            }
-            __syncthreads();
+        double* xs = (double*)wl;                              // [TB][D]
+        for (int e = tid; e < TB * D; e += 256) {
+            const int t = e / D < count ? e / D : 0;
+            xs[e] = load_as_f64<T>(x + (size_t)(g0 + open[t]) * D + e % D);
         }
+        __syncthreads();
         double best_v[TB];
         int best_j[TB];
 #pragma unroll
@@ -699,7 +692,7 @@ assign_kernel(AssignArgs a) {
             best_v[t] = -INFINITY;
             best_j[t] = 0x7fffffff;
         }
-        for (int c = tid; c < k_own; c += 256) {           // ascending per thread: ">" keeps the lowest index
+        for (int c = tid; c < k_own; c += 256) {               // ascending per thread: ">" keeps the lowest index
             const double* wc = a.wt + (size_t)b * D * k_own + c;
             double sum[TB];
 #pragma unroll
@@ -718,21 +711,16 @@ assign_kernel(AssignArgs a) {
                     for (int t = 0; t < TB; ++t) sum[t] = fma(xs[t * D + c0 + u], wv[u], sum[t]);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            const bool general = BIAS || degenerate;
-            const double bj = general ? a.bterm[(size_t)b * k_own + c] : 0.0;
+            const double bj = BIAS ? a.bterm[(size_t)b * k_own + c] : 0.0;
 #pragma unroll
             for (int t = 0; t < TB; ++t) {
-                const double val = general ? 2.0 * sum[t] - nx[t] * bj : sum[t];
+                const double val = BIAS ? 2.0 * sum[t] - bj : sum[t];
                 if (val > best_v[t] || best_j[t] == 0x7fffffff) {
                     best_v[t] = val;
                     best_j[t] = c;
                 }
             }
         }
-        // (value, index) maximum, lowest index among equal values: within the wave, then across the four
-        auto wins = [](double ov, int oj, double v, int jj) {
-            return oj != 0x7fffffff && (jj == 0x7fffffff || ov > v || (ov == v && oj < jj));
-        };
 #pragma unroll
         for (int t = 0; t < TB; ++t) {
 #pragma unroll
@@ -745,72 +733,139 @@ assign_kernel(AssignArgs a) {
                 }
             }
             if (lane == 0) {
-                red_v[wave * TB + t] = best_v[t];
-                red_j[wave * TB + t] = best_j[t];
+                red_v[wave][t] = best_v[t];
+                red_j[wave][t] = best_j[t];
             }
         }
         __syncthreads();
-        if (tid < TB) {
-            double bv = red_v[tid];
-            int jj = red_j[tid];
-            for (int u = 1; u < 4; ++u)
-                if (wins(red_v[u * TB + tid], red_j[u * TB + tid], bv, jj)) {
-                    bv = red_v[u * TB + tid];
-                    jj = red_j[u * TB + tid];
-                }
-            lab[open[p + tid]] = jj == 0x7fffffff ? 0 : jj;
-        }
+        if (tid < count) settle(open[tid], tid);
         __syncthreads();
     };
-    // Many open tokens (a slice with a degenerate anchor, as padding tokens make it, opens all of them): a token
-    // per thread, the score matrix through scalar loads, eight centroids at a time.  A group of four above costs 13 us
-    // whatever it holds, a full workgroup 64 of them.  Two iterations with a twentieth of the tokens zero and one of
-    // them an anchor: 12 x 75,600 x 128 bf16, 256 blocks 46.5 -> 27.8 ms, 12 x 8,190 x 128 float32, 64 blocks
-    // 3.61 -> 1.97 ms.
-    auto decide_many = [&]() {
-        const int at = open[tid];
-        const T* xr = x + (size_t)(g0 + at) * D;
-        double nx = 1.0;
-        if (degenerate) {
-            const double r = sqrt(affinity_norm2<T, D>(xr, a.c_opp + (size_t)b * a.k_opp * D, 0, a.k_opp));
-            nx = r > NORM_FLOOR ? r : NORM_FLOOR;
+    auto decide = [&](auto mt_c, int p0) {
+        constexpr int MT = decltype(mt_c)::value;              // 16-token tiles of this round
+        const int here = n_open - p0 < 16 * MT ? n_open - p0 : 16 * MT;
+        const int i = lane % 16, kq = lane / 16;
+        for (int e = tid; e < 16 * MT * CPR; e += 256) {       // the rows as they are, 16-byte chunks swizzled by row
+            const int r = e / CPR, c = e % CPR;
+            const uint4* src = (const uint4*)(x + (size_t)(g0 + open[p0 + (r < here ? r : 0)]) * D);
+            *(uint4*)(wl + r * ROWB + ((c ^ (r % CPR)) * 16)) = src[c];
+        }
+        __syncthreads();
+        // 16 MT tokens against 16 columns: products with b(step) added in index order; out(m, v, sum) gets token
+        // 16 m + kq + 4 v and column i
+        auto product = [&](const double (&bv)[D / 4], auto out) {
+            f64x4 acc[MT];
+#pragma unroll
+            for (int m = 0; m < MT; ++m) acc[m] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int t = 0; t < D / 4; ++t) {
+                if (t % 4 == 0) __builtin_amdgcn_sched_barrier(0);     // else all of the LDS reads come first
+#pragma unroll
+                for (int m = 0; m < MT; ++m) {
+                    const int at = (4 * t + kq) * (int)sizeof(T), r = 16 * m + i;
+                    const double av = load_as_f64<T>((const T*)(wl + r * ROWB + (((at / 16) ^ (r % CPR)) * 16) + at % 16));
+                    acc[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv[t], acc[m], 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) out(m, v, acc[m][v]);
+        };
+        double bv[D / 4];
+        if (degenerate) {                                      // nx = ||x C_opp^T||
+            double s2[MT][4];
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) s2[m][v] = 0.0;
+            for (int c = 16 * wave + i; c - i < a.k_opp; c += 64) {
+                const double* row = a.c_opp + ((size_t)b * a.k_opp + (c < a.k_opp ? c : a.k_opp - 1)) * D + kq;
+#pragma unroll
+                for (int t = 0; t < D / 4; ++t) bv[t] = c < a.k_opp ? row[4 * t] : 0.0;
+                product(bv, [&](int m, int v, double dot) { s2[m][v] = fma(dot, dot, s2[m][v]); });
+            }
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+#pragma unroll
+                    for (int off = 1; off < 16; off <<= 1) s2[m][v] += __shfl_xor(s2[m][v], off);
+                    if (i == 0) red_v[wave][16 * m + kq + 4 * v] = s2[m][v];
+                }
+            __syncthreads();
+            if (tid < 16 * MT) {
+                const double r = sqrt((red_v[0][tid] + red_v[1][tid]) + (red_v[2][tid] + red_v[3][tid]));
+                norm[tid] = r > NORM_FLOOR ? r : NORM_FLOOR;
+            }
+            __syncthreads();
         }
         const bool general = BIAS || degenerate;
-        double best_v = -INFINITY;
-        int best_j = 0x7fffffff;
-        auto centroids = [&](auto width, int c0) {
-            constexpr int R = decltype(width)::value;
-            const constant_row wt = as_constant(a.wt + (size_t)b * D * k_own + c0);
-            const constant_row bt = as_constant(a.bterm + (size_t)b * k_own + c0);
-            double sum[R];
-            token_dots<T, D, R>(xr, [&](int u, int c) { return wt[(size_t)c * k_own + u]; }, sum);
+        double best_v[MT][4];
+        int best_j[MT][4];
 #pragma unroll
-            for (int u = 0; u < R; ++u) {
-                const double val = general ? 2.0 * sum[u] - nx * bt[u] : sum[u];
-                if (val > best_v || best_j == 0x7fffffff) {
-                    best_v = val;
-                    best_j = c0 + u;
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                best_v[m][v] = -INFINITY;
+                best_j[m][v] = 0x7fffffff;
+            }
+        for (int c = 16 * wave + i; c - i < k_own; c += 64) {  // ascending per lane: ">" keeps the lowest index
+            const int col = c < k_own ? c : k_own - 1;
+            const double* wc = a.wt + ((size_t)b * D + kq) * k_own + col;
+#pragma unroll
+            for (int t = 0; t < D / 4; ++t) bv[t] = wc[(size_t)(4 * t) * k_own];
+            const double bj = general ? a.bterm[(size_t)b * k_own + col] : 0.0;
+            product(bv, [&](int m, int v, double dot) {
+                const double nx = degenerate ? norm[16 * m + kq + 4 * v] : 1.0;        // 1: k-means scores
+                const double val = general ? 2.0 * dot - nx * bj : dot;
+                if (c < k_own && (val > best_v[m][v] || best_j[m][v] == 0x7fffffff)) {
+                    best_v[m][v] = val;
+                    best_j[m][v] = c;
+                }
+            });
+        }
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+#pragma unroll
+                for (int off = 8; off > 0; off >>= 1) {
+                    const double ov = __shfl_xor(best_v[m][v], off);
+                    const int oj = __shfl_xor(best_j[m][v], off);
+                    if (wins(ov, oj, best_v[m][v], best_j[m][v])) {
+                        best_v[m][v] = ov;
+                        best_j[m][v] = oj;
+                    }
+                }
+                if (i == 0) {
+                    red_v[wave][16 * m + kq + 4 * v] = best_v[m][v];
+                    red_j[wave][16 * m + kq + 4 * v] = best_j[m][v];
                 }
             }
-        };
-        int c = 0;
-        for (; c + 8 <= k_own; c += 8) centroids(std::integral_constant<int, 8>{}, c);
-        for (; c < k_own; ++c) centroids(std::integral_constant<int, 1>{}, c);
-        lab[at] = best_j;
-    };
-    int p = 0;
-    if (count > DECIDE_MANY) {
-        if (tid < count) decide_many();
-        p = count;
         __syncthreads();
-    }
-    for (; p + 4 <= count; p += 4) decide(std::integral_constant<int, 4>{}, p);
-    for (; p < count; ++p) decide(std::integral_constant<int, 1>{}, p);
+        if (tid < here) settle(open[p0 + tid], tid);
+        __syncthreads();
+    };
+    const int count = n_open;
+    if (count > 0 && count <= DECIDE_FEW && !degenerate) {
+        if (count == 1)
+            decide_few(std::integral_constant<int, 1>{}, count);
+        else
+            decide_few(std::integral_constant<int, DECIDE_FEW>{}, count);
+    } else for (int p = 0; p < count;)
+        if (count - p <= 16) {
+            decide(std::integral_constant<int, 1>{}, p);
+            p += 16;
+        } else {
+            decide(std::integral_constant<int, DECIDE_TILES>{}, p);
+            p += 16 * DECIDE_TILES;
+        }
 
     // ---- labels and their counts
     if (g0 + tid < n) a.labels[(size_t)b * n + g0 + tid] = lab[tid];
     if (a.chunk_hist) {
-        int32_t* hist = (int32_t*)(wl + 6144);             // behind the decision's scratch
+        int32_t* hist = (int32_t*)wl;
         for (int c = tid; c < k_own; c += 256) hist[c] = 0;
         __syncthreads();
         if (g0 + tid < n) atomicAdd(&hist[lab[tid]], 1);

@@ -158,6 +158,25 @@ def test_assign_when_the_pre_filter_decides_nothing(dtype, d, n, k_own, k_opp, d
             np.testing.assert_array_equal(got[b], ref)
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
+@pytest.mark.parametrize("n", [256 + rest for rest in (1, 2, 4, 5, 16, 17, 32, 33, 49)])
+@pytest.mark.parametrize("k_own,k_opp", [(2, 16), (16, 17), (18, 64), (64, 65), (130, 2)])
+def test_assign_open_tokens_at_the_edges_of_the_matrix_tiles(dtype, d, n, k_own, k_opp):
+    """Every own-side centroid twice, so that all tokens are decided in float64: tiles of 16 tokens in rounds of 32,
+    tiles of 16 centroids dealt to four waves.  The second slice has a zero centroid (general form)."""
+    rng = np.random.default_rng(n + k_own)
+    x, own, opp = (rng.standard_normal(s).astype(np.float32) for s in ((2, n, d), (2, k_own, d), (2, k_opp, d)))
+    own[1, 0] = 0.0
+    own[:, k_own // 2:] = own[:, :k_own // 2]
+    if dtype == "bf16":
+        x = synth.round_to_bf16(x)
+    got = H.to_np(svoo.assign(H.to_dev(x, dtype), H.to_dev(own), H.to_dev(opp)))
+    for b in range(2):
+        ref, best, second = H.oracle_assign(x[b], own[b, :k_own // 2], opp[b])
+        H.compare_labels(got[b], ref, best, second)
+        assert (got[b] < k_own // 2).all()
+
+
 @pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 128)])
 def test_key_partition_follows_the_query_anchors(dtype, d):
     """The paper's intuition example (Sec. 4.2; fixture tests/golden/query_dependent_key_partition.txt) through
