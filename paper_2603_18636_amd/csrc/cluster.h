@@ -11,12 +11,18 @@ typedef __attribute__((ext_vector_type(4))) double f64x4;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
-#define FAST_EPS 3.1e-5f   // 2^-16 + 256 * 2^-24, twice the analytic bound for d <= 128
+// Error of a fast score relative to ||x|| ||W_j||, d <= 128: two bf16 terms 2^-17 + 256 * 2^-24 = 2.3e-5, W rounded to
+// float32 129 * 2^-24 = 7.7e-6.  What is left covers the float32 rounding of the norms themselves (2^-17 of a
+// sum of 128 squares).
+#define FAST_EPS 3.1e-5f
 
-// Below these a token's squared norm or its largest score have lost bits to float32's underflow, and the margins
-// that are built on them say nothing: such tokens are decided in float64.
+// Upper bound of ||x|| max_j ||W_j|| from the float32 squared norm of a token and the largest row norm: what underflow may
+// have taken from the square or from a score is less than FAST_MIN stands for.  With it a margin never says too little:
+// a token so small that the margin exceeds its scores' gap is decided in float64.
 #define FAST_MIN 1e-30f
-__device__ __forceinline__ bool norms_in_range(float xn2, float xw) { return xn2 >= FAST_MIN && xw >= FAST_MIN; }
+__device__ __forceinline__ float score_bound(float xn2, float wmax) {
+    return fmaxf(sqrtf(fmaxf(xn2, FAST_MIN)) * wmax, FAST_MIN);
+}
 
 // Score matrix in the form the pre-filter reads: two bf16 arrays, or one float32 array over the same bytes.
 template <typename T>

@@ -650,10 +650,10 @@ assign_kernel(AssignArgs a) {
         fi = fi < k_own ? fi : k_own - 1;                  // scores that are not numbers may leave any index
         const int tok = t0 + 32 * tb + j;
         if (h == 0) {
-            const float xw = sqrtf(xn2[tb]) * wmax;
+            const float xw = score_bound(xn2[tb], wmax);
             const float margin = BIAS ? 2.0f * (FAST_EPS * xw + 2.4e-7f * (0.5f * wmax * wmax + xw))   // 2^-22
                                       : 2.0f * FAST_EPS * xw;
-            const bool sure = (fb - fs) > margin && norms_in_range(xn2[tb], xw);      // false for NaN as well
+            const bool sure = (fb - fs) > margin;          // false for NaN as well
             lab[tok - g0] = fi;
             if ((degenerate || !sure) && tok < n) open[atomicAdd(&n_open, 1)] = tok - g0;
         }

@@ -247,8 +247,7 @@ assign_small_kernel(SmallAssign a) {
         const float fb = fmaxf(b0, b1), fs = fmaxf(fminf(b0, b1), fmaxf(__int_as_float(rs[0]), __int_as_float(rs[1])));
         if (h == 0 && tok < n) {
             const int fi = b0 >= b1 ? (int)ri[0] : (int)ri[1];
-            const float xw = sqrtf(xn2) * wmax;
-            const bool sure = (fb - fs) > 2.0f * FAST_EPS * xw && norms_in_range(xn2, xw);      // false for NaN as well
+            const bool sure = (fb - fs) > 2.0f * FAST_EPS * score_bound(xn2, wmax);      // false for NaN as well
             if (degenerate || !sure)
                 open[atomicAdd(&n_open, 1)] = tok;
             else

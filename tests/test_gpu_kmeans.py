@@ -109,3 +109,24 @@ def test_layer_with_kmeans_partitioner_and_recall(dtype, d):
     assert np.abs(rec - rec_ref).max() <= tol
     assert abs(rec.mean() - rec_ref.mean()) <= tol / 5
     assert 0.0 < rec_ref.mean() < 1.0
+
+
+@pytest.mark.parametrize("dtype,d,n", [("bf16", 128, 700), ("bf16", 64, 257), ("f32", 128, 300), ("f32", 64, 513)])
+@pytest.mark.parametrize("tie", [False, True])
+def test_kmeans_zero_and_tiny_tokens(dtype, d, n, tie):
+    """A zero token's scores hang on the centroids alone: the pre-filter may decide it, unless the two shortest
+    centroids are equally long (the lower index wins then).  Tokens of 1e-25 are the same to float32."""
+    rng = np.random.default_rng(n)
+    c = (2.0 + rng.random((37, d))).astype(np.float32) * rng.choice([-1.0, 1.0], (37, d)).astype(np.float32)
+    c[5] = synth.round_to_bf16(0.5 * c[5])
+    c[3] = -c[5] if tie else c[3]
+    x = rng.standard_normal((n, d)).astype(np.float32)
+    x[n - 120:] = 0.0
+    x[10:20] *= 1e-25
+    if dtype == "bf16":
+        x = synth.round_to_bf16(x)
+    out = svoo.kmeans(H.to_dev(x[None], dtype), iters=1, init_c=H.to_dev(c[None]))
+    labels = H.to_np(out["labels"])[0]
+    ref = so.kmeans(x, None, 1, init_c=c)
+    H.compare_labels(labels, ref["labels"], ref["trace"][0]["best"], ref["trace"][0]["second"])
+    assert (labels[n - 120:] == (3 if tie else 5)).all()
