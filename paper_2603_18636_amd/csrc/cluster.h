@@ -24,6 +24,9 @@ __device__ __forceinline__ float score_bound(float xn2, float wmax) {
     return fmaxf(sqrtf(fmaxf(xn2, FAST_MIN)) * wmax, FAST_MIN);
 }
 
+// Score of the general form, one rounding: 2 <x, W_j> - nx b_j (k-means: nx = 1, b_j = ||c_j||^2)
+__device__ __forceinline__ double general_score(double dot, double nx, double bj) { return fma(-nx, bj, 2.0 * dot); }
+
 // Score matrix in the form the pre-filter reads: two bf16 arrays, or one float32 array over the same bytes.
 template <typename T>
 __device__ __forceinline__ void store_split(double v, size_t o, uint16_t* w_hi, uint16_t* w_lo);
@@ -67,44 +70,6 @@ template <>
 __device__ __forceinline__ void load8_as_f64<float>(const float* p, double (&v)[8]) {
     const float4 a = *(const float4*)p, b = *(const float4*)(p + 4);
     v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-}
-
-// R dot products of one token per lane against vectors that all lanes share, the products added in index order.
-// w(u, c) is element c of vector u, the same address in every lane: constant_row below makes it a scalar load.
-template <typename T, int D, int R, typename W>
-__device__ __forceinline__ void token_dots(const T* xr, W w, double (&sum)[R]) {
-#pragma unroll
-    for (int u = 0; u < R; ++u) sum[u] = 0.0;
-#pragma unroll 1
-    for (int c0 = 0; c0 < D; c0 += 8) {
-        double xv[8];
-        load8_as_f64<T>(xr + c0, xv);
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-#pragma unroll
-            for (int u = 0; u < R; ++u) sum[u] = fma(xv[e], w(u, c0 + e), sum[u]);
-    }
-}
-
-typedef const __attribute__((address_space(4))) double* constant_row;      // written by an earlier kernel only
-__device__ __forceinline__ constant_row as_constant(const double* p) { return (constant_row)(uintptr_t)p; }
-
-// ||x C_opp^T|| of this lane's token against rows [r0, r1) of C_opp: the squared sum
-template <typename T, int D>
-__device__ __forceinline__ double affinity_norm2(const T* xr, const double* c_opp, int r0, int r1) {
-    double s2 = 0.0;
-    auto rows = [&](auto width, int r) {
-        constexpr int R = decltype(width)::value;
-        const constant_row m = as_constant(c_opp + (size_t)r * D);
-        double dot[R];
-        token_dots<T, D, R>(xr, [&](int u, int c) { return m[u * D + c]; }, dot);
-#pragma unroll
-        for (int u = 0; u < R; ++u) s2 = fma(dot[u], dot[u], s2);
-    };
-    int r = r0;
-    for (; r + 8 <= r1; r += 8) rows(std::integral_constant<int, 8>{}, r);
-    for (; r < r1; ++r) rows(std::integral_constant<int, 1>{}, r);
-    return s2;
 }
 
 // A half-step of few clusters and tokens in two launches (cluster_small.hip): labels, c_own and, where asked for,

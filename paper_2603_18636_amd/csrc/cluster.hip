@@ -714,7 +714,7 @@ assign_kernel(AssignArgs a) {
             const double bj = BIAS ? a.bterm[(size_t)b * k_own + c] : 0.0;
 #pragma unroll
             for (int t = 0; t < TB; ++t) {
-                const double val = BIAS ? 2.0 * sum[t] - bj : sum[t];
+                const double val = BIAS ? general_score(sum[t], 1.0, bj) : sum[t];
                 if (val > best_v[t] || best_j[t] == 0x7fffffff) {
                     best_v[t] = val;
                     best_j[t] = c;
@@ -773,7 +773,9 @@ assign_kernel(AssignArgs a) {
                 for (int v = 0; v < 4; ++v) out(m, v, acc[m][v]);
         };
         double bv[D / 4];
-        if (degenerate) {                                      // nx = ||x C_opp^T||
+        if (degenerate) {
+            // nx = ||x C_opp^T||: rows c, c + 64, .. in a row, these 64 sums in pairs (c, c + 1), then four, ..; the other
+            // routines that need it add it the same way, so that it does not hang on which of them a token meets
             double s2[MT][4];
 #pragma unroll
             for (int m = 0; m < MT; ++m)
@@ -818,7 +820,7 @@ assign_kernel(AssignArgs a) {
             const double bj = general ? a.bterm[(size_t)b * k_own + col] : 0.0;
             product(bv, [&](int m, int v, double dot) {
                 const double nx = degenerate ? norm[16 * m + kq + 4 * v] : 1.0;        // 1: k-means scores
-                const double val = general ? 2.0 * dot - nx * bj : dot;
+                const double val = general ? general_score(dot, nx, bj) : dot;
                 if (c < k_own && (val > best_v[m][v] || best_j[m][v] == 0x7fffffff)) {
                     best_v[m][v] = val;
                     best_j[m][v] = c;

@@ -7,8 +7,8 @@
 //            its 256 tokens: pre-filter, float64 decision of what that leaves open
 //   update   the workgroup of a cluster finds its members in the labels itself (n labels, one pass; the labels
 //            below its own are its offset), so there is no sort; it leaves the cluster-order layout on the way
-// Same arithmetic and the same bits as the general path: the same float64 products in the same order in W and in the
-// decisions, and in the means the same row groups.
+// Same arithmetic and the same bits as the general path, however many tokens are open: the same float64 products in the
+// same order in W, in the scores and in ||x C_opp^T||, and in the means the same row groups.
 // Measured per half-step: 1 x 1,024 x 64 float32, 16 blocks 24.3 -> 14.8 us; 3 x 2,945 x 64 bf16, 24 / 40 blocks
 // 28.8 -> 20.8; 3 x 4,096 x 128, 32 blocks 33.5 -> 25.8.  One workgroup per slice for all iterations (no launches
 // in between) was slower: 22 and 38 us for the first two, the pre-filter alone keeps a compute unit busy for 11-14.
@@ -28,6 +28,61 @@ struct SmallAssign {
     int32_t* labels;
     int n, k_own, k_opp;
 };
+
+// R dot products of one token per lane against vectors that all lanes share, the products added in index order.
+// w(u, c) is element c of vector u, the same address in every lane: constant_row below makes it a scalar load.
+template <typename T, int D, int R, typename W>
+__device__ __forceinline__ void token_dots(const T* xr, W w, double (&sum)[R]) {
+#pragma unroll
+    for (int u = 0; u < R; ++u) sum[u] = 0.0;
+#pragma unroll 1
+    for (int c0 = 0; c0 < D; c0 += 8) {
+        double xv[8];
+        load8_as_f64<T>(xr + c0, xv);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int u = 0; u < R; ++u) sum[u] = fma(xv[e], w(u, c0 + e), sum[u]);
+    }
+}
+
+typedef const __attribute__((address_space(4))) double* constant_row;      // written by an earlier kernel only
+__device__ __forceinline__ constant_row as_constant(const double* p) { return (constant_row)(uintptr_t)p; }
+
+// ||x C_opp^T|| of this lane's token against rows [r0, r0 + 32) of C_opp: the squared sum, added as the other
+// routines add it, lane by lane in pairs
+template <typename T, int D>
+__device__ __forceinline__ double affinity_norm2(const T* xr, const double* c_opp, int r0, int k_opp) {
+    auto rows8 = [&](int r) {
+#pragma clang fp contract(off)
+        double dot[8];
+        if (r + 8 <= k_opp) {
+            const constant_row m = as_constant(c_opp + (size_t)r * D);
+            token_dots<T, D, 8>(xr, [&](int u, int c) { return m[u * D + c]; }, dot);
+        } else {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                dot[u] = 0.0;
+                if (r + u < k_opp) {
+                    const constant_row m = as_constant(c_opp + (size_t)(r + u) * D);
+                    double one[1];
+                    token_dots<T, D, 1>(xr, [&](int, int c) { return m[c]; }, one);
+                    dot[u] = one[0];
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) dot[u] *= dot[u];
+        return ((dot[0] + dot[1]) + (dot[2] + dot[3])) + ((dot[4] + dot[5]) + (dot[6] + dot[7]));
+    };
+    double s2 = 0.0;
+#pragma unroll 1
+    for (int r = r0; r < r0 + 32 && r < k_opp; r += 16) {
+        const double lo = rows8(r);
+        s2 += lo + (r + 8 < k_opp ? rows8(r + 8) : 0.0);
+    }
+    return s2;
+}
 
 // LDS layout in bytes, the same on both sides
 template <typename T, int D>
@@ -266,7 +321,7 @@ assign_small_kernel(SmallAssign a) {
         const T* xr = x + (size_t)t * D;
         double nx = 1.0;
         if (degenerate) {
-            const double s2 = affinity_norm2<T, D>(xr, c_opp, half ? k_opp / 2 : 0, half ? k_opp : k_opp / 2);
+            const double s2 = affinity_norm2<T, D>(xr, c_opp, half ? 32 : 0, k_opp);
             if (half) other_v[at] = s2;
             __syncthreads();
             const double r = sqrt(half ? 0.0 : s2 + other_v[at]);
@@ -284,7 +339,7 @@ assign_small_kernel(SmallAssign a) {
             token_dots<T, D, R>(xr, [&](int u, int c) { return w64[(c0 + u) * WP + c]; }, sum);
 #pragma unroll
             for (int u = 0; u < R; ++u) {
-                const double val = degenerate ? 2.0 * sum[u] - nx * bterm[c0 + u] : sum[u];
+                const double val = degenerate ? general_score(sum[u], nx, bterm[c0 + u]) : sum[u];
                 if (val > best_v || best_j == 0x7fffffff) {
                     best_v = val;
                     best_j = c0 + u;
@@ -323,11 +378,11 @@ assign_small_kernel(SmallAssign a) {
             double s = 0.0;
 #pragma unroll 16
             for (int c = 0; c < D; ++c) s = fma(at(c), row[c], s);
-            double sq = lane < k_opp ? s * s : 0.0;
+            double sq = lane < k_opp ? fma(s, s, 0.0) : 0.0;      // rounded before it is added
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
+            for (int o = 1; o < 64; o <<= 1) sq += __shfl_xor(sq, o);
             const double r = sqrt(sq);
-            val = 2.0 * sum - (r > NORM_FLOOR ? r : NORM_FLOOR) * bterm[lane < k_own ? lane : k_own - 1];
+            val = general_score(sum, r > NORM_FLOOR ? r : NORM_FLOOR, bterm[lane < k_own ? lane : k_own - 1]);
         }
         int idx = lane < k_own ? lane : 0x7fffffff;
 #pragma unroll

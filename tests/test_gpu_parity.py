@@ -177,6 +177,33 @@ def test_assign_open_tokens_at_the_edges_of_the_matrix_tiles(dtype, d, n, k_own,
         assert (got[b] < k_own // 2).all()
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("order", range(4))
+def test_a_label_does_not_hang_on_the_company_of_its_token(dtype, d, order):
+    """Tokens whose affinity to the one ordinary anchor is half their norm up to a few units of float64's last place,
+    beside a zero centroid: 2 <x, W_0> - ||x C_opp^T|| against 0.  The norm's square is 4 large terms and many of 0.4 of
+    its last place each, so the order of the additions decides.  n = 276: workgroups with 256 and with 20 open tokens,
+    on the general path (svoo_assign) and, up to 32 clusters at d = 128, on the two-launch one (svoo_cocluster)."""
+    n, k_opp = 276, 48 if d == 64 else 30
+    rng = np.random.default_rng(order)
+    axis = rng.permutation(k_opp) if order else np.arange(k_opp)
+    x = np.zeros((1, n, d), dtype=np.float32)
+    x[0, :, axis[:4]] = 2.0 ** 20
+    x[0, :, axis[4:]] = 0.0197
+    if dtype == "bf16":
+        x = synth.round_to_bf16(x)
+    opp = np.eye(k_opp, d, dtype=np.float32)
+    own = np.zeros((2, d), dtype=np.float32)
+    own[0, axis[0]] = 1.0
+    excess = (x[0, 0].astype(np.float64) ** 2)[axis[4:]].sum() / 2.0 ** -10
+    assert 8 < excess < 30                                # the norm is above twice the affinity: the zero centroid wins
+    got = H.to_np(svoo.assign(H.to_dev(x, dtype), H.to_dev(own[None]), H.to_dev(opp[None])))
+    assert (got == 1).all()
+    q = rng.standard_normal((1, n, d)).astype(np.float32)
+    res = svoo.cocluster(H.to_dev(q, dtype), H.to_dev(x, dtype), iters=1, init_cq=H.to_dev(opp[None]), init_ck=H.to_dev(own[None]))
+    assert (H.to_np(res["labels_k"]) == 1).all()
+
+
 @pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 128)])
 def test_key_partition_follows_the_query_anchors(dtype, d):
     """The paper's intuition example (Sec. 4.2; fixture tests/golden/query_dependent_key_partition.txt) through
