@@ -4,20 +4,23 @@
 // Sort of one slice (n tokens, K bins) in chunks:
 //   hist     K-entry histogram per chunk: written by the assignment kernel, whose workgroups own a chunk of
 //            256 tokens each, or by one wave per 512 tokens where only labels are at hand
-//   scan     (more than SORT_DIRECT_CHUNKS chunks) per bin, inclusive prefix over the chunks, in place: the
+//   scan     (unless chunks and bins are few) per bin, inclusive prefix over the chunks, in place: the
 //            row before a chunk is where its tokens start, the last row the bin totals.  A workgroup takes
 //            64 bins, its 16 waves a sixteenth of the chunks each
 //   scatter  one wave per chunk walks its tokens 64 at a time in index order; lanes with equal
 //            labels find each other with one ballot per label bit and are ranked by lane, so equal
 //            labels keep ascending token order.  Every workgroup scans the K bin totals for the cluster
-//            offsets itself, and with few chunks it sums the histograms before its own instead of the scan
+//            offsets itself, and without a scan it sums the histograms before its own
 #include "common.h"
 
 #define SORT_WAVES 4
-// Up to this many chunks every scatter wave sums the histograms itself: 32 loads in flight per bin cost less
-// than the scan's launch (1 x 1,024 tokens, 16 bins: 24.7 us per half-step against 26.1 with the scan; 12 x 8,190,
-// 64 bins: 61.0 against 63.3; but 12 x 32,760 = 128 chunks: 97 against 91).
+// With few chunks and bins every scatter wave sums the histograms itself, a batch of loads in flight per bin, instead of
+// the scan's launch.  svoo_permute, 4 slices, direct / scan, us: 2,048 tokens, 512 bins (4 chunks) 28.0 / 31.3;
+// 8,192, 256 (16) 29.5 / 29.4; 16,384, 128 (32) 28.5 / 29.7; but 6,000, 512 (12) 35.0 / 31.8 and 16,384, 1,024 64 / 36.
+// More than 32 chunks never: 12 x 32,760 tokens in 128 chunks of the assignment 97 / 91 per half-step.
 #define SORT_DIRECT_CHUNKS 32
+#define SORT_DIRECT_COUNTS 4096
+#define SORT_DIRECT_BATCH 8
 
 size_t sort_scratch_ints(int bh, int n, int n_clusters, bool have_hist) {
     return (size_t)bh * sort_chunks(n, have_hist) * n_clusters;
@@ -99,11 +102,15 @@ sort_scatter_kernel(const int32_t* __restrict__ labels, const int32_t* __restric
     if (DIRECT) {
         for (int j = lane; j < k; j += SVOO_WAVE) {
             int base = 0, total = 0;
-#pragma unroll 8
-            for (int c = 0; c < nchunks; ++c) {
-                const int v = h[(size_t)c * k + j];
-                total += v;
-                base += c < chunk ? v : 0;
+            for (int c0 = 0; c0 < nchunks; c0 += SORT_DIRECT_BATCH) {      // a batch of loads in flight, also of the rest
+                int v[SORT_DIRECT_BATCH];
+#pragma unroll
+                for (int u = 0; u < SORT_DIRECT_BATCH; ++u) v[u] = c0 + u < nchunks ? h[(size_t)(c0 + u) * k + j] : 0;
+#pragma unroll
+                for (int u = 0; u < SORT_DIRECT_BATCH; ++u) {
+                    total += v[u];
+                    base += c0 + u < chunk ? v[u] : 0;
+                }
             }
             cnt[j] = base;
             if (wave == 0) off[j] = total;
@@ -172,7 +179,7 @@ template <int CHUNK>
 static void launch_scatter(dim3 grid, const int32_t* labels, int32_t* chunk_hist, int32_t* offsets, int32_t* perm, int n,
                            int k, int nchunks, hipStream_t stream) {
     const size_t lds = (size_t)(SORT_WAVES + 1) * k * sizeof(int32_t);
-    if (nchunks <= SORT_DIRECT_CHUNKS) {
+    if (nchunks <= SORT_DIRECT_CHUNKS && nchunks * k <= SORT_DIRECT_COUNTS) {
         hipLaunchKernelGGL((sort_scatter_kernel<true, CHUNK>), grid, dim3(SORT_WAVES * SVOO_WAVE), lds, stream, labels,
                            chunk_hist, offsets, perm, n, k, nchunks);
     } else {

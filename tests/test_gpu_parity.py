@@ -37,6 +37,20 @@ def test_sort_perm_offsets_bit_exact(n, k):
         assert (offsets[b] == o_ref).all()
 
 
+@pytest.mark.parametrize("n,k", [(2048, 1024), (2049, 1024), (8192, 256), (8193, 256), (16384, 128), (16385, 128), (3000, 600),
+                                  (4608, 455), (4609, 455), (16300, 3)])
+def test_sort_on_both_sides_of_the_scan_rule(n, k):
+    """Sums of the histograms in the scatter (up to 32 chunks and 4,096 counts, the last batch of chunks full or not)
+    or a scan of their own, with an empty cluster at the end."""
+    rng = np.random.default_rng(n + k)
+    labels = rng.integers(0, max(1, k - 1), size=(2, n)).astype(np.int32)
+    perm, off, _ = svoo.permute(H.to_dev(labels), k, [])
+    for b in range(2):
+        ref_perm, ref_off = so.stable_permutation(labels[b], k)
+        np.testing.assert_array_equal(H.to_np(perm)[b], ref_perm)
+        np.testing.assert_array_equal(H.to_np(off)[b], ref_off)
+
+
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
 def test_permute_unpermute_rows(dtype, d):
     rng = np.random.default_rng(7)
