@@ -19,7 +19,7 @@
 #define SMALL_MAX_N 8192
 #define SMALL_MAX_K 64
 #define SMALL_WAVES 8      // 32 tokens each
-#define SMALL_MANY 24      // more open tokens of a workgroup than this are decided a token per thread
+#define SMALL_MANY 24      // more open tokens of a workgroup than this are decided in tiles of 16
 
 struct SmallAssign {
     const void* x;
@@ -29,59 +29,25 @@ struct SmallAssign {
     int n, k_own, k_opp;
 };
 
-// R dot products of one token per lane against vectors that all lanes share, the products added in index order.
-// w(u, c) is element c of vector u, the same address in every lane: constant_row below makes it a scalar load.
-template <typename T, int D, int R, typename W>
-__device__ __forceinline__ void token_dots(const T* xr, W w, double (&sum)[R]) {
+// Elements kq, 4 + kq, 8 + kq, .. of a row: what a lane feeds the float64 matrix instruction as the contraction runs on
+template <int D>
+__device__ __forceinline__ void load_every_4th(const uint16_t* row, int kq, double (&v)[D / 4]) {
 #pragma unroll
-    for (int u = 0; u < R; ++u) sum[u] = 0.0;
-#pragma unroll 1
-    for (int c0 = 0; c0 < D; c0 += 8) {
-        double xv[8];
-        load8_as_f64<T>(xr + c0, xv);
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-#pragma unroll
-            for (int u = 0; u < R; ++u) sum[u] = fma(xv[e], w(u, c0 + e), sum[u]);
+    for (int c = 0; c < D / 8; ++c) {
+        const uint4 u = ((const uint4*)row)[c];
+        const uint32_t lo = kq < 2 ? u.x : u.y, hi = kq < 2 ? u.z : u.w;
+        v[2 * c] = (double)__uint_as_float(kq & 1 ? lo & 0xffff0000u : lo << 16);
+        v[2 * c + 1] = (double)__uint_as_float(kq & 1 ? hi & 0xffff0000u : hi << 16);
     }
 }
-
-typedef const __attribute__((address_space(4))) double* constant_row;      // written by an earlier kernel only
-__device__ __forceinline__ constant_row as_constant(const double* p) { return (constant_row)(uintptr_t)p; }
-
-// ||x C_opp^T|| of this lane's token against rows [r0, r0 + 32) of C_opp: the squared sum, added as the other
-// routines add it, lane by lane in pairs
-template <typename T, int D>
-__device__ __forceinline__ double affinity_norm2(const T* xr, const double* c_opp, int r0, int k_opp) {
-    auto rows8 = [&](int r) {
-#pragma clang fp contract(off)
-        double dot[8];
-        if (r + 8 <= k_opp) {
-            const constant_row m = as_constant(c_opp + (size_t)r * D);
-            token_dots<T, D, 8>(xr, [&](int u, int c) { return m[u * D + c]; }, dot);
-        } else {
+template <int D>
+__device__ __forceinline__ void load_every_4th(const float* row, int kq, double (&v)[D / 4]) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                dot[u] = 0.0;
-                if (r + u < k_opp) {
-                    const constant_row m = as_constant(c_opp + (size_t)(r + u) * D);
-                    double one[1];
-                    token_dots<T, D, 1>(xr, [&](int, int c) { return m[c]; }, one);
-                    dot[u] = one[0];
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) dot[u] *= dot[u];
-        return ((dot[0] + dot[1]) + (dot[2] + dot[3])) + ((dot[4] + dot[5]) + (dot[6] + dot[7]));
-    };
-    double s2 = 0.0;
-#pragma unroll 1
-    for (int r = r0; r < r0 + 32 && r < k_opp; r += 16) {
-        const double lo = rows8(r);
-        s2 += lo + (r + 8 < k_opp ? rows8(r + 8) : 0.0);
+    for (int c = 0; c < D / 4; ++c) {
+        const float4 u = ((const float4*)row)[c];
+        const float lo = kq & 1 ? u.y : u.x, hi = kq & 1 ? u.w : u.z;
+        v[c] = (double)(kq & 2 ? hi : lo);
     }
-    return s2;
 }
 
 // LDS layout in bytes, the same on both sides
@@ -113,8 +79,7 @@ assign_small_kernel(SmallAssign a) {
     constexpr int NW = SMALL_WAVES, NT = 64 * NW;
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     __shared__ int32_t wmax_bits, degenerate_s, n_open;
-    __shared__ int32_t open[32 * NW], other_j[32 * NW];
-    __shared__ double other_v[32 * NW];
+    __shared__ int32_t open[32 * NW];
     const int n = a.n, k_own = a.k_own, k_opp = a.k_opp;
     const L l(k_own, k_opp);
     unsigned char* split = lds + l.split;
@@ -312,52 +277,84 @@ assign_small_kernel(SmallAssign a) {
     __syncthreads();
     // ---- float64 decision of the open tokens, one per wave: lane = centroid, products added in index order
     const int count = n_open;
-    // Many (a slice with a degenerate anchor): a token per thread and half of the centroids.  Two iterations with a
-    // twentieth of the tokens zero, 1 x 1,024 x 64 float32, 16 blocks: 624 -> 120 us.
+    // Many (a slice with a degenerate anchor, zero tokens): tiles of 16 tokens on the float64 matrix instruction, a wave
+    // each (assign_kernel says why the bits are the same).  A token per thread and half of the centroids waited for its
+    // loads; one iteration, in us, general path before there was this one / a token per thread / now:
+    // 3 x 8,192 x 64 bf16, 64 blocks, a twentieth of zero tokens 123 / 145 / 114, one of them an anchor 462 / 236 / 235;
+    // 2 x 6,000 x 128 float32, 30 blocks, zero tokens 155 / 191 / 124, an anchor 413 / 406 / 264.
     if (count > SMALL_MANY) {
-        const int half = wave / (NW / 2), at = tid % (32 * NW);      // `half` is uniform
-        const bool has = at < count;
-        const int t = open[has ? at : 0];
-        const T* xr = x + (size_t)t * D;
-        double nx = 1.0;
-        if (degenerate) {
-            const double s2 = affinity_norm2<T, D>(xr, c_opp, half ? 32 : 0, k_opp);
-            if (half) other_v[at] = s2;
-            __syncthreads();
-            const double r = sqrt(half ? 0.0 : s2 + other_v[at]);
-            nx = r > NORM_FLOOR ? r : NORM_FLOOR;
-            if (!half) other_v[at] = nx;
-            __syncthreads();
-            nx = other_v[at];
-            __syncthreads();
-        }
-        double best_v = -INFINITY;
-        int best_j = 0x7fffffff;
-        auto centroids = [&](auto width, int c0) {
-            constexpr int R = decltype(width)::value;
-            double sum[R];
-            token_dots<T, D, R>(xr, [&](int u, int c) { return w64[(c0 + u) * WP + c]; }, sum);
+        for (int p0 = 16 * wave; p0 < count; p0 += 16 * NW) {
+            double av[D / 4];
+            load_every_4th<D>(x + (size_t)open[p0 + i16 < count ? p0 + i16 : p0] * D, kq4, av);
+            double nx[4] = {1.0, 1.0, 1.0, 1.0};       // of token kq + 4 v, as everything below
+            if (degenerate) {                          // nx = ||x C_opp^T||, added in pairs of columns, then of pairs
+                double s2[4] = {0.0, 0.0, 0.0, 0.0}, pair[4];
+                static_assert(SMALL_MAX_K == 64, "two pairs of 16 columns");
+#pragma unroll 1
+                for (int c = 0; c < ct; ++c) {
+                    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+                    const int col = 16 * c + i16;
+                    const double* row = c_opp + (size_t)(col < k_opp ? col : k_opp - 1) * D + kq4;
 #pragma unroll
-            for (int u = 0; u < R; ++u) {
-                const double val = degenerate ? general_score(sum[u], nx, bterm[c0 + u]) : sum[u];
-                if (val > best_v || best_j == 0x7fffffff) {
-                    best_v = val;
-                    best_j = c0 + u;
+                    for (int t = 0; t < D / 4; ++t) {
+                        if (t % 8 == 0) __builtin_amdgcn_sched_barrier(0);     // all loads at once would not fit 128 registers
+                        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[t], row[4 * t], acc, 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        double sq = col < k_opp ? fma(acc[v], acc[v], 0.0) : 0.0;
+#pragma unroll
+                        for (int o = 1; o < 16; o <<= 1) sq += __shfl_xor(sq, o);
+                        pair[v] = c & 1 ? pair[v] + sq : sq;
+                        if (c & 1 || c + 1 == ct) s2[v] += pair[v];
+                    }
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const double r = sqrt(s2[v]);
+                    nx[v] = r > NORM_FLOOR ? r : NORM_FLOOR;
                 }
             }
-        };
-        const int end = half ? k_own : k_own / 2;
-        int c = half ? k_own / 2 : 0;
-        for (; c + 8 <= end; c += 8) centroids(std::integral_constant<int, 8>{}, c);
-        for (; c < end; ++c) centroids(std::integral_constant<int, 1>{}, c);
-        if (half) {
-            other_v[at] = best_v;
-            other_j[at] = best_j;
-        }
-        __syncthreads();
-        if (!half && has) {        // the upper half wins only with a larger score
-            const bool upper = best_j == 0x7fffffff || other_v[at] > best_v;
-            a.labels[(size_t)b * n + t] = upper ? other_j[at] : best_j;
+            double best_v[4];
+            int best_j[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                best_v[v] = -INFINITY;
+                best_j[v] = 0x7fffffff;
+            }
+            for (int c = 0; c < rt; ++c) {             // ascending per lane: ">" keeps the lowest index
+                const int col = 16 * c + i16;
+                const double* wr = w64 + col * WP + kq4;
+                f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int t = 0; t < D / 4; ++t) {
+                    if (t % 8 == 0) __builtin_amdgcn_sched_barrier(0);
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[t], wr[4 * t], acc, 0, 0, 0);
+                }
+                const double bj = bterm[col < k_own ? col : k_own - 1];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const double val = degenerate ? general_score(acc[v], nx[v], bj) : acc[v];
+                    if (col < k_own && (val > best_v[v] || best_j[v] == 0x7fffffff)) {
+                        best_v[v] = val;
+                        best_j[v] = col;
+                    }
+                }
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+#pragma unroll
+                for (int o = 8; o > 0; o >>= 1) {
+                    const double ov = __shfl_xor(best_v[v], o);
+                    const int oj = __shfl_xor(best_j[v], o);
+                    if (oj != 0x7fffffff && (best_j[v] == 0x7fffffff || ov > best_v[v] || (ov == best_v[v] && oj < best_j[v]))) {
+                        best_v[v] = ov;
+                        best_j[v] = oj;
+                    }
+                }
+                const int p = p0 + kq4 + 4 * v;
+                if (i16 == 0 && p < count) a.labels[(size_t)b * n + open[p]] = best_j[v] == 0x7fffffff ? 0 : best_j[v];
+            }
         }
         return;
     }
