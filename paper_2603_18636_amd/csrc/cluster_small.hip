@@ -18,6 +18,7 @@
 
 #define SMALL_MAX_N 8192
 #define SMALL_MAX_K 64
+#define SMALL_MAX_W 4096   // clusters of a side x d
 #define SMALL_WAVES 8      // 32 tokens each
 #define SMALL_MANY 24      // more open tokens of a workgroup than this are decided in tiles of 16
 
@@ -58,7 +59,8 @@ struct SmallLds {
     static constexpr int TERMS = sizeof(T) == 2 ? 2 : 1;
     static constexpr int BLOCK = 32 * ROWB;
     int pitch, split, c_opp, ph, bterm, bytes;         // W in float64 takes C_opp's place once it is used up
-    __host__ __device__ SmallLds(int k_own, int k_opp) {
+    __host__ __device__ constexpr SmallLds(int k_own, int k_opp)
+        : pitch(0), split(0), c_opp(0), ph(0), bterm(0), bytes(0) {
         const int own16 = (k_own + 15) / 16 * 16, own32 = (k_own + 31) / 32 * 32;
         pitch = (k_opp + 15) / 16 * 16 + 2;
         const int c = k_opp * CP * 8, w = own16 * WP * 8;
@@ -150,9 +152,9 @@ assign_small_kernel(SmallAssign a) {
         }
     }
     __syncthreads();
-    // ---- W = P^ C_opp, at most four 16 x 16 tiles per wave, kept in registers until C_opp's LDS is free
+    // ---- W = P^ C_opp, at most two 16 x 16 tiles per wave, kept in registers until C_opp's LDS is free
     {
-        constexpr int JOBS = SMALL_MAX_K / 16 * (D / 16) / NW;
+        constexpr int JOBS = SMALL_MAX_W / (16 * 16 * NW);
         f64x4 acc[JOBS];
 #pragma unroll
         for (int u = 0; u < JOBS; ++u) {
@@ -481,7 +483,8 @@ update_small_kernel(const T* __restrict__ x, const int32_t* __restrict__ labels,
 template <typename T, int D>
 static bool small_assign(const svoo_shape* s, const SmallAssign& a, hipStream_t stream) {
     auto kern = assign_small_kernel<T, D>;
-    constexpr int most = 140 * 1024;                   // 64 + 64 clusters, d = 128: 133 KB
+    constexpr int k_max = SMALL_MAX_W / D;             // 64 clusters of 64, 32 of 128
+    constexpr int most = SmallLds<T, D>(k_max, k_max).bytes;
     static unsigned char opted_in[SVOO_MAX_DEVICES];
     if (!opt_in_dynamic_lds((const void*)kern, most, opted_in)) return false;
     const int bytes = SmallLds<T, D>(a.k_own, a.k_opp).bytes;
@@ -513,7 +516,7 @@ static bool small_half_step(const svoo_shape* s, const SmallStep& st, hipStream_
 bool small_fits(const svoo_shape* s) {
     if (s->n > SMALL_MAX_N || s->kq > SMALL_MAX_K || s->kk > SMALL_MAX_K) return false;
     const long long w = (long long)(s->kq > s->kk ? s->kq : s->kk) * s->d;
-    return w <= 4096 && w * s->bh * ((s->n + 255) / 256) <= 1600000;
+    return w <= SMALL_MAX_W && w * s->bh * ((s->n + 255) / 256) <= 1600000;
 }
 
 int small_half_step(const svoo_shape* s, const SmallStep& st, hipStream_t stream) {
