@@ -53,90 +53,45 @@ __global__ void init_centroids_kernel(InitSide s0, InitSide s1, int n, int d, in
 }
 
 // ---------------------------------------------------------------------------------------------
-// Small batched float64 GEMM with arbitrary strides: C[m, n] = sum_k A(m, k) * B(k, n), on the
-// float64 matrix instruction (v_mfma_f64_16x16x4_f64): one wave per 16 x 32 output tile, operands
-// straight from global memory (the matrices are a few hundred KB and sit in L2) -- lane (i, kq) =
-// (lane % 16, lane / 16) supplies A(m0 + i, k) and B(k, n0 + i), B(k, n0 + 16 + i) for the two
-// contraction indices k = k0 + 2 kq, k0 + 2 kq + 1 of a block of 8 (any assignment of indices to
-// the instruction's four contraction slots is valid as long as A and B agree); accumulator v of
-// the lane holds C(m0 + kq + 4 v, n0 + i).  AK2 / BK2: the lane's two A / B values are adjacent
-// in memory and 16-byte aligned, so one load fetches both.
-// Used for G = C_opp^T C_opp (the other two small
-// products of a half-step are inside anchor_w_kernel; only the objective needs this one).
+// G = C^T C (float64, D x D) of a centroid matrix C [k, D], for the objective: on the float64 matrix instruction
+// (v_mfma_f64_16x16x4_f64), one wave per 16 x 32 output tile, operands straight from global memory (a few
+// hundred KB, in L2).  Lane (i, kq) = (lane % 16, lane / 16) supplies rows k0 + 2 kq and k0 + 2 kq + 1 of a block of 8
+// at columns m0 + i, n0 + i and n0 + 16 + i (any assignment of indices to the instruction's four contraction
+// slots is valid as long as both operands agree); accumulator v of the lane holds G(m0 + kq + 4 v, n0 + i).
 // ---------------------------------------------------------------------------------------------
-struct GemmArgs {
-    const double* a;
-    const double* b;
-    double* c;
-    int m, n, k;
-    long long a_batch, b_batch, c_batch;
-    int a_sm, a_sk, b_sk, b_sn;
-};
-
-template <bool K2>
-__device__ __forceinline__ void load_k_pair(const double* __restrict__ row, int k, int k_end, int sk, double& v0,
-                                            double& v1) {
-    if (K2 && k + 1 < k_end) {
-        const double2 t = *(const double2*)(row + k);
-        v0 = t.x;
-        v1 = t.y;
-    } else {
-        v0 = k < k_end ? row[(size_t)k * sk] : 0.0;
-        v1 = k + 1 < k_end ? row[(size_t)(k + 1) * sk] : 0.0;
-    }
-}
-
-template <bool AK2, bool BK2>
-__global__ void __launch_bounds__(64) gemm_f64_kernel(GemmArgs g) {
-    const double* a = g.a + (size_t)blockIdx.z * g.a_batch;
-    const double* b = g.b + (size_t)blockIdx.z * g.b_batch;
-    double* c = g.c + (size_t)blockIdx.z * g.c_batch;
+template <int D>
+__global__ void __launch_bounds__(64) gram_kernel(const double* __restrict__ c_all, double* __restrict__ gram, int k) {
+    const double* c = c_all + (size_t)blockIdx.z * k * D;
     const int lane = threadIdx.x, i = lane % 16, kq = lane / 16;
     const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 32;
-    // rows / columns past the edge read row / column 0: their products only reach outputs that are not stored
-    const double* ap = a + (size_t)(m0 + i < g.m ? m0 + i : 0) * g.a_sm;
-    const double* bp0 = b + (size_t)(n0 + i < g.n ? n0 + i : 0) * g.b_sn;
-    const double* bp1 = b + (size_t)(n0 + 16 + i < g.n ? n0 + 16 + i : 0) * g.b_sn;
     f64x4 acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = {0.0, 0.0, 0.0, 0.0};
-    for (int k00 = 0; k00 < g.k; k00 += 32) {     // four blocks of 8 per trip: their loads are in flight together
-        double a0[4], a1[4], b00[4], b01[4], b10[4], b11[4];
+    for (int k00 = 0; k00 < k; k00 += 32) {       // four blocks of 8 per trip: their loads are in flight together
+        double a[4][2], b0[4][2], b1[4][2];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int k = k00 + 8 * u + 2 * kq;       // past the end: zeros
-            load_k_pair<AK2>(ap, k, g.k, g.a_sk, a0[u], a1[u]);
-            load_k_pair<BK2>(bp0, k, g.k, g.b_sk, b00[u], b01[u]);
-            load_k_pair<BK2>(bp1, k, g.k, g.b_sk, b10[u], b11[u]);
-        }
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[u], b00[u], acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[u], b10[u], acc1, 0, 0, 0);
-            acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[u], b01[u], acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[u], b11[u], acc1, 0, 0, 0);
-        }
+            for (int e = 0; e < 2; ++e) {
+                const int r = k00 + 8 * u + 2 * kq + e;      // past the end: zeros
+                const double* row = c + (size_t)(r < k ? r : 0) * D;
+                a[u][e] = r < k ? row[m0 + i] : 0.0;
+                b0[u][e] = r < k ? row[n0 + i] : 0.0;
+                b1[u][e] = r < k ? row[n0 + 16 + i] : 0.0;
+            }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][e], b0[u][e], acc0, 0, 0, 0);
+                acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][e], b1[u][e], acc1, 0, 0, 0);
+            }
     }
+    double* g = gram + (size_t)blockIdx.z * D * D;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const int m = m0 + kq + 4 * v;
-        if (m < g.m) {
-            if (n0 + i < g.n) c[(size_t)m * g.n + n0 + i] = acc0[v];
-            if (n0 + 16 + i < g.n) c[(size_t)m * g.n + n0 + 16 + i] = acc1[v];
-        }
+        g[m * D + n0 + i] = acc0[v];
+        g[m * D + n0 + 16 + i] = acc1[v];
     }
-}
-
-static void launch_gemm(const GemmArgs& g, int batch, hipStream_t stream) {
-    dim3 grid((g.n + 31) / 32, (g.m + 15) / 16, batch);
-    const bool ak2 = g.a_sk == 1 && g.a_sm % 2 == 0 && g.a_batch % 2 == 0 && ((uintptr_t)g.a & 15) == 0;
-    const bool bk2 = g.b_sk == 1 && g.b_sn % 2 == 0 && g.b_batch % 2 == 0 && ((uintptr_t)g.b & 15) == 0;
-    if (ak2 && bk2)
-        hipLaunchKernelGGL((gemm_f64_kernel<true, true>), grid, dim3(64), 0, stream, g);
-    else if (ak2)
-        hipLaunchKernelGGL((gemm_f64_kernel<true, false>), grid, dim3(64), 0, stream, g);
-    else if (bk2)
-        hipLaunchKernelGGL((gemm_f64_kernel<false, true>), grid, dim3(64), 0, stream, g);
-    else
-        hipLaunchKernelGGL((gemm_f64_kernel<false, false>), grid, dim3(64), 0, stream, g);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1085,9 +1040,7 @@ static void assign_side_t(const svoo_shape* s, const ClusterWs& w, const void* x
     launch_anchor_w<T, D>(c_own, c_opp, k_own, k_opp, bh, want_objective ? w.w64 : nullptr, w.bterm, w.flags, w.w_hi,
                           w.w_lo, w.wt64, w.wmax_bits, stream);
     if (want_objective) {      // G[a, b] = sum_c c_opp[c, a] * c_opp[c, b], nx^2 = x^T G x
-        GemmArgs g3 = {c_opp, c_opp, w.gram, D, D, k_opp, (long long)k_opp * D, (long long)k_opp * D, (long long)D * D,
-                       1, D, D, 1};
-        launch_gemm(g3, bh, stream);
+        hipLaunchKernelGGL(gram_kernel<D>, dim3(D / 32, D / 16, bh), dim3(64), 0, stream, c_opp, w.gram, k_opp);
         launch_quadform<T, D>(x, w.gram, w.nx2, bh, s->n, stream);
     }
     launch_assign<T, D, false>(s, w, x, c_opp, k_own, k_opp, labels, chunk_hist, stream);
