@@ -101,8 +101,9 @@ size_t svoo_permute_workspace_bytes(const svoo_shape* shape, int32_t n_clusters)
  * objective (nullable) [bh, iters, 2] float64 (sums of N float64 terms; float32 would lose the
  * differences between iterations): sum_i ||P^_i - Pbar^_{L_i}||^2 at assignment time of Step A
  * (index 0) and Step B (index 1) -- a diagnostic, costs one extra pass per half-step.
- * Arithmetic: assignment decisions are taken in float64 (a bf16 matrix-core pass only pre-filters
- * tokens whose best and second-best scores are far apart); centroid means are float64 sums in a
+ * Arithmetic: assignment decisions are taken in float64 (a matrix-core pass, in bf16 for bf16 tokens and
+ * in float32 for float32 ones, only decides tokens whose best and second-best scores are provably far
+ * enough apart); centroid means are float64 sums in a
  * fixed order, carried in float64 between iterations and rounded to float32 on output.
  */
 int svoo_cocluster(const svoo_shape* shape, const void* q, const void* k,
@@ -149,7 +150,7 @@ int svoo_assign(const svoo_shape* shape, const void* x, const float* c_own, int3
  * both are given).  1 <= k <= 1024, k <= n; shape->kq / kk are ignored.
  * Outputs: labels [bh, n]; c [bh, k, d] float32 = means of the returned labels; counts [bh, k];
  * inertia (nullable) [bh, iters] float64 = sum_i ||x_i - c_{labels[i]}||^2 at assignment time.
- * Decisions in float64 behind a bf16 matrix-core pre-filter, as in svoo_cocluster.
+ * Decisions in float64 behind a matrix-core pre-filter, as in svoo_cocluster.
  * Workspace: svoo_workspace_bytes() of a shape whose kq or kk is >= k suffices.
  */
 int svoo_kmeans(const svoo_shape* shape, const void* x, int32_t k, const int32_t* init_idx,
@@ -217,7 +218,8 @@ int svoo_block_mask(const svoo_shape* shape, const float* cq, const float* ck,
  * logits over the kept keys (natural log).  A query block with no kept key writes zeros.
  * scale must be finite and > 0.
  * bf16: both contractions on bf16 matrix cores with float32 accumulation, probabilities rounded to
- * bf16 before the second one; f32: float32 arithmetic throughout.
+ * bf16 before the second one; f32: float32 arithmetic throughout (logits summed in four chains).  Keys
+ * whose logit is -inf weigh nothing; a row with no other keys gets zeros and lse = -inf.
  */
 int svoo_block_sparse_attn(const svoo_shape* shape, const void* q_sorted, const void* k_sorted,
                            const void* v_sorted, const int32_t* q_offsets, const int32_t* k_offsets,

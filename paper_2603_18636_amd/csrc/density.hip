@@ -4,26 +4,28 @@
 // For a query row i with logits s_t = <q_i, k_t> and p_t = softmax_t(scale * s_t) over all n keys,
 // the row's prefix length is the size of the shortest descending-sorted prefix of p whose sum
 // reaches tau.  Nothing is sorted: the row keeps a bracket [lo, hi) of logit values that holds the
-// prefix's last key, and every pass over the keys narrows it DEN_BINS-fold:
+// prefix's last key, and every pass over the keys narrows it BINS-fold (64 bins for bf16, 32 for float32, where
+// a K tile takes twice the LDS):
 //
 //   pass 0      row maximum m and minimum of the logits, mean and variance of a sample of them
-//   pass 1      histogram over all keys of the masses 2^((s_t - m) c2)  (c2 = scale * log2 e): 64 equal
+//   pass 1      histogram over all keys of the masses 2^((s_t - m) c2)  (c2 = scale * log2 e): BINS equal
 //               bins around the value a normal distribution of the logits would give, the outer two
 //               open-ended.  The sum of the bins is Z; the bin in which the running mass from above
 //               meets tau Z is the bracket.
-//   pass 2...   rows whose bracket may hold more than DEN_CAP keys: the same histogram inside the
+//   pass 2...   rows whose bracket may hold more than CAP = 2 BINS keys: the same histogram inside the
 //               bracket only.  Rows with fewer: the keys in it are collected into a list, and those
 //               above it counted; the row is done.
 //
 // and the lists are ordered at the end.  75,600 keys take four or five passes where halving the
-// bracket took 29.  A bracket that shrinks to one float value holds ties, taken one at a time by a
+// bracket took 29 (float32: four at 4,096 to 8,190 keys, 27-30).  Rows whose logits are all equal are done after pass 0.  A bracket that shrinks to one float value holds ties, taken one at a time by a
 // division.  A bracket that equal bins cannot split (its width is not a usable float32) is split by
 // the order of the float bit patterns instead.
 //
 // The logits are recomputed in every pass by the same instruction sequence, so they are
 // bit-identical from pass to pass, and a bin's edges are the exact floats at which the bin function
-// steps, so the histogram, the bracket and the list agree on every key.  Masses are added as 64-bit
-// fixed-point integers (LDS atomics): exact, hence independent of the order of the additions.
+// steps, so the histogram, the bracket and the list agree on every key.  Masses are rounded to a 64-bit
+// fixed-point unit 2^-S and added as integers (LDS atomics): independent of the order of the additions.  The n
+// roundings drop at most n 2^-(S+1); svoo_attention_density chooses S.
 //
 // S^T = K Q^T on the matrix cores (bf16: 32x32x16, float32: 32x32x2), one query per lane column.  A
 // workgroup owns 32 RG query rows and splits the keys KS ways (wave (rg, ks) takes the tiles ks,
@@ -573,8 +575,9 @@ static int launch_density(const DensityArgs& a, hipStream_t stream) {
 }
 
 // One workgroup fits a compute unit (its histograms and K stages fill the LDS) and runs for the whole launch,
-// so the rows per workgroup are the fewest with which one round of the 256 units covers all rows: 12 x 2,048
-// rows are 192 workgroups of 128 rows, a quarter of the chip idle, or 256 of 96.
+// so the rows per workgroup are the fewest with which one round of the 256 units covers all rows, else 128.  That
+// is not always the best split: 12 x 2,048 rows are 264 workgroups of 96 rows, eight too many, and run as 192
+// of 128 (4.0 ms), a quarter of the chip idle; three full rounds of 32-row workgroups have not been measured.
 template <typename T, int D>
 static int dispatch_density(const DensityArgs& a, hipStream_t stream) {
     auto wgs = [&](int rg) { return (long long)((a.n_rows + 32 * rg - 1) / (32 * rg)) * a.bh; };

@@ -52,12 +52,11 @@ def test_density_matches_oracle(dtype, d, grid, tau):
 @pytest.mark.parametrize("d,grid,copies", [(128, (6, 12, 20), 12), (128, (6, 12, 20), 24), (64, (3, 3, 37), 45),
                                            (64, (3, 3, 37), 90), (128, (1, 3, 43), 300)])
 def test_density_in_every_launch_shape(d, grid, copies):
-    """The bf16 kernel splits the keys 4, 2 or 1 ways inside a workgroup depending on how many
-    workgroups the launch has (<= 256, <= 512, more); the small cases above all take the 4-way shape.
-    Here two heads are repeated ``copies`` times so that the same data runs through the other shapes
-    (n = 1440: 12 workgroups per head -> 288 and 576; n = 333, ragged last tile: 3 per head -> 270 and
-    540; n = 129: 2 per head, three 64-key tiles of which the last holds one key -> 1200), each
-    compared with the oracle, and every copy must equal the first."""
+    """The rows of a workgroup are the fewest (32, 64 or 96) with which one round of 256 workgroups covers all rows,
+    else 128; the small cases above all take 32.  Here two heads are repeated ``copies`` times so that the
+    same data runs through workgroups of 128 rows and, with two heads, of 32 (n = 1440; n = 333, ragged last
+    tile; n = 129, three 64-key tiles of which the last holds one key), each compared with the oracle, and
+    every copy must equal the first.  64 and 96 rows: ``test_density_bracket_splits``."""
     cfg = synth.CONFIGS[1]
     heads = [synth.make_head(cfg, 7, hd, grid=grid, n_seeds=8, kq=1, kk=1, d=d, dtype="bf16") for hd in range(2)]
     q = np.tile(np.stack([h["q"] for h in heads]), (copies, 1, 1))
@@ -72,10 +71,10 @@ def test_density_in_every_launch_shape(d, grid, copies):
         ref = so.attention_density(q[b], k[b], scale, tau32)
         compare_prefix(plen[b], ref, max_near=max(2, n // 100))
         assert (plen[b::2] == plen[b]).all() and (dens[b::2] == dens[b]).all() and (passes[b::2] == passes[b]).all()
-    # the 4-way shape on the same two heads
+    # 32-row workgroups on the same two heads
     plen4, _ = svoo.attention_density(H.to_dev(q[:2], "bf16"), H.to_dev(k[:2], "bf16"), tau32, scale)
     differ = int((H.to_np(plen4) != plen[:2]).sum())
-    print(f"{wgs} workgroups: {differ} of {2 * n} prefix lengths differ from the 4-way launch")
+    print(f"{wgs} workgroups: {differ} of {2 * n} prefix lengths differ from the launch of two heads")
     assert differ <= max(2, n // 100)
 
 

@@ -153,8 +153,7 @@ def test_assign_degenerate_anchor_in_one_of_two_slices_many_tiles(dtype):
 @pytest.mark.parametrize("degenerate", [False, True])
 def test_assign_when_the_pre_filter_decides_nothing(dtype, d, n, k_own, k_opp, degenerate):
     """Every own-side centroid twice: best and second-best scores are equal for every token, so all of them are
-    decided in float64 (tokens in groups of four and one at a time, workgroups with 1 to 256 open tokens,
-    more and fewer centroids than threads) and the lower of the two indices must win; with an all-zero
+    decided in float64 (workgroups with 1 to 256 open tokens, more and fewer centroids than threads) and the lower of the two indices must win; with an all-zero
     centroid the general form of the distance decides."""
     rng = np.random.default_rng(n + k_own)
     x, own, opp = (rng.standard_normal(s).astype(np.float32) for s in ((2, n, d), (2, k_own, d), (2, k_opp, d)))
