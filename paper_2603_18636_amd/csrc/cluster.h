@@ -27,6 +27,13 @@ __device__ __forceinline__ float score_bound(float xn2, float wmax) {
 // Score of the general form, one rounding: 2 <x, W_j> - nx b_j (k-means: nx = 1, b_j = ||c_j||^2)
 __device__ __forceinline__ double general_score(double dot, double nx, double bj) { return fma(-nx, bj, 2.0 * dot); }
 
+// (value, index) maximum, lowest index among equal values.  A score that is no number never enters (its index stays
+// NO_INDEX), so a centroid that is NaN wins no token; a token without any score gets cluster 0.
+#define NO_INDEX 0x7fffffff
+__device__ __forceinline__ bool wins(double ov, int oj, double v, int j) {
+    return oj != NO_INDEX && (j == NO_INDEX || ov > v || (ov == v && oj < j));
+}
+
 // Score matrix in the form the pre-filter reads: two bf16 arrays, or one float32 array over the same bytes.
 template <typename T>
 __device__ __forceinline__ void store_split(double v, size_t o, uint16_t* w_hi, uint16_t* w_lo);

@@ -616,10 +616,6 @@ assign_kernel(AssignArgs a) {
     __syncthreads();        // labels and the list of open tokens are there; nobody reads wl any more
 
     // ---- float64 decisions
-    // (value, index) maximum, lowest index among equal values
-    auto wins = [](double ov, int oj, double v, int jj) {
-        return oj != 0x7fffffff && (jj == 0x7fffffff || ov > v || (ov == v && oj < jj));
-    };
     auto settle = [&](int t, int slot) {                       // across the four waves, into token t's label
         double val = red_v[0][slot];
         int jj = red_j[0][slot];
@@ -628,7 +624,7 @@ assign_kernel(AssignArgs a) {
                 val = red_v[u][slot];
                 jj = red_j[u][slot];
             }
-        lab[t] = jj == 0x7fffffff ? 0 : jj;
+        lab[t] = jj == NO_INDEX ? 0 : jj;
     };
     // A few tokens of a slice without degenerate anchors: they sit in LDS, thread j walks column j of W^T, so that the
     // threads read consecutive doubles, and adds the d products in index order.
@@ -645,7 +641,7 @@ assign_kernel(AssignArgs a) {
 #pragma unroll
         for (int t = 0; t < TB; ++t) {
             best_v[t] = -INFINITY;
-            best_j[t] = 0x7fffffff;
+            best_j[t] = NO_INDEX;
         }
         for (int c = tid; c < k_own; c += 256) {               // ascending per thread: ">" keeps the lowest index
             const double* wc = a.wt + (size_t)b * D * k_own + c;
@@ -670,7 +666,7 @@ assign_kernel(AssignArgs a) {
 #pragma unroll
             for (int t = 0; t < TB; ++t) {
                 const double val = BIAS ? general_score(sum[t], 1.0, bj) : sum[t];
-                if (val > best_v[t] || best_j[t] == 0x7fffffff) {
+                if (val > best_v[t]) {
                     best_v[t] = val;
                     best_j[t] = c;
                 }
@@ -765,7 +761,7 @@ assign_kernel(AssignArgs a) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 best_v[m][v] = -INFINITY;
-                best_j[m][v] = 0x7fffffff;
+                best_j[m][v] = NO_INDEX;
             }
         for (int c = 16 * wave + i; c - i < k_own; c += 64) {  // ascending per lane: ">" keeps the lowest index
             const int col = c < k_own ? c : k_own - 1;
@@ -776,7 +772,7 @@ assign_kernel(AssignArgs a) {
             product(bv, [&](int m, int v, double dot) {
                 const double nx = degenerate ? norm[16 * m + kq + 4 * v] : 1.0;        // 1: k-means scores
                 const double val = general ? general_score(dot, nx, bj) : dot;
-                if (c < k_own && (val > best_v[m][v] || best_j[m][v] == 0x7fffffff)) {
+                if (c < k_own && val > best_v[m][v]) {
                     best_v[m][v] = val;
                     best_j[m][v] = c;
                 }

@@ -322,7 +322,7 @@ assign_small_kernel(SmallAssign a) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 best_v[v] = -INFINITY;
-                best_j[v] = 0x7fffffff;
+                best_j[v] = NO_INDEX;
             }
             for (int c = 0; c < rt; ++c) {             // ascending per lane: ">" keeps the lowest index
                 const int col = 16 * c + i16;
@@ -337,7 +337,7 @@ assign_small_kernel(SmallAssign a) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const double val = degenerate ? general_score(acc[v], nx[v], bj) : acc[v];
-                    if (col < k_own && (val > best_v[v] || best_j[v] == 0x7fffffff)) {
+                    if (col < k_own && val > best_v[v]) {
                         best_v[v] = val;
                         best_j[v] = col;
                     }
@@ -349,13 +349,13 @@ assign_small_kernel(SmallAssign a) {
                 for (int o = 8; o > 0; o >>= 1) {
                     const double ov = __shfl_xor(best_v[v], o);
                     const int oj = __shfl_xor(best_j[v], o);
-                    if (oj != 0x7fffffff && (best_j[v] == 0x7fffffff || ov > best_v[v] || (ov == best_v[v] && oj < best_j[v]))) {
+                    if (wins(ov, oj, best_v[v], best_j[v])) {
                         best_v[v] = ov;
                         best_j[v] = oj;
                     }
                 }
                 const int p = p0 + kq4 + 4 * v;
-                if (i16 == 0 && p < count) a.labels[(size_t)b * n + open[p]] = best_j[v] == 0x7fffffff ? 0 : best_j[v];
+                if (i16 == 0 && p < count) a.labels[(size_t)b * n + open[p]] = best_j[v] == NO_INDEX ? 0 : best_j[v];
             }
         }
         return;
@@ -383,17 +383,17 @@ assign_small_kernel(SmallAssign a) {
             const double r = sqrt(sq);
             val = general_score(sum, r > NORM_FLOOR ? r : NORM_FLOOR, bterm[lane < k_own ? lane : k_own - 1]);
         }
-        int idx = lane < k_own ? lane : 0x7fffffff;
+        int idx = lane < k_own && val > -INFINITY ? lane : NO_INDEX;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
             const double ov = __shfl_xor(val, o);
             const int oi = __shfl_xor(idx, o);
-            if (oi != 0x7fffffff && (idx == 0x7fffffff || ov > val || (ov == val && oi < idx))) {
+            if (wins(ov, oi, val, idx)) {
                 val = ov;
                 idx = oi;
             }
         }
-        if (lane == 0) a.labels[(size_t)b * n + t] = idx;
+        if (lane == 0) a.labels[(size_t)b * n + t] = idx == NO_INDEX ? 0 : idx;
     }
 }
 

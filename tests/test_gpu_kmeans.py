@@ -130,3 +130,31 @@ def test_kmeans_zero_and_tiny_tokens(dtype, d, n, tie):
     ref = so.kmeans(x, None, 1, init_c=c)
     H.compare_labels(labels, ref["labels"], ref["trace"][0]["best"], ref["trace"][0]["second"])
     assert (labels[n - 120:] == (3 if tie else 5)).all()
+
+
+@pytest.mark.parametrize("dtype,d,n", [("bf16", 128, 259), ("f32", 128, 515), ("f32", 64, 300), ("bf16", 64, 266)])
+def test_a_centroid_that_is_nan_wins_no_token(dtype, d, n):
+    """One own-side centroid is NaN (what a NaN token leaves behind): the other tokens go to the best of the other
+    centroids, decided in float64 in workgroups with 256 and with a few open tokens, on all three paths."""
+    rng = np.random.default_rng(n)
+    x = rng.standard_normal((n, d)).astype(np.float32)
+    x = synth.round_to_bf16(x) if dtype == "bf16" else x
+    for k in (24, 90):
+        c = rng.standard_normal((k, d)).astype(np.float32)
+        for lost in (0, 7, k - 1):
+            bad = c.copy()
+            bad[lost, d // 2] = np.nan
+            rest = np.delete(np.arange(k), lost)
+            got = H.to_np(svoo.kmeans(H.to_dev(x[None], dtype), iters=1, init_c=H.to_dev(bad[None]))["labels"])[0]
+            ref = so.kmeans(x, None, 1, init_c=c[rest])
+            assert (got != lost).all()
+            H.compare_labels(got - (got > lost), ref["labels"], ref["trace"][0]["best"], ref["trace"][0]["second"])
+            opp = rng.standard_normal((20, d)).astype(np.float32)
+            ref = H.oracle_assign(x, c[rest], opp)
+            got = H.to_np(svoo.assign(H.to_dev(x[None], dtype), H.to_dev(bad[None]), H.to_dev(opp[None])))[0]
+            assert (got != lost).all()
+            H.compare_labels(got - (got > lost), *ref)
+            q = H.to_dev(rng.standard_normal((1, n, d)).astype(np.float32), dtype)
+            got = H.to_np(svoo.cocluster(q, H.to_dev(x[None], dtype), iters=1, init_cq=H.to_dev(opp[None]),
+                                         init_ck=H.to_dev(bad[None]))["labels_k"])[0]
+            H.compare_labels(got - (got > lost), *ref)
