@@ -270,45 +270,69 @@ sparse_attn_bf16_kernel(AttnArgs a) {
     // 2 adjacent 32-byte column segments; XOR-ing the 64-byte granule index with the row spreads
     // those 8 segments over all banks (K keeps the 16-byte swizzle by row).
     auto vswz = [](int rho) { return ((rho / (256 / ROWB)) % (ROWB / 64)) << 2; };
-    // ---- key-stream walk: this lane tracks tile row RW*wave + lane%RW from tile to tile
-    int seg = 0, seg_end = 0, seg_delta = 0;
+    // ---- key stream.  A tile inside one key block is 64 adjacent rows: its loads take a scalar base address and offsets that
+    // never change.  Where key blocks meet, `next_base` is -1 and `next_rows` the row of each load.  The rows of a tile are
+    // looked up one tile ahead of their use (segment tables in LDS), so that only the loads stand behind the barrier.
+    // Against looking up every lane's row of every tile (a lane exchange and 20 vector instructions a tile), d = 128:
+    // reuse of 12 x 75,600 (295 keys a block) 12.04 -> 11.71 ms, dense 12 x 32,760 5.58 -> 5.47; blocks of 74 keys, where two
+    // of three tiles hold an edge, unchanged.
+    int seg = 0, seg_end = 0, seg_delta = 0;      // uniform: the segment of the last tile's first key
     if (total > 0) {
-        seg_end = seg_cum[1];
-        seg_delta = seg_start[0] - seg_cum[0];
+        seg_end = __builtin_amdgcn_readfirstlane(seg_cum[1]);
+        seg_delta = __builtin_amdgcn_readfirstlane(seg_start[0] - seg_cum[0]);
     }
-    // The key rows of a tile are looked up (segment walk through LDS tables, then a lane exchange)
-    // one tile ahead of their use, while matrix instructions of the current tile are in flight, so
-    // that issuing the loads right after the barrier costs address arithmetic only.
-    int next_rows[LPW];
-    auto prepare_tile = [&](int t) {          // call with t = 0, 1, 2, ... in order
-        int p = t * KT + RW * wave + (lane % RW);
-        p = p < total ? p : total - 1;        // rows past the end re-read the last key (masked later)
-        while (p >= seg_end) {                // terminates: p < total = seg_cum[n_seg]
+    int next_base = -1, next_rows[LPW];
+    auto prepare_tile = [&](int t) {              // call with t = 0, 1, 2, ... in order, t < n_tiles
+        const int p0 = t * KT;
+        while (p0 >= seg_end && seg + 1 < ti.n_seg) {
             ++seg;
-            seg_end = seg_cum[seg + 1];
-            seg_delta = seg_start[seg] - seg_cum[seg];
+            seg_end = __builtin_amdgcn_readfirstlane(seg_cum[seg + 1]);
+            seg_delta = __builtin_amdgcn_readfirstlane(seg_start[seg] - seg_cum[seg]);
         }
-        const int myrow = p + seg_delta;
+        if (p0 + KT <= seg_end) {
+            next_base = p0 + seg_delta;
+        } else {
+            next_base = -1;
+            int p = p0 + RW * wave + (lane % RW);
+            p = p < total ? p : total - 1;        // rows past the end re-read the last key (masked later)
+            int sg = seg, end = seg_end, delta = seg_delta;
+            while (p >= end) {                    // terminates: p < total = seg_cum[n_seg]
+                ++sg;
+                end = seg_cum[sg + 1];
+                delta = seg_start[sg] - seg_cum[sg];
+            }
+            const int myrow = p + delta;
 #pragma unroll
-        for (int i = 0; i < LPW; ++i) next_rows[i] = __shfl(myrow, i * RPL + lane / CPR);
+            for (int i = 0; i < LPW; ++i) next_rows[i] = __shfl(myrow, i * RPL + lane / CPR);
+        }
     };
     // Tile row rho = RW wave + i RPL + lane / CPR is fetched by this lane's i-th wave-load; the three terms
     // occupy disjoint bits, so the swizzled 16-byte chunk of load i is that of load 0 XOR a constant
-    // (K) or the same (V: its swizzle only looks at row bits below RPL).  The loads take the slice's
-    // base address as a scalar and a 32-bit byte offset per lane: one shift-add per load, no 64-bit
-    // address arithmetic in vector registers.
+    // (K) or the same (V: its swizzle only looks at row bits below RPL).  Offsets are 32 bits: n <= 2^24 rows of at most
+    // 256 bytes.
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
+    const uint32_t rho0 = (uint32_t)((RW * wave + lane / CPR) * ROWB);
     const uint32_t kx0 = (uint32_t)(((lane % CPR) ^ ((RW * wave + lane / CPR) % CPR)) * 16);
     const uint32_t vx0 = (uint32_t)(((lane % CPR) ^ vswz(RW * wave + lane / CPR)) * 16);
+    uint32_t kc[LPW], vc[LPW];                    // offsets inside a tile of adjacent rows, without the load's own i KB
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) {
+        kc[i] = rho0 + (kx0 ^ (uint32_t)(((i * RPL) % CPR) * 16));
+        vc[i] = rho0 + vx0;
+    }
     auto issue_prepared = [&](int buf) {
+        const uint32_t loff = lds0 + buf * TILE + RW * wave * ROWB;
+        const int base = __builtin_amdgcn_readfirstlane(next_base);
+        if (base >= 0) {
+            load_adjacent_to_lds_16(kc, kg + (size_t)(uint32_t)base * ROWB, loff);
+            load_adjacent_to_lds_16(vc, vg + (size_t)(uint32_t)base * ROWB, loff + NBUF * TILE);
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < LPW; ++i) {
-            const uint32_t row_off = (uint32_t)next_rows[i] * ROWB;      // < 2^32: n <= 2^24 rows of at most 256 bytes
-            const uint32_t koffs = row_off + (kx0 ^ (uint32_t)(((i * RPL) % CPR) * 16));
-            const uint32_t voffs = row_off + vx0;
-            const uint32_t loff = lds0 + buf * TILE + (RW * wave + i * RPL) * ROWB;
-            load_rows_to_lds_16(koffs, kg, loff);
-            load_rows_to_lds_16(voffs, vg, loff + NBUF * TILE);
+            const uint32_t row_off = (uint32_t)next_rows[i] * ROWB;
+            load_rows_to_lds_16(row_off + (kc[i] - rho0), kg, loff + i * 1024);
+            load_rows_to_lds_16(row_off + vx0, vg, loff + i * 1024 + NBUF * TILE);
         }
     };
 
@@ -464,12 +488,14 @@ sparse_attn_bf16_kernel(AttnArgs a) {
         }
         // ragged last tile: keys past the end of the stream get -inf
         if (kt == n_tiles - 1 && (total % KT) != 0) {
-            const int base = kt * KT + 4 * h;
+            int left = total - (kt * KT + 4 * h + kb_off);
 #pragma unroll
             for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    if (base + kb_off + 32 * kb + 8 * (v / 4) + (v % 4) >= total) s[kb][v] = -INFINITY;
+                for (int v = 0; v < 16; ++v) {
+                    s[kb][v] = 32 * kb + 8 * (v / 4) + (v % 4) >= left ? -INFINITY : s[kb][v];
+                    asm volatile("" : "+v"(left));     // one comparison at a time: all at once would fill the scalar registers
+                }
         }
         float mx = s[0][0];
 #pragma unroll
@@ -493,19 +519,26 @@ sparse_attn_bf16_kernel(AttnArgs a) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
         }
+        // The row sum takes the two ROUNDED probabilities, the same values the second contraction multiplies: one
+        // dot-product instruction with (1, 1) instead of two adds.  A dot product shares the matrix pipe: alone on a SIMD, one
+        // between two matrix instructions costs 17 cycles, each further one of a run 4.  Where the waves of a SIMD run in
+        // step (the dense shape, one barrier for both), the sums of a tile are one run behind the second product: 12 x 32,760 x
+        // 128 5.71 -> 5.58 ms.  Two independent workgroups fill each other's gaps: there a run is 0.5 % slower.
+        constexpr bool DOTS_LAST = NW == 8 && D == 128;
         const bf16x2 ones2 = __builtin_bit_cast(bf16x2, 0x3f803f80u);
+        uint32_t pw[NKB][2][4];
+        auto add_to_sum = [&](uint32_t w) {
+            lsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones2, lsum, false);
+        };
         auto probs = [&](int kb, int t) {
-            uint32_t w[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const float p0 = __builtin_amdgcn_exp2f(fmaf(s[kb][8 * t + 2 * e], c2, neg_mb));
                 const float p1 = __builtin_amdgcn_exp2f(fmaf(s[kb][8 * t + 2 * e + 1], c2, neg_mb));
-                w[e] = pack2_bf16(p0, p1);
-                // the row sum takes the two ROUNDED probabilities, the same values the second
-                // contraction multiplies: one dot-product instruction with (1, 1) instead of two adds
-                lsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w[e]), ones2, lsum, false);
+                pw[kb][t][e] = pack2_bf16(p0, p1);
+                if (!DOTS_LAST) add_to_sum(pw[kb][t][e]);
             }
-            return __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3]));
+            return __builtin_bit_cast(bf16x8, make_uint4(pw[kb][t][0], pw[kb][t][1], pw[kb][t][2], pw[kb][t][3]));
         };
         // ---- O^T += V^T P^T, block by block
         bf16x8 pf[2];
@@ -527,7 +560,7 @@ sparse_attn_bf16_kernel(AttnArgs a) {
 #pragma unroll
             for (int db = 0; db < DB; ++db)
                 o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[t][db], pf[t], o[db], 0, 0, 0);
-        constexpr int PVALU = 48;   // VALU/transcendental instructions of one 32-key block's probabilities
+        constexpr int PVALU = DOTS_LAST ? 40 : 48;   // VALU/transcendental instructions of one 32-key block's probabilities
         // pipeline: exponentials of the first block, then (two-block tiles) each MFMA of block 0
         // paired with two V reads of block 1 and a slice of block 1's exponentials, then the rest
         __builtin_amdgcn_sched_group_barrier(0x402, PVALU, 0);
@@ -540,6 +573,15 @@ sparse_attn_bf16_kernel(AttnArgs a) {
             }
         }
         __builtin_amdgcn_sched_group_barrier(0x008, 2 * DB, 0);
+        if (DOTS_LAST) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) add_to_sum(pw[kb][t][e]);
+        }
     };
 
     // Have the Q fragments arrive here: otherwise the compiler's wait for them sits inside the tile

@@ -51,6 +51,29 @@ __device__ __forceinline__ void load_rows_to_lds_16(uint32_t byte_offset, const 
                  : "v"(byte_offset), "s"(uniform_base), "s"(__builtin_amdgcn_readfirstlane(lds_addr))
                  : "memory", "m0");
 }
+
+// N of them whose rows lie behind one another, 1 KB apart in memory and in LDS (an immediate offset counts for both).
+template <int N>
+__device__ __forceinline__ void load_adjacent_to_lds_16(const uint32_t (&byte_offset)[N], const void* uniform_base, uint32_t lds_addr) {
+    static_assert(N == 1 || N == 2 || N == 4, "one statement each");
+    lds_addr = __builtin_amdgcn_readfirstlane(lds_addr);
+    if constexpr (N == 1)
+        load_rows_to_lds_16(byte_offset[0], uniform_base, lds_addr);
+    else if constexpr (N == 2)
+        asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2\n\t"
+                     "global_load_lds_dwordx4 %1, %2 offset:1024"
+                     :
+                     : "v"(byte_offset[0]), "v"(byte_offset[1]), "s"(uniform_base), "s"(lds_addr)
+                     : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %4\n\t"
+                     "global_load_lds_dwordx4 %1, %4 offset:1024\n\tglobal_load_lds_dwordx4 %2, %4 offset:2048\n\t"
+                     "global_load_lds_dwordx4 %3, %4 offset:3072"
+                     :
+                     : "v"(byte_offset[0]), "v"(byte_offset[1]), "v"(byte_offset[2]), "v"(byte_offset[3]),
+                       "s"(uniform_base), "s"(lds_addr)
+                     : "memory", "m0");
+}
 #pragma clang diagnostic pop
 
 __device__ __forceinline__ uint32_t lds_address(const void* p) {

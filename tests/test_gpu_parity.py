@@ -676,6 +676,34 @@ def test_sparse_attn_short_query_blocks_and_short_key_streams(d):
     np.testing.assert_allclose(lse, lse_ref, atol=2e-2)
 
 
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("order", range(3))
+def test_sparse_attn_key_blocks_at_the_edges_of_the_tiles(d, order):
+    """Kept key blocks that begin and end on, one before and one behind the edge of a 64-key tile (tiles of adjacent rows),
+    tiles in which two or many blocks meet, and one block of a single tile; the query blocks fill one, two and four waves."""
+    rng = np.random.default_rng(90 + d + order)
+    k_sizes = [64, 1, 63, 65, 128, 127, 129, 2, 192, 30, 34, 100]
+    if order:
+        k_sizes = list(rng.permutation(k_sizes))
+    q_sizes = [128, 40, 100, 20]
+    n = sum(k_sizes)
+    q_sizes.append(n - sum(q_sizes))
+    kq, kk = len(q_sizes), len(k_sizes)
+    lq, lk = (np.repeat(np.arange(len(z)), z).astype(np.int32) for z in (q_sizes, k_sizes))
+    mask = rng.random((kq, kk)) < np.array([1.0, 0.5, 0.7, 0.5, 0.2])[:, None]
+    mask[np.arange(kq), rng.integers(0, kk, kq)] = True
+    q, k, v = (rng.standard_normal((n, d)).astype(np.float32) for _ in range(3))
+    qd, kd, vd = (H.to_dev(x[None], "bf16") for x in (1.5 * q, 1.5 * k, v))
+    q, k, v = (H.to_np(x)[0].astype(np.float64) for x in (qd, kd, vd))
+    cnt = mask.sum(1).astype(np.int32)
+    lst = np.full((kq, kk), -1, dtype=np.int32)
+    for r in range(kq):
+        lst[r, :cnt[r]] = np.nonzero(mask[r])[0]
+    off = lambda z: H.to_dev(np.concatenate([[0], np.cumsum(z)]).astype(np.int32)[None])
+    out = svoo.block_sparse_attn(qd, kd, vd, off(q_sizes), off(k_sizes), H.to_dev(cnt[None]), H.to_dev(lst[None]), H.scale_of(d))
+    H.assert_attn_close(H.to_np(out)[0], so.sparse_attention(q, k, v, lq, lk, mask, H.scale_of(d)), "bf16", "tile edges")
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_sparse_attn_with_index_arrays_that_break_the_contract(dtype):
     """Offsets, block counts and block lists full of arbitrary integers (negative, far beyond n, not
