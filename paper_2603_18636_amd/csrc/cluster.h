@@ -11,10 +11,12 @@ typedef __attribute__((ext_vector_type(4))) double f64x4;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
-// Error of a fast score relative to ||x|| ||W_j||, d <= 128: two bf16 terms 2^-17 + 256 * 2^-24 = 2.3e-5, W rounded to
-// float32 129 * 2^-24 = 7.7e-6.  What is left covers the float32 rounding of the norms themselves (2^-17 of a
-// sum of 128 squares).
-#define FAST_EPS 3.1e-5f
+// Error of a fast score relative to ||x|| ||W_j||, d <= 128.  bf16 tokens: what two bf16 terms of W leave, 2^-17, and 256
+// additions of 2^-24: 2.3e-5.  float32 tokens: 2^-18 left of W, 2^-18 left of x, 2^-18 for the product of the two lower terms,
+// 384 additions: 3.5e-5.  The rest covers the float32 rounding of the norms themselves (2^-17 of a sum of 128 squares).
+template <typename T> constexpr float fast_eps();
+template <> constexpr float fast_eps<uint16_t>() { return 3.1e-5f; }
+template <> constexpr float fast_eps<float>() { return 4.6e-5f; }
 
 // Upper bound of ||x|| max_j ||W_j|| from the float32 squared norm of a token and the largest row norm: what underflow may
 // have taken from the square or from a score is less than FAST_MIN stands for.  With it a margin never says too little:
@@ -34,23 +36,55 @@ __device__ __forceinline__ bool wins(double ov, int oj, double v, int j) {
     return oj != NO_INDEX && (j == NO_INDEX || ov > v || (ov == v && oj < j));
 }
 
-// Score matrix in the form the pre-filter reads: two bf16 arrays, or one float32 array over the same bytes.
-template <typename T>
-__device__ __forceinline__ void store_split(double v, size_t o, uint16_t* w_hi, uint16_t* w_lo);
-template <>
-__device__ __forceinline__ void store_split<uint16_t>(double v, size_t o, uint16_t* w_hi, uint16_t* w_lo) {
+// Score matrix in the form the pre-filter reads: two bf16 arrays
+__device__ __forceinline__ void store_split(double v, size_t o, uint16_t* w_hi, uint16_t* w_lo) {
     const uint16_t hb = f32_to_bf16((float)v);
     w_hi[o] = hb;
     w_lo[o] = f32_to_bf16((float)(v - (double)bf16_to_f32(hb)));
 }
-template <>
-__device__ __forceinline__ void store_split<float>(double v, size_t o, uint16_t* w_hi, uint16_t*) {
-    ((float*)w_hi)[o] = (float)v;
+
+// Eight token elements as B operands of the pre-filter: bf16 tokens as they are, float32 tokens as two bf16 terms, each
+// rounded to nearest.  A lower term of an infinity is no number, which leaves the token open.
+template <int TERMS>
+struct TokenChunk { bf16x8_t term[TERMS]; };
+__device__ __forceinline__ void load_chunk(const uint16_t* p, TokenChunk<1>& out) {
+    out.term[0] = __builtin_bit_cast(bf16x8_t, *(const uint4*)p);
+}
+__device__ __forceinline__ void load_chunk(const float* p, TokenChunk<2>& out) {
+    const float4 a = *(const float4*)p, b = *(const float4*)(p + 4);
+    const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const __bf16 hi = (__bf16)v[e];
+        out.term[0][e] = hi;
+        out.term[1][e] = (__bf16)(v[e] - (float)hi);
+    }
 }
 
+// squares of a chunk added to acc (float32 tokens: of the sum of the two terms, within 2^-17)
+__device__ __forceinline__ float add_squares(const TokenChunk<1>& x, float acc) {
+    const uint4 u = __builtin_bit_cast(uint4, x.term[0]);
+    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const bf16x2_t pr = __builtin_bit_cast(bf16x2_t, w[e]);
+        acc = __builtin_amdgcn_fdot2_f32_bf16(pr, pr, acc, false);
+    }
+    return acc;
+}
+__device__ __forceinline__ float add_squares(const TokenChunk<2>& x, float acc) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const float v = (float)x.term[0][e] + (float)x.term[1][e];
+        acc = fmaf(v, v, acc);
+    }
+    return acc;
+}
+
+// 1e-33: rows of W whose lower bf16 terms are subnormal (and lose bits of their own) have norms far below it
 __device__ __forceinline__ float norm_rounded_up(double sq) {
     float nrm = (float)sqrt(sq);
-    nrm = nrm * 1.0000002f + 1e-37f;
+    nrm = nrm * 1.0000002f + 1e-33f;
     return nrm < 3.0e38f ? nrm : 3.0e38f;      // NaN as well
 }
 

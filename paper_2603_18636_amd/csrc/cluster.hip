@@ -180,8 +180,9 @@ static void launch_quadform(const void* x, const double* gram, double* quad_out,
 // bf16 tokens: W is split into two bf16 terms, W = W_hi + W_lo + r with |r| <= 2^-17 |W| element-wise;
 // tokens are exact in bf16, so  f_j = <x, W_hi_j> + <x, W_lo_j>  (fp32 accumulation on the matrix cores)
 // satisfies |f_j - <x, W_j>| <= eps ||x|| ||W_j|| with eps covering the split remainder and the
-// fp32 accumulation of 2 d products.  float32 tokens: W rounded to float32, f_j on the float32 matrix
-// instruction; rounding (2^-24) and the accumulation of d products stay within the same eps.  If
+// fp32 accumulation of 2 d products.  float32 tokens are split the same way, x = x_hi + x_lo, and
+// f_j = <x_hi, W_hi_j> + <x_hi, W_lo_j> + <x_lo, W_hi_j>: 3 x 32 cycles per 16 elements where the float32 matrix instruction
+// takes 512, for a margin half as wide again (12 x 8,190 x 128, 64 centroids: 32.5 -> 24 us).  If
 // best - second > 2 eps ||x|| max_j ||W_j|| the fast argmax is the exact argmax; otherwise (and for every
 // token of a slice with a degenerate anchor) the workgroup decides the token in float64.  Equal
 // scores have gap 0 and are therefore always decided in float64, lowest index first.
@@ -207,7 +208,7 @@ kmeans_w_kernel(const double* __restrict__ c64, uint16_t* __restrict__ w_hi, uin
         for (int t = lane; t < D; t += 64) {
             const size_t o = ((size_t)b * k + j) * D + t;
             const double v = c64[o];
-            store_split<T>(v, o, w_hi, w_lo);
+            store_split(v, o, w_hi, w_lo);
             wt[((size_t)b * D + t) * k + j] = v;
             sq = fma(v, v, sq);
         }
@@ -358,7 +359,7 @@ anchor_w_kernel(const double* __restrict__ c_own, const double* __restrict__ c_o
             const size_t o = ((size_t)b * k_own + j) * D + t;
             const double v = wtile[(RPW * wave + r) * (D + 2) + t];
             if (w64) w64[o] = v;
-            store_split<T>(v, o, w_hi, w_lo);
+            store_split(v, o, w_hi, w_lo);
             wt[((size_t)b * D + t) * k_own + j] = v;
             sq = fma(v, v, sq);
         }
@@ -394,8 +395,8 @@ static void launch_anchor_w(const double* c_own, const double* c_opp, int k_own,
 
 struct AssignArgs {
     const void* x;
-    const uint16_t* w_hi;          // bf16: high term; float32: W
-    const uint16_t* w_lo;          // bf16: low term
+    const uint16_t* w_hi;          // upper and lower bf16 terms of W
+    const uint16_t* w_lo;
     const double* wt;              // W^T [d, k_own]
     const double* bterm;           // anchor terms b_j (k-means: ||c_j||^2)
     const double* c_opp;           // [k_opp, d]: token norms of slices with a degenerate anchor
@@ -435,14 +436,15 @@ struct AssignArgs {
 template <typename T, int D, bool BIAS>
 __global__ void __launch_bounds__(256, 2)
 assign_kernel(AssignArgs a) {
-    constexpr bool BF16 = std::is_same<T, uint16_t>::value;
-    constexpr int ROWB = D * (int)sizeof(T), CPR = ROWB / 16, DC = ROWB / 32;
-    constexpr int BLOCK = 32 * ROWB;         // 32 centroids of one term
-    constexpr int TERMS = BF16 ? 2 : 1;
-    constexpr int RPL = 64 / CPR;            // rows per wave-load
+    constexpr int ROWB = D * (int)sizeof(T), CPR = ROWB / 16;        // token rows
+    constexpr int WROWB = 2 * D, WCPR = WROWB / 16, DC = D / 16;     // rows of one term of W
+    constexpr int BLOCK = 32 * WROWB;        // 32 centroids of one term
+    constexpr int TERMS = 2, XT = sizeof(T) == 2 ? 1 : 2;            // terms of W, of a token
+    constexpr int PROD = TERMS + XT - 1;     // products: W_hi x_hi, W_lo x_hi, W_hi x_lo
+    constexpr int RPL = 64 / WCPR;           // rows per wave-load
     constexpr int LPW = (32 / RPL) / 4;      // wave-loads per wave for one block of one term
     static_assert(LPW >= 1 && ASSIGN_CHUNK == 256, "geometry");
-    __shared__ __attribute__((aligned(1024))) unsigned char wl[2 * TERMS * BLOCK];   // [buf][term][32][ROWB]
+    __shared__ __attribute__((aligned(1024))) unsigned char wl[2 * TERMS * BLOCK];   // [buf][term][32][WROWB]
     __shared__ int32_t lab[256], open[256], n_open;
     __shared__ double red_v[4][16 * DECIDE_TILES], norm[16 * DECIDE_TILES];
     __shared__ int32_t red_j[4][16 * DECIDE_TILES];
@@ -451,8 +453,8 @@ assign_kernel(AssignArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64);     // uniform: what derives from it stays scalar
     const int g0 = blockIdx.x * 256, t0 = g0 + 64 * wave;
     const T* x = (const T*)a.x + (size_t)b * n * D;
-    const unsigned char* whb = (const unsigned char*)a.w_hi + (size_t)b * k_own * ROWB;
-    const unsigned char* wlb = (const unsigned char*)a.w_lo + (size_t)b * k_own * ROWB;
+    const unsigned char* whb = (const unsigned char*)a.w_hi + (size_t)b * k_own * WROWB;
+    const unsigned char* wlb = (const unsigned char*)a.w_lo + (size_t)b * k_own * WROWB;
     const int n_blocks = (k_own + 31) / 32;
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(wl));
     if (tid == 0) n_open = 0;
@@ -460,14 +462,14 @@ assign_kernel(AssignArgs a) {
     auto issue_block = [&](int cb, int buf) {
 #pragma unroll
         for (int i = 0; i < LPW; ++i) {
-            const int rl = (wave * LPW + i) * RPL + lane / CPR;     // row of the block, 0..31
+            const int rl = (wave * LPW + i) * RPL + lane / WCPR;    // row of the block, 0..31
             int row = 32 * cb + rl;
             row = row < k_own ? row : k_own - 1;
-            const int chunk = (lane % CPR) ^ (rl % CPR);
-            const uint32_t goff = (uint32_t)row * ROWB + chunk * 16;
-            const uint32_t loff = lds0 + buf * TERMS * BLOCK + (wave * LPW + i) * RPL * ROWB;
+            const int chunk = (lane % WCPR) ^ (rl % WCPR);
+            const uint32_t goff = (uint32_t)row * WROWB + chunk * 16;
+            const uint32_t loff = lds0 + buf * TERMS * BLOCK + (wave * LPW + i) * RPL * WROWB;
             load_rows_to_lds_16(goff, whb, loff);
-            if (BF16) load_rows_to_lds_16(goff, wlb, loff + BLOCK);
+            load_rows_to_lds_16(goff, wlb, loff + BLOCK);
         }
     };
     issue_block(0, 0);
@@ -475,27 +477,17 @@ assign_kernel(AssignArgs a) {
     // token fragments and squared norms (the norm only scales the margin below, whose constant has a factor
     // of two in hand: the packed dot product's own rounding does not matter).  Rows past the end are read
     // from the last token instead of being predicated; their results are never stored.
-    uint4 xf[2][DC];
+    TokenChunk<XT> xf[2][DC];
     float xn2[2];
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb) {
         const int tok = t0 + 32 * tb + j;
-        const uint4* src = (const uint4*)(x + (size_t)(tok < n ? tok : n - 1) * D);
+        const T* src = x + (size_t)(tok < n ? tok : n - 1) * D;
         float acc = 0.f;
 #pragma unroll
         for (int c = 0; c < DC; ++c) {
-            const uint4 u = src[2 * c + h];
-            xf[tb][c] = u;
-            const uint32_t wds[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if constexpr (BF16) {
-                    const bf16x2_t pr = __builtin_bit_cast(bf16x2_t, wds[e]);
-                    acc = __builtin_amdgcn_fdot2_f32_bf16(pr, pr, acc, false);
-                } else {
-                    acc = fmaf(__uint_as_float(wds[e]), __uint_as_float(wds[e]), acc);
-                }
-            }
+            load_chunk(src + 16 * c + 8 * h, xf[tb][c]);
+            acc = add_squares(xf[tb][c], acc);
         }
         const int ai = __float_as_int(acc);
         auto r = __builtin_amdgcn_permlane32_swap(ai, ai, false, false);
@@ -503,12 +495,14 @@ assign_kernel(AssignArgs a) {
     }
     int koff[DC];
 #pragma unroll
-    for (int c = 0; c < DC; ++c) koff[c] = j * ROWB + (((2 * c + h) ^ (j % CPR)) * 16);
+    for (int c = 0; c < DC; ++c) koff[c] = j * WROWB + (((2 * c + h) ^ (j % WCPR)) * 16);
     // the compiler's wait for the token loads must not end up inside the block loop
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
-        for (int c = 0; c < DC; ++c) asm volatile("" ::"v"(xf[tb][c].x), "v"(xf[tb][c].y), "v"(xf[tb][c].z), "v"(xf[tb][c].w));
+        for (int c = 0; c < DC; ++c)
+#pragma unroll
+            for (int t = 0; t < XT; ++t) asm volatile("" ::"v"(xf[tb][c].term[t]));
 
     float best[2] = {-INFINITY, -INFINITY}, second[2] = {-INFINITY, -INFINITY};
     int bidx[2] = {0, 0}, lidx[2] = {0, 0};
@@ -525,25 +519,13 @@ assign_kernel(AssignArgs a) {
             for (int v = 0; v < 16; ++v) acc[tb][v] = 0.f;
 #pragma unroll
         for (int c = 0; c < DC; ++c) {
-            const uint4 wh = *(const uint4*)(base + koff[c]);
-            if constexpr (BF16) {
-                const bf16x8_t ah = __builtin_bit_cast(bf16x8_t, wh);
-                const bf16x8_t al = __builtin_bit_cast(bf16x8_t, *(const uint4*)(base + BLOCK + koff[c]));
+            const bf16x8_t wh = __builtin_bit_cast(bf16x8_t, *(const uint4*)(base + koff[c]));
+            const bf16x8_t wlow = __builtin_bit_cast(bf16x8_t, *(const uint4*)(base + BLOCK + koff[c]));
 #pragma unroll
-                for (int tb = 0; tb < 2; ++tb) {
-                    const bf16x8_t xv = __builtin_bit_cast(bf16x8_t, xf[tb][c]);
-                    acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, xv, acc[tb], 0, 0, 0);
-                    acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, xv, acc[tb], 0, 0, 0);
-                }
-            } else {
-                const float wv[4] = {__uint_as_float(wh.x), __uint_as_float(wh.y), __uint_as_float(wh.z), __uint_as_float(wh.w)};
-#pragma unroll
-                for (int tb = 0; tb < 2; ++tb) {
-                    const uint4 u = xf[tb][c];
-                    const float xv[4] = {__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w)};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[tb] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[e], xv[e], acc[tb], 0, 0, 0);
-                }
+            for (int tb = 0; tb < 2; ++tb) {
+                acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wh, xf[tb][c].term[0], acc[tb], 0, 0, 0);
+                acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wlow, xf[tb][c].term[0], acc[tb], 0, 0, 0);
+                if constexpr (XT == 2) acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wh, xf[tb][c].term[1], acc[tb], 0, 0, 0);
             }
         }
         const int cbase = 32 * cb;      // uniform; the lane's own offset 4 h is added to the winner once, after the loop
@@ -606,8 +588,8 @@ assign_kernel(AssignArgs a) {
         const int tok = t0 + 32 * tb + j;
         if (h == 0) {
             const float xw = score_bound(xn2[tb], wmax);
-            const float margin = BIAS ? 2.0f * (FAST_EPS * xw + 2.4e-7f * (0.5f * wmax * wmax + xw))   // 2^-22
-                                      : 2.0f * FAST_EPS * xw;
+            const float margin = BIAS ? 2.0f * (fast_eps<T>() * xw + 2.4e-7f * (0.5f * wmax * wmax + xw))   // 2^-22
+                                      : 2.0f * fast_eps<T>() * xw;
             const bool sure = (fb - fs) > margin;          // false for NaN as well
             lab[tok - g0] = fi;
             if ((degenerate || !sure) && tok < n) open[atomicAdd(&n_open, 1)] = tok - g0;
@@ -1003,7 +985,7 @@ static ClusterWs carve_cluster_ws(const svoo_shape* s, void* ws) {
     w.bterm = c.take<double>(bh * kmax);
     w.nx2 = c.take<double>(bh * (size_t)s->n);
     w.terms = c.take<double>(bh * (size_t)s->n);
-    w.w_hi = c.take<uint16_t>(2 * bh * kmax * s->d);      // two bf16 terms, or one float32 array
+    w.w_hi = c.take<uint16_t>(2 * bh * kmax * s->d);      // two bf16 terms
     w.w_lo = w.w_hi + bh * kmax * s->d;
     w.half_sq = c.take<float>(bh * ((kmax + 31) / 32 * 32));
     w.flags = c.take<int32_t>(2 * bh);      // flags | wmax_bits, cleared together

@@ -55,8 +55,8 @@ __device__ __forceinline__ void load_every_4th(const float* row, int kq, double 
 template <typename T, int D>
 struct SmallLds {
     static constexpr int CP = D + 2, WP = D + 1;       // row pitches in doubles: C_opp (pairs), W (columns)
-    static constexpr int ROWB = D * (int)sizeof(T);    // one term of one row of the split
-    static constexpr int TERMS = sizeof(T) == 2 ? 2 : 1;
+    static constexpr int ROWB = 2 * D;                 // one term of one row of the split
+    static constexpr int TERMS = 2;
     static constexpr int BLOCK = 32 * ROWB;
     int pitch, split, c_opp, ph, bterm, bytes;         // W in float64 takes C_opp's place once it is used up
     __host__ __device__ constexpr SmallLds(int k_own, int k_opp)
@@ -76,8 +76,8 @@ template <typename T, int D>
 __global__ void __launch_bounds__(64 * SMALL_WAVES)
 assign_small_kernel(SmallAssign a) {
     using L = SmallLds<T, D>;
-    constexpr bool BF16 = std::is_same<T, uint16_t>::value;
     constexpr int CP = L::CP, WP = L::WP, ROWB = L::ROWB, CPR = ROWB / 16, DC = ROWB / 32, BLOCK = L::BLOCK;
+    constexpr int XT = sizeof(T) == 2 ? 1 : 2;         // terms of a token
     constexpr int NW = SMALL_WAVES, NT = 64 * NW;
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     __shared__ int32_t wmax_bits, degenerate_s, n_open;
@@ -99,11 +99,11 @@ assign_small_kernel(SmallAssign a) {
 
     // ---- this wave's tokens, for later; C_opp into LDS
     const int tok = blockIdx.x * (32 * NW) + 32 * wave + j;
-    uint4 xf[DC];
+    TokenChunk<XT> xf[DC];
     {
-        const uint4* src = (const uint4*)(x + (size_t)(tok < n ? tok : n - 1) * D);
+        const T* src = x + (size_t)(tok < n ? tok : n - 1) * D;
 #pragma unroll
-        for (int c = 0; c < DC; ++c) xf[c] = src[2 * c + h];
+        for (int c = 0; c < DC; ++c) load_chunk(src + 16 * c + 8 * h, xf[c]);
     }
     for (int e = tid; e < k_opp * D / 2; e += NT) {
         const int r = e / (D / 2), t = e % (D / 2);
@@ -195,9 +195,9 @@ assign_small_kernel(SmallAssign a) {
 #pragma unroll
         for (int t = lane; t < D; t += 64) {
             const double v = w64[r * WP + t];
-            const int byte = t * (int)sizeof(T);
+            const int byte = t * 2;
             const int at = rl * ROWB + (((byte / 16) ^ (rl % CPR)) * 16) + byte % 16;
-            store_split<T>(v, 0, (uint16_t*)(blk + at), (uint16_t*)(blk + BLOCK + at));
+            store_split(v, 0, (uint16_t*)(blk + at), (uint16_t*)(blk + BLOCK + at));
             sq = fma(v, v, sq);
         }
 #pragma unroll
@@ -212,18 +212,7 @@ assign_small_kernel(SmallAssign a) {
     {
         float xn2 = 0.f;
 #pragma unroll
-        for (int c = 0; c < DC; ++c) {
-            const uint32_t wds[4] = {xf[c].x, xf[c].y, xf[c].z, xf[c].w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if constexpr (BF16) {
-                    const bf16x2_t pr = __builtin_bit_cast(bf16x2_t, wds[e]);
-                    xn2 = __builtin_amdgcn_fdot2_f32_bf16(pr, pr, xn2, false);
-                } else {
-                    xn2 = fmaf(__uint_as_float(wds[e]), __uint_as_float(wds[e]), xn2);
-                }
-            }
-        }
+        for (int c = 0; c < DC; ++c) xn2 = add_squares(xf[c], xn2);
         auto swap = [](float v) {
             return __builtin_amdgcn_permlane32_swap(__float_as_int(v), __float_as_int(v), false, false);
         };
@@ -241,18 +230,11 @@ assign_small_kernel(SmallAssign a) {
 #pragma unroll
             for (int c = 0; c < DC; ++c) {
                 const int at = ((2 * c + h) ^ (j % CPR)) * 16;
-                const uint4 wh = *(const uint4*)(base + at);
-                if constexpr (BF16) {
-                    const bf16x8_t xv = __builtin_bit_cast(bf16x8_t, xf[c]);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, wh), xv, acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        __builtin_bit_cast(bf16x8_t, *(const uint4*)(base + BLOCK + at)), xv, acc, 0, 0, 0);
-                } else {
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(wh.x), __uint_as_float(xf[c].x), acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(wh.y), __uint_as_float(xf[c].y), acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(wh.z), __uint_as_float(xf[c].z), acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(wh.w), __uint_as_float(xf[c].w), acc, 0, 0, 0);
-                }
+                const bf16x8_t wh = __builtin_bit_cast(bf16x8_t, *(const uint4*)(base + at));
+                const bf16x8_t wl = __builtin_bit_cast(bf16x8_t, *(const uint4*)(base + BLOCK + at));
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wh, xf[c].term[0], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wl, xf[c].term[0], acc, 0, 0, 0);
+                if constexpr (XT == 2) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wh, xf[c].term[1], acc, 0, 0, 0);
             }
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
@@ -269,7 +251,7 @@ assign_small_kernel(SmallAssign a) {
         const float fb = fmaxf(b0, b1), fs = fmaxf(fminf(b0, b1), fmaxf(__int_as_float(rs[0]), __int_as_float(rs[1])));
         if (h == 0 && tok < n) {
             const int fi = b0 >= b1 ? (int)ri[0] : (int)ri[1];
-            const bool sure = (fb - fs) > 2.0f * FAST_EPS * score_bound(xn2, wmax);      // false for NaN as well
+            const bool sure = (fb - fs) > 2.0f * fast_eps<T>() * score_bound(xn2, wmax);      // false for NaN as well
             if (degenerate || !sure)
                 open[atomicAdd(&n_open, 1)] = tok;
             else

@@ -158,3 +158,21 @@ def test_a_centroid_that_is_nan_wins_no_token(dtype, d, n):
             got = H.to_np(svoo.cocluster(q, H.to_dev(x[None], dtype), iters=1, init_cq=H.to_dev(opp[None]),
                                          init_ck=H.to_dev(bad[None]))["labels_k"])[0]
             H.compare_labels(got - (got > lost), *ref)
+
+
+@pytest.mark.parametrize("d,n,k", [(64, 700, 40), (128, 700, 33), (128, 9000, 130)])
+@pytest.mark.parametrize("scale", [1.0, 1e-17, 1e17])
+def test_float32_labels_with_centroids_closer_than_two_bf16_terms_tell(d, n, k, scale):
+    """Float32 tokens and centroids in pairs 2^-14 .. 2^-22 apart: the pre-filter on two bf16 terms of each must leave
+    open what it cannot tell, down to products that are subnormal and up to squares near the end of float32."""
+    rng = np.random.default_rng(d + n)
+    x = (scale * rng.standard_normal((1, n, d))).astype(np.float32)
+    c = x[:, rng.choice(n, k, replace=False)].copy()
+    for j in range(1, k, 2):
+        c[0, j] = c[0, j - 1] * np.float32(1 + 2.0 ** -(14 + j % 9))
+    got = H.to_np(svoo.kmeans(H.to_dev(x, "f32"), iters=1, init_c=torch.from_numpy(c).to(H.DEV))["labels"])[0]
+    xx, cc = x[0].astype(np.float64) / scale, c[0].astype(np.float64) / scale
+    score = 2.0 * xx @ cc.T - (cc * cc).sum(1)
+    best = score.argmax(1)
+    gap = score[np.arange(n), best] - score[np.arange(n), got]
+    assert (gap <= 1e-13 * np.abs(score).max()).all(), (int((gap > 0).sum()), float(gap.max()))
