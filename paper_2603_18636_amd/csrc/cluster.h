@@ -13,7 +13,8 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 // Error of a fast score relative to ||x|| ||W_j||, d <= 128.  bf16 tokens: what two bf16 terms of W leave, 2^-17, and 256
 // additions of 2^-24: 2.3e-5.  float32 tokens: 2^-18 left of W, 2^-18 left of x, 2^-18 for the product of the two lower terms,
-// 384 additions: 3.5e-5.  The rest covers the float32 rounding of the norms themselves (2^-17 of a sum of 128 squares).
+// 384 additions: 3.5e-5.  Where a score's last four bits hold a place, 15 2^-23 = 1.8e-6 more.  The rest covers the
+// float32 rounding of the norms themselves (2^-17 of a sum of 128 squares).
 template <typename T> constexpr float fast_eps();
 template <> constexpr float fast_eps<uint16_t>() { return 3.1e-5f; }
 template <> constexpr float fast_eps<float>() { return 4.6e-5f; }

@@ -176,3 +176,23 @@ def test_float32_labels_with_centroids_closer_than_two_bf16_terms_tell(d, n, k, 
     best = score.argmax(1)
     gap = score[np.arange(n), best] - score[np.arange(n), got]
     assert (gap <= 1e-13 * np.abs(score).max()).all(), (int((gap > 0).sum()), float(gap.max()))
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
+@pytest.mark.parametrize("k", [1, 2, 17, 31, 32, 33, 63, 65, 97, 1000])
+@pytest.mark.parametrize("twins", [False, True])
+def test_every_place_of_a_block_of_centroids_can_win(dtype, d, k, twins):
+    """One token per centroid, on it: its label is that centroid, at every place of the 32-centroid blocks and in
+    short last blocks.  Twins: centroids 2i and 2i + 1 coincide (a tie inside one pair of scores), the lower wins."""
+    rng = np.random.default_rng(k)
+    x = rng.standard_normal((k, d)).astype(np.float32)
+    want = np.arange(k)
+    if twins:
+        x[1::2] = x[:k - 1:2] if k % 2 else x[::2]
+        want[1::2] -= 1
+    order = rng.permutation(k)                     # token order[j] is centroid j
+    tokens = np.empty_like(x)
+    tokens[order] = x
+    xd = H.to_dev(tokens[None], dtype)
+    out = svoo.kmeans(xd, H.to_dev(order[None].astype(np.int32)), 1)
+    assert (H.to_np(out["labels"])[0][order] == want).all()
