@@ -446,7 +446,7 @@ __device__ __forceinline__ float max3_raw(float a, float b, float c) {
 #define DECIDE_FEW 4     // open tokens that a thread per centroid decides
 #define DECIDE_TILES 2   // 16-token tiles of open tokens decided at a time
 template <typename T, int D, bool BIAS>
-__global__ void __launch_bounds__(256, 2)
+__global__ void __launch_bounds__(256, sizeof(T) == 2 || D == 64 ? 3 : 2)
 assign_kernel(AssignArgs a) {
     constexpr int ROWB = D * (int)sizeof(T), CPR = ROWB / 16;        // token rows
     constexpr int WROWB = 2 * D, WCPR = WROWB / 16, DC = D / 16;     // rows of one term of W
@@ -469,6 +469,10 @@ assign_kernel(AssignArgs a) {
     const unsigned char* wlb = (const unsigned char*)a.w_lo + (size_t)b * k_own * WROWB;
     const int n_blocks = (k_own + 31) / 32;
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(wl));
+    // in LDS: a load from memory inside the block loop would be waited for behind the next block's
+    __shared__ __attribute__((aligned(16))) float bias[BIAS ? SVOO_MAX_K : 4];
+    if (BIAS)
+        for (int e = tid; e < 32 * n_blocks; e += 256) bias[e] = a.half_sq[(size_t)b * (32 * n_blocks) + e];
     if (tid == 0) n_open = 0;
 
     auto issue_block = [&](int cb, int buf) {
@@ -485,6 +489,9 @@ assign_kernel(AssignArgs a) {
         }
     };
     issue_block(0, 0);
+
+    const float wmax = __int_as_float(a.wmax_bits[b]);        // here: behind the block loop nothing would hide these loads
+    const bool degenerate = !BIAS && a.flags[b] != 0;
 
     // token fragments and squared norms (the norm only scales the margin below, whose constant has a factor
     // of two in hand: the packed dot product's own rounding does not matter).  Rows past the end are read
@@ -534,15 +541,27 @@ assign_kernel(AssignArgs a) {
             const bf16x8_t wh = __builtin_bit_cast(bf16x8_t, *(const uint4*)(base + koff[c]));
             const bf16x8_t wlow = __builtin_bit_cast(bf16x8_t, *(const uint4*)(base + BLOCK + koff[c]));
 #pragma unroll
-            for (int tb = 0; tb < 2; ++tb) {
-                acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wh, xf[tb][c].term[0], acc[tb], 0, 0, 0);
+            for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+                for (int t = 0; t < XT; ++t)
+                    acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wh, xf[tb][c].term[t], acc[tb], 0, 0, 0);
+#pragma unroll
+            for (int tb = 0; tb < 2; ++tb)
                 acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wlow, xf[tb][c].term[0], acc[tb], 0, 0, 0);
-                if constexpr (XT == 2) acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wh, xf[tb][c].term[1], acc[tb], 0, 0, 0);
-            }
         }
+        // Two chunks of W in flight: left alone, the compiler reads a chunk when the last one is used up and waits for it.
+        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+        for (int c = 0; c < DC - 2; ++c) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 2 * XT, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 2 * (2 * XT + 2), 0);
         const int cbase = 32 * cb;      // uniform; the lane's own offset 4 h is added to the winner once, after the loop
         if (BIAS) {
-            const float4* hb = (const float4*)(a.half_sq + (size_t)b * (32 * n_blocks) + cbase + 4 * h);
+            const float4* hb = (const float4*)(bias + cbase + 4 * h);
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const float4 t = hb[2 * g];
@@ -593,8 +612,6 @@ assign_kernel(AssignArgs a) {
         const int v = __float_as_int(best[tb]) & 15;
         bidx[tb] += 8 * (v / 4) + (v % 4) + 4 * h;
     }
-    const float wmax = __int_as_float(a.wmax_bits[b]);
-    const bool degenerate = !BIAS && a.flags[b] != 0;
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb) {
         auto rb = __builtin_amdgcn_permlane32_swap(__float_as_int(best[tb]), __float_as_int(best[tb]), false, false);
