@@ -34,8 +34,10 @@
 //
 // Bound (12 x 2,048 rows x 75,600 keys, d = 128, bf16): vector issue.  A logit of a histogram pass
 // costs ~60 vector cycles (exponential 16, bin index 12, fixed-point mass 20) against 16 of its
-// share of the matrix instruction.  Measured there: 24.7 ms for 29 passes of halving, 4.0-4.5 ms for
-// the four passes here (pass 0 0.6, pass 1 1.05, pass 2 1.4, the collecting pass 0.85).
+// share of the matrix instruction.  Measured there: 24.7 ms for 29 passes of halving, 4.3 ms for four
+// passes with a branch per logit in the later ones, 4.0 ms here: of a lane's 16 logits two bit masks say which are
+// inside the bracket, and every lane of the wave picks its next one (1.5 % of the keys are inside in pass 2:
+// two rounds for all 64 lanes, where 10 of 16 branches were taken for some lane).
 #include <math.h>
 
 #include <type_traits>
@@ -44,6 +46,7 @@
 
 #define LOG2E_F 1.4426950408889634f
 #define DEN_REFINE_N (1 << 18)   // more keys: masses in the unit of the row (svoo_attention_density says why)
+#define DEN_PICK 4          // keys inside the bracket, of a lane's 16, up to which they are picked one by one
 #define DEN_MAX_PASSES 48   // pass 0, pass 1, and far more splits than a float interval allows; a hard stop
 
 typedef __attribute__((ext_vector_type(8))) __bf16 den_bf16x8;
@@ -85,6 +88,9 @@ __device__ __forceinline__ den_u64 to_fixed(float p, double fix) {
     const long long u = __double_as_longlong(fma((double)p, fix, 4503599627370496.0));
     return (den_u64)u & 0xfffffffffffffULL;
 }
+
+// by value: of two array elements the compiler would select the address, and keep the array in memory
+__device__ __forceinline__ float pick(bool second, float b, float a) { return second ? b : a; }
 
 // What a lane needs of its row during a pass.
 struct Bracket {
@@ -479,24 +485,43 @@ density_kernel(DensityArgs a) {
         }
     }
     while (!__syncthreads_and(!owner || br.mode == DEN_DONE) && pass < DEN_MAX_PASSES) {
-        // ---- later passes: only keys inside the bracket cost more than three comparisons
+        // ---- later passes: only keys inside the bracket cost more than two comparisons
         int cnt = 0;
         {
             const Bracket r = {st_lo[row], st_hi[row], st_inv[row], st_off[row], st_mode[row]};
             const float nmb = st_nmb[row];
+            auto take = [&](float x) __attribute__((always_inline)) {      // a key inside the bracket
+                if (r.mode == DEN_COLLECT) {
+                    const int e = atomicAdd(&st_len[row], 1);
+                    if (e < CAP) list[2 * ((e / 2) * ROWS + row) + e % 2] = x;
+                } else {
+                    const float p = __builtin_amdgcn_exp2f(fmaf(x, c2, nmb));
+                    atomicAdd(&hist[bracket_bin<BINS>(x, r) * ROWS + row], to_fixed(p, fix));
+                }
+            };
             over_keys([&](const den_f32x16& s, bool, int) {
+                uint32_t from_lo = 0, from_hi = 0;         // bit v: s[v] is at or above the edge
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const bool above = s[v] >= r.hi;
-                    cnt += above ? 1 : 0;
-                    if (!above && s[v] >= r.lo) {
-                        if (r.mode == DEN_COLLECT) {
-                            const int e = atomicAdd(&st_len[row], 1);
-                            if (e < CAP) list[2 * ((e / 2) * ROWS + row) + e % 2] = s[v];
-                        } else {
-                            const float p = __builtin_amdgcn_exp2f(fmaf(s[v], c2, nmb));
-                            atomicAdd(&hist[bracket_bin<BINS>(s[v], r) * ROWS + row], to_fixed(p, fix));
-                        }
+                for (int v = 15; v >= 0; --v) {
+                    from_lo = from_lo + from_lo + (s[v] >= r.lo ? 1u : 0u);
+                    from_hi = from_hi + from_hi + (s[v] >= r.hi ? 1u : 0u);
+                }
+                cnt += __popc(from_hi);
+                uint32_t in = from_lo & ~from_hi;
+                if (__any(__popc(in) > DEN_PICK)) {        // a wide bracket: most logits have some lane's work
+#pragma unroll
+                    for (int v = 0; v < 16; ++v)
+                        if (in >> v & 1u) take(s[v]);
+                } else {
+                    while (in) {                           // every lane its next key
+                        const int v = __ffs(in) - 1;
+                        in &= in - 1;
+                        float t[8], u[4];
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) t[i] = pick(v & 1, s[2 * i + 1], s[2 * i]);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) u[i] = pick(v & 2, t[2 * i + 1], t[2 * i]);
+                        take(pick(v & 8, pick(v & 4, u[3], u[2]), pick(v & 4, u[1], u[0])));
                     }
                 }
             });

@@ -247,3 +247,28 @@ def test_density_sees_the_mass_of_a_million_tiny_keys(dtype):
     rows = torch.arange(40, dtype=torch.int32, device=H.DEV)
     plen, _ = svoo.attention_density(q, k, float(np.float32(1.0 - 2.0 ** -24)), 43.0 * math.log(2.0), rows=rows)
     assert (np.abs(H.to_np(plen) - 2.0 ** 19) <= 16).all()
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
+@pytest.mark.parametrize("group", [1, 4, 5, 32, 5003])
+def test_density_does_not_hang_on_the_order_of_the_keys(dtype, d, group):
+    """Runs of ``group`` keys of neighbouring logits: from none to all 16 of a lane's logits lie inside the bracket, on
+    both sides of the rule that picks a few one by one.  Masses are integers, so the lengths equal those of the
+    unordered keys."""
+    rng = np.random.default_rng(d)
+    n = 5003
+    head = synth.make_head(synth.CONFIGS[1], 4, 0, grid=(1, 1, n), n_seeds=8, kq=1, kk=1, d=d, dtype=dtype)
+    q, k = head["q"][:97], head["k"]
+    by_logit = np.argsort(k.astype(np.float64) @ q[0].astype(np.float64))
+    runs = [by_logit[i:i + group] for i in range(0, n, group)]
+    order = np.concatenate([runs[i] for i in rng.permutation(len(runs))])
+    rows = np.zeros((n, d), q.dtype)
+    rows[:97] = q[0] + 1e-3 * (q - q[0])             # rows that order the keys much as row 0 does
+    rows = H.to_np(H.to_dev(rows, dtype).float()).astype(q.dtype)
+    scale, tau = H.scale_of(d), float(np.float32(0.95))
+    which = H.to_dev(np.arange(97, dtype=np.int32))
+    got = [H.to_np(svoo.attention_density(H.to_dev(rows[None], dtype), H.to_dev(np.ascontiguousarray(x)[None], dtype), tau, scale,
+                                          rows=which)[0])[0] for x in (k, k[order])]
+    assert (got[0] == got[1]).all()
+    ref = so.attention_density(rows[:97], k, scale, tau)
+    compare_prefix(got[1], ref)
