@@ -393,6 +393,18 @@ static void launch_anchor_w(const double* c_own, const double* c_opp, int k_own,
                        k_opp, w64, bterm, flags, w_hi, w_lo, wt, wmax_bits);
 }
 
+// v_max_f32 and v_max3_f32 as they are: of fmaxf the compiler makes a canonicalised operand each time
+__device__ __forceinline__ float max_raw(float a, float b) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ float max3_raw(float a, float b, float c) {
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
 struct AssignArgs {
     const void* x;
     const uint16_t* w_hi;          // upper and lower bf16 terms of W
@@ -427,21 +439,14 @@ struct AssignArgs {
 // The workgroup also knows the label counts of its ASSIGN_CHUNK tokens, which saves the sort its pass over the
 // labels.
 //
+// Bound, 12 x 75,600 x 128 bf16 against 256 centroids: matrix and vector work, which hardly overlap, 9.7 us per block of 32
+// (7.1 of them matrix pipe), 38 us of token rows from memory, norms and counts, 7.5 us of decisions: 134 -> 123 us with
+// the place of a centroid in its score's last bits, two chunks of W in flight and three workgroups a compute unit (float32,
+// d = 128: 210 registers, two).  Reading whole token rows through LDS changed nothing.
+//
 // BIAS: score_j = <x, W_j> - half_sq[j] (k-means on raw rows: W = C, half_sq = ||c_j||^2 / 2, one
 // float per centroid, slices padded to a multiple of 32 entries); the margin then also covers the
 // float32 rounding of the bias and of the subtraction.
-// v_max_f32 and v_max3_f32 as they are: of fmaxf the compiler makes a canonicalised operand each time
-__device__ __forceinline__ float max_raw(float a, float b) {
-    float r;
-    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-__device__ __forceinline__ float max3_raw(float a, float b, float c) {
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-
 #define LIST_BATCH 32    // loads of W^T in flight per thread
 #define DECIDE_FEW 4     // open tokens that a thread per centroid decides
 #define DECIDE_TILES 2   // 16-token tiles of open tokens decided at a time
