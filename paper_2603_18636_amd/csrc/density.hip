@@ -35,7 +35,7 @@
 // Bound (12 x 2,048 rows x 75,600 keys, d = 128, bf16): vector issue.  A logit of a histogram pass
 // costs ~60 vector cycles (exponential 16, bin index 12, fixed-point mass 20) against 16 of its
 // share of the matrix instruction.  Measured there: 24.7 ms for 29 passes of halving, 4.3 ms for four
-// passes with a branch per logit in the later ones, 4.0 ms here: of a lane's 16 logits two bit masks say which are
+// passes with a branch per logit in the later ones (4.55 on a slower card), 4.0 (4.2) here: of a lane's 16 logits two bit masks say which are
 // inside the bracket, and every lane of the wave picks its next one (1.5 % of the keys are inside in pass 2:
 // two rounds for all 64 lanes, where 10 of 16 branches were taken for some lane).
 #include <math.h>
@@ -602,7 +602,7 @@ static int launch_density(const DensityArgs& a, hipStream_t stream) {
 // One workgroup fits a compute unit (its histograms and K stages fill the LDS) and runs for the whole launch,
 // so the rows per workgroup are the fewest with which one round of the 256 units covers all rows, else 128.  That
 // is not always the best split: 12 x 2,048 rows are 264 workgroups of 96 rows, eight too many, and run as 192
-// of 128 (4.0 ms), a quarter of the chip idle; three full rounds of 32-row workgroups have not been measured.
+// of 128 (4.0-4.2 ms), a quarter of the chip idle; three full rounds of 32-row workgroups have not been measured.
 template <typename T, int D>
 static int dispatch_density(const DensityArgs& a, hipStream_t stream) {
     auto wgs = [&](int rg) { return (long long)((a.n_rows + 32 * rg - 1) / (32 * rg)) * a.bh; };
