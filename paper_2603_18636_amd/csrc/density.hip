@@ -35,7 +35,7 @@
 // Bound (12 x 2,048 rows x 75,600 keys, d = 128, bf16): vector issue.  A logit of a histogram pass
 // costs ~60 vector cycles (exponential 16, bin index 12, fixed-point mass 20) against 16 of its
 // share of the matrix instruction.  Measured there: 24.7 ms for 29 passes of halving, 4.3 ms for four
-// passes with a branch per logit in the later ones (4.55 on a slower card), 4.0 (4.2) here: of a lane's 16 logits two bit masks say which are
+// passes with a branch per logit in the later ones (4.55 on another card), 4.0 (4.2) here: of a lane's 16 logits two bit masks say which are
 // inside the bracket, and every lane of the wave picks its next one (1.5 % of the keys are inside in pass 2:
 // two rounds for all 64 lanes, where 10 of 16 branches were taken for some lane).
 #include <math.h>
