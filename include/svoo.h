@@ -101,9 +101,9 @@ size_t svoo_permute_workspace_bytes(const svoo_shape* shape, int32_t n_clusters)
  * objective (nullable) [bh, iters, 2] float64 (sums of N float64 terms; float32 would lose the
  * differences between iterations): sum_i ||P^_i - Pbar^_{L_i}||^2 at assignment time of Step A
  * (index 0) and Step B (index 1) -- a diagnostic, costs one extra pass per half-step.
- * Arithmetic: assignment decisions are taken in float64 (a matrix-core pass, in bf16 for bf16 tokens and
- * in float32 for float32 ones, only decides tokens whose best and second-best scores are provably far
- * enough apart); centroid means are float64 sums in a
+ * Arithmetic: assignment decisions are taken in float64 (a matrix-core pass on two bf16 terms of the
+ * score matrix, and of float32 tokens, only decides tokens whose best and second-best scores are provably
+ * far enough apart); centroid means are float64 sums in a
  * fixed order, carried in float64 between iterations and rounded to float32 on output.
  */
 int svoo_cocluster(const svoo_shape* shape, const void* q, const void* k,

@@ -12,12 +12,13 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 // Error of a fast score relative to ||x|| ||W_j||, d <= 128.  bf16 tokens: what two bf16 terms of W leave, 2^-17, and 256
-// additions of 2^-24: 2.3e-5.  float32 tokens: 2^-18 left of W, 2^-18 left of x, 2^-18 for the product of the two lower terms,
-// 384 additions: 3.5e-5.  Where a score's last four bits hold a place, 15 2^-23 = 1.8e-6 more.  The rest covers the
-// float32 rounding of the norms themselves (2^-17 of a sum of 128 squares).
+// additions of 2^-24: 2.29e-5.  float32 tokens: 2^-17 left of W, 2^-17 left of x, 2^-16 for the product of the two lower terms
+// (each up to 2^-8 of its element: 1 + 2^-8 and its like), 384 additions: 5.34e-5.  Where a score's last four bits hold a
+// place, 15 2^-23 = 1.8e-6 more: 2.47e-5 and 5.52e-5.  The rest covers the float32 rounding of the norms themselves (below
+// 2^-15 of them).
 template <typename T> constexpr float fast_eps();
 template <> constexpr float fast_eps<uint16_t>() { return 3.1e-5f; }
-template <> constexpr float fast_eps<float>() { return 4.6e-5f; }
+template <> constexpr float fast_eps<float>() { return 5.8e-5f; }
 
 // Upper bound of ||x|| max_j ||W_j|| from the float32 squared norm of a token and the largest row norm: what underflow may
 // have taken from the square or from a score is less than FAST_MIN stands for.  With it a margin never says too little:

@@ -182,7 +182,7 @@ static void launch_quadform(const void* x, const double* gram, double* quad_out,
 // satisfies |f_j - <x, W_j>| <= eps ||x|| ||W_j|| with eps covering the split remainder and the
 // fp32 accumulation of 2 d products.  float32 tokens are split the same way, x = x_hi + x_lo, and
 // f_j = <x_hi, W_hi_j> + <x_hi, W_lo_j> + <x_lo, W_hi_j>: 3 x 32 cycles per 16 elements where the float32 matrix instruction
-// takes 512, for a margin half as wide again (12 x 8,190 x 128, 64 centroids: 32.5 -> 24 us).  If
+// takes 512, for a margin not twice as wide (12 x 8,190 x 128, 64 centroids: 32.5 -> 24 us).  If
 // best - second > 2 eps ||x|| max_j ||W_j|| the fast argmax is the exact argmax; otherwise (and for every
 // token of a slice with a degenerate anchor) the workgroup decides the token in float64.  Equal
 // scores have gap 0 and are therefore always decided in float64, lowest index first.
@@ -457,7 +457,6 @@ assign_kernel(AssignArgs a) {
     constexpr int WROWB = 2 * D, WCPR = WROWB / 16, DC = D / 16;     // rows of one term of W
     constexpr int BLOCK = 32 * WROWB;        // 32 centroids of one term
     constexpr int TERMS = 2, XT = sizeof(T) == 2 ? 1 : 2;            // terms of W, of a token
-    constexpr int PROD = TERMS + XT - 1;     // products: W_hi x_hi, W_lo x_hi, W_hi x_lo
     constexpr int RPL = 64 / WCPR;           // rows per wave-load
     constexpr int LPW = (32 / RPL) / 4;      // wave-loads per wave for one block of one term
     static_assert(LPW >= 1 && ASSIGN_CHUNK == 256, "geometry");
@@ -498,8 +497,8 @@ assign_kernel(AssignArgs a) {
     const float wmax = __int_as_float(a.wmax_bits[b]);        // here: behind the block loop nothing would hide these loads
     const bool degenerate = !BIAS && a.flags[b] != 0;
 
-    // token fragments and squared norms (the norm only scales the margin below, whose constant has a factor
-    // of two in hand: the packed dot product's own rounding does not matter).  Rows past the end are read
+    // token fragments and squared norms (the norm only scales the margin below, whose constant has 5 % in hand, bf16
+    // tokens 25 %: the rounding of the 128 squares, below 2^-16, does not matter).  Rows past the end are read
     // from the last token instead of being predicated; their results are never stored.
     TokenChunk<XT> xf[2][DC];
     float xn2[2];

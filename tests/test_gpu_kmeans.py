@@ -160,13 +160,22 @@ def test_a_centroid_that_is_nan_wins_no_token(dtype, d, n):
             H.compare_labels(got - (got > lost), *ref)
 
 
+def split_worst_rows(rng, n, d):
+    """Rows whose elements split worst into two bf16 terms: half-way between two bf16 numbers next to a power of two
+    (lower terms of either sign, 2^-8 of the element), with a remainder behind the lower term."""
+    x = rng.choice([1 + 2.0 ** -8, 1 + 3 * 2.0 ** -8], (n, d)) - rng.choice([0.0, 2.0 ** -17, 2.0 ** -16 + 2.0 ** -17], (n, d))
+    return x * rng.choice([-1.0, 1.0], (n, d)) * 2.0 ** rng.integers(-1, 2, (n, d))
+
+
 @pytest.mark.parametrize("d,n,k", [(64, 700, 40), (128, 700, 33), (128, 9000, 130)])
 @pytest.mark.parametrize("scale", [1.0, 1e-17, 1e17])
-def test_float32_labels_with_centroids_closer_than_two_bf16_terms_tell(d, n, k, scale):
+@pytest.mark.parametrize("worst", [False, True])
+def test_float32_labels_with_centroids_closer_than_two_bf16_terms_tell(d, n, k, scale, worst):
     """Float32 tokens and centroids in pairs 2^-14 .. 2^-22 apart: the pre-filter on two bf16 terms of each must leave
     open what it cannot tell, down to products that are subnormal and up to squares near the end of float32."""
     rng = np.random.default_rng(d + n)
-    x = (scale * rng.standard_normal((1, n, d))).astype(np.float32)
+    scale = 2.0 ** round(np.log2(scale)) if worst else scale
+    x = (scale * (split_worst_rows(rng, n, d) if worst else rng.standard_normal((n, d))))[None].astype(np.float32)
     c = x[:, rng.choice(n, k, replace=False)].copy()
     for j in range(1, k, 2):
         c[0, j] = c[0, j - 1] * np.float32(1 + 2.0 ** -(14 + j % 9))
@@ -176,6 +185,27 @@ def test_float32_labels_with_centroids_closer_than_two_bf16_terms_tell(d, n, k, 
     best = score.argmax(1)
     gap = score[np.arange(n), best] - score[np.arange(n), got]
     assert (gap <= 1e-13 * np.abs(score).max()).all(), (int((gap > 0).sum()), float(gap.max()))
+
+
+@pytest.mark.parametrize("d,n,k", [(64, 700, 40), (128, 700, 32), (64, 9000, 40), (128, 9000, 130)])
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** 57])
+@pytest.mark.parametrize("worst", [False, True])
+def test_float32_co_clustering_with_anchors_closer_than_two_bf16_terms_tell(d, n, k, scale, worst):
+    """The same for co-clustering, on the path of few clusters and tokens and on the general one: own-side centroids in
+    pairs that differ by 2^-14 .. 2^-22 element-wise, scores <x, W_j> in float64 beside the labels."""
+    rng = np.random.default_rng(d + n + k)
+    rows = (lambda m: split_worst_rows(rng, m, d)) if worst else (lambda m: rng.standard_normal((m, d)))
+    x, q, opp = ((scale * rows(m)).astype(np.float32) for m in (n, n, 24))
+    own = x[rng.choice(n, k, replace=False)].copy()
+    for j in range(1, k, 2):
+        own[j] = own[j - 1] * (1 + 2.0 ** -(14 + j % 9) * rng.uniform(-1, 1, d)).astype(np.float32)
+    got = H.to_np(svoo.cocluster(H.to_dev(q[None], "f32"), H.to_dev(x[None], "f32"), iters=1, init_cq=H.to_dev(opp[None]),
+                                 init_ck=H.to_dev(own[None]))["labels_k"])[0]
+    xx, oo, pp = (a.astype(np.float64) / scale for a in (x, own, opp))
+    aff = oo @ pp.T
+    score = (xx @ pp.T) @ (aff / np.linalg.norm(aff, axis=1, keepdims=True)).T
+    gap = score.max(1) - score[np.arange(n), got]
+    assert (gap <= 1e-12 * np.abs(score).max()).all(), (int((gap > 0).sum()), float(gap.max()))
 
 
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
