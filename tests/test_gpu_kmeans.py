@@ -168,11 +168,11 @@ def split_worst_rows(rng, n, d):
 
 
 @pytest.mark.parametrize("d,n,k", [(64, 700, 40), (128, 700, 33), (128, 9000, 130)])
-@pytest.mark.parametrize("scale", [1.0, 1e-17, 1e17])
+@pytest.mark.parametrize("scale", [1.0, 1e-17, 1e17, 3e18])
 @pytest.mark.parametrize("worst", [False, True])
 def test_float32_labels_with_centroids_closer_than_two_bf16_terms_tell(d, n, k, scale, worst):
     """Float32 tokens and centroids in pairs 2^-14 .. 2^-22 apart: the pre-filter on two bf16 terms of each must leave
-    open what it cannot tell, down to products that are subnormal and up to squares near the end of float32."""
+    open what it cannot tell, down to products that are subnormal, up to squares near the end of float32 and beyond."""
     rng = np.random.default_rng(d + n)
     scale = 2.0 ** round(np.log2(scale)) if worst else scale
     x = (scale * (split_worst_rows(rng, n, d) if worst else rng.standard_normal((n, d))))[None].astype(np.float32)
@@ -188,7 +188,7 @@ def test_float32_labels_with_centroids_closer_than_two_bf16_terms_tell(d, n, k, 
 
 
 @pytest.mark.parametrize("d,n,k", [(64, 700, 40), (128, 700, 32), (64, 9000, 40), (128, 9000, 130)])
-@pytest.mark.parametrize("scale", [1.0, 2.0 ** 57])
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** 57, 2.0 ** 60, 2.0 ** 62])
 @pytest.mark.parametrize("worst", [False, True])
 def test_float32_co_clustering_with_anchors_closer_than_two_bf16_terms_tell(d, n, k, scale, worst):
     """The same for co-clustering, on the path of few clusters and tokens and on the general one: own-side centroids in
@@ -206,6 +206,33 @@ def test_float32_co_clustering_with_anchors_closer_than_two_bf16_terms_tell(d, n
     score = (xx @ pp.T) @ (aff / np.linalg.norm(aff, axis=1, keepdims=True)).T
     gap = score.max(1) - score[np.arange(n), got]
     assert (gap <= 1e-12 * np.abs(score).max()).all(), (int((gap > 0).sum()), float(gap.max()))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("partitioner", ["kmeans", "cocluster"])
+def test_large_tokens_take_no_longer(dtype, partitioner):
+    """Scores between 1e37 and the end of float32 go through the pre-filter like any others: a power of two changes
+    neither a label nor the time (deciding every token in float64 takes twice as long)."""
+    gen = torch.Generator(device=H.DEV).manual_seed(7)
+    x, y = (torch.randn(4, 30000, 128, generator=gen, device=H.DEV).to(H.torch_dtype(dtype)) for _ in range(2))
+    labels, times = [], []
+    for scale in (1.0, 2.0 ** 59):
+        xs, ys = x * scale, y * scale
+        cx, cy = xs[:, :160].float().contiguous(), ys[:, :160].float().contiguous()
+        run = (lambda: svoo.kmeans(xs, iters=1, init_c=cx)["labels"]) if partitioner == "kmeans" else \
+            (lambda: svoo.cocluster(xs, ys, iters=1, init_cq=cx, init_ck=cy)["labels_k"])
+        labels.append(run())
+        took = []
+        for _ in range(20):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            run()
+            b.record()
+            b.synchronize()
+            took.append(a.elapsed_time(b))
+        times.append(min(took))
+    assert torch.equal(*labels)
+    assert times[1] < 1.25 * times[0], times
 
 
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
