@@ -27,6 +27,9 @@ template <> constexpr float fast_eps<float>() { return 5.8e-5f; }
 __device__ __forceinline__ float score_bound(float xn2, float wmax) {
     return fmaxf(sqrtf(fmaxf(xn2, FAST_MIN)) * wmax, FAST_MIN);
 }
+// Scores bounded by less never overflow on the way: two bf16 terms of x and W add up to (1 + 2^-8)^2 + 2^-7 (1 + 2^-8) =
+// 1.016 of their product at most.
+#define SCORE_MAX 3.34e38f
 
 // Score of the general form, one rounding: 2 <x, W_j> - nx b_j (k-means: nx = 1, b_j = ||c_j||^2)
 __device__ __forceinline__ double general_score(double dot, double nx, double bj) { return fma(-nx, bj, 2.0 * dot); }
@@ -83,11 +86,12 @@ __device__ __forceinline__ float add_squares(const TokenChunk<2>& x, float acc) 
     return acc;
 }
 
-// 1e-33: rows of W whose lower bf16 terms are subnormal (and lose bits of their own) have norms far below it
+// 1e-33: rows of W whose lower bf16 terms are subnormal (and lose bits of their own) have norms far below it.  A norm beyond
+// float32, or of a row that is NaN, is infinite: it bounds no score, so every token of the slice is open.
 __device__ __forceinline__ float norm_rounded_up(double sq) {
     float nrm = (float)sqrt(sq);
     nrm = nrm * 1.0000002f + 1e-33f;
-    return nrm < 3.0e38f ? nrm : 3.0e38f;      // NaN as well
+    return nrm < 3.0e38f ? nrm : INFINITY;
 }
 
 template <typename T>

@@ -450,7 +450,6 @@ struct AssignArgs {
 #define LIST_BATCH 32    // loads of W^T in flight per thread
 #define DECIDE_FEW 4     // open tokens that a thread per centroid decides
 #define DECIDE_TILES 2   // 16-token tiles of open tokens decided at a time
-#define SCORE_MAX 3.34e38f   // 1.016 of it is a finite float32
 template <typename T, int D, bool BIAS>
 __global__ void __launch_bounds__(256, sizeof(T) == 2 || D == 64 ? 3 : 2)
 assign_kernel(AssignArgs a) {
@@ -632,11 +631,10 @@ assign_kernel(AssignArgs a) {
         const int tok = t0 + 32 * tb + j;
         if (h == 0) {
             const float xw = score_bound(xn2[tb], wmax);
-            const float bound = BIAS ? 0.5f * wmax * wmax + xw : xw;       // of every score, and of its sums but for 1.6 %
+            const float bound = BIAS ? 0.5f * wmax * wmax + xw : xw;       // of every score
             // 2.1e-6: 2^-22 for the rounding of the bias, 15 2^-23 for the place in a score's last bits
             const float margin = 2.0f * (fast_eps<T>() * xw + (BIAS ? 2.1e-6f * bound : 0.0f));
-            // False for NaN as well.  A score that overflowed has lost its infinity to the place, so none may have: two bf16
-            // terms of x and W add up to (1 + 2^-8)^2 + 2^-7 (1 + 2^-8) = 1.016 of their product at most.
+            // false for NaN as well; a score that overflowed has lost its infinity to the place, so none may have
             const bool sure = (fb - fs) > margin && bound < SCORE_MAX;
             lab[tok - g0] = fi;
             if ((degenerate || !sure) && tok < n) open[atomicAdd(&n_open, 1)] = tok - g0;

@@ -251,7 +251,8 @@ assign_small_kernel(SmallAssign a) {
         const float fb = fmaxf(b0, b1), fs = fmaxf(fminf(b0, b1), fmaxf(__int_as_float(rs[0]), __int_as_float(rs[1])));
         if (h == 0 && tok < n) {
             const int fi = b0 >= b1 ? (int)ri[0] : (int)ri[1];
-            const bool sure = (fb - fs) > 2.0f * fast_eps<T>() * score_bound(xn2, wmax);      // false for NaN as well
+            const float xw = score_bound(xn2, wmax);
+            const bool sure = (fb - fs) > 2.0f * fast_eps<T>() * xw && xw < SCORE_MAX;        // false for NaN as well
             if (degenerate || !sure)
                 open[atomicAdd(&n_open, 1)] = tok;
             else

@@ -235,6 +235,27 @@ def test_large_tokens_take_no_longer(dtype, partitioner):
     assert times[1] < 1.25 * times[0], times
 
 
+@pytest.mark.parametrize("dtype,d,n", [("bf16", 128, 700), ("f32", 128, 700), ("bf16", 64, 9000), ("f32", 64, 9000)])
+@pytest.mark.parametrize("tiny", [2.0 ** -30, 2.0 ** -40])
+def test_anchors_whose_scores_no_float32_holds(dtype, d, n, tiny):
+    """Rows of the score matrix beyond float32 (elements, or only their norms) against tokens so small that their scores
+    are ordinary numbers: no bound in float32 covers them, so every token is decided in float64."""
+    rng = np.random.default_rng(d)
+    bits = lambda a: synth.round_to_bf16(a.astype(np.float32))
+    x, own = bits(tiny * rng.standard_normal((n, d))), bits(tiny * rng.standard_normal((30, d)))
+    opp = bits(2.0 ** 126 * rng.uniform(1.0, 1.9, (24, d)) * rng.choice([-1.0, 1.0], (24, d)))
+    own[7] = 2.0 ** -24 * own[7] + 0.5 * own[8]
+    got = H.to_np(svoo.assign(H.to_dev(x[None], dtype), H.to_dev(own[None]), H.to_dev(opp[None])))[0]
+    both = H.to_np(svoo.cocluster(H.to_dev(x[None], dtype), H.to_dev(x[None], dtype), iters=1, init_cq=H.to_dev(opp[None]),
+                                  init_ck=H.to_dev(own[None]))["labels_k"])[0]
+    xx, oo, pp = x.astype(np.float64), own.astype(np.float64), opp.astype(np.float64) / 2.0 ** 126
+    aff = oo @ pp.T
+    score = (xx @ pp.T) @ (aff / np.linalg.norm(aff, axis=1, keepdims=True)).T
+    for labels in (got, both):
+        gap = score.max(1) - score[np.arange(n), labels]
+        assert (gap <= 1e-12 * np.abs(score).max()).all(), (int((gap > 0).sum()), float(gap.max() / np.abs(score).max()))
+
+
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
 @pytest.mark.parametrize("k", [1, 2, 17, 31, 32, 33, 63, 65, 97, 1000])
 @pytest.mark.parametrize("twins", [False, True])
