@@ -270,55 +270,57 @@ sparse_attn_bf16_kernel(AttnArgs a) {
     // 2 adjacent 32-byte column segments; XOR-ing the 64-byte granule index with the row spreads
     // those 8 segments over all banks (K keeps the 16-byte swizzle by row).
     auto vswz = [](int rho) { return ((rho / (256 / ROWB)) % (ROWB / 64)) << 2; };
-    // ---- key stream.  A tile inside one key block is 64 adjacent rows: its loads take a scalar base address and offsets that
-    // never change.  Where key blocks meet, `next_base` is -1 and `next_rows` the row of each load.  The rows of a tile are
-    // looked up one tile ahead of their use (segment tables in LDS), so that only the loads stand behind the barrier.
-    // Against looking up every lane's row of every tile (a lane exchange and 20 vector instructions a tile), d = 128:
-    // reuse of 12 x 75,600 (295 keys a block) 12.04 -> 11.71 ms, dense 12 x 32,760 5.58 -> 5.47; blocks of 74 keys, where two
-    // of three tiles hold an edge, unchanged.
-    int seg = 0, seg_end = 0, seg_delta = 0;      // uniform: the segment of the last tile's first key
+    // ---- key stream.  A tile inside one key block is 64 adjacent rows: its loads take a scalar base address (row `next_base`
+    // for this wave) and offsets that never change.  Where key blocks meet, every lane looks up a row (segment tables in LDS), one
+    // tile ahead of its use, so that only the loads stand behind the barrier: lanes below 32 those of this wave's RW rows, the
+    // others the first row of the tile behind, which says whether that one needs a look-up at all.  A lane keeps its place in
+    // the tables from one look-up to the next: with a walk from the tile's first key block, blocks of 8 / 2 keys (4 x 8,192 and
+    // 4 x 2,048 x 128, a quarter kept) took 102 / 57 us where they take 82 / 36.
+    // Against looking up every tile, d = 128: 12 x 75,600 (295 keys a block) 10.6 -> 10.3 ms, dense 12 x 32,760
+    // 5.78 -> 5.52; blocks of 74 keys, where two of three tiles hold an edge, -1 %; 8 to 40 keys, where all do, +1 to 4 %.
+    int seg = 0, seg_end = 0, seg_delta = 0;      // of the row this lane looked up last
+    int tile_end = 0, tile_delta = 0;             // uniform: of the first row behind the tile of the last look-up
     if (total > 0) {
-        seg_end = __builtin_amdgcn_readfirstlane(seg_cum[1]);
-        seg_delta = __builtin_amdgcn_readfirstlane(seg_start[0] - seg_cum[0]);
+        seg_end = seg_cum[1];
+        seg_delta = seg_start[0] - seg_cum[0];
     }
     int next_base = -1, next_rows[LPW];
     auto prepare_tile = [&](int t) {              // call with t = 0, 1, 2, ... in order, t < n_tiles
-        const int p0 = t * KT;
-        while (p0 >= seg_end && seg + 1 < ti.n_seg) {
+        const int p0 = t * KT, mine = p0 + RW * wave;
+        if (p0 + KT <= tile_end) {
+            next_base = mine + tile_delta;
+            return;
+        }
+        int p = lane < 32 ? mine + lane % RW : p0 + KT;
+        p = p < total ? p : total - 1;            // rows past the end re-read the last key (masked later)
+        while (p >= seg_end) {                    // terminates: p < total = seg_cum[n_seg]
             ++seg;
-            seg_end = __builtin_amdgcn_readfirstlane(seg_cum[seg + 1]);
-            seg_delta = __builtin_amdgcn_readfirstlane(seg_start[seg] - seg_cum[seg]);
+            seg_end = seg_cum[seg + 1];
+            seg_delta = seg_start[seg] - seg_cum[seg];
         }
-        if (p0 + KT <= seg_end) {
-            next_base = p0 + seg_delta;
-        } else {
-            next_base = -1;
-            int p = p0 + RW * wave + (lane % RW);
-            p = p < total ? p : total - 1;        // rows past the end re-read the last key (masked later)
-            int sg = seg, end = seg_end, delta = seg_delta;
-            while (p >= end) {                    // terminates: p < total = seg_cum[n_seg]
-                ++sg;
-                end = seg_cum[sg + 1];
-                delta = seg_start[sg] - seg_cum[sg];
-            }
-            const int myrow = p + delta;
+        tile_end = __builtin_amdgcn_readlane(seg_end, 32);
+        tile_delta = __builtin_amdgcn_readlane(seg_delta, 32);
+        next_base = -1;
+        const int row = p + seg_delta;
 #pragma unroll
-            for (int i = 0; i < LPW; ++i) next_rows[i] = __shfl(myrow, i * RPL + lane / CPR);
-        }
+        for (int i = 0; i < LPW; ++i) next_rows[i] = __shfl(row, i * RPL + lane / CPR);
     };
     // Tile row rho = RW wave + i RPL + lane / CPR is fetched by this lane's i-th wave-load; the three terms
     // occupy disjoint bits, so the swizzled 16-byte chunk of load i is that of load 0 XOR a constant
     // (K) or the same (V: its swizzle only looks at row bits below RPL).  Offsets are 32 bits: n <= 2^24 rows of at most
     // 256 bytes.
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
-    const uint32_t rho0 = (uint32_t)((RW * wave + lane / CPR) * ROWB);
+    const uint32_t lane_row = (uint32_t)(lane / CPR * ROWB);
     const uint32_t kx0 = (uint32_t)(((lane % CPR) ^ ((RW * wave + lane / CPR) % CPR)) * 16);
     const uint32_t vx0 = (uint32_t)(((lane % CPR) ^ vswz(RW * wave + lane / CPR)) * 16);
-    uint32_t kc[LPW], vc[LPW];                    // offsets inside a tile of adjacent rows, without the load's own i KB
+    uint32_t kx[LPW];                             // inside a row
+    uint32_t kc[LPW], vc[LPW];                    // inside the wave's rows if they are adjacent, without the load's own i KB
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
-        kc[i] = rho0 + (kx0 ^ (uint32_t)(((i * RPL) % CPR) * 16));
-        vc[i] = rho0 + vx0;
+        kx[i] = kx0 ^ (uint32_t)(((i * RPL) % CPR) * 16);
+        if (LPW == 4) asm volatile("" : "+v"(kx[i]));      // kept: four subtractions a tile less (1 % of one with an edge)
+        kc[i] = lane_row + kx[i];
+        vc[i] = lane_row + vx0;
     }
     auto issue_prepared = [&](int buf) {
         const uint32_t loff = lds0 + buf * TILE + RW * wave * ROWB;
@@ -330,8 +332,8 @@ sparse_attn_bf16_kernel(AttnArgs a) {
         }
 #pragma unroll
         for (int i = 0; i < LPW; ++i) {
-            const uint32_t row_off = (uint32_t)next_rows[i] * ROWB;
-            load_rows_to_lds_16(row_off + (kc[i] - rho0), kg, loff + i * 1024);
+            const uint32_t row_off = (uint32_t)next_rows[i] * ROWB;     // here: by now the lane exchange has arrived
+            load_rows_to_lds_16(row_off + kx[i], kg, loff + i * 1024);
             load_rows_to_lds_16(row_off + vx0, vg, loff + i * 1024 + NBUF * TILE);
         }
     };

@@ -704,6 +704,34 @@ def test_sparse_attn_key_blocks_at_the_edges_of_the_tiles(d, order):
     H.assert_attn_close(H.to_np(out)[0], so.sparse_attention(q, k, v, lq, lk, mask, H.scale_of(d)), "bf16", "tile edges")
 
 
+@pytest.mark.parametrize("d", [128, 64])
+def test_sparse_attn_of_one_key_stream_in_blocks_of_any_length(d):
+    """The same keys in the same order, cut into blocks of 1 to 256: the same bits, and blocks of 4 keys take hardly longer than
+    blocks of 64 (1.1 - 1.4 times; 1.8 - 2.2 with a walk over the blocks of every tile)."""
+    bh, n, times, first = 8, 4096, {}, None
+    gen = torch.Generator(device=H.DEV).manual_seed(d)
+    q, k, v = (torch.randn(bh, n, d, generator=gen, device=H.DEV).bfloat16() for _ in range(3))
+    for rows, size in ((n, 256), (n, 64), (n, 61), (n, 17), (n, 16), (n, 4), (1000, 64), (1000, 3), (1000, 1)):
+        cuts = list(range(0, rows, size)) + [rows]
+        off = lambda c: torch.tensor(c, dtype=torch.int32, device=H.DEV).repeat(bh, 1)
+        count = torch.full((bh, rows // 100), len(cuts) - 1, dtype=torch.int32, device=H.DEV)
+        lst = torch.arange(len(cuts) - 1, dtype=torch.int32, device=H.DEV).expand(bh, rows // 100, -1).contiguous()
+        args = [x[:, :rows].contiguous() for x in (q, k, v)]
+        args += [off([rows * i // (rows // 100) for i in range(rows // 100 + 1)]), off(cuts), count, lst, H.scale_of(d)]
+        took = []
+        for _ in range(20):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            out = svoo.block_sparse_attn(*args)
+            b.record()
+            b.synchronize()
+            took.append(a.elapsed_time(b))
+        times[rows, size] = min(took)
+        first = out if size == (256 if rows == n else 64) else first
+        assert torch.equal(out, first), (rows, size)
+    assert times[n, 4] < 1.55 * times[n, 64], times
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_sparse_attn_with_index_arrays_that_break_the_contract(dtype):
     """Offsets, block counts and block lists full of arbitrary integers (negative, far beyond n, not
