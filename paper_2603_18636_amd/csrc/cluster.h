@@ -48,28 +48,45 @@ __device__ __forceinline__ void store_split(double v, size_t o, uint16_t* w_hi, 
     w_lo[o] = f32_to_bf16((float)(v - (double)bf16_to_f32(hb)));
 }
 
-// Eight token elements as B operands of the pre-filter: bf16 tokens as they are, float32 tokens as two bf16 terms, each
-// rounded to nearest.  A lower term of an infinity is no number, which leaves the token open.
+// Eight token elements as they are loaded, and as B operands of the pre-filter: bf16 tokens unchanged, float32 tokens as two
+// bf16 terms, each rounded to nearest.  A lower term of an infinity is no number, which leaves the token open.
+template <typename T> struct RawChunk;
+template <> struct RawChunk<uint16_t> { uint4 u; };
+template <> struct RawChunk<float> { float4 a, b; };
 template <int TERMS>
 struct TokenChunk { bf16x8_t term[TERMS]; };
-__device__ __forceinline__ void load_chunk(const uint16_t* p, TokenChunk<1>& out) {
-    out.term[0] = __builtin_bit_cast(bf16x8_t, *(const uint4*)p);
+__device__ __forceinline__ void load_raw(const uint16_t* p, RawChunk<uint16_t>& out) { out.u = *(const uint4*)p; }
+__device__ __forceinline__ void load_raw(const float* p, RawChunk<float>& out) {
+    out.a = *(const float4*)p;
+    out.b = *(const float4*)(p + 4);
 }
-__device__ __forceinline__ void load_chunk(const float* p, TokenChunk<2>& out) {
-    const float4 a = *(const float4*)p, b = *(const float4*)(p + 4);
-    const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+__device__ __forceinline__ TokenChunk<1> split_chunk(const RawChunk<uint16_t>& raw) {
+    TokenChunk<1> out;
+    out.term[0] = __builtin_bit_cast(bf16x8_t, raw.u);
+    return out;
+}
+__device__ __forceinline__ TokenChunk<2> split_chunk(const RawChunk<float>& raw) {
+    const float v[8] = {raw.a.x, raw.a.y, raw.a.z, raw.a.w, raw.b.x, raw.b.y, raw.b.z, raw.b.w};
+    TokenChunk<2> out;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         const __bf16 hi = (__bf16)v[e];
         out.term[0][e] = hi;
         out.term[1][e] = (__bf16)(v[e] - (float)hi);
     }
+    return out;
+}
+// What is computed from the chunk below this line is computed below it
+__device__ __forceinline__ void keep_raw(RawChunk<uint16_t>& c) {
+    asm volatile("" : "+v"(c.u.x), "+v"(c.u.y), "+v"(c.u.z), "+v"(c.u.w));
+}
+__device__ __forceinline__ void keep_raw(RawChunk<float>& c) {
+    asm volatile("" : "+v"(c.a.x), "+v"(c.a.y), "+v"(c.a.z), "+v"(c.a.w), "+v"(c.b.x), "+v"(c.b.y), "+v"(c.b.z), "+v"(c.b.w));
 }
 
-// squares of a chunk added to acc (float32 tokens: of the sum of the two terms, within 2^-17)
-__device__ __forceinline__ float add_squares(const TokenChunk<1>& x, float acc) {
-    const uint4 u = __builtin_bit_cast(uint4, x.term[0]);
-    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+// squares of a chunk added to acc
+__device__ __forceinline__ float add_squares(const RawChunk<uint16_t>& x, float acc) {
+    const uint32_t w[4] = {x.u.x, x.u.y, x.u.z, x.u.w};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const bf16x2_t pr = __builtin_bit_cast(bf16x2_t, w[e]);
@@ -77,12 +94,10 @@ __device__ __forceinline__ float add_squares(const TokenChunk<1>& x, float acc) 
     }
     return acc;
 }
-__device__ __forceinline__ float add_squares(const TokenChunk<2>& x, float acc) {
+__device__ __forceinline__ float add_squares(const RawChunk<float>& x, float acc) {
+    const float v[8] = {x.a.x, x.a.y, x.a.z, x.a.w, x.b.x, x.b.y, x.b.z, x.b.w};
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const float v = (float)x.term[0][e] + (float)x.term[1][e];
-        acc = fmaf(v, v, acc);
-    }
+    for (int e = 0; e < 8; ++e) acc = fmaf(v[e], v[e], acc);
     return acc;
 }
 

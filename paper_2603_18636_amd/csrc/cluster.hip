@@ -509,8 +509,10 @@ assign_kernel(AssignArgs a) {
         float acc = 0.f;
 #pragma unroll
         for (int c = 0; c < DC; ++c) {
-            load_chunk(src + 16 * c + 8 * h, xf[tb][c]);
-            acc = add_squares(xf[tb][c], acc);
+            RawChunk<T> raw;
+            load_raw(src + 16 * c + 8 * h, raw);
+            xf[tb][c] = split_chunk(raw);
+            acc = add_squares(raw, acc);
         }
         const int ai = __float_as_int(acc);
         auto r = __builtin_amdgcn_permlane32_swap(ai, ai, false, false);

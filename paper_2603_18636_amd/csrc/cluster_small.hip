@@ -99,11 +99,11 @@ assign_small_kernel(SmallAssign a) {
 
     // ---- this wave's tokens, for later; C_opp into LDS
     const int tok = blockIdx.x * (32 * NW) + 32 * wave + j;
-    TokenChunk<XT> xf[DC];
+    RawChunk<T> xr[DC];
     {
         const T* src = x + (size_t)(tok < n ? tok : n - 1) * D;
 #pragma unroll
-        for (int c = 0; c < DC; ++c) load_chunk(src + 16 * c + 8 * h, xf[c]);
+        for (int c = 0; c < DC; ++c) load_raw(src + 16 * c + 8 * h, xr[c]);
     }
     for (int e = tid; e < k_opp * D / 2; e += NT) {
         const int r = e / (D / 2), t = e % (D / 2);
@@ -206,13 +206,17 @@ assign_small_kernel(SmallAssign a) {
     }
     __syncthreads();
 
-    // ---- pre-filter (assign_kernel's arithmetic and margin)
+    // ---- pre-filter: assign_kernel's products and margin, without the places in the scores.  Tokens are split here and no
+    // earlier: in two terms while W was built they took 228 registers (d = 128 float32), one workgroup of a compute unit's two,
+    // and the loads were waited for first: 12 x 8,000 x 128, 32 blocks, two iterations 225 us, 193 now (207 with the float32 matrix instruction).
+#pragma unroll
+    for (int c = 0; c < DC; ++c) keep_raw(xr[c]);
     const float wmax = __int_as_float(wmax_bits);
     const bool degenerate = degenerate_s != 0;
     {
         float xn2 = 0.f;
 #pragma unroll
-        for (int c = 0; c < DC; ++c) xn2 = add_squares(xf[c], xn2);
+        for (int c = 0; c < DC; ++c) xn2 = add_squares(xr[c], xn2);
         auto swap = [](float v) {
             return __builtin_amdgcn_permlane32_swap(__float_as_int(v), __float_as_int(v), false, false);
         };
@@ -232,9 +236,10 @@ assign_small_kernel(SmallAssign a) {
                 const int at = ((2 * c + h) ^ (j % CPR)) * 16;
                 const bf16x8_t wh = __builtin_bit_cast(bf16x8_t, *(const uint4*)(base + at));
                 const bf16x8_t wl = __builtin_bit_cast(bf16x8_t, *(const uint4*)(base + BLOCK + at));
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wh, xf[c].term[0], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wl, xf[c].term[0], acc, 0, 0, 0);
-                if constexpr (XT == 2) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wh, xf[c].term[1], acc, 0, 0, 0);
+                const TokenChunk<XT> xf = split_chunk(xr[c]);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wh, xf.term[0], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wl, xf.term[0], acc, 0, 0, 0);
+                if constexpr (XT == 2) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wh, xf.term[1], acc, 0, 0, 0);
             }
 #pragma unroll
             for (int v = 0; v < 16; ++v) {

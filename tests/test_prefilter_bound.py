@@ -38,5 +38,5 @@ def test_margin_constant_covers_the_split_and_the_additions(token_type, products
         error += left * (1.0 + 2 * low) + low * low             # of the token; the product of the lower terms is left out
     error += products * 128 * U                                 # d <= 128
     error += 15 * 2.0 ** -23                                    # the place in a score's last four bits
-    norms = 1.0 + 2.0 ** -15                                    # 2^-17 of the split, 128 squares and a root in float32
+    norms = 1.0 + 2.0 ** -15                                    # 128 squares and a root in float32
     assert error * norms <= fast_eps(token_type), (error, fast_eps(token_type))
