@@ -524,8 +524,10 @@ sparse_attn_bf16_kernel(AttnArgs a) {
         // The row sum takes the two ROUNDED probabilities, the same values the second contraction multiplies: one
         // dot-product instruction with (1, 1) instead of two adds.  A dot product shares the matrix pipe: alone on a SIMD, one
         // between two matrix instructions costs 17 cycles, each further one of a run 4.  Where the waves of a SIMD run in
-        // step (the dense shape, one barrier for both), the sums of a tile are one run behind the second product: 12 x 32,760 x
-        // 128 5.71 -> 5.58 ms.  Two independent workgroups fill each other's gaps: there a run is 0.5 % slower.
+        // step (the dense shape, one barrier for both), the sums of a tile are one run behind the second product.  d = 128, n =
+        // 1,024 / 2,945 / 8,190 / 32,760 / 60,000: -2.6 / -3.3 / -2.5 / -3.3 / -1.6 %.  At d = 64, with half the matrix
+        // instructions to a tile, the run costs 0.7 to 2.6 %; two independent workgroups fill each other's gaps, there it is
+        // within 1.3 % at both d.
         constexpr bool DOTS_LAST = NW == 8 && D == 128;
         const bf16x2 ones2 = __builtin_bit_cast(bf16x2, 0x3f803f80u);
         uint32_t pw[NKB][2][4];

@@ -439,10 +439,11 @@ struct AssignArgs {
 // The workgroup also knows the label counts of its ASSIGN_CHUNK tokens, which saves the sort its pass over the
 // labels.
 //
-// Bound, 12 x 75,600 x 128 bf16 against 256 centroids: matrix and vector work, which hardly overlap, 9.7 us per block of 32
-// (7.1 of them matrix pipe), 38 us of token rows from memory, norms and counts, 7.5 us of decisions: 134 -> 123 us with
-// the place of a centroid in its score's last bits, two chunks of W in flight and three workgroups a compute unit (float32,
-// d = 128: 210 registers, two).  Reading whole token rows through LDS changed nothing.
+// Bound, 12 x 75,600 x 128 bf16 against 256 centroids: matrix and vector work, of which a fifth overlaps (counters), 9.7 us
+// per block of 32 (7.1 of them matrix pipe), 38 us of token rows from memory, norms and counts, 7.5 us of decisions: 134 ->
+// 123 us with the place of a centroid in its score's last bits, a constant buffer index and two chunks of W in flight.
+// Three workgroups share a compute unit, as they did before (float32, d = 128: 210 registers, two); the launch bound keeps
+// it so.  Reading whole token rows through LDS changed nothing.
 //
 // BIAS: score_j = <x, W_j> - half_sq[j] (k-means on raw rows: W = C, half_sq = ||c_j||^2 / 2, one
 // float per centroid, slices padded to a multiple of 32 entries); the margin then also covers the

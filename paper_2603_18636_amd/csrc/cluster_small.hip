@@ -208,7 +208,8 @@ assign_small_kernel(SmallAssign a) {
 
     // ---- pre-filter: assign_kernel's products and margin, without the places in the scores.  Tokens are split here and no
     // earlier: in two terms while W was built they took 228 registers (d = 128 float32), one workgroup of a compute unit's two,
-    // and the loads were waited for first: 12 x 8,000 x 128, 32 blocks, two iterations 225 us, 193 now (207 with the float32 matrix instruction).
+    // and the loads were waited for first: 12 x 8,000 x 128, 32 blocks, two iterations 225 us, 193 now (207 with the float32
+    // matrix instruction).
 #pragma unroll
     for (int c = 0; c < DC; ++c) keep_raw(xr[c]);
     const float wmax = __int_as_float(wmax_bits);

@@ -17,9 +17,9 @@
 //               above it counted; the row is done.
 //
 // and the lists are ordered at the end.  75,600 keys take four or five passes where halving the
-// bracket took 29 (float32: four at 4,096 to 8,190 keys, 27-30).  Rows whose logits are all equal are done after pass 0.  A bracket that shrinks to one float value holds ties, taken one at a time by a
-// division.  A bracket that equal bins cannot split (its width is not a usable float32) is split by
-// the order of the float bit patterns instead.
+// bracket took 29 (float32: four at 4,096 to 8,190 keys, 27-30).  Rows whose logits are all equal are done after
+// pass 0.  A bracket that shrinks to one float value holds ties, taken one at a time by a division.  A bracket that
+// equal bins cannot split (its width is not a usable float32) is split by the order of the float bit patterns instead.
 //
 // The logits are recomputed in every pass by the same instruction sequence, so they are
 // bit-identical from pass to pass, and a bin's edges are the exact floats at which the bin function
@@ -34,10 +34,10 @@
 //
 // Bound (12 x 2,048 rows x 75,600 keys, d = 128, bf16): vector issue.  A logit of a histogram pass
 // costs ~60 vector cycles (exponential 16, bin index 12, fixed-point mass 20) against 16 of its
-// share of the matrix instruction.  Measured there: 24.7 ms for 29 passes of halving, 4.3 ms for four
-// passes with a branch per logit in the later ones (4.55 on another card), 4.0 (4.2) here: of a lane's 16 logits two bit masks say which are
-// inside the bracket, and every lane of the wave picks its next one (1.5 % of the keys are inside in pass 2:
-// two rounds for all 64 lanes, where 10 of 16 branches were taken for some lane).
+// share of the matrix instruction.  Measured there: 24.7 ms for 29 passes of halving; four passes with a branch per
+// logit in the later ones 4.3 - 4.55 ms, as they are 4.0 - 4.2.  Of a lane's 16 logits two bit masks say which are inside
+// the bracket, and every lane of the wave picks its next one: 1.5 % of the keys are inside in pass 2, two rounds for all
+// 64 lanes, where 10 of 16 branches were taken for some lane.
 #include <math.h>
 
 #include <type_traits>
@@ -46,7 +46,10 @@
 
 #define LOG2E_F 1.4426950408889634f
 #define DEN_REFINE_N (1 << 18)   // more keys: masses in the unit of the row (svoo_attention_density says why)
-#define DEN_PICK 4          // keys inside the bracket, of a lane's 16, up to which they are picked one by one
+// Keys inside the bracket, of a lane's 16, up to which they are picked one by one.  On normal logits up to 1 / 2 / 3 cost up to
+// 20 / 9 / 2.5 % against 4, and 6 or 8 nothing either way; always picking saves 1 - 3 % there but costs 2 - 25 % where
+// outliers leave most keys inside.
+#define DEN_PICK 4
 #define DEN_MAX_PASSES 48   // pass 0, pass 1, and far more splits than a float interval allows; a hard stop
 
 typedef __attribute__((ext_vector_type(8))) __bf16 den_bf16x8;

@@ -92,7 +92,9 @@ extern "C" int svoo_microbench_copy(const void* src, void* dst, size_t bytes, vo
 // reads (ds_read_b128), 32 V fragment reads (transposing ds_read_b64_tr_b16), 8 direct global->LDS
 // loads of 1 KB (the workgroup's 32 KB tile, out of L2), and the 32 matrix instructions they feed --
 // any subset, chosen by `parts` (bit 0 K reads, 1 V reads, 2 direct loads, 3 matrix instructions).
-// Same LDS layout, swizzles and read addresses as the attention kernel; one barrier per step.
+// Same LDS layout, swizzles and read addresses as the attention kernel; one barrier per step.  The direct loads take an offset
+// per lane and one LDS address each, as the kernel's do where key blocks meet; inside a block the kernel issues four to an
+// address and saves the address arithmetic, which this loop has no use for.
 // ---------------------------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 
