@@ -47,6 +47,9 @@ def kernels(tmp_path_factory):
     ("assign_kernelI[tf]Li64E", {"t": 168, "f": 168}),                      # three workgroups of four waves
     ("assign_kernelI[tf]Li128E", {"t": 168, "f": 256}),                     # float32 tokens: two
     ("sparse_attn_bf16_kernel", {"": 256}),                                 # eight waves, two a SIMD
+    ("sparse_attn_f32_kernelILi64E", {"": 168}),                            # three workgroups of four waves
+    ("sparse_attn_f32_kernelILi128E", {"": 256}),                           # two
+    ("sparse_attn_f32_few_kernelILi64E", {"": 256}),                        # two
 ])
 def test_registers_leave_room_for_the_workgroups_of_a_unit(kernels, name, registers):
     mine = {k: v for k, v in kernels.items() if re.search(r"^_Z\d+%s" % name, k)}
