@@ -60,20 +60,37 @@ struct SmallLds {
     static constexpr int ROWB = 2 * D;                 // one term of one row of the split
     static constexpr int TERMS = 2;
     static constexpr int BLOCK = 32 * ROWB;
-    int pitch, split, c_opp, ph, bterm, open, bytes;   // W in float64 takes C_opp's place once it is used up
+    static constexpr bool ROOM = sizeof(T) == 2 || D == 64;    // 128 registers hold more than the tokens
+    int pitch, split, c_opp, ph, bterm, open, fixed, bytes;    // W in float64 takes C_opp's place once it is used up
     __host__ __device__ constexpr SmallLds(int k_own, int k_opp)
-        : pitch(0), split(0), c_opp(0), ph(0), bterm(0), open(0), bytes(0) {
+        : pitch(0), split(0), c_opp(0), ph(0), bterm(0), open(0), fixed(0), bytes(0) {
         const int own16 = (k_own + 15) / 16 * 16, own32 = (k_own + 31) / 32 * 32;
         pitch = (k_opp + 15) / 16 * 16 + 2;
         const int c = k_opp * CP * 8, w = own16 * WP * 8;
         split = 0;                                     // first: its swizzle wants whole rows aligned
-        c_opp = split + own32 / 32 * TERMS * BLOCK;
+        bterm = split + own32 / 32 * TERMS * BLOCK;
+        c_opp = bterm + own16 * 8;
         ph = c_opp + (c > w ? c : w);
-        bterm = ph + own16 * pitch * 8;
-        open = bterm + own16 * 8;                      // rows of the open tokens, in float32
-        bytes = open + SMALL_MANY * D * 4;
+        fixed = ph + own16 * pitch * 8;
+        open = c_opp + w;                              // rows of the open tokens, in float32, where P was
+        const int end = open + (ROOM ? SMALL_MANY * D * 4 : 0);
+        bytes = end > fixed ? end : fixed;
     }
 };
+// 16 waves of 128 registers fill a compute unit: the rows of the open tokens must not cost one of its two workgroups.  In a place of
+// their own they did at 48 / 64 clusters of 64: 12 x 8,192 tokens (384 workgroups), two iterations, 153 us, now 133.
+template <typename T, int D>
+constexpr bool open_rows_keep_two_workgroups() {
+    constexpr int HALF = 80 * 1024 - 2048;              // less the other shared variables
+    for (int own = 1; own <= SMALL_MAX_W / D; ++own)
+        for (int opp = 1; opp <= SMALL_MAX_W / D; ++opp) {
+            const SmallLds<T, D> l(own, opp);
+            if (l.fixed <= HALF && l.bytes > HALF) return false;
+        }
+    return true;
+}
+static_assert(open_rows_keep_two_workgroups<uint16_t, 64>() && open_rows_keep_two_workgroups<float, 64>() &&
+              open_rows_keep_two_workgroups<uint16_t, 128>() && open_rows_keep_two_workgroups<float, 128>(), "a workgroup lost");
 
 template <typename T, int D>
 __global__ void __launch_bounds__(64 * SMALL_WAVES)
@@ -82,7 +99,7 @@ assign_small_kernel(SmallAssign a) {
     constexpr int CP = L::CP, WP = L::WP, ROWB = L::ROWB, CPR = ROWB / 16, DC = ROWB / 32, BLOCK = L::BLOCK;
     constexpr int XT = sizeof(T) == 2 ? 1 : 2;         // terms of a token
     constexpr int NW = SMALL_WAVES, NT = 64 * NW;
-    constexpr bool ROOM = sizeof(T) == 2 || D == 64;   // 128 registers hold more than the tokens
+    constexpr bool ROOM = L::ROOM;
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     __shared__ int32_t wmax_bits, degenerate_s, n_open;
     __shared__ int32_t open[32 * NW];
