@@ -102,10 +102,11 @@ def test_layer_random_small_shapes(seed):
         H.assert_attn_close(out[b], ref, dtype, what)
 
 
-@pytest.mark.parametrize("d,n,kq,copies", [(128, 257, 5, 40), (64, 400, 9, 24), (128, 63, 2, 90), (64, 129, 1, 70)])
+@pytest.mark.parametrize("d,n,kq,copies", [(128, 257, 5, 40), (64, 400, 9, 24), (128, 63, 2, 90), (64, 129, 1, 70), (64, 129, 1, 90),
+                                              (64, 193, 6, 40)])
 def test_float32_attention_with_enough_tiles_for_64_row_workgroups(d, n, kq, copies):
     """The cases above have so few tiles that float32 runs in 32-row workgroups; here the slice is repeated
-    until the 64-row ones are chosen (ragged query tiles and key stages, a query block without keys, row
+    until the 64-row ones are chosen, but for the sparse half of 70 copies (ragged query tiles and key stages, a query block without keys, row
     moves through q_perm, log-sum-exp).  Bound: the acceptance bar of float32 inputs (1e-5)."""
     rng = np.random.default_rng(n)
     q, k, v = ((1.5 * rng.standard_normal((1, n, d))).astype(np.float32) for _ in range(3))
