@@ -218,7 +218,11 @@ int svoo_block_mask(const svoo_shape* shape, const float* cq, const float* ck,
  * logits over the kept keys (natural log).  A query block with no kept key writes zeros.
  * scale must be finite and > 0.
  * bf16: both contractions on bf16 matrix cores with float32 accumulation, probabilities rounded to
- * bf16 before the second one; f32: float32 arithmetic throughout (logits summed in four chains).  Keys
+ * bf16 before the second one.  f32: float32 accumulation, products as exact as float32's own rounding (2^-24).  Small calls
+ * use the float32 matrix instruction (logits summed in four chains); others write every number as three bf16 terms and add
+ * six products of terms, and go back to the float32 instruction for query rows that meet numbers without such terms: in Q or K
+ * 2^60 / max(scale, 1) and more, in V below 2^-100 (other than 0) or 2^100 and more, infinities and NaN (slower,
+ * the same results).  Keys
  * whose logit is -inf weigh nothing; a row with no other keys gets zeros and lse = -inf.
  */
 int svoo_block_sparse_attn(const svoo_shape* shape, const void* q_sorted, const void* k_sorted,
